@@ -156,7 +156,8 @@ size_t lamps_block_bytes(const lamps_config *cfg);
 /* Bytes the caller must allocate for EACH of the two pools. */
 size_t lamps_pool_bytes(const lamps_config *cfg);
 /* Bytes of device workspace the caller must allocate (256-byte aligned):
- * split partition partials and the two swap staging areas. */
+ * split partition partials (of decode calls, and of lamps_prefill_attn calls that
+ * cut long contexts into runs) and the two swap staging areas. */
 size_t lamps_workspace_bytes(const lamps_config *cfg);
 
 /* ---- life cycle ---- */

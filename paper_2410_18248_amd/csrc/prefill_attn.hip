@@ -6,6 +6,8 @@
 // tokens are already in the cache (lamps_kv_append_tokens).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "attn_reducers.h"
 #include "internal.h"
 
@@ -105,7 +107,124 @@ constexpr float kSlack = 8.0f;           // log2 of the largest weight before th
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(4))) const int32_t *table_ptr;   // read-only: scalar loads
 
-template <int D, bool TILED, int kCols, int GRP>
+// s_waitcnt immediate: wait until at most n of the wave's vector memory operations are outstanding
+constexpr int vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
+
+// Splitting a tile's cached positions.  One workgroup per (request, kv head, tile) leaves most of
+// the chip idle when few requests bring few new tokens -- the API responses of a dozen requests
+// are 100 to 200 workgroups, each a serial walk over a whole context.  Then the stages of every
+// tile are cut into runs of `per` stages, each a workgroup of its own that leaves its columns'
+// (reference, sum, unnormalised output) in the workspace; the last of a tile to do so adds them up
+// in order.  `per` is the smallest that gives no more runs than there are workgroups (slots), so the
+// work of the launch is even whatever the contexts are and no workgroup is started for nothing in
+// front of one that has work (a workgroup that finds nothing to do holds its LDS for 2 us).
+// Bound by the walk over K / V and the hand-over: a dozen requests with 6 to 58 new tokens on 345 to
+// 2 490 cached, 32 / 8 heads of 128 (50 MB): 63 us for this kernel before, 25 now; append + attention
+// of one request with 16 new on 3 000: 80 us before, 32 now.  (Adding the runs up in a second launch
+// instead is 1-8 us faster on such a call and 4 us slower on every one that has nothing to add up.)
+constexpr int kSplitSlots = 512;         // two workgroups per CU
+constexpr int kSplitRequests = 64;       // one per lane
+constexpr int kSplitStages = 32;         // a block-table row of fewer (1024 positions) is not split: the hand-over costs
+                                         // what a dozen stages do
+constexpr int kMinRun = 12;              // stages: 384 positions (8 and 16 measured 0-4 % and 0-10 % slower)
+
+struct Run {
+    int r, g, tile;                      // request, kv head, tile of new tokens (r < 0: nothing to do)
+    int first, n_new, ctx;               // of the request: first new row, new rows, context length
+    int first_item, stride;              // items (= workgroups, partial slots) of the tile's runs
+    int per;                             // stages per run
+};
+
+// Inclusive sum over the lanes of a wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_shifted(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x += dpp_shifted<0x111, 0xF>(x);                  // row_shr 1, 2, 4, 8: inside each row of 16
+    x += dpp_shifted<0x112, 0xF>(x);
+    x += dpp_shifted<0x114, 0xF>(x);
+    x += dpp_shifted<0x118, 0xF>(x);
+    x += dpp_shifted<0x142, 0xA>(x);                  // row_bcast 15: into rows 1 and 3
+    x += dpp_shifted<0x143, 0xC>(x);                  // row_bcast 31: into rows 2 and 3
+    return x;
+}
+
+// What workgroup `item` of a split launch is to do.  Items are ordered (request, run, kv head,
+// tile).  Every wave works it out for itself from q_start and ctx_lens, one request per lane: one
+// round trip to memory, no barrier.  (The launcher has checked that the sums fit 32 bits.)
+__device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT, int item)
+{
+    const DecodeArgs &a = p.d;
+    const int lane = threadIdx.x & 63;
+    int first = 0, n_new = 0, ctx = 0, stages = 0, n_tiles = 0;
+    if (lane < a.batch) {
+        first = p.q_start[lane];
+        n_new = p.q_start[lane + 1] - first;
+        ctx = a.ctx_lens[lane];
+        // a context shorter than its new tokens, or longer than the block-table row, is the
+        // caller's mistake: nothing is read or written for it
+        if (n_new > 0 && ctx >= n_new && ctx <= a.max_blocks * a.block_size) {
+            n_tiles = min((n_new + WT - 1) / WT, tiles);
+            stages = (ctx - 1) / kStage + 1;          // of the last tile; no tile has more
+        }
+    }
+    const int sum_stages = __builtin_amdgcn_readlane(wave_scan(stages * n_tiles), 63);
+    const int sum_tiles = __builtin_amdgcn_readlane(wave_scan(n_tiles), 63);
+    // a tile's last run may be short: the sum over tiles of ceil(stages / per) stays within the slots
+    const int spare = max(1, p.slots / a.num_kv_heads - sum_tiles);
+    Run run;
+    run.per = max(kMinRun, (sum_stages + spare - 1) / spare);
+    const int items = n_tiles * ((stages + run.per - 1) / run.per) * a.num_kv_heads;
+    const int before = wave_scan(items) - items;
+    const unsigned long long hit = __ballot(item >= before && item < before + items);
+    run.r = __ffsll((long long)hit) - 1;
+    if (run.r < 0) return run;
+    const int nt = __builtin_amdgcn_readlane(n_tiles, run.r), base = __builtin_amdgcn_readlane(before, run.r);
+    run.first = __builtin_amdgcn_readlane(first, run.r);
+    run.n_new = __builtin_amdgcn_readlane(n_new, run.r);
+    run.ctx = __builtin_amdgcn_readlane(ctx, run.r);
+    run.stride = a.num_kv_heads * nt;
+    run.g = (item - base) / nt % a.num_kv_heads;
+    run.tile = (item - base) % nt;
+    run.first_item = base + run.g * nt + run.tile;
+    return run;
+}
+
+// Memory of a split launch behind DecodeArgs::partials, per item: the unnormalised outputs of each
+// block of 16 columns as its wave holds them, [pair of registers][lane] -- whole lines, written and
+// read by 512 contiguous bytes per instruction (by column, in pieces of 8 bytes, the hand-over of a
+// tile took 25 us) --, the columns' (reference, sum), and the arrival count of the tile whose
+// first item it is.
+constexpr size_t split_item_bytes(int D, int columns) { return (size_t)columns * (D + 2) * sizeof(float) + sizeof(uint64_t); }
+
+// The hand-over between the runs of a tile goes through memory that every XCD sees alike:
+// agent-scope accesses, relaxed; the writer waits for its stores before it reports.  (A release or
+// acquire fence would write back or invalidate a whole L2.)
+__device__ __forceinline__ void put_shared(float *p, float x, float y)
+{
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, make_float2(x, y)), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_shared(const float *p)
+{
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_AGENT));
+}
+// Reports one run of `total` at the tile's count; true for the last.  A count is (tag, reports so
+// far); the tag is the launch's own, so whatever the memory held before counts as none, and the last
+// report takes the tag away again (a graph replays its launches with the same tag).
+__device__ __forceinline__ bool report_run(uint64_t *count, uint64_t tag, int total)
+{
+    uint64_t old = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) {                                        // (each failure is another run's report: at most total)
+        const int n = (old >> 16) == tag ? (int)(old & 0xFFFF) + 1 : 1;
+        const uint64_t want = n == total ? 0 : (tag << 16) + (uint64_t)n;
+        if (__hip_atomic_compare_exchange_strong(count, &old, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            return n == total;
+    }
+}
+
+template <int D, bool TILED, int kCols, int GRP, bool SPLIT>
 __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void prefill_mfma(const PrefillArgs p, const int tiles, const int full_groups)
 {
     constexpr int kColBlocks = kCols / 16;
@@ -116,7 +235,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     // The pool's tiles go to LDS as they are, by loads that write LDS directly
     // (global_load_lds_dwordx4: lane l of a wave writes 16 bytes at base + 16 l, read from any
     // address); two stage buffers (64 KiB at head_dim 256).
-    constexpr int NB = 2;                            // stage buffers
+    constexpr int NB = SPLIT && D <= 128 ? 4 : 2;    // group buffers
     constexpr int NU = D / 8;                        // 16-byte units of one row (plain layout)
     constexpr int SUBB = 16 * D * 2;                 // one 16-position sub-tile of K or V
     constexpr int VOFF = 2 * SUBB;                   // V follows the two K sub-tiles
@@ -135,26 +254,47 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     // holds for the pairs that fill whole groups of 8; the (pair, tile) items of the remaining
     // 1..7 pairs are dealt round-robin over all XCDs instead of leaving some of them empty.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int pairs = a.num_kv_heads * a.batch;
-    int pair, t;
-    if (slot < full_groups * tiles) {
-        pair = xcd + 8 * (slot / tiles);
-        t = slot % tiles;
-    } else {
-        const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
-        const int item = (slot - full_groups * tiles) * 8 + xcd;
-        pair = 8 * full_groups + item % rest;
-        t = item / rest;
-        if (t >= tiles) return;
-    }
-    const int tile = tiles - 1 - t;
-    const int r = pair / a.num_kv_heads, g = pair - r * a.num_kv_heads;
-    const int G = a.num_q_heads / a.num_kv_heads;
-    const int TW = kCols / G;                        // new tokens per wave (G <= kCols)
+    const int TW = kCols / (a.num_q_heads / a.num_kv_heads);   // new tokens per wave (G <= kCols)
     const int WT = kWaves * TW;                      // ... per workgroup
-    const int first = p.q_start[r], n_new = p.q_start[r + 1] - first;
-    if (tile * WT >= n_new) return;
-    const int C = a.ctx_lens[r];
+    int r, g, tile, first, n_new, C;
+    int item = 0, st0 = 0, per = 0x7fffffff;         // SPLIT: the workgroup's item, first stage, most stages,
+    int first_item = 0, item_stride = 0;             // ... and the items of its tile's runs
+    if constexpr (SPLIT) {
+        item = xcd * (p.slots >> 3) + slot;          // neighbours in item order share blocks: one XCD
+        const Run run = locate(p, tiles, WT, item);
+        if (run.r < 0) return;
+        r = run.r;
+        g = run.g;
+        tile = run.tile;
+        first = run.first;
+        n_new = run.n_new;
+        C = run.ctx;
+        per = run.per;
+        first_item = run.first_item;
+        item_stride = run.stride;
+        st0 = (item - run.first_item) / run.stride * per;
+    } else {
+        const int pairs = a.num_kv_heads * a.batch;
+        int pair, t;
+        if (slot < full_groups * tiles) {
+            pair = xcd + 8 * (slot / tiles);
+            t = slot % tiles;
+        } else {
+            const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
+            const int at = (slot - full_groups * tiles) * 8 + xcd;
+            pair = 8 * full_groups + at % rest;
+            t = at / rest;
+            if (t >= tiles) return;
+        }
+        tile = tiles - 1 - t;
+        r = pair / a.num_kv_heads;
+        g = pair - r * a.num_kv_heads;
+        first = p.q_start[r];
+        n_new = p.q_start[r + 1] - first;
+        if (tile * WT >= n_new) return;
+        C = a.ctx_lens[r];
+    }
+    const int G = a.num_q_heads / a.num_kv_heads;
     const int base_pos = C - n_new;                  // position of the request's first new token
     // a context shorter than its new tokens, or longer than the block-table row, is the caller's
     // mistake: nothing is read or written for it
@@ -192,8 +332,15 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     }
     wave_maxpos = __builtin_amdgcn_readfirstlane(wave_maxpos);
     wave_minpos = __builtin_amdgcn_readfirstlane(wave_minpos);
-    const int wg_maxpos = base_pos + min(n_new, (tile + 1) * WT) - 1;
-    const int n_stages = wg_maxpos / kStage + 1;
+    int wg_maxpos = base_pos + min(n_new, (tile + 1) * WT) - 1;
+    int n_stages = wg_maxpos / kStage + 1;
+    int n_runs = 1;                                   // workgroups that share the tile
+    if constexpr (SPLIT) {
+        if (st0 >= n_stages) return;                  // a tile before the request's last one has fewer
+        n_runs = (n_stages + per - 1) / per;
+        n_stages = min(n_stages, st0 + per);
+        wg_maxpos = min(wg_maxpos, n_stages * kStage - 1);
+    }
 
     float m[kColBlocks];
     f32x4 o[kColBlocks][NS];                          // out^T: dims 16 s + 4 qd + e, this lane's column
@@ -220,7 +367,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     uint32_t ent[2 * GRP];
     const uint32_t last_entry = (uint32_t)wg_maxpos >> a.log2_block_size;   // nothing past it is looked up
     const uint32_t last_block = (uint32_t)a.num_blocks - 1;
-    auto lookup = [&](int grp) {
+    auto lookup = [&](int grp, uint32_t (&ent)[2 * GRP]) {
         const uint32_t t0 = (uint32_t)(grp * GRP * kStage);
 #pragma unroll
         for (int i = 0; i < 2 * GRP; ++i)               // (an entry that names no block of the pool is the caller's
@@ -239,8 +386,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         lane_v[k] = (uint32_t)(TILED ? x : row * NU + (sl ^ ((2 * row) & (NU - 1)))) * 16;
     }
     // The stage's tiles from the pools straight into LDS buffer `buf`, each wave instruction one
-    // run of 64 units (1 KiB).  Sub-tiles past the workgroup's last position are not loaded (LDS is
-    // cleared once at the start, and every column's weight for those positions is zero).  Nothing
+    // run of 64 units (1 KiB).  Sub-tiles past the workgroup's last position are not loaded.  Nothing
     // waits here: the caller waits for vmcnt before the barrier that publishes the stage.
     // The address is a scalar base (pool + block + sub-tile, all on the scalar unit, 32 x 32 -> 64
     // bit) plus the lane's constant 32-bit offset: no vector arithmetic per load.
@@ -266,18 +412,20 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
             }
         }
     };
-    // Value slots at or past the context's end are zeroed once the stage is in LDS (they may hold
-    // anything, and a zero weight does not silence a NaN).
+    // Value slots at or past the context's end, and those of a sub-tile that was not loaded, are
+    // zeroed once the stage is in LDS (they may hold anything, and a zero weight does not silence
+    // a NaN; the scores of such positions are masked whatever the keys are).
+    const int valid_end = min(C, (wg_maxpos | 15) + 1);
     auto zero_tail = [&](int st, char *buf) {
 #pragma unroll
         for (int k = 0; k < LPT; ++k) {
             const int x = tid + kThreads * k, u = x / U, unit = x % U;
             if (!TILED) {                             // a slot is part of one row: position 16 u + unit / NU
-                if (st * kStage + 16 * u + unit / NU >= C)
+                if (st * kStage + 16 * u + unit / NU >= valid_end)
                     *reinterpret_cast<uint4 *>(buf + VOFF + x * 16) = make_uint4(0, 0, 0, 0);
                 continue;
             }
-            const int valid = C - (st * kStage + 16 * u + 4 * ((unit >> 4) & 3));
+            const int valid = valid_end - (st * kStage + 16 * u + 4 * ((unit >> 4) & 3));
             if (valid < 4) {
                 uint4 *slot = reinterpret_cast<uint4 *>(buf + VOFF + x * 16);
                 uint4 v = *slot;
@@ -396,32 +544,44 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
             for (int b = 0; b < kColBlocks; ++b) o[b][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[s], pw[b], o[b][s], 0, 0, 0);
     };
 
-    auto dma_group = [&](int grp, char *buf) {
+    auto dma_group = [&](int grp, char *buf, const uint32_t (&ent)[2 * GRP]) {
 #pragma unroll
         for (int h = 0; h < GRP; ++h) dma(grp * GRP + h, buf + h * STAGE, ent[2 * h], ent[2 * h + 1]);
     };
-    lookup(0);
-    // what is never loaded (sub-tiles past the workgroup's last position) reads as zero
-    for (int i = tid; i < NB * GSTAGE / 16; i += kThreads) reinterpret_cast<uint4 *>(lds)[i] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    dma_group(0, lds);
-    lookup(1);
-    dma_group(1, lds + GSTAGE);
-    lookup(2);
-    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): both groups have landed
-    __syncthreads();
+    const int grp0 = SPLIT ? st0 : 0;                 // SPLIT: one stage per group
+    constexpr int kGroupLoads = GRP * 2 * LPT;        // of one wave
+    {
+        uint32_t first_ent[NB][2 * GRP];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) lookup(grp0 + i, first_ent[i]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) dma_group(grp0 + i, lds + i * GSTAGE, first_ent[i]);
+    }
+    lookup(grp0 + NB, ent);
+    // Waits for group grp with the loads of `ahead` groups behind it on their way.  (Where the last
+    // of those loads less than a whole group, or nothing, the count says nothing: all are waited for.)
+    auto landed = [&](int grp, auto ahead) {
+        if (ahead > 0 && (grp + ahead + 1) * GRP * kStage <= wg_maxpos + 1)
+            __builtin_amdgcn_s_waitcnt(vmcnt(ahead * kGroupLoads));
+        else
+            __builtin_amdgcn_s_waitcnt(vmcnt(0));
+        __syncthreads();
+    };
+    // (two buffers: with group 0 alone waited for here, the two workgroups of a CU fall into a
+    // rhythm that is 14 % slower at head_dim 256)
+    landed(grp0, std::integral_constant<int, NB == 2 ? 0 : NB - 1>{});
     // At head_dim 256 the K and V operands of a stage are 64 registers each.  With 16 columns per
     // wave they are read one after the other, K right before the scores and V behind them: the
     // wave then stays under 256 registers and two workgroups share a CU here as well.
     constexpr bool kLean = D >= 256 && kCols <= 16;
     if (!kLean) read_k(lds);
     const int n_groups = (n_stages + GRP - 1) / GRP;
-    for (int grp = 0; grp < n_groups; ++grp) {
-        char *cur = lds + (grp & 1) * GSTAGE, *nxt = lds + ((grp + 1) & 1) * GSTAGE;
-        if ((grp + 1) * GRP * kStage > C) {           // the group holds the context's last stage: uniform
+    for (int grp = grp0; grp < n_groups; ++grp) {
+        char *cur = lds + ((grp - grp0) & (NB - 1)) * GSTAGE, *nxt = lds + ((grp - grp0 + 1) & (NB - 1)) * GSTAGE;
+        if ((grp + 1) * GRP * kStage > valid_end) {   // the group holds the last stage: uniform
 #pragma unroll
             for (int h = 0; h < GRP; ++h)
-                if ((grp * GRP + h) * kStage + kStage > C) zero_tail(grp * GRP + h, cur + h * STAGE);
+                if ((grp * GRP + h) * kStage + kStage > valid_end) zero_tail(grp * GRP + h, cur + h * STAGE);
             __syncthreads();
         }
 #pragma unroll
@@ -437,16 +597,80 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
                 softmax(st * kStage);
             }
             if (h == GRP - 1) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): group grp + 1, on its way since the last barrier
-                __syncthreads();                      // ... is in LDS for everyone; this group's operands are in registers
-                dma_group(grp + 2, cur);              // in flight until the next barrier (a third buffer and
-                lookup(grp + 3);                      // loads two barriers ahead were measured: slower)
+                landed(grp + 1, std::integral_constant<int, NB - 2>{});                    // in LDS for everyone; this group's operands are in registers
+                dma_group(grp + NB, cur, ent);        // NB == 2: in flight until the next barrier (a third buffer and
+                lookup(grp + NB + 1, ent);            // loads two barriers ahead were measured: slower)
             }
             if (!kLean && st + 1 < n_stages) read_k(h == GRP - 1 ? nxt : at + STAGE);   // needed at the top of the next stage
             if (live) accumulate();
         }
     }
 
+    if (SPLIT && n_runs > 1) {
+        constexpr int kAll = kWaves * kCols;          // columns of an item
+        float *out = a.partials, *stats = out + (size_t)p.slots * kAll * D;
+        uint64_t *count = reinterpret_cast<uint64_t *>(stats + (size_t)p.slots * kAll * 2);
+        if (wave_maxpos >= 0) {                       // uniform: the wave has columns
+#pragma unroll
+            for (int b = 0; b < kColBlocks; ++b) {
+                const size_t at = (size_t)item * (kAll / 16) + wv * kColBlocks + b;
+#pragma unroll
+                for (int s = 0; s < 2 * NS; ++s)
+                    put_shared(out + at * 16 * D + s * 128 + 2 * lane, o[b][s >> 1][2 * (s & 1)], o[b][s >> 1][2 * (s & 1) + 1]);
+                if (qd == 0) put_shared(stats + (at * 16 + j) * 2, m[b], l[b][0]);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(vmcnt(0));
+        __syncthreads();                              // the workgroup's stores have arrived, and its LDS is free
+        int *is_last = reinterpret_cast<int *>(lds);
+        if (tid == 0) *is_last = report_run(count + first_item, p.tag, n_runs);
+        __syncthreads();
+        if (!*is_last) return;
+        // the runs in order, whichever workgroup this is: bit-reproducible
+#pragma unroll
+        for (int b = 0; b < kColBlocks; ++b) {
+            if (wave_maxpos < 0) break;               // uniform: the wave has no columns
+            const size_t at0 = (size_t)first_item * (kAll / 16) + wv * kColBlocks + b, step = (size_t)item_stride * (kAll / 16);
+            constexpr int N = D >= 256 ? 2 : 4;       // runs whose loads are in flight together
+            float M = kLowest, L = 0.0f;
+            f32x4 A[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) A[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int k0 = 0; k0 < n_runs; k0 += N) {
+                float2 ml[N], x[N][2 * NS];
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    const size_t at = at0 + min(k0 + k, n_runs - 1) * step;
+                    ml[k] = get_shared(stats + (at * 16 + j) * 2);
+#pragma unroll
+                    for (int s = 0; s < 2 * NS; ++s) x[k][s] = get_shared(out + at * 16 * D + s * 128 + 2 * lane);
+                }
+                float Mn = M;
+#pragma unroll
+                for (int k = 0; k < N; ++k) Mn = fmaxf(Mn, ml[k].x);   // (the last run once more changes nothing)
+                const float f0 = fast_exp2(M - Mn);
+                M = Mn;
+                L *= f0;
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) A[s][e] *= f0;
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    const float f = k0 + k < n_runs ? fast_exp2(ml[k].x - M) : 0.0f;
+                    L += ml[k].y * f;
+#pragma unroll
+                    for (int s = 0; s < 2 * NS; ++s) {
+                        A[s >> 1][2 * (s & 1)] += x[k][s].x * f;
+                        A[s >> 1][2 * (s & 1) + 1] += x[k][s].y * f;
+                    }
+                }
+            }
+            l[b][0] = L;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) o[b][s] = A[s];
+        }
+    }
 #pragma unroll
     for (int b = 0; b < kColBlocks; ++b) {
         if (pos[b] < 0) continue;
@@ -463,10 +687,43 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     }
 }
 
+// The split launch if it is the right one for the sizes; *done says whether it was.
+template <int D, bool TILED, int kCols>
+hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
+{
+    *done = false;
+    const int G = p.d.num_q_heads / p.d.num_kv_heads, Hkv = p.d.num_kv_heads;
+    if (G > kCols || p.d.batch > kSplitRequests) return hipSuccess;
+    const int WT = kWaves * (kCols / G);
+    const long long tiles = (p.max_new_tokens + WT - 1) / WT;          // of one request, at most
+    const long long all = Hkv * min(tiles * p.d.batch, (long long)p.total_tokens / WT + p.d.batch);
+    const long long stages = ((long long)p.d.max_blocks * p.d.block_size - 1) / kStage + 1;   // of one request, at most
+    p.slots = (int)min((size_t)kSplitSlots, p.d.partial_capacity / split_item_bytes(D, kWaves * kCols)) / 8 * 8;
+    // Half the slots must be left to cut into: with more tiles than that the chip is busy anyhow.
+    // (Tiles of 128: a quarter.  They come with many new tokens, most of a prompt, where the causal
+    // half of the items is empty: one prompt of 1 000 on 8 kv heads took 46 us split, 34 not.)
+    if (all > p.slots / (kCols == 16 ? 2 : 4) || stages < kSplitStages || all * stages > 0x7fffffff) return hipSuccess;
+    hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, true>), dim3(p.slots), dim3(kThreads), 0, s, p, (int)tiles, 0);
+    *done = true;
+    return hipGetLastError();
+}
+
 template <int D, bool TILED, int kCols = kMaxCols>
 hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
 {
     const int G = p.d.num_q_heads / p.d.num_kv_heads;
+    // Split launches: tiles of 64 columns leave no wave without work when a request brings a few
+    // tokens (16 new on 3 000 cached, 32 / 8 heads: 32 us against 35 with tiles of 128, one tile's
+    // append + attention; 40 on 1 000, 8 requests: 32 against 36); from 16 such tiles per request on
+    // each K / V byte is read 16 times and more, and tiles of 128 are the better ones (512 new on
+    // 3 000: 67 us against 92).
+    bool done = false;
+    hipError_t e;
+    if (G <= 16 && (kCols == 16 || (long long)p.max_new_tokens * G < 1024))
+        e = launch_split_prefill<D, TILED, 16>(p, s, &done);
+    else
+        e = launch_split_prefill<D, TILED, kCols>(p, s, &done);
+    if (e != hipSuccess || done) return e;
     const int WT = kWaves * (kCols / G);
     const long long tiles = (p.max_new_tokens + WT - 1) / WT;
     const long long pairs = (long long)p.d.num_kv_heads * p.d.batch;
@@ -478,10 +735,10 @@ hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
     // finer grain is the faster one (+3 %).
     constexpr bool kFits = 2 * 2 * (4 * 16 * D * 2) <= 65536;
     if (kFits && tiles > 1)
-        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, kFits ? 2 : 1>), dim3((unsigned)grid), dim3(kThreads), 0, s, p,
+        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, kFits ? 2 : 1, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, p,
                            (int)tiles, (int)full);
     else
-        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1>), dim3((unsigned)grid), dim3(kThreads), 0, s, p, (int)tiles,
+        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, p, (int)tiles,
                            (int)full);
     return hipGetLastError();
 }
