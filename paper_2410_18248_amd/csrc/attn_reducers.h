@@ -1,7 +1,8 @@
 // Per-wavefront attention reducers shared by the decode and the prefill kernels:
 // the online-softmax pass of one wavefront over a token range of one request's
 // paged K/V (arXiv 2410.18248, Section 2.2 equation; paging as in Section 7),
-// on the vector ALUs (ValuReducer) or on the matrix cores (MfmaReducer).
+// on the vector ALUs (ValuReducer) or on the matrix cores (MfmaReducer: bf16,
+// MfmaF32Tile: fp32, many new tokens).
 // Device code; include from a .hip file only.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -490,6 +491,182 @@ struct MfmaReducer {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) sink(j, 16 * sidx + 4 * qd + e, m, l, o[sidx][e]);
         }
+    }
+};
+
+// ---------------------------------------------------------------- MFMA tile reducer, 32 bits
+
+// fp32, plain pool layout, up to 16 columns -- (query row, limit) pairs -- of one kv head, on the fp32
+// matrix instruction (16x16x4: full fp32 products and sums).  Both operands come out of memory as
+// they are, 16 bytes per lane.  Scores^T[token][column] = K . q^T: the contraction index may be
+// permuted, so a lane's 16 bytes of row lane % 16 feed four MFMAs.  The result leaves a lane with
+// four consecutive tokens of its column; its register e is, unchanged, the operand p^T[token][column]
+// of the MFMAs that take tokens 4 (lane / 16) + e, and the V operand of those is what the lane gets
+// from 16 bytes (8 at head_dim 32) of that token's row: four dims, one for each of four MFMAs.
+// (Decode with grouped heads keeps the vector ALUs: there, 24 requests of 17 to 2 500 tokens, 32 / 8
+// heads of 128, this reducer took 34 us against 27, two waves per SIMD against four.)
+template <int DIM>
+struct MfmaF32Tile {
+    static constexpr int D = DIM;
+    static constexpr int CT = 16;                     // tokens per chunk
+    static constexpr int NK = D / 16;                 // K loads per chunk, four score MFMAs each
+    static constexpr int VW = D >= 64 ? 4 : 2;        // dims of one V load
+    static constexpr int NC = D / (16 * VW);          // V loads per token group
+    typedef __attribute__((ext_vector_type(VW))) float vvec;
+
+    struct State {                                    // of column lane % 16: the same m and l in its four lanes
+        float m, l;
+        f32x4 o[NC][VW];                              // [c][v][e]: dim 16 VW c + VW (4 (lane / 16) + e) + v
+    };
+
+    // Reduces cached positions [t_begin, t_end) of request r, kv head g, taking every `stride`-th
+    // chunk of 16; t_begin is a multiple of 16.  q: the lane's column's row (nullptr: no column), of
+    // which positions at or past `limit` do not count; every column sees the positions before min_limit.
+    static __device__ __forceinline__ void reduce(const DecodeArgs &a, int r, int g, const float *q, int limit, int min_limit,
+                                                  int t_begin, int t_end, int stride, State &st)
+    {
+        const int lane = threadIdx.x & 63, j = lane & 15, qd = lane >> 4;
+        f32x4 qb[NK];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {
+            qb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (q) qb[i] = *reinterpret_cast<const f32x4 *>(q + 16 * i + 4 * qd);
+        }
+        float m = kLowest, l = 0.0f;                  // l: of this lane's tokens, until the end
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int v = 0; v < VW; ++v) st.o[c][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+        const int n_chunks = (t_end - t_begin + CT * stride - 1) / (CT * stride);
+        const int32_t *table = a.block_table + (size_t)r * a.max_blocks;
+        const size_t tile = (size_t)a.block_size * D, block_stride = (size_t)a.num_layers * a.num_kv_heads * tile;
+        const size_t head_off = ((size_t)a.layer * a.num_kv_heads + g) * tile;
+        const float *kp = static_cast<const float *>(a.k_pool) + head_off + j * D + 4 * qd;
+        const float *vp = static_cast<const float *>(a.v_pool) + head_off + 4 * qd * D + VW * j;
+
+        // As in MfmaReducer: chunk c + 1 is asked for before chunk c is consumed, the table entry of
+        // chunk c + 2 with it.
+        auto entry = [&](int c) -> int {
+            return c < n_chunks ? table[(t_begin + c * CT * stride) >> a.log2_block_size] : 0;
+        };
+        auto issue = [&](int c, int block, f32x4 (&kx)[NK], vvec (&vx)[4][NC]) {
+            const int t = t_begin + c * CT * stride;
+            const size_t off = (size_t)block * block_stride + (size_t)(t & (a.block_size - 1)) * D;
+            // (wave-uniform) an entry that names no block of the pool counts as zeros
+            if ((unsigned)block < (unsigned)a.num_blocks) {
+#pragma unroll
+                for (int i = 0; i < NK; ++i) kx[i] = *reinterpret_cast<const f32x4 *>(kp + off + 16 * i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = *reinterpret_cast<const vvec *>(vp + off + e * D + 16 * VW * c2);
+            } else {
+#pragma unroll
+                for (int i = 0; i < NK; ++i) kx[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = vvec{};
+            }
+        };
+        f32x4 kx[NK], kn[NK];
+        vvec vx[4][NC], vn[4][NC];
+        int pb1 = entry(1);
+        if (n_chunks > 0) issue(0, entry(0), kx, vx);
+        for (int ch = 0; ch < n_chunks; ++ch) {
+            const int t0 = t_begin + ch * CT * stride;
+            const int pb2 = entry(ch + 2);
+            if (ch + 1 < n_chunks) issue(ch + 1, pb1, kn, vn);
+            pb1 = pb2;
+
+            f32x4 s = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};   // tokens t0 + 4 qd + e of the lane's column
+#pragma unroll
+            for (int i = 0; i < NK; ++i) {            // two chains: an MFMA does not wait for the one before it
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][0], qb[i][0], s, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][1], qb[i][1], s2, 0, 0, 0);
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][2], qb[i][2], s, 0, 0, 0);
+                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][3], qb[i][3], s2, 0, 0, 0);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] = (s[e] + s2[e]) * a.scale_log2e;
+            bool wild = false;                        // uniform: a value that not every column sees is no finite number
+            if (t0 + CT > min_limit || t0 + CT > t_end) {   // uniform: some column does not see the whole chunk
+                const int seen = min(limit, t_end) - (t0 + 4 * qd);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e >= seen) s[e] = -INFINITY;
+                if (t0 + CT > t_end)                  // a zero weight does not silence a NaN: slots past the end are zeroed
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (t0 + 4 * qd + e >= t_end)
+#pragma unroll
+                            for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = vvec{};
+                if (min_limit < t_end) {
+                    float z = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int c2 = 0; c2 < NC; ++c2)
+#pragma unroll
+                            for (int v = 0; v < VW; ++v) z = fmaf(vx[e][c2][v], 0.0f, z);
+                    wild = __any(z != 0.0f);          // (NaN)
+                }
+            }
+            float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mn = fmaxf(m, mx);
+            const float sc = fast_exp2(m - mn);
+            m = mn;
+            float ps = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                s[e] = fast_exp2(s[e] - mn);
+                ps += s[e];
+            }
+            l = l * sc + ps;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int v = 0; v < VW; ++v)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st.o[c][v][e] *= sc;
+            if (!wild) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int v = 0; v < VW; ++v)
+                            st.o[c][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(vx[e][c][v], s[e], st.o[c][v], 0, 0, 0);
+            } else {                                  // once per limit, the values past it zeroed, kept by its columns
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+#pragma unroll
+                    for (int v = 0; v < VW; ++v) {
+                        f32x4 kept = st.o[c][v];
+                        for (int lim = min_limit; lim <= t_end; ++lim) {
+                            f32x4 t = st.o[c][v];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                t = __builtin_amdgcn_mfma_f32_16x16x4f32(t0 + 4 * qd + e < lim ? vx[e][c][v] : 0.0f, s[e], t, 0, 0, 0);
+                            if (limit == lim) kept = t;
+                        }
+                        st.o[c][v] = kept;
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < NK; ++i) kx[i] = kn[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = vn[e][c2];
+        }
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        st.m = m;
+        st.l = l;
     }
 };
 

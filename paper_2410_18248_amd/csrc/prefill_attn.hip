@@ -27,8 +27,7 @@ __device__ __forceinline__ int request_of(const int32_t *q_start, int batch, int
 
 // One wavefront per (new token, kv head / pass): the decode reducer over the
 // token's own prefix.  Every K/V byte is read once per new token, so this form
-// is for few new tokens per request and for the geometries the matrix-core
-// kernel does not cover.
+// is for the geometries the matrix-core kernels do not cover, and on request.
 template <typename R>
 __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
 {
@@ -58,7 +57,126 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
     });
 }
 
-// ---------------------------------------------------------------- matrix cores
+// Which (request, kv head) pair and tile of new tokens a workgroup of a grid of `pairs` x `tiles`
+// takes.  All tiles of one pair run on one XCD (workgroups are dealt to the 8 XCDs round-robin in
+// launch order), so its K/V stream is fetched into one L2 and shared there; consecutive kv heads go
+// to different XCDs; the longest tiles of a pair start first.  That holds for the pairs that fill
+// whole groups of 8; the (pair, tile) items of the remaining 1..7 pairs are dealt round-robin over
+// all XCDs instead of leaving some of them empty.
+__device__ __forceinline__ bool pair_and_tile(int pairs, int tiles, int full_groups, int &pair, int &tile)
+{
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    int t;
+    if (slot < full_groups * tiles) {
+        pair = xcd + 8 * (slot / tiles);
+        t = slot % tiles;
+    } else {
+        const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
+        const int at = (slot - full_groups * tiles) * 8 + xcd;
+        pair = 8 * full_groups + at % rest;
+        t = at / rest;
+    }
+    tile = tiles - 1 - t;
+    return t < tiles;
+}
+// The grid for it; 0: too large.
+unsigned pair_grid(long long pairs, long long tiles, int *full_groups)
+{
+    const long long full = pairs / 8, rest = pairs % 8;
+    const long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
+    *full_groups = (int)full;
+    return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
+}
+
+// ---------------------------------------------------------------- matrix cores, 32 bits
+
+// fp32.  A workgroup takes one tile of 16 columns -- (new token, head of the pass) pairs of one kv
+// head -- and its four waves every fourth chunk of 16 positions each; their states are added up
+// through LDS.  Bound by the fp32 matrix rate on long prompts (each K / V byte from L2 serves 16
+// columns) and by the walk over the positions on short ones, which is why the waves share it:
+// six prompts of 17 to 700 tokens, 8 heads of 64: 27 us with a wavefront per token on the vector ALUs
+// (every K / V byte read once per token), 13 now.
+// Heads of a group that share a tile: the largest divisor up to 16.
+__host__ __device__ __forceinline__ int f32_tile_heads(int group)
+{
+    int gh = group < 16 ? group : 16;
+    while (group % gh) --gh;
+    return gh;
+}
+
+template <int D>
+__global__ __launch_bounds__(kThreads) void prefill_tiles_f32(const PrefillArgs p, const int tiles, const int full_groups)
+{
+    typedef MfmaF32Tile<D> R;
+    constexpr int ROW = D + 4;                        // floats; 16-byte aligned, rows in different banks
+    __shared__ __align__(16) float part[kWaves][16][ROW];
+    __shared__ float2 stat[kWaves][16];
+    const DecodeArgs &a = p.d;
+    const int G = a.num_q_heads / a.num_kv_heads, GH = f32_tile_heads(G), passes = G / GH, HC = a.num_kv_heads * passes;
+    const int TW = 16 / GH;                           // new tokens per tile
+    int pair, tile;
+    if (!pair_and_tile(HC * a.batch, tiles, full_groups, pair, tile)) return;
+    const int r = pair / HC, hc = pair - r * HC, g = hc / passes, h0 = g * G + hc % passes * GH;
+    const int first = p.q_start[r], n_new = p.q_start[r + 1] - first;
+    if (tile * TW >= n_new) return;
+    const int C = a.ctx_lens[r], base_pos = C - n_new;
+    // a context shorter than its new tokens, or longer than the block-table row, is the caller's
+    // mistake: nothing is read or written for it
+    if (base_pos < 0 || C > a.max_blocks * a.block_size) return;
+    const int lane = threadIdx.x & 63, j = lane & 15, qd = lane >> 4, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int toks = min(TW, n_new - tile * TW);
+    const int tok = j / GH;                           // this lane's column: token tile * TW + tok, head h0 + j % GH
+    const bool ok = tok < toks;
+    const float *q = static_cast<const float *>(a.q) + ((size_t)(first + tile * TW + tok) * a.num_q_heads + h0 + j % GH) * D;
+    const int seen = base_pos + tile * TW + 1;        // positions the tile's first token attends to
+    typename R::State st;
+    R::reduce(a, r, g, ok ? q : nullptr, ok ? seen + tok : 0, seen, 16 * wv, seen + toks - 1, kWaves, st);
+    if (qd == 0) stat[wv][j] = make_float2(st.m, st.l);
+#pragma unroll
+    for (int c = 0; c < R::NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < R::VW; ++v) part[wv][j][16 * R::VW * c + R::VW * (4 * qd + e) + v] = st.o[c][v][e];
+    __syncthreads();
+    const int col = threadIdx.x >> 4, x = threadIdx.x & 15, t = col / GH;
+    if (t >= toks) return;
+    float M = kLowest, L = 0.0f, f[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, stat[w][col].x);
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        f[w] = fast_exp2(stat[w][col].x - M);
+        L += stat[w][col].y * f[w];
+    }
+    float *out = static_cast<float *>(a.out) + ((size_t)(first + tile * TW + t) * a.num_q_heads + h0 + col % GH) * D;
+    for (int d = 4 * x; d < D; d += 64) {
+        f32x4 A = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const f32x4 o = *reinterpret_cast<const f32x4 *>(&part[w][col][d]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) A[e] += o[e] * f[w];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) A[e] = L > 0.0f ? A[e] / L : 0.0f;
+        *reinterpret_cast<f32x4 *>(out + d) = A;
+    }
+}
+
+template <int D>
+hipError_t launch_tiles_f32(const PrefillArgs &p, hipStream_t s)
+{
+    const int GH = f32_tile_heads(p.d.num_q_heads / p.d.num_kv_heads), TW = 16 / GH;
+    const long long pairs = (long long)p.d.num_q_heads / GH * p.d.batch, tiles = (p.max_new_tokens + TW - 1) / TW;
+    int full = 0;
+    const unsigned grid = pair_grid(pairs, tiles, &full);
+    if (grid == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(prefill_tiles_f32<D>, dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- matrix cores, bf16
 
 // bf16, up to 32 query heads per kv head.  With many new tokens per request both
 // products of the Section 2.2 equation are real contractions: for one kv head,
@@ -248,19 +366,13 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     __shared__ __align__(16) char lds[NB * GSTAGE];
 
     const DecodeArgs &a = p.d;
-    // All tiles of one (request, kv head) run on one XCD (workgroups are dealt to the 8 XCDs
-    // round-robin in launch order), so its K/V stream is fetched into one L2 and shared there;
-    // consecutive kv heads go to different XCDs; the longest tiles of a pair start first.  That
-    // holds for the pairs that fill whole groups of 8; the (pair, tile) items of the remaining
-    // 1..7 pairs are dealt round-robin over all XCDs instead of leaving some of them empty.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int TW = kCols / (a.num_q_heads / a.num_kv_heads);   // new tokens per wave (G <= kCols)
     const int WT = kWaves * TW;                      // ... per workgroup
     int r, g, tile, first, n_new, C;
     int item = 0, st0 = 0, per = 0x7fffffff;         // SPLIT: the workgroup's item, first stage, most stages,
     int first_item = 0, item_stride = 0;             // ... and the items of its tile's runs
     if constexpr (SPLIT) {
-        item = xcd * (p.slots >> 3) + slot;          // neighbours in item order share blocks: one XCD
+        item = (blockIdx.x & 7) * (p.slots >> 3) + (blockIdx.x >> 3);   // neighbours in item order share blocks: one XCD
         const Run run = locate(p, tiles, WT, item);
         if (run.r < 0) return;
         r = run.r;
@@ -274,19 +386,8 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         item_stride = run.stride;
         st0 = (item - run.first_item) / run.stride * per;
     } else {
-        const int pairs = a.num_kv_heads * a.batch;
-        int pair, t;
-        if (slot < full_groups * tiles) {
-            pair = xcd + 8 * (slot / tiles);
-            t = slot % tiles;
-        } else {
-            const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
-            const int at = (slot - full_groups * tiles) * 8 + xcd;
-            pair = 8 * full_groups + at % rest;
-            t = at / rest;
-            if (t >= tiles) return;
-        }
-        tile = tiles - 1 - t;
+        int pair;
+        if (!pair_and_tile(a.num_kv_heads * a.batch, tiles, full_groups, pair, tile)) return;
         r = pair / a.num_kv_heads;
         g = pair - r * a.num_kv_heads;
         first = p.q_start[r];
@@ -727,19 +828,17 @@ hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
     const int WT = kWaves * (kCols / G);
     const long long tiles = (p.max_new_tokens + WT - 1) / WT;
     const long long pairs = (long long)p.d.num_kv_heads * p.d.batch;
-    const long long full = pairs / 8, rest = pairs % 8;   // whole groups of 8 pairs, and the pairs left over
-    const long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
-    if (tiles < 1 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    int full = 0;
+    const unsigned grid = pair_grid(pairs, tiles, &full);
+    if (grid == 0) return hipErrorInvalidValue;
     // Two stages per barrier where they fit and a request has many new tokens (the matrix cores
     // bind: +2-5 %); with one tile per request the kernel is a stream over the cache, and the
     // finer grain is the faster one (+3 %).
     constexpr bool kFits = 2 * 2 * (4 * 16 * D * 2) <= 65536;
     if (kFits && tiles > 1)
-        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, kFits ? 2 : 1, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, p,
-                           (int)tiles, (int)full);
+        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, kFits ? 2 : 1, false>), dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
     else
-        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, false>), dim3((unsigned)grid), dim3(kThreads), 0, s, p, (int)tiles,
-                           (int)full);
+        hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, false>), dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
     return hipGetLastError();
 }
 
@@ -753,17 +852,13 @@ hipError_t launch_rows(const PrefillArgs &p, hipStream_t s)
     return hipGetLastError();
 }
 
-template <bool BF16, int LPT>
-hipError_t launch_rows_valu(const PrefillArgs &p, hipStream_t s)
+template <int LPT>
+hipError_t launch_rows_f32(const PrefillArgs &p, hipStream_t s)
 {
     switch (p.d.heads_per_pass) {
-    case 1: return launch_rows<ValuReducer<BF16, LPT, 1, kHalves>>(p, s);
-    case 2:
-        if constexpr (!BF16) return launch_rows<ValuReducer<BF16, LPT, 2, kHalves>>(p, s);
-        break;
-    case 4:
-        if constexpr (!BF16) return launch_rows<ValuReducer<BF16, LPT, 4, 1>>(p, s);
-        break;
+    case 1: return launch_rows<ValuReducer<false, LPT, 1, kHalves>>(p, s);
+    case 2: return launch_rows<ValuReducer<false, LPT, 2, kHalves>>(p, s);
+    case 4: return launch_rows<ValuReducer<false, LPT, 4, 1>>(p, s);
     }
     return hipErrorInvalidValue;
 }
@@ -794,13 +889,17 @@ hipError_t launch_prefill(const PrefillArgs &p, hipStream_t stream)
         if (a.head_dim == 128) return launch_rows<MfmaReducer<128>>(p, stream);
         if (a.head_dim == 256) return launch_rows<MfmaReducer<256>>(p, stream);
     } else if (a.bf16) {
-        if (lpt == 8) return launch_rows_valu<true, 8>(p, stream);
-        if (lpt == 16) return launch_rows_valu<true, 16>(p, stream);
-        if (lpt == 32) return launch_rows_valu<true, 32>(p, stream);
+        if (lpt == 8) return launch_rows<ValuReducer<true, 8, 1, kHalves>>(p, stream);
+        if (lpt == 16) return launch_rows<ValuReducer<true, 16, 1, kHalves>>(p, stream);
+        if (lpt == 32) return launch_rows<ValuReducer<true, 32, 1, kHalves>>(p, stream);
+    } else if (!p.force_rows) {
+        if (a.head_dim == 32) return launch_tiles_f32<32>(p, stream);
+        if (a.head_dim == 64) return launch_tiles_f32<64>(p, stream);
+        if (a.head_dim == 128) return launch_tiles_f32<128>(p, stream);
     } else {
-        if (lpt == 8) return launch_rows_valu<false, 8>(p, stream);
-        if (lpt == 16) return launch_rows_valu<false, 16>(p, stream);
-        if (lpt == 32) return launch_rows_valu<false, 32>(p, stream);
+        if (lpt == 8) return launch_rows_f32<8>(p, stream);
+        if (lpt == 16) return launch_rows_f32<16>(p, stream);
+        if (lpt == 32) return launch_rows_f32<32>(p, stream);
     }
     return hipErrorInvalidValue;
 }
