@@ -164,11 +164,18 @@ __device__ __forceinline__ int chunks_of(int running, int C, int CT)
 // position inside a head's stretch, XCD 0 first: the waves that walk the same
 // blocks at the same time then sit on one XCD, next to each other.  With pools of
 // 100 GB and more this is worth several per cent; with small pools it is neutral.
-template <typename R>
+//
+// TOGETHER: a share belongs to a workgroup, whose four waves take a quarter of each of its ranges
+// and add the quarters up in LDS.  For launches with few ranges for the waves (a few requests, or
+// long ones): a quarter of the pieces to write, and to read and add up in the second kernel.  Both
+// launches, a share per wave -> per workgroup: 24 fp32 requests of 17 to 2 500 tokens, 32 / 8 heads of
+// 128, 40.8 -> 33.0 us; 19 of 32 requests of 4 096 to 32 768 tokens, 32 / 8 heads, 209.7 -> 205.3; one
+// request of 1 999 tokens 14.5 -> 13.2.
+template <typename R, bool TOGETHER>
 __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 {
     constexpr int D = R::D, CT = R::CT;
-    extern __shared__ int prefix[];
+    extern __shared__ int prefix[];                   // TOGETHER: then [wave][head][D + 2] floats
     __shared__ int wave_total[kWaves], wave_longest[kWaves];
 
     const int B = a.batch;
@@ -219,16 +226,18 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     const int T = __builtin_amdgcn_readfirstlane(prefix[B]);   // chunks per head / pass
     const long long total = (long long)HC * T;
     longest = __builtin_amdgcn_readfirstlane(longest);
-    // from here on every wave is on its own: no barrier below
-    int P = gridDim.x * kWaves;
-    int share = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(wv);
+    // from here on every wave is on its own: no barrier below (TOGETHER: every workgroup, and its waves alike)
+    constexpr int kOwnShares = TOGETHER ? 1 : kWaves;  // of a workgroup
+    const int sub = TOGETHER ? 0 : __builtin_amdgcn_readfirstlane(wv);
+    int P = gridDim.x * kOwnShares;
+    int share = blockIdx.x * kOwnShares + sub;
     // A launch with little work and a long range in it: equal shares over all wavefronts would
     // cut that range into hundreds of pieces of a chunk each, and the merge of one range is a
     // chain of dependent loads (a 40 000-token request among 70 short ones, 2 heads: 10 us of
     // attention, 200 us of merge).  Then only as many shares are used as gives each 2, 4 or
     // 8 chunks -- for a longest range of 256, 512, 1024 chunks and more -- and the rest stay
-    // empty.
-    const int log2_share_chunks = longest >= 1024 ? 3 : longest >= 512 ? 2 : longest >= 256 ? 1 : 0;
+    // empty.  TOGETHER: a chunk per wave at least, and the rest as for a range a quarter as long.
+    const int log2_share_chunks = TOGETHER ? (longest >= 4096 ? 5 : longest >= 2048 ? 4 : longest >= 1024 ? 3 : 2) : longest >= 1024 ? 3 : longest >= 512 ? 2 : longest >= 256 ? 1 : 0;
     const long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
     if (wanted < P) {
         P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
@@ -240,8 +249,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         // rank = (share * HC mod P) + share / (P / gcd) orders the shares by where they
         // start inside a head's stretch; this wave takes the share of rank
         // (XCD, index inside the XCD), found by inverting that
-        const int rank = (blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3) * kWaves +
-                         __builtin_amdgcn_readfirstlane(wv);
+        const int rank = (blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3) * kOwnShares + sub;
         const int tie = rank % a.share_gcd, period = P / a.share_gcd;
         share = (int)((long long)(rank / a.share_gcd) * a.share_inv % period) + tie * period;
     }
@@ -278,13 +286,40 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         // a share's first range goes to slot 0, a later partial one (its last) to slot 1
         float *slot = a.partials + ((size_t)share * 2 + (x == x_begin ? 0 : 1)) * GH * (D + 2);
         const size_t rh0 = (size_t)r * a.num_q_heads + h0;
-        R::run(a, r, (size_t)r, g, h0, GH, c0 * CT, min(C, (c0 + len) * CT),
-               [&](int h, int d, float M, float L, float A) {
-                   if (whole)
-                       store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
-                   else
-                       store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
-               });
+        if constexpr (TOGETHER) {
+            float *part = reinterpret_cast<float *>(prefix) + ((B + 4) & ~3);
+            const int each = (len + kWaves - 1) / kWaves, from = min(len, each * __builtin_amdgcn_readfirstlane(wv));
+            float *mine = part + (size_t)__builtin_amdgcn_readfirstlane(wv) * GH * (D + 2);
+            R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * CT, min(C, (c0 + min(len, from + each)) * CT),
+                   [&](int h, int d, float M, float L, float A) { store_partial(mine + h * (D + 2), D, d, M, L, A); });
+            __syncthreads();
+            for (int i = tid; i < GH * D; i += kThreads) {
+                const int h = i / D, d = i % D;
+                const float *x = part + h * (D + 2);
+                float M = kLowest, L = 0.0f, A = 0.0f;
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) M = fmaxf(M, x[w * GH * (D + 2) + D]);
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) {
+                    const float f = fast_exp2(x[w * GH * (D + 2) + D] - M);
+                    L += x[w * GH * (D + 2) + D + 1] * f;
+                    A += x[w * GH * (D + 2) + d] * f;
+                }
+                if (whole)
+                    store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+                else
+                    store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
+            }
+            __syncthreads();                          // before the next range's parts
+        } else {
+            R::run(a, r, (size_t)r, g, h0, GH, c0 * CT, min(C, (c0 + len) * CT),
+                   [&](int h, int d, float M, float L, float A) {
+                       if (whole)
+                           store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+                       else
+                           store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
+                   });
+        }
         if (c0 == 0 && len < nr)
             owned = make_int4(r, hc, (int)share_of(x + nr - 1, total, P),
                               kShareOwner | (x == x_begin ? 0 : kShareSlot1));
@@ -295,24 +330,27 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
             } while (prefix[r + 1] == prefix[r]);
         }
     }
-    if (lane == 0) a.share_info[share] = owned;
+    if (TOGETHER ? tid == 0 : lane == 0) a.share_info[share] = owned;
 }
 
-// N pieces of a split range, their loads in flight together, folded into the running
-// (M, L, A0, A1) of the lane's two outputs.  slot holds one piece per lane (-1: an empty
-// share); i0 and cnt are the same in every lane.
+// N pieces of a split range (first, first + 1, ... in slot order; at most cnt of them), their loads
+// in flight together, folded into the running (M, L, A0, A1) of the lane's two outputs.
 template <int N>
-__device__ __forceinline__ void merge_pieces(const float *partials, int slot, int i0, int cnt, int GH, int h,
+__device__ __forceinline__ void merge_pieces(const float *partials, int w, int w_first, int first_slot, int cnt, int GH, int h,
                                              int D, int d, float &M, float &L, float &A0, float &A1)
 {
     float2 ml[N], ao[N];                               // rows of the partials are 8-byte aligned
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const int pc = __builtin_amdgcn_readlane(slot, min(i0 + k, 63));
-        const bool have = i0 + k < cnt && pc >= 0;
-        const float2 *x = reinterpret_cast<const float2 *>(partials + ((size_t)max(pc, 0) * GH + h) * (D + 2));
-        ml[k] = have ? x[D / 2] : make_float2(kLowest, 0.0f);
-        ao[k] = have ? x[d / 2] : make_float2(0.0f, 0.0f);
+        // the range's first share knows its slot; later ones start inside the range: slot 0
+        ml[k] = make_float2(kLowest, 0.0f);
+        ao[k] = make_float2(0.0f, 0.0f);
+        if (k < cnt) {                                 // uniform
+            const int slot = 2 * (w + k) + (w + k == w_first ? first_slot : 0);
+            const float2 *x = reinterpret_cast<const float2 *>(partials + ((size_t)slot * GH + h) * (D + 2));
+            ml[k] = x[D / 2];
+            ao[k] = x[d / 2];
+        }
     }
     float Mn = M;
 #pragma unroll
@@ -331,163 +369,86 @@ __device__ __forceinline__ void merge_pieces(const float *partials, int slot, in
     }
 }
 
-// Merges the pieces of every (request, kv head / pass) that was split over
-// several shares, in share order (= token order).  One wavefront per share and
-// slice of 128 (head, dim) outputs, two outputs per lane: the share that holds the
-// start of a split range merges it, eight pieces' loads in flight at a time (most
-// waves find nothing to do and leave after one load).  A wave works alone: the
-// piece list lives in a register, one piece per lane, and is read with readlane.
-// The grid is small on purpose (the launcher also folds up to 16 wavefronts into a
-// workgroup): launching a workgroup that leaves at once costs
-// about a nanosecond, and a block per share and 256 outputs spent most of this
-// kernel's time on that.
+// Merges the pieces of every (request, kv head / pass) that was split over several shares, in
+// share order (= token order).  A workgroup looks at kMergeShares consecutive shares -- one wavefront
+// each, and a slice of 128 (head, dim) outputs, two per lane -- and merges the ranges that start in
+// them.  The wavefronts divide those ranges evenly: with one range per share each has one and
+// works alone; with few and therefore long ranges (a small batch of long contexts: hundreds of
+// pieces each) several wavefronts take a stretch of the same range's pieces and the first of them
+// adds the stretches up, in order, through LDS.  Two round trips to memory, the share records and the
+// pieces, whatever the lengths: up to 128 pieces are asked for at once.  (What the kernel costs is its
+// launch and those round trips: 4.2-5.5 us on batches of 1 to 256 requests.  Before, a wave walked
+// each range alone, eight pieces and a list of their slots at a time: the fp32 batch above, 21 pieces
+// per range, 13.2 us, 12.2 with the waves sharing, 4.3 with a quarter of the pieces.)
+constexpr int kMergeShares = 16;
+
 template <bool BF16>
-__global__ __launch_bounds__(1024) void decode_merge_balanced(const DecodeArgs a)
+__global__ __launch_bounds__(64 * kMergeShares) void decode_merge_balanced(const DecodeArgs a, const int shares)
 {
-    const int lane = threadIdx.x & 63;
-    const int w_first = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    const int4 owned = a.share_info[w_first];
-    if (!(owned.w & kShareOwner)) return;
-    const int r = __builtin_amdgcn_readfirstlane(owned.x), hc = __builtin_amdgcn_readfirstlane(owned.y);
-    const int w_last = __builtin_amdgcn_readfirstlane(owned.z);
-    const int first_flags = __builtin_amdgcn_readfirstlane(owned.w);
+    __shared__ float4 stretch[kMergeShares][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int base = blockIdx.x * kMergeShares;
+    int4 rec = make_int4(0, 0, 0, 0);                  // lane i: the record of share base + i
+    if (lane < kMergeShares && base + lane < shares) rec = a.share_info[base + lane];
+    const unsigned owners = (unsigned)__ballot(rec.w & kShareOwner);
+    const int n = __popc(owners);                      // ranges that start here
+    if (n == 0) return;                                // uniform over the workgroup, like everything but `part`
+    const bool any_long = __any((rec.w & kShareOwner) && rec.z - (base + lane) >= 8);   // more than one round of loads
+    const int parts = any_long ? kMergeShares / n : 1, part = wv / n;
+    unsigned left = owners;
+    for (int k = wv % n; k > 0; --k) left &= left - 1;
+    const int own = __ffs((int)left) - 1;              // this wave's range: the (wv % n)th of them
+    const int r = __builtin_amdgcn_readlane(rec.x, own), hc = __builtin_amdgcn_readlane(rec.y, own);
+    const int w_first = base + own, w_last = __builtin_amdgcn_readlane(rec.z, own);
+    const int first_slot = (__builtin_amdgcn_readlane(rec.w, own) & kShareSlot1) ? 1 : 0;
     const int D = a.head_dim;
     const int G = a.num_q_heads / a.num_kv_heads;
     const int GH = a.heads_per_pass;
     const int passes = G / GH;
-    const size_t rh0 = (size_t)r * a.num_q_heads + (hc / passes) * G + (hc % passes) * GH;
     const int idx = blockIdx.y * 128 + 2 * lane;       // the lane's two outputs: same head, d even
     const bool live = idx < GH * D;
     const int h = live ? idx / D : 0, d = live ? idx % D : 0;
     float M = kLowest, L = 0.0f, A0 = 0.0f, A1 = 0.0f;
-    // lane i: where piece i of a pass of 64 lies.  The first share knows its slot; later ones
-    // start inside the range: slot 0.
-    auto slots_of = [&](int w0) {
-        const int w = w0 + lane;
-        if (w > w_last) return -1;
-        const int f = w == w_first ? first_flags : a.share_info[w].w;
-        return (f & kShareEmpty) ? -1 : w * 2 + ((w == w_first && (f & kShareSlot1)) ? 1 : 0);
-    };
-    int slot_next = slots_of(w_first);
-    for (int w0 = w_first; w0 <= w_last; w0 += 64) {
-        const int cnt = min(64, w_last - w0 + 1);
-        const int slot = slot_next;
-        slot_next = slots_of(w0 + 64);                 // asked for together with this pass's pieces
-        for (int i0 = 0; i0 < cnt; i0 += 8)            // share order = token order
-            merge_pieces<8>(a.partials, slot, i0, cnt, GH, h, D, d, M, L, A0, A1);
+    const int each = (w_last - w_first + parts) / parts;
+    const int w_end = min(w_last + 1, w_first + (part + 1) * each);
+    if (part < parts)
+        for (int w = w_first + part * each; w < w_end; w += 8)
+            merge_pieces<8>(a.partials, w, w_first, first_slot, min(8, w_end - w), GH, h, D, d, M, L, A0, A1);
+    if (parts > 1) {
+        stretch[wv][lane] = make_float4(M, L, A0, A1);
+        __syncthreads();
+    }
+    if (part > 0) return;
+    if (parts > 1) {
+        for (int k = 1; k < parts; ++k) {
+            const float4 o = stretch[wv + k * n][lane];
+            const float Mn = fmaxf(M, o.x), f0 = fast_exp2(M - Mn), f1 = fast_exp2(o.x - Mn);
+            L = L * f0 + o.y * f1;
+            A0 = A0 * f0 + o.z * f1;
+            A1 = A1 * f0 + o.w * f1;
+            M = Mn;
+        }
     }
     if (live) {
-        store_out<BF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A0 / L : 0.0f);
-        store_out<BF16>(a.out, (rh0 + h) * D + d + 1, L > 0.0f ? A1 / L : 0.0f);
-    }
-}
-
-// The same merge for a small batch of long contexts.  A range then has hundreds of
-// pieces, and one lane per output pair walking them eight at a time is a long serial
-// chain.  Here a block looks at 16 shares and, for each owner among them (there are
-// few), takes 32 outputs of one query head of its range: 32 groups of 8 threads,
-// four outputs per thread; group j merges the pieces j, j + 32, ... eight in flight
-// per thread, so one pass covers the 256 pieces that the piece list resolves at a
-// time; the groups' states are merged by a fixed tree through LDS at the end.
-template <bool BF16, int D>
-__global__ __launch_bounds__(256) void decode_merge_wide(const DecodeArgs a)
-{
-    constexpr int QUADS = 8, GROUPS = 32, INFL = 8;
-    const int tid = threadIdx.x, j = tid / QUADS, q = tid % QUADS;
-    const int G = a.num_q_heads / a.num_kv_heads;
-    const int GH = a.heads_per_pass;
-    const int passes = G / GH;
-    const int h = blockIdx.y;                          // query head of the pass
-    const int d0 = blockIdx.z * 32 + 4 * q;            // first of this thread's four outputs
-    __shared__ int4 owners[kWideShares];
-    __shared__ int piece[256];
-    __shared__ float state[GROUPS][QUADS][6];
-    if (tid < kWideShares) owners[tid] = a.share_info[blockIdx.x * kWideShares + tid];
-    __syncthreads();
-    for (int s = 0; s < kWideShares; ++s) {
-        const int4 owned = owners[s];
-        if (!(owned.w & kShareOwner)) continue;        // the same for the whole block
-        const int r = owned.x, hc = owned.y;
-        const int w_first = blockIdx.x * kWideShares + s, w_last = owned.z;
-        const size_t row = (size_t)r * a.num_q_heads + (hc / passes) * G + (hc % passes) * GH + h;
-        float M = kLowest, L = 0.0f, A[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int w0 = w_first; w0 <= w_last; w0 += 256) {
-            const int cnt = min(256, w_last - w0 + 1);
-            __syncthreads();
-            if (tid < cnt) {
-                const int w = w0 + tid;
-                const int f = w == w_first ? owned.w : a.share_info[w].w;
-                piece[tid] = (f & kShareEmpty) ? -1 : w * 2 + ((w == w_first && (f & kShareSlot1)) ? 1 : 0);
-            }
-            __syncthreads();
-            float2 ml[INFL], ao[INFL][2];              // rows of the partials are 8-byte aligned
-#pragma unroll
-            for (int k = 0; k < INFL; ++k) {
-                const int i = j + k * GROUPS;
-                const int pc = i < cnt ? piece[i] : -1;
-                const float2 *x = reinterpret_cast<const float2 *>(
-                    a.partials + ((size_t)max(pc, 0) * GH + h) * (D + 2));
-                ml[k] = pc >= 0 ? x[D / 2] : make_float2(kLowest, 0.0f);
-                ao[k][0] = pc >= 0 ? x[d0 / 2] : make_float2(0.0f, 0.0f);
-                ao[k][1] = pc >= 0 ? x[d0 / 2 + 1] : make_float2(0.0f, 0.0f);
-            }
-            float Mn = M;
-#pragma unroll
-            for (int k = 0; k < INFL; ++k) Mn = fmaxf(Mn, ml[k].x);
-            const float f0 = fast_exp2(M - Mn);
-            L *= f0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) A[e] *= f0;
-            M = Mn;
-#pragma unroll
-            for (int k = 0; k < INFL; ++k) {
-                const float f = fast_exp2(ml[k].x - M);
-                L += ml[k].y * f;
-                A[0] += ao[k][0].x * f;
-                A[1] += ao[k][0].y * f;
-                A[2] += ao[k][1].x * f;
-                A[3] += ao[k][1].y * f;
-            }
-        }
-        __syncthreads();                               // the state of the owner before is read
-        float *mine = state[j][q];
-        mine[0] = M;
-        mine[1] = L;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mine[2 + e] = A[e];
-        __syncthreads();
-        for (int half = GROUPS / 2; half >= 1; half /= 2) {   // a fixed tree over the groups
-            if (j < half) {
-                const float *t = state[j + half][q];
-                const float Mn = fmaxf(M, t[0]);
-                const float f0 = fast_exp2(M - Mn), f1 = fast_exp2(t[0] - Mn);
-                L = L * f0 + t[1] * f1;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) A[e] = A[e] * f0 + t[2 + e] * f1;
-                M = Mn;
-            }
-            __syncthreads();
-            if (j >= half / 2 && j < half) {           // the upper half of the next level publishes
-                mine[0] = M;
-                mine[1] = L;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) mine[2 + e] = A[e];
-            }
-            __syncthreads();
-        }
-        if (j == 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                store_out<BF16>(a.out, row * D + d0 + e, L > 0.0f ? A[e] / L : 0.0f);
-        }
+        const size_t at = ((size_t)r * a.num_q_heads + (hc / passes) * G + (hc % passes) * GH + h) * D + d;
+        store_out<BF16>(a.out, at, L > 0.0f ? A0 / L : 0.0f);
+        store_out<BF16>(a.out, at + 1, L > 0.0f ? A1 / L : 0.0f);
     }
 }
 
 // ---------------------------------------------------------------- launchers
 
-// Workgroups the chip holds at once for decode_balanced<R>, per device (asked once per device and
+// LDS of a decode_balanced launch: the chunk prefix and, TOGETHER, the waves' parts.
+template <typename R, bool TOGETHER>
+size_t balanced_lds(int batch, int heads_per_pass)
+{
+    return TOGETHER ? ((batch + 4) & ~3) * sizeof(int) + (size_t)kWaves * heads_per_pass * (R::D + 2) * sizeof(float)
+                    : (batch + 1) * sizeof(int);
+}
+
+// Workgroups the chip holds at once for decode_balanced<R, TOGETHER>, per device (asked once per device and
 // instantiation; every thread that asks computes the same).
-template <typename R>
+template <typename R, bool TOGETHER>
 hipError_t resident_workgroups(const DecodeArgs &a, int *out)
 {
     static std::atomic<int> resident_on[kMaxDevices];
@@ -500,8 +461,8 @@ hipError_t resident_workgroups(const DecodeArgs &a, int *out)
         int cus = 0, per_cu = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_balanced<R>, kThreads,
-                                                             (a.max_batch + 1) * sizeof(int));
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_balanced<R, TOGETHER>, kThreads,
+                                                             balanced_lds<R, false>(a.max_batch, 1));
         if (e != hipSuccess) return e;
         if (cus < 1 || per_cu < 1) return hipErrorInvalidValue;
         resident = cus * per_cu;
@@ -509,6 +470,37 @@ hipError_t resident_workgroups(const DecodeArgs &a, int *out)
     }
     *out = resident;
     return hipSuccess;
+}
+
+// The two launches of the balanced scheme over `wgs` workgroups.
+template <typename R, bool TOGETHER>
+hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
+{
+    const int HC = a.num_q_heads / a.heads_per_pass;
+    const int P = wgs * (TOGETHER ? 1 : kWaves);
+    DecodeArgs b = a;
+    b.share_gcd = b.share_inv = 0;                    // shares in launch order
+    if (wgs % 8 == 0) {                               // whole rounds over the XCDs: ranked shares
+        int g = HC, t = P;
+        while (t) { const int m = g % t; g = t; t = m; }
+        // inverse of HC / g modulo P / g (the two are coprime), by the extended Euclidean algorithm
+        const int period = P / g;
+        long long r0 = period, r1 = HC / g % period, t0 = 0, t1 = 1;
+        while (r1 > 1) {
+            const long long q = r0 / r1, r2 = r0 - q * r1, t2 = t0 - q * t1;
+            r0 = r1; r1 = r2; t0 = t1; t1 = t2;
+        }
+        b.share_gcd = g;
+        b.share_inv = period > 1 ? (int)((t1 % period + period) % period) : 0;
+    }
+    hipLaunchKernelGGL((decode_balanced<R, TOGETHER>), dim3(wgs), dim3(kThreads), (balanced_lds<R, TOGETHER>(a.batch, a.heads_per_pass)),
+                       s, b);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int slices = (a.heads_per_pass * a.head_dim + 127) / 128;
+    hipLaunchKernelGGL(decode_merge_balanced<R::kBF16>, dim3((P + kMergeShares - 1) / kMergeShares, slices), dim3(64 * kMergeShares), 0,
+                       s, a, P);
+    return hipGetLastError();
 }
 
 // demand != nullptr: nothing is launched; *demand receives the bytes of partial slots the
@@ -532,7 +524,7 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     // balanced: as many workgroups as the chip holds at once for this kernel (fewer
     // if the partial slots of that many wave shares would not fit behind a.partials)
     int resident = 0;
-    hipError_t e = resident_workgroups<R>(a, &resident);
+    hipError_t e = resident_workgroups<R, false>(a, &resident);
     if (e != hipSuccess) return e;
     const size_t per_share = decode_share_bytes(a.heads_per_pass, a.head_dim);
     if (demand) {
@@ -542,38 +534,15 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     const size_t fit = min((size_t)kMaxShares, a.partial_capacity / per_share);
     const int wgs = min(resident, (int)(fit / kWaves));
     if (wgs < 1) return hipErrorInvalidValue;
-    const size_t lds = (size_t)(a.batch + 1) * sizeof(int);
-    DecodeArgs b = a;
-    b.share_gcd = b.share_inv = 0;                    // shares in launch order
-    if (wgs % 8 == 0) {                               // whole rounds over the XCDs: ranked shares
-        const int P = wgs * kWaves;
-        int g = HC, t = P;
-        while (t) { const int m = g % t; g = t; t = m; }
-        // inverse of HC / g modulo P / g (the two are coprime), by the extended Euclidean algorithm
-        const int period = P / g;
-        long long r0 = period, r1 = HC / g % period, t0 = 0, t1 = 1;
-        while (r1 > 1) {
-            const long long q = r0 / r1, r2 = r0 - q * r1, t2 = t0 - q * t1;
-            r0 = r1; r1 = r2; t0 = t1; t1 = t2;
-        }
-        b.share_gcd = g;
-        b.share_inv = period > 1 ? (int)((t1 % period + period) % period) : 0;
+    // With eight waves and more to a range (if every request runs) they are better off together; with
+    // six (16 requests of 60 to 1 500 tokens, 40 heads) the barriers cost 4 % more than they save.
+    constexpr int kTogetherWaves = 8;
+    if ((long long)a.batch * HC * kTogetherWaves <= (long long)wgs * kWaves) {
+        int together = 0;
+        if ((e = resident_workgroups<R, true>(a, &together)) != hipSuccess) return e;
+        return launch_balanced<R, true>(a, min(together, wgs), s);
     }
-    hipLaunchKernelGGL(decode_balanced<R>, dim3(wgs), dim3(kThreads), lds, s, b);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // a batch so small that its ranges average 64 pieces and more: pieces in parallel
-    const int P = wgs * kWaves;
-    if ((long long)a.batch * HC * 64 <= P && P % kWideShares == 0) {
-        hipLaunchKernelGGL((decode_merge_wide<R::kBF16, R::D>),
-                           dim3(P / kWideShares, a.heads_per_pass, R::D / 32), dim3(256), 0, s, a);
-        return hipGetLastError();
-    }
-    const int slices = (a.heads_per_pass * a.head_dim + 127) / 128;
-    // (workgroups of 16 wavefronts where the share count allows: fewer, larger workgroups launch faster)
-    const int fold = wgs % 4 == 0 ? 4 : wgs % 2 == 0 ? 2 : 1;
-    hipLaunchKernelGGL(decode_merge_balanced<R::kBF16>, dim3(wgs / fold, slices), dim3(256 * fold), 0, s, a);
-    return hipGetLastError();
+    return launch_balanced<R, false>(a, wgs, s);
 }
 
 template <bool BF16, int LPT>
