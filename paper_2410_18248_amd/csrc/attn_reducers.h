@@ -161,12 +161,13 @@ struct ValuReducer {
     static constexpr int HT = TPW * kLoads;           // tokens per half-chunk (<= 16 <= block_size)
     static constexpr int NL = NH * kLoads;            // wave-wide loads per chunk and pool
     static constexpr int CT = HT * NH;                // tokens per chunk
+    static constexpr int GT = HT;                     // a range may begin at, and be cut by, any half-chunk
 
     // One wavefront reduces cached positions [t_begin, t_end) of request r (kv
     // head g, query heads h0 .. h0+GH-1), chunk after chunk, then calls
     // sink(h, d, M, L, A) once for every (head, dim): M = running max (log2
     // domain), L = sum of weights, A = weighted sum of V[:, d].  t_begin is a
-    // multiple of CT.  No barrier, no LDS: waves of a workgroup are independent.
+    // multiple of GT.  No barrier, no LDS: waves of a workgroup are independent.
     // q is row `qrow` of a.q ([rows][H][D]); the block table row is r (decode: the same).
     template <typename Sink>
     static __device__ __forceinline__ void run(const DecodeArgs &a, int r, size_t qrow, int g, int h0, int,
@@ -342,7 +343,7 @@ template <int DIM>
 struct MfmaReducer {
     static constexpr bool kBF16 = true;
     static constexpr int D = DIM;
-    static constexpr int CT = 16;                     // tokens per chunk = one sub-tile
+    static constexpr int CT = 16, GT = 16;            // tokens per chunk = one sub-tile
     static constexpr int NK = D / 32;                 // K loads = score MFMAs per sub-tile
     static constexpr int NS = D / 32;                 // V loads per sub-tile (two 16-dim slabs each)
 
@@ -579,16 +580,22 @@ struct MfmaF32Tile {
             if (ch + 1 < n_chunks) issue(ch + 1, pb1, kn, vn);
             pb1 = pb2;
 
-            f32x4 s = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};   // tokens t0 + 4 qd + e of the lane's column
+            // tokens t0 + 4 qd + e of the lane's column; eight chains: no MFMA waits for the one before
+            // it, and the sums are short (their error stays that of the vector ALUs' pairwise ones)
+            f32x4 p8[8];
 #pragma unroll
-            for (int i = 0; i < NK; ++i) {            // two chains: an MFMA does not wait for the one before it
-                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][0], qb[i][0], s, 0, 0, 0);
-                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][1], qb[i][1], s2, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][2], qb[i][2], s, 0, 0, 0);
-                s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][3], qb[i][3], s2, 0, 0, 0);
-            }
+            for (int e = 0; e < 8; ++e) p8[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] = (s[e] + s2[e]) * a.scale_log2e;
+            for (int i = 0; i < NK; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    f32x4 &x = p8[4 * (i & 1) + e];
+                    x = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][e], qb[i][e], x, 0, 0, 0);
+                }
+            float s[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                s[e] = (((p8[0][e] + p8[1][e]) + (p8[2][e] + p8[3][e])) + ((p8[4][e] + p8[5][e]) + (p8[6][e] + p8[7][e]))) * a.scale_log2e;
             bool wild = false;                        // uniform: a value that not every column sees is no finite number
             if (t0 + CT > min_limit || t0 + CT > t_end) {   // uniform: some column does not see the whole chunk
                 const int seen = min(limit, t_end) - (t0 + 4 * qd);
@@ -625,34 +632,37 @@ struct MfmaF32Tile {
                 ps += s[e];
             }
             l = l * sc + ps;
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-#pragma unroll
-                for (int v = 0; v < VW; ++v)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) st.o[c][v][e] *= sc;
+            // the chunk's sums start at zero and join the outputs in the multiply-add that rescales those
             if (!wild) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int c = 0; c < NC; ++c) {
+                    f32x4 t[VW];
 #pragma unroll
-                    for (int c = 0; c < NC; ++c)
+                    for (int v = 0; v < VW; ++v) t[v] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int v = 0; v < VW; ++v)
-                            st.o[c][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(vx[e][c][v], s[e], st.o[c][v], 0, 0, 0);
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int v = 0; v < VW; ++v) t[v] = __builtin_amdgcn_mfma_f32_16x16x4f32(vx[e][c][v], s[e], t[v], 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < VW; ++v)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) st.o[c][v][e] = fmaf(st.o[c][v][e], sc, t[v][e]);
+                }
             } else {                                  // once per limit, the values past it zeroed, kept by its columns
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
 #pragma unroll
                     for (int v = 0; v < VW; ++v) {
-                        f32x4 kept = st.o[c][v];
+                        f32x4 kept = {0.f, 0.f, 0.f, 0.f};
                         for (int lim = min_limit; lim <= t_end; ++lim) {
-                            f32x4 t = st.o[c][v];
+                            f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
                                 t = __builtin_amdgcn_mfma_f32_16x16x4f32(t0 + 4 * qd + e < lim ? vx[e][c][v] : 0.0f, s[e], t, 0, 0, 0);
                             if (limit == lim) kept = t;
                         }
-                        st.o[c][v] = kept;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) st.o[c][v][e] = fmaf(st.o[c][v][e], sc, kept[e]);
                     }
             }
 #pragma unroll
