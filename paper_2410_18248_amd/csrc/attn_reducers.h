@@ -51,6 +51,29 @@ __device__ __forceinline__ float dpp_add(float x)
     return x + __int_as_float(y);
 }
 
+// Inclusive sum (or, for values that are not negative, maximum) over the lanes of a wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_shifted(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int x)
+{
+    x += dpp_shifted<0x111, 0xF>(x);                  // row_shr 1, 2, 4, 8: inside each row of 16
+    x += dpp_shifted<0x112, 0xF>(x);
+    x += dpp_shifted<0x114, 0xF>(x);
+    x += dpp_shifted<0x118, 0xF>(x);
+    x += dpp_shifted<0x142, 0xA>(x);                  // row_bcast 15: into rows 1 and 3
+    x += dpp_shifted<0x143, 0xC>(x);                  // row_bcast 31: into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ int wave_max_to(int x)
+{
+    x = max(x, dpp_shifted<0x111, 0xF>(x));
+    x = max(x, dpp_shifted<0x112, 0xF>(x));
+    x = max(x, dpp_shifted<0x114, 0xF>(x));
+    x = max(x, dpp_shifted<0x118, 0xF>(x));
+    x = max(x, dpp_shifted<0x142, 0xA>(x));
+    return max(x, dpp_shifted<0x143, 0xC>(x));
+}
+
 // Sum over the LPT consecutive lanes that hold one token; every lane gets the
 // same bits (each step adds the same two numbers on both sides).
 template <int LPT>

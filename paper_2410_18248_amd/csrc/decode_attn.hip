@@ -6,7 +6,8 @@
 // block table (paged attention, Section 7).
 //
 // Work decomposition.  The unit of work is a chunk of CT tokens of one
-// (request, kv head, pass over GH query heads of the group).  Two schemes share
+// (request, kv head, pass over GH query heads of the group), in the balanced scheme
+// cut in GT tokens.  Two schemes share
 // the same inner loops:
 //   balanced (default): all chunks of all running requests form one flat
 //     sequence (head outermost, then request, then position); as many
@@ -137,18 +138,34 @@ __global__ void decode_merge(const DecodeArgs a)
 
 // ---------------------------------------------------------------- balanced shares
 
-// Position x of the flat chunk sequence belongs to the share w with
-// floor(w * total / P) <= x < floor((w + 1) * total / P).
-__device__ __forceinline__ long long share_of(long long x, long long total, int P)
+// Share w of P has the positions [floor(w * total / P), floor((w + 1) * total / P)) of the flat chunk
+// sequence.  The sequence practically always has less than 2^31 positions, and then a few 32-bit
+// divisions do: the general 64-bit ones were 1 us in the prologue of every wave, of 3 to 4.
+__device__ __forceinline__ bool fits32(long long total) { return total <= 0x7fffffff; }
+__device__ __forceinline__ long long share_begin(int w, long long total, int P)
 {
-    return ((x + 1) * P - 1) / total;
+    if (!fits32(total)) return (long long)w * total / P;
+    const unsigned q = (unsigned)total / (unsigned)P, rem = (unsigned)total - q * (unsigned)P;
+    return w * q + (unsigned)w * rem / (unsigned)P;   // w * rem < kMaxShares^2
+}
+// The share that position x belongs to.
+__device__ __forceinline__ int share_of(long long x, long long total, int P)
+{
+    if (!fits32(total)) return (int)(((x + 1) * P - 1) / total);
+    // exact: the quotient is a multiple of 1 / total and below kMaxShares, and rounding to 53 bits
+    // cannot carry one that is no whole number up to the next
+    return (int)((double)((x + 1) * P - 1) / (double)total);
 }
 
 // Chunks a running request contributes per (kv head, pass): an empty context
 // still gets one (empty) chunk so that its zero row is written.
-__device__ __forceinline__ int chunks_of(int running, int C, int CT)
+__device__ __forceinline__ int chunks_of(const DecodeArgs &a, int r, int GT)
 {
-    return running ? max(1, (C + CT - 1) / CT) : 0;
+    const int running = a.running[r];
+    int C = a.ctx_lens[r];
+    asm volatile("" : "+v"(C));                       // asked for together with the mask, not after it
+    C = min(C, a.max_blocks * a.block_size);
+    return running ? max(1, (C + GT - 1) / GT) : 0;
 }
 
 // gridDim.x * 4 wavefronts, each an equal contiguous share of the flat chunk
@@ -165,6 +182,11 @@ __device__ __forceinline__ int chunks_of(int running, int C, int CT)
 // blocks at the same time then sit on one XCD, next to each other.  With pools of
 // 100 GB and more this is worth several per cent; with small pools it is neutral.
 //
+// Small launches are bound by the way to the first K / V byte: mask and lengths are asked for
+// together, scans are DPP adds, divisions 32 bits wide, and the cut is by half-chunks, so that no
+// wave has twice another's work.  One request of 1 999 tokens, both launches: 13.2 -> 10.3 us (2.6 of
+// the 6.3 us of this kernel pass before its first range, 4.0 before).
+//
 // TOGETHER: a share belongs to a workgroup, whose four waves take a quarter of each of its ranges
 // and add the quarters up in LDS.  For launches with few ranges for the waves (a few requests, or
 // long ones): a quarter of the pieces to write, and to read and add up in the second kernel.  Both
@@ -174,7 +196,8 @@ __device__ __forceinline__ int chunks_of(int running, int C, int CT)
 template <typename R, bool TOGETHER>
 __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 {
-    constexpr int D = R::D, CT = R::CT;
+    constexpr int D = R::D, GT = R::GT;               // below, a chunk is GT tokens
+    constexpr int kWhole = R::CT / GT;                // ... and this many are what a wave loads at a time: 1 or 2
     extern __shared__ int prefix[];                   // TOGETHER: then [wave][head][D + 2] floats
     __shared__ int wave_total[kWaves], wave_longest[kWaves];
 
@@ -185,19 +208,13 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     for (int i = 0; i < per; ++i) {
         const int r = tid * per + i;
         if (r < B) {
-            const int n = chunks_of(a.running[r], ctx_len(a, r), CT);
+            const int n = chunks_of(a, r, GT);
             mine += n;
             longest = max(longest, n);
         }
     }
-#pragma unroll
-    for (int dlt = 1; dlt < 64; dlt *= 2) longest = max(longest, __shfl_xor(longest, dlt));
-    int incl = mine;                                  // inclusive scan inside the wave
-#pragma unroll
-    for (int dlt = 1; dlt < 64; dlt *= 2) {
-        const int up = __shfl_up(incl, dlt);
-        if (lane >= dlt) incl += up;
-    }
+    longest = wave_max_to(longest);
+    const int incl = wave_scan(mine);                 // inclusive scan inside the wave
     if (lane == 63) {
         wave_total[wv] = incl;
         wave_longest[wv] = longest;
@@ -206,20 +223,24 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww) longest = max(longest, wave_longest[ww]);
     int run = incl - mine;
-    for (int ww = 0; ww < wv; ++ww) run += wave_total[ww];
+#pragma unroll
+    for (int ww = 0; ww < kWaves - 1; ++ww) run += ww < wv ? wave_total[ww] : 0;
     if (tid == 0) prefix[0] = 0;
-    for (int i = 0; i < per; ++i) {
-        const int r = tid * per + i;
-        if (r < B) {
-            run += chunks_of(a.running[r], ctx_len(a, r), CT);
-            prefix[r + 1] = run;
+    if (per == 1) {
+        if (tid < B) prefix[tid + 1] = run + mine;
+    } else {
+        for (int i = 0; i < per; ++i) {
+            const int r = tid * per + i;
+            if (r < B) {
+                run += chunks_of(a, r, GT);
+                prefix[r + 1] = run;
+            }
         }
     }
     __syncthreads();
 
-    const int G = a.num_q_heads / a.num_kv_heads;
     const int GH = a.heads_per_pass;
-    const int passes = G / GH;
+    const int passes = a.passes;
     const int HC = a.num_kv_heads * passes;
     // (values that are the same in every lane are told so: the compiler cannot see it
     // through LDS and the shuffles, and would keep the range arithmetic in vector registers)
@@ -237,8 +258,13 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     // attention, 200 us of merge).  Then only as many shares are used as gives each 2, 4 or
     // 8 chunks -- for a longest range of 256, 512, 1024 chunks and more -- and the rest stay
     // empty.  TOGETHER: a chunk per wave at least, and the rest as for a range a quarter as long.
-    const int log2_share_chunks = TOGETHER ? (longest >= 4096 ? 5 : longest >= 2048 ? 4 : longest >= 1024 ? 3 : 2) : longest >= 1024 ? 3 : longest >= 512 ? 2 : longest >= 256 ? 1 : 0;
-    const long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
+    const int span = longest / kWhole;
+    const int log2_share_chunks = (TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
+                                            : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + (kWhole > 1 ? 1 : 0);
+    long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
+    // as many for every head: with one request no share straddles two ranges (a second range is a second
+    // chain of dependent loads: 3.5 us)
+    if (wanted < P) wanted = min((long long)P, (wanted + HC - 1) / HC * HC);
     if (wanted < P) {
         P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
         if (share >= P) {
@@ -250,38 +276,38 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         // start inside a head's stretch; this wave takes the share of rank
         // (XCD, index inside the XCD), found by inverting that
         const int rank = (blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3) * kOwnShares + sub;
-        const int tie = rank % a.share_gcd, period = P / a.share_gcd;
-        share = (int)((long long)(rank / a.share_gcd) * a.share_inv % period) + tie * period;
+        const unsigned turn = (unsigned)rank / (unsigned)a.share_gcd, tie = (unsigned)rank - turn * (unsigned)a.share_gcd;
+        share = (int)(turn * (unsigned)a.share_inv % (unsigned)a.share_period + tie * (unsigned)a.share_period);   // < kMaxShares^2
     }
     // What the merge kernel needs to know about this share: whether it is empty,
     // and the (request, head) range it starts but does not finish, if any (only
     // its last range can be one): request, head/pass, last share of the range,
     // and the slot this share's piece went to.
     int4 owned = make_int4(0, 0, 0, 0);
-    const long long x_begin = (long long)share * total / P;
-    const long long x_end = (long long)(share + 1) * total / P;
+    const long long x_begin = share_begin(share, total, P), x_end = share_begin(share + 1, total, P);
     if (x_begin >= x_end) {
         if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
         return;
     }
 
     // request that holds position x_begin of its head: the last r with prefix[r] <= it
-    const int first_pos = (int)(x_begin % T);
+    const int first_hc = fits32(total) ? (int)((unsigned)x_begin / (unsigned)T) : (int)(x_begin / T);
+    const int first_pos = (int)(x_begin - (long long)first_hc * T);
     int lo = 0, hi = B;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (prefix[mid] <= first_pos) lo = mid; else hi = mid;
     }
-    int r = __builtin_amdgcn_readfirstlane(lo);
+    int r = __builtin_amdgcn_readfirstlane(lo), hc = __builtin_amdgcn_readfirstlane(first_hc);
     long long x = x_begin;
     while (x < x_end) {
         const int base = __builtin_amdgcn_readfirstlane(prefix[r]);
         const int nr = __builtin_amdgcn_readfirstlane(prefix[r + 1]) - base;   // > 0 here
-        const int hc = (int)(x / T), c0 = (int)(x % T) - base;
+        const int c0 = (int)(x - (long long)hc * T) - base;
         const int len = (int)min((long long)(nr - c0), x_end - x);
         const int C = ctx_len(a, r);
-        const int g = hc / passes;
-        const int h0 = g * G + (hc % passes) * GH;
+        int g = hc, h0 = hc * GH;                     // (GH == G, or a pass over part of the group)
+        if (passes > 1) g = hc / passes;
         const bool whole = (c0 == 0 && len == nr);
         // a share's first range goes to slot 0, a later partial one (its last) to slot 1
         float *slot = a.partials + ((size_t)share * 2 + (x == x_begin ? 0 : 1)) * GH * (D + 2);
@@ -290,7 +316,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
             float *part = reinterpret_cast<float *>(prefix) + ((B + 4) & ~3);
             const int each = (len + kWaves - 1) / kWaves, from = min(len, each * __builtin_amdgcn_readfirstlane(wv));
             float *mine = part + (size_t)__builtin_amdgcn_readfirstlane(wv) * GH * (D + 2);
-            R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * CT, min(C, (c0 + min(len, from + each)) * CT),
+            R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * GT, min(C, (c0 + min(len, from + each)) * GT),
                    [&](int h, int d, float M, float L, float A) { store_partial(mine + h * (D + 2), D, d, M, L, A); });
             __syncthreads();
             for (int i = tid; i < GH * D; i += kThreads) {
@@ -312,7 +338,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
             }
             __syncthreads();                          // before the next range's parts
         } else {
-            R::run(a, r, (size_t)r, g, h0, GH, c0 * CT, min(C, (c0 + len) * CT),
+            R::run(a, r, (size_t)r, g, h0, GH, c0 * GT, min(C, (c0 + len) * GT),
                    [&](int h, int d, float M, float L, float A) {
                        if (whole)
                            store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
@@ -326,7 +352,10 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         x += len;
         if (c0 + len == nr) {                         // request finished: next one with work,
             do {                                      // after the last one the next head's first
-                if (++r == B) r = 0;
+                if (++r == B) {
+                    r = 0;
+                    ++hc;
+                }
             } while (prefix[r + 1] == prefix[r]);
         }
     }
@@ -479,7 +508,7 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
     const int HC = a.num_q_heads / a.heads_per_pass;
     const int P = wgs * (TOGETHER ? 1 : kWaves);
     DecodeArgs b = a;
-    b.share_gcd = b.share_inv = 0;                    // shares in launch order
+    b.share_gcd = b.share_inv = b.share_period = 0;                    // shares in launch order
     if (wgs % 8 == 0) {                               // whole rounds over the XCDs: ranked shares
         int g = HC, t = P;
         while (t) { const int m = g % t; g = t; t = m; }
@@ -491,6 +520,7 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
             r0 = r1; r1 = r2; t0 = t1; t1 = t2;
         }
         b.share_gcd = g;
+        b.share_period = period;
         b.share_inv = period > 1 ? (int)((t1 % period + period) % period) : 0;
     }
     hipLaunchKernelGGL((decode_balanced<R, TOGETHER>), dim3(wgs), dim3(kThreads), (balanced_lds<R, TOGETHER>(a.batch, a.heads_per_pass)),

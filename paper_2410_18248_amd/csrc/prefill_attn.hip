@@ -253,20 +253,6 @@ struct Run {
     int per;                             // stages per run
 };
 
-// Inclusive sum over the lanes of a wave.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_shifted(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false); }
-__device__ __forceinline__ int wave_scan(int x)
-{
-    x += dpp_shifted<0x111, 0xF>(x);                  // row_shr 1, 2, 4, 8: inside each row of 16
-    x += dpp_shifted<0x112, 0xF>(x);
-    x += dpp_shifted<0x114, 0xF>(x);
-    x += dpp_shifted<0x118, 0xF>(x);
-    x += dpp_shifted<0x142, 0xA>(x);                  // row_bcast 15: into rows 1 and 3
-    x += dpp_shifted<0x143, 0xC>(x);                  // row_bcast 31: into rows 2 and 3
-    return x;
-}
-
 // What workgroup `item` of a split launch is to do.  Items are ordered (request, run, kv head,
 // tile).  Every wave works it out for itself from q_start and ctx_lens, one request per lane: one
 // round trip to memory, no barrier.  (The launcher has checked that the sums fit 32 bits.)
