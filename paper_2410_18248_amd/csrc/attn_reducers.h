@@ -101,6 +101,13 @@ __device__ __forceinline__ uint16_t to_bf16_rne(float f)
     return (uint16_t)((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
 }
 
+// Two of them by the conversion instruction (RNE too; a NaN stays one).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+
 template <bool BF16>
 __device__ __forceinline__ void store_out(void *out, size_t i, float o)
 {

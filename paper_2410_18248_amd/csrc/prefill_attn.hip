@@ -57,34 +57,105 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
     });
 }
 
-// Which (request, kv head) pair and tile of new tokens a workgroup of a grid of `pairs` x `tiles`
-// takes.  All tiles of one pair run on one XCD (workgroups are dealt to the 8 XCDs round-robin in
-// launch order), so its K/V stream is fetched into one L2 and shared there; consecutive kv heads go
-// to different XCDs; the longest tiles of a pair start first.  That holds for the pairs that fill
-// whole groups of 8; the (pair, tile) items of the remaining 1..7 pairs are dealt round-robin over
-// all XCDs instead of leaving some of them empty.
-__device__ __forceinline__ bool pair_and_tile(int pairs, int tiles, int full_groups, int &pair, int &tile)
+// Which request, kv head (or pass) of `heads` and tile of new tokens a workgroup takes, and the
+// request's first row, new rows and context length; false: none.
+//
+// full_groups >= 0: a grid of (request, head) pairs x tiles, tiles being the most any request has.
+// All tiles of one pair run on one XCD (workgroups are dealt to the 8 XCDs round-robin in launch
+// order), so its K/V stream is fetched into one L2 and shared there; consecutive heads go to
+// different XCDs; the longest tiles of a pair start first.  That holds for the pairs that fill whole
+// groups of 8; the (pair, tile) items of the remaining 1..7 pairs are dealt round-robin over all
+// XCDs instead of leaving some of them empty.
+//
+// full_groups < 0, for ragged batches: only the tiles there are, (tile, request, head) with the last
+// tiles first, found by every wave from q_start, a few requests per lane.  A workgroup without a
+// tile holds its slot (LDS and registers) for 2 us, and workgroups start in order: 24 prompts of 16 to
+// 700 tokens on 40 heads kept 300 to 440 of 512 slots busy with 5 760 workgroups for 1 560 tiles, and
+// 400 to 512 this way: 55 -> 48 us for the kernel.  With the number of heads a multiple of 8 a pair's
+// tiles stay on one XCD here too.
+constexpr int kRagged = 4;               // requests per lane
+struct Place {
+    int r, head, tile, first, n_new, ctx;
+};
+__device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles, int full_groups, int WT, Place &at)
 {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    int t;
-    if (slot < full_groups * tiles) {
-        pair = xcd + 8 * (slot / tiles);
-        t = slot % tiles;
+    const DecodeArgs &a = p.d;
+    if (full_groups >= 0) {
+        const int pairs = heads * a.batch;
+        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+        int pair, t;
+        if (slot < full_groups * tiles) {
+            pair = xcd + 8 * (slot / tiles);
+            t = slot % tiles;
+        } else {
+            const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
+            const int i = (slot - full_groups * tiles) * 8 + xcd;
+            pair = 8 * full_groups + i % rest;
+            t = i / rest;
+        }
+        if (t >= tiles) return false;
+        at.tile = tiles - 1 - t;
+        at.r = pair / heads;
+        at.head = pair - at.r * heads;
+        at.first = p.q_start[at.r];
+        at.n_new = p.q_start[at.r + 1] - at.first;
+        if (at.tile * WT >= at.n_new) return false;
+        at.ctx = a.ctx_lens[at.r];
     } else {
-        const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
-        const int at = (slot - full_groups * tiles) * 8 + xcd;
-        pair = 8 * full_groups + at % rest;
-        t = at / rest;
+        const int lane = threadIdx.x & 63;
+        int first[kRagged], n_new[kRagged], ctx[kRagged], n_tiles[kRagged], most = 0;
+#pragma unroll
+        for (int k = 0; k < kRagged; ++k) {
+            const int r = 64 * k + lane;
+            first[k] = n_new[k] = ctx[k] = n_tiles[k] = 0;
+            if (64 * k < a.batch && r < a.batch) {
+                first[k] = p.q_start[r];
+                n_new[k] = p.q_start[r + 1] - first[k];
+                ctx[k] = a.ctx_lens[r];
+                n_tiles[k] = n_new[k] > 0 ? min((n_new[k] + WT - 1) / WT, tiles) : 0;
+            }
+            most = max(most, n_tiles[k]);
+        }
+        most = __builtin_amdgcn_readlane(wave_max_to(most), 63);
+        int left = blockIdx.x / heads;                    // requests' tiles before this one
+        at.head = blockIdx.x - left * heads;
+        at.r = -1;
+        for (int t = most - 1; t >= 0 && at.r < 0; --t)
+#pragma unroll
+            for (int k = 0; k < kRagged; ++k)
+                if (64 * k < a.batch && at.r < 0) {
+                    const unsigned long long have = __ballot(n_tiles[k] > t);
+                    const int n = __popcll(have);
+                    if (left < n) {
+                        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(have >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)have, 0));
+                        const int l = __ffsll((long long)__ballot(n_tiles[k] > t && before == left)) - 1;
+                        at.r = 64 * k + l;
+                        at.tile = t;
+                        at.first = __builtin_amdgcn_readlane(first[k], l);
+                        at.n_new = __builtin_amdgcn_readlane(n_new[k], l);
+                        at.ctx = __builtin_amdgcn_readlane(ctx[k], l);
+                    } else {
+                        left -= n;
+                    }
+                }
+        if (at.r < 0) return false;
     }
-    tile = tiles - 1 - t;
-    return t < tiles;
+    // a context shorter than its new tokens, or longer than the block-table row, is the caller's
+    // mistake: nothing is read or written for it
+    return at.ctx >= at.n_new && at.ctx <= a.max_blocks * a.block_size;
 }
-// The grid for it; 0: too large.
-unsigned pair_grid(long long pairs, long long tiles, int *full_groups)
+// The grid for it and what place() needs to know; 0: too large.
+unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int WT, bool ragged, int *full_groups)
 {
-    const long long full = pairs / 8, rest = pairs % 8;
-    const long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
+    const long long pairs = heads * p.d.batch, full = pairs / 8, rest = pairs % 8;
+    long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
     *full_groups = (int)full;
+    // the tiles of all requests are at most this many; a quarter fewer workgroups pay for finding them
+    const long long most = heads * ((long long)p.total_tokens / WT + p.d.batch);
+    if (ragged && p.d.batch <= 64 * kRagged && most + most / 4 < grid) {
+        grid = most;
+        *full_groups = -1;
+    }
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
 }
 
@@ -114,15 +185,10 @@ __global__ __launch_bounds__(kThreads) void prefill_tiles_f32(const PrefillArgs 
     const DecodeArgs &a = p.d;
     const int G = a.num_q_heads / a.num_kv_heads, GH = f32_tile_heads(G), passes = G / GH, HC = a.num_kv_heads * passes;
     const int TW = 16 / GH;                           // new tokens per tile
-    int pair, tile;
-    if (!pair_and_tile(HC * a.batch, tiles, full_groups, pair, tile)) return;
-    const int r = pair / HC, hc = pair - r * HC, g = hc / passes, h0 = g * G + hc % passes * GH;
-    const int first = p.q_start[r], n_new = p.q_start[r + 1] - first;
-    if (tile * TW >= n_new) return;
-    const int C = a.ctx_lens[r], base_pos = C - n_new;
-    // a context shorter than its new tokens, or longer than the block-table row, is the caller's
-    // mistake: nothing is read or written for it
-    if (base_pos < 0 || C > a.max_blocks * a.block_size) return;
+    Place at;
+    if (!place(p, HC, tiles, full_groups, TW, at)) return;
+    const int r = at.r, tile = at.tile, first = at.first, n_new = at.n_new, base_pos = at.ctx - n_new;
+    const int g = at.head / passes, h0 = at.head * GH;
     const int lane = threadIdx.x & 63, j = lane & 15, qd = lane >> 4, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int toks = min(TW, n_new - tile * TW);
     const int tok = j / GH;                           // this lane's column: token tile * TW + tok, head h0 + j % GH
@@ -168,9 +234,9 @@ template <int D>
 hipError_t launch_tiles_f32(const PrefillArgs &p, hipStream_t s)
 {
     const int GH = f32_tile_heads(p.d.num_q_heads / p.d.num_kv_heads), TW = 16 / GH;
-    const long long pairs = (long long)p.d.num_q_heads / GH * p.d.batch, tiles = (p.max_new_tokens + TW - 1) / TW;
+    const long long tiles = (p.max_new_tokens + TW - 1) / TW;
     int full = 0;
-    const unsigned grid = pair_grid(pairs, tiles, &full);
+    const unsigned grid = place_grid(p, p.d.num_q_heads / GH, tiles, TW, false, &full);   // (a workgroup for nothing holds little here)
     if (grid == 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prefill_tiles_f32<D>, dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
     return hipGetLastError();
@@ -372,20 +438,17 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         item_stride = run.stride;
         st0 = (item - run.first_item) / run.stride * per;
     } else {
-        int pair;
-        if (!pair_and_tile(a.num_kv_heads * a.batch, tiles, full_groups, pair, tile)) return;
-        r = pair / a.num_kv_heads;
-        g = pair - r * a.num_kv_heads;
-        first = p.q_start[r];
-        n_new = p.q_start[r + 1] - first;
-        if (tile * WT >= n_new) return;
-        C = a.ctx_lens[r];
+        Place at;
+        if (!place(p, a.num_kv_heads, tiles, full_groups, WT, at)) return;
+        r = at.r;
+        g = at.head;
+        tile = at.tile;
+        first = at.first;
+        n_new = at.n_new;
+        C = at.ctx;
     }
     const int G = a.num_q_heads / a.num_kv_heads;
     const int base_pos = C - n_new;                  // position of the request's first new token
-    // a context shorter than its new tokens, or longer than the block-table row, is the caller's
-    // mistake: nothing is read or written for it
-    if (base_pos < 0 || C > a.max_blocks * a.block_size) return;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, qd = lane >> 4;
@@ -767,8 +830,8 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             uint2 w;
-            w.x = (uint32_t)to_bf16_rne(o[b][s][0] * inv) | ((uint32_t)to_bf16_rne(o[b][s][1] * inv) << 16);
-            w.y = (uint32_t)to_bf16_rne(o[b][s][2] * inv) | ((uint32_t)to_bf16_rne(o[b][s][3] * inv) << 16);
+            w.x = pack_bf16(o[b][s][0] * inv, o[b][s][1] * inv);
+            w.y = pack_bf16(o[b][s][2] * inv, o[b][s][3] * inv);
             *reinterpret_cast<uint2 *>(dst + 16 * s + 4 * qd) = w;
         }
     }
@@ -813,9 +876,8 @@ hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
     if (e != hipSuccess || done) return e;
     const int WT = kWaves * (kCols / G);
     const long long tiles = (p.max_new_tokens + WT - 1) / WT;
-    const long long pairs = (long long)p.d.num_kv_heads * p.d.batch;
     int full = 0;
-    const unsigned grid = pair_grid(pairs, tiles, &full);
+    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, true, &full);
     if (grid == 0) return hipErrorInvalidValue;
     // Two stages per barrier where they fit and a request has many new tokens (the matrix cores
     // bind: +2-5 %); with one tile per request the kernel is a stream over the cache, and the
