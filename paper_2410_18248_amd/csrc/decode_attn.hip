@@ -168,6 +168,12 @@ __device__ __forceinline__ int chunks_of(const DecodeArgs &a, int r, int GT)
     return running ? max(1, (C + GT - 1) / GT) : 0;
 }
 
+// Ints of a balanced launch's dynamic LDS: the chunk prefix, and that of the pieces of a small launch.
+__host__ __device__ __forceinline__ int balanced_ints(int batch)
+{
+    return ((batch + 1) * (batch <= kThreads ? 2 : 1) + 3) & ~3;
+}
+
 // gridDim.x * 4 wavefronts, each an equal contiguous share of the flat chunk
 // sequence ordered (kv head / pass, request, chunk).  prefix[] (dynamic LDS,
 // batch + 1 ints) holds the running chunk count per request; every workgroup
@@ -198,7 +204,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 {
     constexpr int D = R::D, GT = R::GT;               // below, a chunk is GT tokens
     constexpr int kWhole = R::CT / GT;                // ... and this many are what a wave loads at a time: 1 or 2
-    extern __shared__ int prefix[];                   // TOGETHER: then [wave][head][D + 2] floats
+    extern __shared__ int prefix[];                   // then pieces[] (balanced_ints), and, TOGETHER, [wave][head][D + 2] floats
     __shared__ int wave_total[kWaves], wave_longest[kWaves];
 
     const int B = a.batch;
@@ -247,7 +253,8 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     const int T = __builtin_amdgcn_readfirstlane(prefix[B]);   // chunks per head / pass
     const long long total = (long long)HC * T;
     longest = __builtin_amdgcn_readfirstlane(longest);
-    // from here on every wave is on its own: no barrier below (TOGETHER: every workgroup, and its waves alike)
+    // from here on every wave is on its own (TOGETHER: every workgroup, and its waves alike); the one
+    // barrier pair below is for all or none
     constexpr int kOwnShares = TOGETHER ? 1 : kWaves;  // of a workgroup
     const int sub = TOGETHER ? 0 : __builtin_amdgcn_readfirstlane(wv);
     int P = gridDim.x * kOwnShares;
@@ -261,30 +268,68 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     const int span = longest / kWhole;
     const int log2_share_chunks = (TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
                                             : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + (kWhole > 1 ? 1 : 0);
-    long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
-    // as many for every head: with one request no share straddles two ranges (a second range is a second
-    // chain of dependent loads: 3.5 us)
-    if (wanted < P) wanted = min((long long)P, (wanted + HC - 1) / HC * HC);
-    if (wanted < P) {
-        P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
-        if (share >= P) {
-            if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
-            return;
+    const long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
+    // A launch with less work than that for every share is bound by latency, and a share that straddles
+    // two ranges is two chains of dependent loads (3.5 us each) behind each other: its shares are pieces
+    // of one range each, if there are enough of them.  Both launches, straddling -> pieces: 4 layers of 8
+    // requests of 20 to 159 tokens, 16 heads of 256, append included, 72 -> 57 us; 4 requests of 20 to 40
+    // tokens, 32 / 8 heads, 9.2 -> 7.8.
+    long long x_begin = -1, x_end = 0;
+    int last_share = 0;                               // of the range that x_begin is in
+    if (wanted < P && B <= kThreads) {
+        int *pieces = prefix + B + 1;                 // before request r, of one head
+        const int n = (mine + (1 << log2_share_chunks) - 1) >> log2_share_chunks, n_to = wave_scan(n);
+        if (lane == 63) wave_total[wv] = n_to;
+        __syncthreads();
+        int before = n_to - n;
+#pragma unroll
+        for (int ww = 0; ww < kWaves - 1; ++ww) before += ww < wv ? wave_total[ww] : 0;
+        if (tid < B) pieces[tid + 1] = before + n;
+        if (tid == 0) pieces[0] = 0;
+        __syncthreads();
+        const int all = __builtin_amdgcn_readfirstlane(pieces[B]);
+        if ((long long)all * HC <= P) {
+            if (share >= all * HC) {
+                if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
+                return;
+            }
+            const int head = share / all, at = share - head * all;
+            int lo = 0, hi = B;                       // the last request with pieces[r] <= at
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (pieces[mid] <= at) lo = mid; else hi = mid;
+            }
+            const int nr = prefix[lo + 1] - prefix[lo], np = pieces[lo + 1] - pieces[lo], k = at - pieces[lo];
+            const int each = (nr + np - 1) / np;
+            x_begin = (long long)head * T + prefix[lo] + k * each;
+            x_end = min(x_begin + each, (long long)head * T + prefix[lo + 1]);
+            last_share = share - k + np - 1;
         }
-    } else if (a.share_gcd > 0) {
-        // rank = (share * HC mod P) + share / (P / gcd) orders the shares by where they
-        // start inside a head's stretch; this wave takes the share of rank
-        // (XCD, index inside the XCD), found by inverting that
-        const int rank = (blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3) * kOwnShares + sub;
-        const unsigned turn = (unsigned)rank / (unsigned)a.share_gcd, tie = (unsigned)rank - turn * (unsigned)a.share_gcd;
-        share = (int)(turn * (unsigned)a.share_inv % (unsigned)a.share_period + tie * (unsigned)a.share_period);   // < kMaxShares^2
+    }
+    if (x_begin < 0) {
+        if (wanted < P) {
+            P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
+            if (share >= P) {
+                if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
+                return;
+            }
+        } else if (a.share_gcd > 0) {
+            // rank = (share * HC mod P) + share / (P / gcd) orders the shares by where they
+            // start inside a head's stretch; this wave takes the share of rank
+            // (XCD, index inside the XCD), found by inverting that
+            const int rank = (blockIdx.x & 7) * (P >> 3) + (blockIdx.x >> 3) * kOwnShares + sub;
+            const unsigned turn = (unsigned)rank / (unsigned)a.share_gcd, tie = (unsigned)rank - turn * (unsigned)a.share_gcd;
+            share = (int)(turn * (unsigned)a.share_inv % (unsigned)a.share_period + tie * (unsigned)a.share_period);   // < kMaxShares^2
+        }
+        x_begin = share_begin(share, total, P);
+        x_end = share_begin(share + 1, total, P);
+        last_share = -1;                              // worked out where it is needed
     }
     // What the merge kernel needs to know about this share: whether it is empty,
     // and the (request, head) range it starts but does not finish, if any (only
     // its last range can be one): request, head/pass, last share of the range,
     // and the slot this share's piece went to.
     int4 owned = make_int4(0, 0, 0, 0);
-    const long long x_begin = share_begin(share, total, P), x_end = share_begin(share + 1, total, P);
     if (x_begin >= x_end) {
         if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
         return;
@@ -313,7 +358,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         float *slot = a.partials + ((size_t)share * 2 + (x == x_begin ? 0 : 1)) * GH * (D + 2);
         const size_t rh0 = (size_t)r * a.num_q_heads + h0;
         if constexpr (TOGETHER) {
-            float *part = reinterpret_cast<float *>(prefix) + ((B + 4) & ~3);
+            float *part = reinterpret_cast<float *>(prefix) + balanced_ints(B);
             const int each = (len + kWaves - 1) / kWaves, from = min(len, each * __builtin_amdgcn_readfirstlane(wv));
             float *mine = part + (size_t)__builtin_amdgcn_readfirstlane(wv) * GH * (D + 2);
             R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * GT, min(C, (c0 + min(len, from + each)) * GT),
@@ -347,7 +392,7 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
                    });
         }
         if (c0 == 0 && len < nr)
-            owned = make_int4(r, hc, (int)share_of(x + nr - 1, total, P),
+            owned = make_int4(r, hc, last_share >= 0 ? last_share : share_of(x + nr - 1, total, P),
                               kShareOwner | (x == x_begin ? 0 : kShareSlot1));
         x += len;
         if (c0 + len == nr) {                         // request finished: next one with work,
@@ -467,12 +512,11 @@ __global__ __launch_bounds__(64 * kMergeShares) void decode_merge_balanced(const
 
 // ---------------------------------------------------------------- launchers
 
-// LDS of a decode_balanced launch: the chunk prefix and, TOGETHER, the waves' parts.
+// LDS of a decode_balanced launch.
 template <typename R, bool TOGETHER>
 size_t balanced_lds(int batch, int heads_per_pass)
 {
-    return TOGETHER ? ((batch + 4) & ~3) * sizeof(int) + (size_t)kWaves * heads_per_pass * (R::D + 2) * sizeof(float)
-                    : (batch + 1) * sizeof(int);
+    return balanced_ints(batch) * sizeof(int) + (TOGETHER ? (size_t)kWaves * heads_per_pass * (R::D + 2) * sizeof(float) : 0);
 }
 
 // Workgroups the chip holds at once for decode_balanced<R, TOGETHER>, per device (asked once per device and
