@@ -453,35 +453,10 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, qd = lane >> 4;
 
-    // this lane's column in each block: (token, head), its position, its q slices
-    int pos[kColBlocks];                             // -1: no such column
-    size_t orow[kColBlocks];                         // element offset of its output row
-    bf16x8 qb[kColBlocks][NK];
-    int wave_maxpos = -1, wave_minpos = 0x7fffffff;  // over the wave's valid columns
-#pragma unroll
-    for (int b = 0; b < kColBlocks; ++b) {
-        const int c = b * 16 + j;
-        const int tl = c / G, hd = c - tl * G;
-        const int tok = tile * WT + wv * TW + tl;
-        const bool ok = c < TW * G && tok < n_new;
-        pos[b] = ok ? base_pos + tok : -1;
-        orow[b] = ((size_t)(first + (ok ? tok : 0)) * a.num_q_heads + g * G + hd) * D;
-#pragma unroll
-        for (int i = 0; i < NK; ++i) {
-            uint4 t = make_uint4(0, 0, 0, 0);
-            if (ok) t = *reinterpret_cast<const uint4 *>(static_cast<const char *>(a.q) + (orow[b] + 32 * i + 8 * qd) * 2);
-            qb[b][i] = __builtin_bit_cast(bf16x8, t);
-        }
-        wave_maxpos = max(wave_maxpos, pos[b]);
-        if (ok) wave_minpos = min(wave_minpos, pos[b]);
-    }
-#pragma unroll
-    for (int dlt = 32; dlt >= 1; dlt >>= 1) {
-        wave_maxpos = max(wave_maxpos, __shfl_xor(wave_maxpos, dlt));
-        wave_minpos = min(wave_minpos, __shfl_xor(wave_minpos, dlt));
-    }
-    wave_maxpos = __builtin_amdgcn_readfirstlane(wave_maxpos);
-    wave_minpos = __builtin_amdgcn_readfirstlane(wave_minpos);
+    // the wave's columns see the positions up to wave_maxpos, every one of them those up to wave_minpos
+    const int wave_tok = tile * WT + wv * TW;        // the wave's first new token
+    const int wave_maxpos = __builtin_amdgcn_readfirstlane(wave_tok < n_new ? base_pos + min(n_new, wave_tok + TW) - 1 : -1);
+    const int wave_minpos = __builtin_amdgcn_readfirstlane(wave_tok < n_new ? base_pos + wave_tok : 0x7fffffff);
     int wg_maxpos = base_pos + min(n_new, (tile + 1) * WT) - 1;
     int n_stages = wg_maxpos / kStage + 1;
     int n_runs = 1;                                   // workgroups that share the tile
@@ -491,18 +466,6 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         n_stages = min(n_stages, st0 + per);
         wg_maxpos = min(wg_maxpos, n_stages * kStage - 1);
     }
-
-    float m[kColBlocks];
-    f32x4 o[kColBlocks][NS];                          // out^T: dims 16 s + 4 qd + e, this lane's column
-    f32x4 l[kColBlocks];                              // the column's sum of weights, four copies
-#pragma unroll
-    for (int b = 0; b < kColBlocks; ++b) {
-        m[b] = kLowest;
-        l[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < NS; ++s) o[b][s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
 
     const table_ptr table = (table_ptr)(uintptr_t)(a.block_table + (size_t)r * a.max_blocks);
     const uint32_t tile_bytes = (uint32_t)a.block_size * D * 2;
@@ -562,6 +525,53 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
             }
         }
     };
+    auto dma_group = [&](int grp, char *buf, const uint32_t (&ent)[2 * GRP]) {
+#pragma unroll
+        for (int h = 0; h < GRP; ++h) dma(grp * GRP + h, buf + h * STAGE, ent[2 * h], ent[2 * h + 1]);
+    };
+    const int grp0 = SPLIT ? st0 : 0;                 // SPLIT: one stage per group
+    constexpr int kGroupLoads = GRP * 2 * LPT;        // of one wave
+    {
+        uint32_t first_ent[NB][2 * GRP];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) lookup(grp0 + i, first_ent[i]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) dma_group(grp0 + i, lds + i * GSTAGE, first_ent[i]);
+    }
+
+    // this lane's column in each block: (token, head), its position, its q slices (asked for behind the
+    // first tiles: nothing depends on them until those are there)
+    int pos[kColBlocks];                             // -1: no such column
+    size_t orow[kColBlocks];                         // element offset of its output row
+    bf16x8 qb[kColBlocks][NK];
+#pragma unroll
+    for (int b = 0; b < kColBlocks; ++b) {
+        const int c = b * 16 + j;
+        const int tl = c / G, hd = c - tl * G;
+        const int tok = wave_tok + tl;
+        const bool ok = c < TW * G && tok < n_new;
+        pos[b] = ok ? base_pos + tok : -1;
+        orow[b] = ((size_t)(first + (ok ? tok : 0)) * a.num_q_heads + g * G + hd) * D;
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {
+            uint4 t = make_uint4(0, 0, 0, 0);
+            if (ok) t = *reinterpret_cast<const uint4 *>(static_cast<const char *>(a.q) + (orow[b] + 32 * i + 8 * qd) * 2);
+            qb[b][i] = __builtin_bit_cast(bf16x8, t);
+        }
+    }
+
+    float m[kColBlocks];
+    f32x4 o[kColBlocks][NS];                          // out^T: dims 16 s + 4 qd + e, this lane's column
+    f32x4 l[kColBlocks];                              // the column's sum of weights, four copies
+#pragma unroll
+    for (int b = 0; b < kColBlocks; ++b) {
+        m[b] = kLowest;
+        l[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) o[b][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+
     // Value slots at or past the context's end, and those of a sub-tile that was not loaded, are
     // zeroed once the stage is in LDS (they may hold anything, and a zero weight does not silence
     // a NaN; the scores of such positions are masked whatever the keys are).
@@ -694,19 +704,6 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
             for (int b = 0; b < kColBlocks; ++b) o[b][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[s], pw[b], o[b][s], 0, 0, 0);
     };
 
-    auto dma_group = [&](int grp, char *buf, const uint32_t (&ent)[2 * GRP]) {
-#pragma unroll
-        for (int h = 0; h < GRP; ++h) dma(grp * GRP + h, buf + h * STAGE, ent[2 * h], ent[2 * h + 1]);
-    };
-    const int grp0 = SPLIT ? st0 : 0;                 // SPLIT: one stage per group
-    constexpr int kGroupLoads = GRP * 2 * LPT;        // of one wave
-    {
-        uint32_t first_ent[NB][2 * GRP];
-#pragma unroll
-        for (int i = 0; i < NB; ++i) lookup(grp0 + i, first_ent[i]);
-#pragma unroll
-        for (int i = 0; i < NB; ++i) dma_group(grp0 + i, lds + i * GSTAGE, first_ent[i]);
-    }
     lookup(grp0 + NB, ent);
     // Waits for group grp with the loads of `ahead` groups behind it on their way.  (Where the last
     // of those loads less than a whole group, or nothing, the count says nothing: all are waited for.)
