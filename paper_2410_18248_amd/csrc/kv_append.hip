@@ -24,11 +24,36 @@ namespace {
 
 constexpr int kAppendThreads = 256;
 
-// Writes the key and value vectors kn, vn ([H_kv][D]) of one token at cached
-// position t of request r.  Called by a whole workgroup.  A position outside the
-// block-table row, or a block id outside the pool, writes nothing.
+// The last request r < batch with key(q_start[r], r) <= x; key grows with r.  By every wave, 64
+// requests per round trip to memory (one by one halving, each round waits for the one before: 4 to 6
+// of them were half the time of a call with few tokens).
+template <typename Key>
+__device__ __forceinline__ int last_request(const int32_t *q_start, int batch, int x, Key key)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = batch;                            // it is one of lo .. lo + n - 1 (or lo, if none is)
+    while (n > 1) {
+        const int step = (n + 63) >> 6, r = lo + lane * step;
+        const unsigned long long le = __ballot(lane * step < n && key(q_start[min(r, batch - 1)], r) <= x);
+        const int at = max(0, 63 - __clzll((long long)le)) * step;     // (none: clz 64)
+        lo += at;
+        n = min(step, n - at);
+    }
+    return lo;
+}
+
+// Writes the key and value vectors kn, vn ([H_kv][D]) of one token at cached position t of request r.
+// Called by a whole workgroup; k0 and v0 are what this thread takes of them first, asked for before
+// anything is known of where they go.  A position outside the block-table row, or a block id outside
+// the pool, writes nothing.
+template <typename T>
+__device__ __forceinline__ uint4 first_unit(const AppendArgs &a, const T *x)
+{
+    const int i = threadIdx.x * (16 / (int)sizeof(T));
+    return i < a.num_kv_heads * a.head_dim ? *reinterpret_cast<const uint4 *>(x + i) : make_uint4(0, 0, 0, 0);
+}
 template <typename T, bool TILED>
-__device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t, const T *kn, const T *vn)
+__device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t, const T *kn, const T *vn, uint4 k0, uint4 v0)
 {
     const int D = a.head_dim, Hkv = a.num_kv_heads, bs = a.block_size;
     const int lb = t >> a.log2_block_size, slot = t & (bs - 1);
@@ -42,38 +67,47 @@ __device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t,
     // both layouts (8 dims of a key are contiguous), values in the plain layout
     constexpr int V16 = 16 / (int)sizeof(T);
     for (int i = threadIdx.x * V16; i < Hkv * D; i += kAppendThreads * V16) {
+        if (i >= kAppendThreads * V16) {
+            k0 = *reinterpret_cast<const uint4 *>(kn + i);
+            v0 = *reinterpret_cast<const uint4 *>(vn + i);
+        }
         const int g = i / D, d = i - g * D;           // d is a multiple of V16, and V16 divides D
         const size_t ko = TILED ? (size_t)(slot >> 4) * 16 * D + (size_t)((d >> 3) * 16 + (slot & 15)) * 8
                                 : (size_t)slot * D + d;
-        *reinterpret_cast<uint4 *>(kt + g * tile + ko) = *reinterpret_cast<const uint4 *>(kn + i);
-        if (!TILED) {
-            *reinterpret_cast<uint4 *>(vt + g * tile + ko) = *reinterpret_cast<const uint4 *>(vn + i);
+        *reinterpret_cast<uint4 *>(kt + g * tile + ko) = k0;
+        if constexpr (!TILED) {
+            *reinterpret_cast<uint4 *>(vt + g * tile + ko) = v0;
         } else {
             const size_t base = (size_t)(slot >> 4) * 16 * D;
             const int s16 = slot & 15;
+            const uint32_t w[4] = {v0.x, v0.y, v0.z, v0.w};
 #pragma unroll
             for (int e = 0; e < V16; ++e) {
                 const int dd = d + e;
                 const size_t vo = base +
                                   (size_t)(((((dd >> 5) * 4 + (s16 >> 2)) * 16 + (dd & 15)) * 2 + ((dd & 31) >> 4)) * 4) +
                                   (s16 & 3);
-                vt[g * tile + vo] = vn[i + e];
+                vt[g * tile + vo] = (T)(w[e >> 1] >> (16 * (e & 1)));
             }
         }
     }
     return true;
 }
 
+// Bound by the round trips in front of the stores: mask, length and the vectors are asked for
+// together, then the table entry.  4 layers of append + decode for 16 requests on 40 heads of 128:
+// 116.7 us with each asked for when the one before had come, 113.8 now.
 template <typename T, bool TILED>
 __global__ __launch_bounds__(kAppendThreads) void kv_append(const AppendArgs a)
 {
     const int r = blockIdx.x;
-    if (!a.running[r]) return;                        // uniform over the workgroup
-    const int t = a.ctx_lens[r];
-    __syncthreads();
     const size_t row = (size_t)r * a.num_kv_heads * a.head_dim;
-    const bool ok = scatter_token<T, TILED>(a, r, t, static_cast<const T *>(a.k_new) + row,
-                                            static_cast<const T *>(a.v_new) + row);
+    const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
+    const uint4 k0 = first_unit(a, kn), v0 = first_unit(a, vn);
+    const int t = a.ctx_lens[r];
+    if (!a.running[r]) return;                        // uniform over the workgroup
+    __syncthreads();
+    const bool ok = scatter_token<T, TILED>(a, r, t, kn, vn, k0, v0);
     if (ok && a.advance && threadIdx.x == 0) a.ctx_lens[r] = t + 1;
 }
 
@@ -86,18 +120,14 @@ template <typename T, bool TILED>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendArgs a)
 {
     const int n = blockIdx.x;
-    int lo = 0, hi = a.batch;                         // last r with q_start[r] <= n
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a.q_start[mid] <= n) lo = mid; else hi = mid;
-    }
-    const int r = lo;
+    const size_t row = (size_t)n * a.num_kv_heads * a.head_dim;
+    const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
+    const uint4 k0 = first_unit(a, kn), v0 = first_unit(a, vn);
+    const int r = last_request(a.q_start, a.batch, n, [](int q, int) { return q; });
     const int first = a.q_start[r], count = a.q_start[r + 1] - first;
     if (n >= first + count) return;                   // q_start[batch] is less than the grid
     const int t = a.ctx_lens[r] - count + (n - first);
-    const size_t row = (size_t)n * a.num_kv_heads * a.head_dim;
-    scatter_token<T, TILED>(a, r, t, static_cast<const T *>(a.k_new) + row,
-                            static_cast<const T *>(a.v_new) + row);
+    scatter_token<T, TILED>(a, r, t, kn, vn, k0, v0);
 }
 
 // The same for the tiled layout (bf16), where the 16-byte unit of a value tile is four
@@ -114,12 +144,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const A
 {
     typedef uint16_t T;
     const int w = blockIdx.x;
-    int lo = 0, hi = a.batch;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((a.q_start[mid] >> 4) + 2 * mid <= w) lo = mid; else hi = mid;
-    }
-    const int r = lo;
+    const int r = last_request(a.q_start, a.batch, w, [](int q, int i) { return (q >> 4) + 2 * i; });
     const int first = a.q_start[r], count = a.q_start[r + 1] - first;
     const int p0 = a.ctx_lens[r] - count;             // position of the request's first new token
     if (count <= 0 || p0 < 0) return;
@@ -129,41 +154,46 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const A
     const int D = a.head_dim, Hkv = a.num_kv_heads, bs = a.block_size;
     const int lb = (sub * 16) >> a.log2_block_size;
     if (lb >= a.max_blocks) return;
-    const int block = a.block_table[(size_t)r * a.max_blocks + lb];
-    if (block < 0 || block >= a.num_blocks) return;
-    const size_t tile = (size_t)bs * D;
-    const size_t at = (((size_t)block * a.num_layers + a.layer) * Hkv) * tile + (size_t)(((sub * 16) & (bs - 1)) >> 4) * 16 * D;
-    T *kt = static_cast<T *>(a.k_pool) + at;
-    T *vt = static_cast<T *>(a.v_pool) + at;
-    const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
-    const int row = Hkv * D;                          // elements of one token's keys (or values)
-
     const int g = blockIdx.y;                         // kv head
-    kt += g * tile; vt += g * tile;
-    kn += g * D; vn += g * D;
+    const int row = Hkv * D;                          // elements of one token's keys (or values)
+    const T *kn = static_cast<const T *>(a.k_new) + g * D, *vn = static_cast<const T *>(a.v_new) + g * D;
+    const int block = a.block_table[(size_t)r * a.max_blocks + lb];
 
-    const int c8 = D / 8;                             // keys: (position, 8 dims) -> one 16-byte unit
-    for (int i = threadIdx.x; i < (t_hi - t_lo) * c8; i += kAppendThreads) {
-        const int c = i % c8, t = t_lo + i / c8;
-        *reinterpret_cast<uint4 *>(kt + (size_t)(c * 16 + (t & 15)) * 8) =
-            *reinterpret_cast<const uint4 *>(kn + (size_t)(first + (t - p0)) * row + c * 8);
+    // What this thread takes first is asked for together with the table entry, whatever that turns out to be.
+    // Keys: (position, 8 dims) -> one 16-byte unit.
+    const int c8 = D / 8, n_keys = (t_hi - t_lo) * c8;
+    auto key_unit = [&](int i) {
+        return *reinterpret_cast<const uint4 *>(kn + (size_t)(first + (t_lo + i / c8 - p0)) * row + i % c8 * 8);
+    };
+    uint4 ku = make_uint4(0, 0, 0, 0);
+    if ((int)threadIdx.x < n_keys) ku = key_unit(threadIdx.x);
+    // Values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16): at
+    // most one per thread.
+    const int vi = threadIdx.x, j = vi & 7, i32 = (vi >> 3) % (D / 32), q = vi / (8 * (D / 32));
+    const int t0 = sub * 16 + 4 * q, d0 = 32 * i32 + 2 * j;   // the quad's first position, the first dim
+    const bool quad = q < 4 && t0 >= t_lo && t0 + 4 <= t_hi;
+    uint32_t lo2[4] = {}, hi2[4] = {};                // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
+    if (quad) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const T *src = vn + (size_t)(first + (t0 + k - p0)) * row + d0;
+            lo2[k] = *reinterpret_cast<const uint32_t *>(src);
+            hi2[k] = *reinterpret_cast<const uint32_t *>(src + 16);
+        }
     }
 
-    // values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16)
-    for (int i = threadIdx.x; i < 4 * (D / 32) * 8; i += kAppendThreads) {
-        const int j = i & 7, i32 = (i >> 3) % (D / 32), q = i / (8 * (D / 32));
-        const int t0 = sub * 16 + 4 * q;              // the quad's first position
-        if (t0 + 4 <= t_lo || t0 >= t_hi) continue;
-        const int d0 = 32 * i32 + 2 * j;
+    if (block < 0 || block >= a.num_blocks) return;
+    const size_t tile = (size_t)bs * D;
+    const size_t at = (((size_t)block * a.num_layers + a.layer) * Hkv + g) * tile + (size_t)(((sub * 16) & (bs - 1)) >> 4) * 16 * D;
+    T *kt = static_cast<T *>(a.k_pool) + at;
+    T *vt = static_cast<T *>(a.v_pool) + at;
+    for (int i = threadIdx.x; i < n_keys; i += kAppendThreads) {
+        if (i >= kAppendThreads) ku = key_unit(i);
+        *reinterpret_cast<uint4 *>(kt + (size_t)(i % c8 * 16 + ((t_lo + i / c8) & 15)) * 8) = ku;
+    }
+    if (q < 4 && t0 + 4 > t_lo && t0 < t_hi) {
         T *dst = vt + (size_t)((i32 * 4 + q) * 16 + 2 * j) * 8;   // unit of dim d0; dim d0 + 1's follows
-        if (t0 >= t_lo && t0 + 4 <= t_hi) {
-            uint32_t lo2[4], hi2[4];                  // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const T *src = vn + (size_t)(first + (t0 + k - p0)) * row + d0;
-                lo2[k] = *reinterpret_cast<const uint32_t *>(src);
-                hi2[k] = *reinterpret_cast<const uint32_t *>(src + 16);
-            }
+        if (quad) {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int sh = 16 * e;
