@@ -87,6 +87,11 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
         if (slot < full_groups * tiles) {
             pair = xcd + 8 * (slot / tiles);
             t = slot % tiles;
+            // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
+            // second turn begins with a pair, its pairs start with their short tiles, so that a CU has
+            // a long and a short one: 4 prompts of 512 on 16 heads of 256, append included, 41.2 -> 37.6
+            // us, 2 of 1 000 54.6 -> 49.3.  (Beginning inside a pair's tiles: 2 % slower than without.)
+            if (gridDim.x <= 512 && 32 % tiles == 0 && (slot & 32)) t = tiles - 1 - t;
         } else {
             const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
             const int i = (slot - full_groups * tiles) * 8 + xcd;

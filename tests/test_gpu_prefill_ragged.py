@@ -1,5 +1,5 @@
-"""lamps_prefill_attn on batches whose requests bring very different numbers of new tokens: the launches
-that start workgroups for the tiles there are only, against the fp64 oracle -- requests without new
+"""lamps_prefill_attn: which workgroup takes which tile.  Batches whose requests bring very different
+numbers of new tokens, where workgroups are started for the tiles there are only, against the fp64 oracle -- requests without new
 tokens, one long prompt among short ones, up to and beyond the requests one wave keeps track of, head
 counts that are no multiple of 8, every head size and layout."""
 import numpy as np
@@ -32,6 +32,19 @@ def test_ragged_batches(H, Hkv, D, n_req, most, cached):
     rng = np.random.RandomState(n_req)
     new = [int(round(most ** u)) - 1 for u in rng.uniform(0, 0.7, n_req)]
     new[int(rng.randint(n_req))] = most
+    _check(H, Hkv, D, new, cached, rng)
+
+
+#  launches that fit the chip at once, where half of the pairs take their tiles the other way round (4 and 8
+#  tiles a pair), or not, as the second turn begins inside a pair's tiles (5, 12 and 7)
+@pytest.mark.parametrize("H,Hkv,D,n_req,most,cached", [(8, 8, 64, 8, 640, 0), (8, 8, 64, 5, 1500, 0), (8, 8, 256, 5, 440, 70),
+                                                       (16, 8, 128, 8, 512, 9), (8, 8, 128, 6, 500, 40)])
+def test_even_batches(H, Hkv, D, n_req, most, cached):
+    _check(H, Hkv, D, [most] * n_req, cached, np.random.RandomState(n_req))
+
+
+def _check(H, Hkv, D, new, cached, rng):
+    n_req = len(new)
     ctx = [max(n + int(rng.randint(cached + 1)), 1) for n in new]
     bs = 16
     blocks = [(c + bs - 1) // bs for c in ctx]
