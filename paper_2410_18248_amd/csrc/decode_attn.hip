@@ -202,8 +202,9 @@ __host__ __device__ __forceinline__ int balanced_ints(int batch)
 template <typename R, bool TOGETHER>
 __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 {
-    constexpr int D = R::D, GT = R::GT;               // below, a chunk is GT tokens
-    constexpr int kWhole = R::CT / GT;                // ... and this many are what a wave loads at a time: 1 or 2
+    constexpr int D = R::D;
+    // below, a chunk is GT tokens, and a wave loads one of them, or two, at a time
+    const int GT = R::CT == R::GT || a.whole_chunks ? R::CT : R::GT, log2_whole = GT == R::CT ? 0 : 1;
     extern __shared__ int prefix[];                   // then pieces[] (balanced_ints), and, TOGETHER, [wave][head][D + 2] floats
     __shared__ int wave_total[kWaves], wave_longest[kWaves];
 
@@ -265,9 +266,9 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     // attention, 200 us of merge).  Then only as many shares are used as gives each 2, 4 or
     // 8 chunks -- for a longest range of 256, 512, 1024 chunks and more -- and the rest stay
     // empty.  TOGETHER: a chunk per wave at least, and the rest as for a range a quarter as long.
-    const int span = longest / kWhole;
+    const int span = longest >> log2_whole;
     const int log2_share_chunks = (TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
-                                            : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + (kWhole > 1 ? 1 : 0);
+                                            : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + log2_whole;
     const long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
     // A launch with less work than that for every share is bound by latency, and a share that straddles
     // two ranges is two chains of dependent loads (3.5 us each) behind each other: its shares are pieces
@@ -552,6 +553,11 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
     const int HC = a.num_q_heads / a.heads_per_pass;
     const int P = wgs * (TOGETHER ? 1 : kWaves);
     DecodeArgs b = a;
+    // Cutting by half-chunks evens small launches out (4 layers of 8 requests of 20 to 159 tokens, 16
+    // heads of 256: 57 us, by whole chunks 64), and costs a half-empty load where a range is cut, which is
+    // all that is left where a share is several ranges long (512 short requests on 40 heads, 40 layers:
+    // 14.70 ms, by whole chunks 14.62).
+    b.whole_chunks = (long long)a.batch * HC >= 2LL * P;
     b.share_gcd = b.share_inv = b.share_period = 0;                    // shares in launch order
     if (wgs % 8 == 0) {                               // whole rounds over the XCDs: ranked shares
         int g = HC, t = P;
