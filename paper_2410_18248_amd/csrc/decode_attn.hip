@@ -603,8 +603,9 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     }
     // balanced: as many workgroups as the chip holds at once for this kernel (fewer
     // if the partial slots of that many wave shares would not fit behind a.partials)
-    int resident = 0;
+    int resident = 0, together = 0;                   // (both asked for at once: a later call may be under capture)
     hipError_t e = resident_workgroups<R, false>(a, &resident);
+    if (e == hipSuccess) e = resident_workgroups<R, true>(a, &together);
     if (e != hipSuccess) return e;
     const size_t per_share = decode_share_bytes(a.heads_per_pass, a.head_dim);
     if (demand) {
@@ -617,11 +618,8 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     // With eight waves and more to a range (if every request runs) they are better off together; with
     // six (16 requests of 60 to 1 500 tokens, 40 heads) the barriers cost 4 % more than they save.
     constexpr int kTogetherWaves = 8;
-    if ((long long)a.batch * HC * kTogetherWaves <= (long long)wgs * kWaves) {
-        int together = 0;
-        if ((e = resident_workgroups<R, true>(a, &together)) != hipSuccess) return e;
+    if ((long long)a.batch * HC * kTogetherWaves <= (long long)wgs * kWaves)
         return launch_balanced<R, true>(a, min(together, wgs), s);
-    }
     return launch_balanced<R, false>(a, wgs, s);
 }
 
