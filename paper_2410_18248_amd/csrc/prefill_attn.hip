@@ -121,28 +121,43 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
             }
             most = max(most, n_tiles[k]);
         }
-        most = __builtin_amdgcn_readlane(wave_max_to(most), 63);
+        // tiles of index t and above, of one head; decreasing in t
+        auto above = [&](int t) {
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < kRagged; ++k) n += max(0, n_tiles[k] - t);
+            return __builtin_amdgcn_readlane(wave_scan(n), 63);
+        };
         int left = blockIdx.x / heads;                    // requests' tiles before this one
         at.head = blockIdx.x - left * heads;
         at.r = -1;
-        for (int t = most - 1; t >= 0 && at.r < 0; --t)
+        // the level: above(lo) > left >= above(hi).  (One level after the other, 45 of them on prompts of
+        // up to 1 413 tokens with 4 heads per kv head, was 2 us and made that launch 5 % slower than the
+        // full grid.)
+        int lo = 0, hi = __builtin_amdgcn_readlane(wave_max_to(most), 63);
+        if (above(0) <= left) return false;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (above(mid) > left) lo = mid; else hi = mid;
+        }
+        left -= above(lo + 1);
+        at.tile = lo;
 #pragma unroll
-            for (int k = 0; k < kRagged; ++k)
-                if (64 * k < a.batch && at.r < 0) {
-                    const unsigned long long have = __ballot(n_tiles[k] > t);
-                    const int n = __popcll(have);
-                    if (left < n) {
-                        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(have >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)have, 0));
-                        const int l = __ffsll((long long)__ballot(n_tiles[k] > t && before == left)) - 1;
-                        at.r = 64 * k + l;
-                        at.tile = t;
-                        at.first = __builtin_amdgcn_readlane(first[k], l);
-                        at.n_new = __builtin_amdgcn_readlane(n_new[k], l);
-                        at.ctx = __builtin_amdgcn_readlane(ctx[k], l);
-                    } else {
-                        left -= n;
-                    }
+        for (int k = 0; k < kRagged; ++k)
+            if (64 * k < a.batch && at.r < 0) {
+                const unsigned long long have = __ballot(n_tiles[k] > lo);
+                const int n = __popcll(have);
+                if (left < n) {
+                    const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(have >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)have, 0));
+                    const int l = __ffsll((long long)__ballot(n_tiles[k] > lo && before == left)) - 1;
+                    at.r = 64 * k + l;
+                    at.first = __builtin_amdgcn_readlane(first[k], l);
+                    at.n_new = __builtin_amdgcn_readlane(n_new[k], l);
+                    at.ctx = __builtin_amdgcn_readlane(ctx[k], l);
+                } else {
+                    left -= n;
                 }
+            }
         if (at.r < 0) return false;
     }
     // a context shorter than its new tokens, or longer than the block-table row, is the caller's
