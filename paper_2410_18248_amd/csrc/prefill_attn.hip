@@ -10,6 +10,7 @@
 
 #include "attn_reducers.h"
 #include "internal.h"
+#include "prefill_split.h"
 
 namespace lamps {
 namespace {
@@ -316,33 +317,31 @@ constexpr int vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
 
 // Splitting a tile's cached positions.  One workgroup per (request, kv head, tile) leaves most of
 // the chip idle when few requests bring few new tokens -- the API responses of a dozen requests
-// are 100 to 200 workgroups, each a serial walk over a whole context.  Then the stages of every
-// tile are cut into runs of `per` stages, each a workgroup of its own that leaves its columns'
+// are 100 to 200 workgroups, each a serial walk over a whole context.  Then the stages of the tiles
+// are cut into runs (prefill_split.h), each a workgroup of its own that leaves its columns'
 // (reference, sum, unnormalised output) in the workspace; the last of a tile to do so adds them up
-// in order.  `per` is the smallest that gives no more runs than there are workgroups (slots), so the
-// work of the launch is even whatever the contexts are and no workgroup is started for nothing in
-// front of one that has work (a workgroup that finds nothing to do holds its LDS for 2 us).
+// in order.  The references of the runs differ from that of an uncut walk, and so do the roundings of
+// the bf16 weights: a request's output depends on how it is cut, that is on the other requests of the
+// call, by what another order of the same sums gives.
 // Bound by the walk over K / V and the hand-over: a dozen requests with 6 to 58 new tokens on 345 to
-// 2 490 cached, 32 / 8 heads of 128 (50 MB): 63 us for this kernel before, 25 now; append + attention
-// of one request with 16 new on 3 000: 80 us before, 32 now.  (Adding the runs up in a second launch
-// instead is 1-8 us faster on such a call and 4 us slower on every one that has nothing to add up.)
+// 2 490 cached, 32 / 8 heads of 128 (50 MB): 63 us for this kernel before, 25 now; one request with 16
+// new on 3 000: 75 us before, 21 now.  (Adding the runs up in a second launch instead is 1-8 us faster
+// on such a call and 4 us slower on every one that has nothing to add up.)
 constexpr int kSplitSlots = 512;         // two workgroups per CU
 constexpr int kSplitRequests = 64;       // one per lane
-constexpr int kSplitStages = 32;         // a block-table row of fewer (1024 positions) is not split: the hand-over costs
-                                         // what a dozen stages do
-constexpr int kMinRun = 12;              // stages: 384 positions (8 and 16 measured 0-4 % and 0-10 % slower)
+constexpr int kSplitStages = 32;         // a block-table row of fewer (1024 positions) is not split
 
 struct Run {
     int r, g, tile;                      // request, kv head, tile of new tokens (r < 0: nothing to do)
     int first, n_new, ctx;               // of the request: first new row, new rows, context length
-    int first_item, stride;              // items (= workgroups, partial slots) of the tile's runs
-    int per;                             // stages per run
+    int item, first_item, stride;        // the workgroup's item (= partial slot); those of the tile's runs
+    int index, per;                      // which of the tile's runs, and stages per run
 };
 
-// What workgroup `item` of a split launch is to do.  Items are ordered (request, run, kv head,
-// tile).  Every wave works it out for itself from q_start and ctx_lens, one request per lane: one
-// round trip to memory, no barrier.  (The launcher has checked that the sums fit 32 bits.)
-__device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT, int item)
+// What a workgroup of a split launch is to do.  Every wave works it out for itself from q_start and
+// ctx_lens, one request per lane: one round trip to memory, no barrier.  (The launcher has checked that
+// the sums fit 32 bits.)
+__device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT)
 {
     const DecodeArgs &a = p.d;
     const int lane = threadIdx.x & 63;
@@ -354,29 +353,32 @@ __device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT, i
         // a context shorter than its new tokens, or longer than the block-table row, is the
         // caller's mistake: nothing is read or written for it
         if (n_new > 0 && ctx >= n_new && ctx <= a.max_blocks * a.block_size) {
-            n_tiles = min((n_new + WT - 1) / WT, tiles);
+            n_tiles = split::tiles_of(n_new, WT, tiles);
             stages = (ctx - 1) / kStage + 1;          // of the last tile; no tile has more
         }
     }
-    const int sum_stages = __builtin_amdgcn_readlane(wave_scan(stages * n_tiles), 63);
-    const int sum_tiles = __builtin_amdgcn_readlane(wave_scan(n_tiles), 63);
-    // a tile's last run may be short: the sum over tiles of ceil(stages / per) stays within the slots
-    const int spare = max(1, p.slots / a.num_kv_heads - sum_tiles);
+    split::Sums sums;
+    sums.stages = __builtin_amdgcn_readlane(wave_scan(stages * n_tiles), 63);
+    sums.tiles = __builtin_amdgcn_readlane(wave_scan(n_tiles), 63);
+    const int per = split::run_length(sums, p.head_slots);
+    int runs = 1;
+    if (__any(stages > per)) runs = split::runs_of(max(stages, 1), per, p.slots);
+    const int items = n_tiles * runs * a.num_kv_heads, upto = wave_scan(items);
     Run run;
-    run.per = max(kMinRun, (sum_stages + spare - 1) / spare);
-    const int items = n_tiles * ((stages + run.per - 1) / run.per) * a.num_kv_heads;
-    const int before = wave_scan(items) - items;
-    const unsigned long long hit = __ballot(item >= before && item < before + items);
-    run.r = __ffsll((long long)hit) - 1;
-    if (run.r < 0) return run;
-    const int nt = __builtin_amdgcn_readlane(n_tiles, run.r), base = __builtin_amdgcn_readlane(before, run.r);
+    run.item = split::item_of(blockIdx.x, __builtin_amdgcn_readlane(upto, 63), p.slots);
+    run.r = __ffsll((long long)__ballot(run.item >= upto - items && run.item < upto)) - 1;
+    if (run.r < 0) return run;                        // (no items: those of -1, too)
+    const int nt = __builtin_amdgcn_readlane(n_tiles, run.r), nr = __builtin_amdgcn_readlane(runs, run.r);
+    const split::Piece at = split::piece_of(run.item - __builtin_amdgcn_readlane(upto - items, run.r), nt, nr);
+    run.g = at.head;
+    run.tile = at.tile;
     run.first = __builtin_amdgcn_readlane(first, run.r);
     run.n_new = __builtin_amdgcn_readlane(n_new, run.r);
     run.ctx = __builtin_amdgcn_readlane(ctx, run.r);
-    run.stride = a.num_kv_heads * nt;
-    run.g = (item - base) / nt % a.num_kv_heads;
-    run.tile = (item - base) % nt;
-    run.first_item = base + run.g * nt + run.tile;
+    run.stride = nt;
+    run.first_item = run.item - at.run * nt;
+    run.index = at.run;
+    run.per = per;
     return run;
 }
 
@@ -444,9 +446,9 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     int item = 0, st0 = 0, per = 0x7fffffff;         // SPLIT: the workgroup's item, first stage, most stages,
     int first_item = 0, item_stride = 0;             // ... and the items of its tile's runs
     if constexpr (SPLIT) {
-        item = (blockIdx.x & 7) * (p.slots >> 3) + (blockIdx.x >> 3);   // neighbours in item order share blocks: one XCD
-        const Run run = locate(p, tiles, WT, item);
+        const Run run = locate(p, tiles, WT);
         if (run.r < 0) return;
+        item = run.item;
         r = run.r;
         g = run.g;
         tile = run.tile;
@@ -456,7 +458,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         per = run.per;
         first_item = run.first_item;
         item_stride = run.stride;
-        st0 = (item - run.first_item) / run.stride * per;
+        st0 = run.index * per;
     } else {
         Place at;
         if (!place(p, a.num_kv_heads, tiles, full_groups, WT, at)) return;
@@ -482,8 +484,10 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     int n_runs = 1;                                   // workgroups that share the tile
     if constexpr (SPLIT) {
         if (st0 >= n_stages) return;                  // a tile before the request's last one has fewer
-        n_runs = (n_stages + per - 1) / per;
-        n_stages = min(n_stages, st0 + per);
+        if (n_stages > per) {
+            n_runs = (int)((unsigned)(n_stages + per - 1) / (unsigned)per);
+            n_stages = min(n_stages, st0 + per);
+        }
         wg_maxpos = min(wg_maxpos, n_stages * kStage - 1);
     }
 
@@ -870,6 +874,7 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
     // (Tiles of 128: a quarter.  They come with many new tokens, most of a prompt, where the causal
     // half of the items is empty: one prompt of 1 000 on 8 kv heads took 46 us split, 34 not.)
     if (all > p.slots / (kCols == 16 ? 2 : 4) || stages < kSplitStages || all * stages > 0x7fffffff) return hipSuccess;
+    p.head_slots = p.slots / Hkv;
     hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, true>), dim3(p.slots), dim3(kThreads), 0, s, p, (int)tiles, 0);
     *done = true;
     return hipGetLastError();
