@@ -329,6 +329,7 @@ constexpr int vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
 // on such a call and 4 us slower on every one that has nothing to add up.)
 constexpr int kSplitSlots = 512;         // two workgroups per CU
 constexpr int kSplitRequests = 64;       // one per lane
+constexpr int kWhole = 1 << 26;          // stages per run of a request that is not cut: more than any context has
 constexpr int kSplitStages = 32;         // a block-table row of fewer (1024 positions) is not split
 
 struct Run {
@@ -341,6 +342,7 @@ struct Run {
 // What a workgroup of a split launch is to do.  Every wave works it out for itself from q_start and
 // ctx_lens, one request per lane: one round trip to memory, no barrier.  (The launcher has checked that
 // the sums fit 32 bits.)
+template <int D, bool WIDE, int GRP>
 __device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT)
 {
     const DecodeArgs &a = p.d;
@@ -360,9 +362,10 @@ __device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT)
     split::Sums sums;
     sums.stages = __builtin_amdgcn_readlane(wave_scan(stages * n_tiles), 63);
     sums.tiles = __builtin_amdgcn_readlane(wave_scan(n_tiles), 63);
-    const int per = split::run_length(sums, p.head_slots);
+    sums.most = WIDE ? __builtin_amdgcn_readlane(wave_max_to(stages), 63) : 0;
+    const split::Cut cut = split::cut_of(sums, p.head_slots, a.num_kv_heads, GRP, D, WIDE);
     int runs = 1;
-    if (__any(stages > per)) runs = split::runs_of(max(stages, 1), per, p.slots);
+    if (__any(stages > cut.worth)) runs = split::runs_of(stages, cut, p.slots);
     const int items = n_tiles * runs * a.num_kv_heads, upto = wave_scan(items);
     Run run;
     run.item = split::item_of(blockIdx.x, __builtin_amdgcn_readlane(upto, 63), p.slots);
@@ -378,7 +381,7 @@ __device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT)
     run.stride = nt;
     run.first_item = run.item - at.run * nt;
     run.index = at.run;
-    run.per = per;
+    run.per = nr > 1 ? cut.per : kWhole;
     return run;
 }
 
@@ -427,7 +430,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     // The pool's tiles go to LDS as they are, by loads that write LDS directly
     // (global_load_lds_dwordx4: lane l of a wave writes 16 bytes at base + 16 l, read from any
     // address); two stage buffers (64 KiB at head_dim 256).
-    constexpr int NB = SPLIT && D <= 128 ? 4 : 2;    // group buffers
+    constexpr int NB = SPLIT && D <= 128 && GRP == 1 ? 4 : 2;   // group buffers
     constexpr int NU = D / 8;                        // 16-byte units of one row (plain layout)
     constexpr int SUBB = 16 * D * 2;                 // one 16-position sub-tile of K or V
     constexpr int VOFF = 2 * SUBB;                   // V follows the two K sub-tiles
@@ -446,7 +449,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     int item = 0, st0 = 0, per = 0x7fffffff;         // SPLIT: the workgroup's item, first stage, most stages,
     int first_item = 0, item_stride = 0;             // ... and the items of its tile's runs
     if constexpr (SPLIT) {
-        const Run run = locate(p, tiles, WT);
+        const Run run = locate<D, (D >= 256 || kCols > 16), GRP>(p, tiles, WT);
         if (run.r < 0) return;
         item = run.item;
         r = run.r;
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
 #pragma unroll
         for (int h = 0; h < GRP; ++h) dma(grp * GRP + h, buf + h * STAGE, ent[2 * h], ent[2 * h + 1]);
     };
-    const int grp0 = SPLIT ? st0 : 0;                 // SPLIT: one stage per group
+    const int grp0 = SPLIT ? st0 / GRP : 0;           // (a run begins with a group)
     constexpr int kGroupLoads = GRP * 2 * LPT;        // of one wave
     {
         uint32_t first_ent[NB][2 * GRP];
@@ -875,7 +878,10 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
     // half of the items is empty: one prompt of 1 000 on 8 kv heads took 46 us split, 34 not.)
     if (all > p.slots / (kCols == 16 ? 2 : 4) || stages < kSplitStages || all * stages > 0x7fffffff) return hipSuccess;
     p.head_slots = p.slots / Hkv;
-    hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, 1, true>), dim3(p.slots), dim3(kThreads), 0, s, p, (int)tiles, 0);
+    // Two stages per barrier for tiles of 128 as on the plain grid, so that a launch that cuts nothing is as
+    // fast as there (one stage and four buffers: 900 new, 16 / 1 heads of 128, 30.3 us against 27.3); one
+    // stage and four buffers for tiles of 64, which wait for memory.
+    hipLaunchKernelGGL((prefill_mfma<D, TILED, kCols, (D <= 128 && kCols > 16 ? 2 : 1), true>), dim3(p.slots), dim3(kThreads), 0, s, p, (int)tiles, 0);
     *done = true;
     return hipGetLastError();
 }

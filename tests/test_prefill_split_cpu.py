@@ -15,8 +15,12 @@ SOURCE = """
 using namespace lamps::split;
 extern "C" {
 int c_tiles(int n, int wt, int tiles) { return tiles_of(n, wt, tiles); }
-int c_per(int stages, int tiles, int head_slots) { return run_length({stages, tiles}, head_slots); }
-int c_runs(int stages, int per, int slots) { return runs_of(stages, per, slots); }
+void c_cut(int stages, int tiles, int most, int head_slots, int heads, int group, int dim, int wide, int *out)
+{
+    const Cut c = cut_of({stages, tiles, most}, head_slots, heads, group, dim, wide);
+    out[0] = c.per; out[1] = c.worth;
+}
+int c_runs(int stages, int per, int worth, int slots) { return runs_of(stages, {per, worth}, slots); }
 int c_item(int block, int items, int slots) { return item_of(block, items, slots); }
 void c_piece(int x, int tiles, int runs, int *out)
 {
@@ -38,15 +42,16 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
-def _plan(lib, heads, new, ctx, wt, slots):
+def _plan(lib, heads, new, ctx, wt, slots, group, wide, dim=128):
     """What the workgroups do: a list of (block, item, request, head, tile, run), per, and the requests' runs."""
     tiles = -(-max(new) // wt)
     nt = [lib.c_tiles(n, wt, tiles) if n else 0 for n in new]
     assert nt == [-(-n // wt) for n in new]
     stages = [(c - 1) // 32 + 1 if n else 0 for n, c in zip(new, ctx)]
     out = (ctypes.c_int * 3)()
-    per = lib.c_per(sum(a * b for a, b in zip(stages, nt)), sum(nt), slots // heads)
-    runs = [lib.c_runs(max(s, 1), per, slots) for s in stages]
+    lib.c_cut(sum(a * b for a, b in zip(stages, nt)), sum(nt), max(stages), slots // heads, heads, group, dim, wide, out)
+    per, worth = out[0], out[1]
+    runs = [lib.c_runs(s, per, worth, slots) for s in stages]
     items = [a * b * heads for a, b in zip(nt, runs)]
     upto = np.cumsum(items)
     work = []
@@ -60,9 +65,9 @@ def _plan(lib, heads, new, ctx, wt, slots):
     return work, per, runs, nt, stages
 
 
-@pytest.mark.parametrize("seed", [4, 5])
-def test_every_piece_has_one_workgroup(lib, seed):
-    rng = random.Random(seed)
+@pytest.mark.parametrize("wide,group,dim", [(False, 1, 128), (True, 1, 256), (True, 2, 128)])
+def test_every_piece_has_one_workgroup(lib, wide, group, dim):
+    rng = random.Random(3 + group)
     done = 0
     while done < 300:
         heads = rng.choice([1, 2, 3, 4, 5, 8, 16, 32, 40])
@@ -76,8 +81,8 @@ def test_every_piece_has_one_workgroup(lib, seed):
         if sum(-(-n // wt) for n in new) * heads > slots // 2:      # the launcher does not split such a call
             continue
         done += 1
-        work, per, runs, nt, stages = _plan(lib, heads, new, ctx, wt, slots)
-        assert per >= 12
+        work, per, runs, nt, stages = _plan(lib, heads, new, ctx, wt, slots, group, wide, dim)
+        assert per % group == 0 and per >= 12
         total = sum(t * k * heads for t, k in zip(nt, runs))
         assert total <= slots                                        # a partial slot for each
         assert [w[1] for w in sorted(work, key=lambda w: w[1])] == list(range(total))
@@ -96,11 +101,20 @@ def test_every_piece_has_one_workgroup(lib, seed):
 
 def test_empty_runs_do_not_gather_on_one_xcd(lib):
     """Tiles of a prompt that see half the context have half the runs: what is left to do is even over the XCDs."""
-    work, per, runs, nt, stages = _plan(lib, 8, [200], [1300], 16, 512)
+    work, per, runs, nt, stages = _plan(lib, 8, [200], [1300], 16, 512, 1, False)
     assert runs[0] > 2
     live = [w for w in work if w[5] * per < (1100 + min(200, 16 * (w[4] + 1)) - 1) // 32 + 1]
     share = np.bincount([w[0] % 8 for w in live], minlength=8)
     assert share.max() - share.min() <= 2, share
+
+
+def test_requests_that_gain_nothing_are_not_cut(lib):
+    for n, c, cut in [(400, 400, False), (16, 384, False), (16, 640, True), (16, 3000, True)]:
+        assert (_plan(lib, 8, [n], [c], 16, 512, 1, False)[2][0] > 1) == cut, (n, c)
+    for n, c, cut in [(400, 1000, False), (500, 500, False), (130, 3130, True), (400, 3400, True)]:
+        assert (_plan(lib, 8, [n], [c], 32, 512, 2, True)[2][0] > 1) == cut, (n, c)
+    for n, c, cut in [(500, 500, False), (900, 1600, False), (400, 1100, True), (700, 3700, True)]:
+        assert (_plan(lib, 16, [n], [c], 64, 512, 1, True, 256)[2][0] > 1) == cut, (n, c)
 
 
 def test_lying_arguments_stay_in_the_slots(lib):
@@ -108,7 +122,7 @@ def test_lying_arguments_stay_in_the_slots(lib):
     for items in [513, 600, 4096, 1 << 24]:
         got = [lib.c_item(b, items, 512) for b in range(512)]
         assert min(got) >= 0 and max(got) < 512 and len(set(got)) == 512
-    assert lib.c_runs(1 << 25, 12, 512) == 512
+    assert lib.c_runs(1 << 25, 12, 18, 512) == 512
 
 
 def test_small_division(lib):
