@@ -558,7 +558,13 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     };
     const int grp0 = SPLIT ? st0 / GRP : 0;           // (a run begins with a group)
     constexpr int kGroupLoads = GRP * 2 * LPT;        // of one wave
-    {
+    // The first tiles are asked for in front of the queries, which nothing depends on until the tiles are
+    // there, by the kernels that load two stages at a time (24 prompts of 16 to 700 tokens on 40 heads, with
+    // the append: 71.3 -> 70.2 us); behind them by the others, which are slower that way: 20 responses
+    // of up to 30 tokens, 32 / 8 heads of 128, 69.3 us and 71.1; 4 of 16 on 1 500, 16 / 8 heads of 256, 26.1 and
+    // 31.5 (registers).
+    constexpr bool kTilesFirst = GRP > 1;            // (written twice: in a lambda it costs the wider kernels registers)
+    if constexpr (kTilesFirst) {
         uint32_t first_ent[NB][2 * GRP];
 #pragma unroll
         for (int i = 0; i < NB; ++i) lookup(grp0 + i, first_ent[i]);
@@ -566,8 +572,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         for (int i = 0; i < NB; ++i) dma_group(grp0 + i, lds + i * GSTAGE, first_ent[i]);
     }
 
-    // this lane's column in each block: (token, head), its position, its q slices (asked for behind the
-    // first tiles: nothing depends on them until those are there)
+    // this lane's column in each block: (token, head), its position, its q slices
     int pos[kColBlocks];                             // -1: no such column
     size_t orow[kColBlocks];                         // element offset of its output row
     bf16x8 qb[kColBlocks][NK];
@@ -585,6 +590,13 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
             if (ok) t = *reinterpret_cast<const uint4 *>(static_cast<const char *>(a.q) + (orow[b] + 32 * i + 8 * qd) * 2);
             qb[b][i] = __builtin_bit_cast(bf16x8, t);
         }
+    }
+    if constexpr (!kTilesFirst) {
+        uint32_t first_ent[NB][2 * GRP];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) lookup(grp0 + i, first_ent[i]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) dma_group(grp0 + i, lds + i * GSTAGE, first_ent[i]);
     }
 
     float m[kColBlocks];
