@@ -616,9 +616,14 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
     // a NaN; the scores of such positions are masked whatever the keys are).
     const int valid_end = min(C, (wg_maxpos | 15) + 1);
     auto zero_tail = [&](int st, char *buf) {
+        int me = tid;
+        // Worked out here at head size 256: kept in registers over the loop, what follows made tiles of 64 columns
+        // in the tiled layout spill into it, with a wait for every load on its way (4 x 16 new on 1 500, 16 / 8 heads:
+        // 26.1 us, 22.7 so).  At smaller head sizes there are registers, and it is 1-2 % slower so.
+        if constexpr (D >= 256) asm volatile("" : "+v"(me));
 #pragma unroll
         for (int k = 0; k < LPT; ++k) {
-            const int x = tid + kThreads * k, u = x / U, unit = x % U;
+            const int x = me + kThreads * k, u = x / U, unit = x % U;
             if (!TILED) {                             // a slot is part of one row: position 16 u + unit / NU
                 if (st * kStage + 16 * u + unit / NU >= valid_end)
                     *reinterpret_cast<uint4 *>(buf + VOFF + x * 16) = make_uint4(0, 0, 0, 0);

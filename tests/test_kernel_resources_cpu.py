@@ -1,0 +1,57 @@
+"""What the compiler made of the kernels, from the metadata of the built library: registers, LDS and scratch that
+the launch rules and the figures in the comments count on."""
+import re
+import struct
+
+import pytest
+
+import paper_2410_18248_amd as P
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def _code_objects(blob):
+    """The gfx950 code objects in the clang offload bundles of a host library."""
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
+        base = m.start()
+        n, = struct.unpack_from("<Q", blob, base + 24)
+        at = base + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", blob, at)
+            triple = blob[at + 24:at + 24 + length]
+            at += 24 + length
+            if b"gfx950" in triple and size:
+                yield blob[base + off:base + off + size]
+
+
+def _metadata(elf):
+    """The kernels of the AMDGPU metadata note."""
+    phoff, = struct.unpack_from("<Q", elf, 32)
+    phentsize, phnum = struct.unpack_from("<HH", elf, 54)
+    for i in range(phnum):
+        kind, = struct.unpack_from("<I", elf, phoff + i * phentsize)
+        offset, = struct.unpack_from("<Q", elf, phoff + i * phentsize + 8)
+        size, = struct.unpack_from("<Q", elf, phoff + i * phentsize + 32)
+        at = offset
+        while kind == 4 and at < offset + size:                          # PT_NOTE
+            namesz, descsz, note = struct.unpack_from("<III", elf, at)
+            desc = at + 12 + (namesz + 3) // 4 * 4
+            if note == 32 and elf[at + 12:at + 18] == b"AMDGPU":
+                return msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]
+            at = desc + (descsz + 3) // 4 * 4
+    return []
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    found = {k[".name"]: k for co in _code_objects(open(P.lib_path(), "rb").read()) for k in _metadata(co)}
+    assert len(found) > 60
+    return found
+
+
+def test_nothing_spills_into_a_loop(kernels):
+    """A handful of values may go out before a kernel's loop and come back behind it; a reload inside waits for
+    every load on its way."""
+    for name, k in kernels.items():
+        assert k[".private_segment_fixed_size"] <= 16, (name, k[".private_segment_fixed_size"])
+
