@@ -78,7 +78,7 @@ constexpr int kRagged = 4;               // requests per lane
 struct Place {
     int r, head, tile, first, n_new, ctx;
 };
-__device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles, int full_groups, int WT, Place &at)
+__device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles, int full_groups, int WT, bool two_per_cu, Place &at)
 {
     const DecodeArgs &a = p.d;
     if (full_groups >= 0) {
@@ -91,8 +91,11 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
             // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
             // second turn begins with a pair, its pairs start with their short tiles, so that a CU has
             // a long and a short one: 4 prompts of 512 on 16 heads of 256, append included, 41.2 -> 37.6
-            // us, 2 of 1 000 54.6 -> 49.3.  (Beginning inside a pair's tiles: 2 % slower than without.)
-            if (gridDim.x <= 512 && 32 % tiles == 0 && (slot & 32)) t = tiles - 1 - t;
+            // us, 2 of 1 000 54.6 -> 49.3; fp32, 2 of 512 on 8 heads of 64, 17.0 -> 12.8, 2 of 256 on 16 of 128,
+            // 19.6 -> 15.2.  (Beginning inside a pair's tiles: 2 % slower than without.)  Not where a CU holds
+            // one workgroup: the second turn then waits for the first, and has to begin with its long tiles
+            // (4 prompts of 512, 32 / 4 heads of 256: 55.3 us, 42.3 in order).
+            if (two_per_cu && gridDim.x <= 512 && 32 % tiles == 0 && (slot & 32)) t = tiles - 1 - t;
         } else {
             const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
             const int i = (slot - full_groups * tiles) * 8 + xcd;
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void prefill_tiles_f32(const PrefillArgs 
     const int G = a.num_q_heads / a.num_kv_heads, GH = f32_tile_heads(G), passes = G / GH, HC = a.num_kv_heads * passes;
     const int TW = 16 / GH;                           // new tokens per tile
     Place at;
-    if (!place(p, HC, tiles, full_groups, TW, at)) return;
+    if (!place(p, HC, tiles, full_groups, TW, true, at)) return;
     const int r = at.r, tile = at.tile, first = at.first, n_new = at.n_new, base_pos = at.ctx - n_new;
     const int g = at.head / passes, h0 = at.head * GH;
     const int lane = threadIdx.x & 63, j = lane & 15, qd = lane >> 4, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -464,7 +467,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         st0 = run.index * per;
     } else {
         Place at;
-        if (!place(p, a.num_kv_heads, tiles, full_groups, WT, at)) return;
+        if (!place(p, a.num_kv_heads, tiles, full_groups, WT, !(D >= 256 && kCols > 16), at)) return;
         r = at.r;
         g = at.head;
         tile = at.tile;

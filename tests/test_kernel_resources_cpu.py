@@ -49,9 +49,35 @@ def kernels():
     return found
 
 
+def _prefill(kernels):
+    """(D, tiled, columns, stages per barrier, split) -> metadata."""
+    out = {}
+    for name, k in kernels.items():
+        m = re.search(r"prefill_mfmaILi(\d+)ELb(\d)ELi(\d+)ELi(\d+)ELb(\d)E", name)
+        if m:
+            out[tuple(int(x) for x in m.groups())] = k
+    assert len(out) >= 18
+    return out
+
+
+def _workgroups(k):
+    """Workgroups of 256 threads a CU holds: 512 registers per lane and SIMD in steps of 8, 160 KiB of LDS."""
+    regs = (k[".vgpr_count"] + 7) // 8 * 8               # (accumulation registers are counted in)
+    return min(512 // regs, (160 << 10) // max(k[".group_segment_fixed_size"], 1))
+
+
 def test_nothing_spills_into_a_loop(kernels):
     """A handful of values may go out before a kernel's loop and come back behind it; a reload inside waits for
     every load on its way."""
     for name, k in kernels.items():
         assert k[".private_segment_fixed_size"] <= 16, (name, k[".private_segment_fixed_size"])
 
+
+def test_prefill_workgroups_per_cu(kernels):
+    """Launches of up to 512 workgroups count on two per CU, except those with tiles of 128 columns of head size
+    256, which are dealt their tiles in order for that."""
+    for (D, tiled, cols, stages, split), k in _prefill(kernels).items():
+        assert (_workgroups(k) >= 2) == (not (D >= 256 and cols > 16)), (D, tiled, cols, stages, split, k[".vgpr_count"])
+    for name, k in kernels.items():
+        if "prefill_tiles_f32" in name:
+            assert _workgroups(k) >= 2, name
