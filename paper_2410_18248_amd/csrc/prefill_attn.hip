@@ -11,6 +11,7 @@
 #include "attn_reducers.h"
 #include "internal.h"
 #include "prefill_split.h"
+#include "requests.h"
 
 namespace lamps {
 namespace {
@@ -73,11 +74,14 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
 // tile holds its slot (LDS and registers) for 2 us, and workgroups start in order: 24 prompts of 16 to
 // 700 tokens on 40 heads kept 300 to 440 of 512 slots busy with 5 760 workgroups for 1 560 tiles, and
 // 400 to 512 this way: 55 -> 48 us for the kernel.  With the number of heads a multiple of 8 a pair's
-// tiles stay on one XCD here too.
+// tiles stay on one XCD here too.  More requests than a wave keeps (kByStart): numbered by request, each
+// getting the tiles it can have at most, its start in tiles plus one per request before it.
 constexpr int kRagged = 4;               // requests per lane
+constexpr int kByStart = -2;
 struct Place {
     int r, head, tile, first, n_new, ctx;
 };
+template <bool BY_START>
 __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles, int full_groups, int WT, bool two_per_cu, Place &at)
 {
     const DecodeArgs &a = p.d;
@@ -110,6 +114,15 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
         at.n_new = p.q_start[at.r + 1] - at.first;
         if (at.tile * WT >= at.n_new) return false;
         at.ctx = a.ctx_lens[at.r];
+    } else if (BY_START && full_groups == kByStart) {
+        const int item = blockIdx.x / heads;
+        at.head = blockIdx.x - item * heads;
+        at.r = last_request(p.q_start, a.batch, item, [WT](int start, int r) { return start / WT + r; });
+        at.first = p.q_start[at.r];
+        at.n_new = p.q_start[at.r + 1] - at.first;
+        at.ctx = a.ctx_lens[at.r];
+        at.tile = item - (at.first / WT + at.r);
+        if (at.tile >= tiles || at.tile * WT >= at.n_new) return false;
     } else {
         const int lane = threadIdx.x & 63;
         int first[kRagged], n_new[kRagged], ctx[kRagged], n_tiles[kRagged], most = 0;
@@ -168,17 +181,18 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     // mistake: nothing is read or written for it
     return at.ctx >= at.n_new && at.ctx <= a.max_blocks * a.block_size;
 }
-// The grid for it and what place() needs to know; 0: too large.
-unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int WT, bool ragged, int *full_groups)
+// The grid for it and what place() needs to know; 0: too large.  `spare`: workgroups without a tile that
+// cost less than finding one's place among the tiles there are.
+unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int *full_groups)
 {
     const long long pairs = heads * p.d.batch, full = pairs / 8, rest = pairs % 8;
     long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
     *full_groups = (int)full;
     // the tiles of all requests are at most this many; a quarter fewer workgroups pay for finding them
     const long long most = heads * ((long long)p.total_tokens / WT + p.d.batch);
-    if (ragged && p.d.batch <= 64 * kRagged && most + most / 4 < grid) {
+    if ((by_start || p.d.batch <= 64 * kRagged) && most + most / 4 + spare < grid) {
         grid = most;
-        *full_groups = -1;
+        *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
     }
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
 }
@@ -210,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void prefill_tiles_f32(const PrefillArgs 
     const int G = a.num_q_heads / a.num_kv_heads, GH = f32_tile_heads(G), passes = G / GH, HC = a.num_kv_heads * passes;
     const int TW = 16 / GH;                           // new tokens per tile
     Place at;
-    if (!place(p, HC, tiles, full_groups, TW, true, at)) return;
+    if (!place<true>(p, HC, tiles, full_groups, TW, true, at)) return;
     const int r = at.r, tile = at.tile, first = at.first, n_new = at.n_new, base_pos = at.ctx - n_new;
     const int g = at.head / passes, h0 = at.head * GH;
     const int lane = threadIdx.x & 63, j = lane & 15, qd = lane >> 4, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -260,7 +274,11 @@ hipError_t launch_tiles_f32(const PrefillArgs &p, hipStream_t s)
     const int GH = f32_tile_heads(p.d.num_q_heads / p.d.num_kv_heads), TW = 16 / GH;
     const long long tiles = (p.max_new_tokens + TW - 1) / TW;
     int full = 0;
-    const unsigned grid = place_grid(p, p.d.num_q_heads / GH, tiles, TW, false, &full);   // (a workgroup for nothing holds little here)
+    // Up to 1 024 workgroups for nothing cost less than finding the tiles there are: 3 prompts of 100 to 500 tokens,
+    // 8 heads of 64 (768 workgroups, 400 tiles), 10.2 us on the full grid, 11.8 ragged; 12 of 8 to 300, 16 / 2
+    // heads (3 600 and 1 000), 25.5 and 15.4.  The full grid alone grew with requests x tokens where the most
+    // new tokens are not known: 64 prompts of 100, 32 / 8 heads of 128, 1 200 us, 203 so.
+    const unsigned grid = place_grid(p, p.d.num_q_heads / GH, tiles, TW, true, 1024, &full);
     if (grid == 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prefill_tiles_f32<D>, dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
     return hipGetLastError();
@@ -467,7 +485,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : 1) void p
         st0 = run.index * per;
     } else {
         Place at;
-        if (!place(p, a.num_kv_heads, tiles, full_groups, WT, !(D >= 256 && kCols > 16), at)) return;
+        if (!place<false>(p, a.num_kv_heads, tiles, full_groups, WT, !(D >= 256 && kCols > 16), at)) return;
         r = at.r;
         g = at.head;
         tile = at.tile;
@@ -925,7 +943,7 @@ hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
     const int WT = kWaves * (kCols / G);
     const long long tiles = (p.max_new_tokens + WT - 1) / WT;
     int full = 0;
-    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, true, &full);
+    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, false, 0, &full);
     if (grid == 0) return hipErrorInvalidValue;
     // Two stages per barrier where they fit and a request has many new tokens (the matrix cores
     // bind: +2-5 %); with one tile per request the kernel is a stream over the cache, and the

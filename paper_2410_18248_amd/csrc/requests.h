@@ -1,0 +1,28 @@
+// Finding the request a workgroup works for.  Device code; include from a .hip file only.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace lamps {
+namespace {
+
+// The last request r < batch with key(q_start[r], r) <= x; key grows with r.  By every wave, 64
+// requests per round trip to memory (one by one halving, each round waits for the one before: 4 to 6
+// of them were half the time of a call with few tokens).
+template <typename Key>
+__device__ __forceinline__ int last_request(const int32_t *q_start, int batch, int x, Key key)
+{
+    const int lane = threadIdx.x & 63;
+    int lo = 0, n = batch;                            // it is one of lo .. lo + n - 1 (or lo, if none is)
+    while (n > 1) {
+        const int step = (n + 63) >> 6, r = lo + lane * step;
+        const unsigned long long le = __ballot(lane * step < n && key(q_start[min(r, batch - 1)], r) <= x);
+        const int at = max(0, 63 - __clzll((long long)le)) * step;     // (none: clz 64)
+        lo += at;
+        n = min(step, n - at);
+    }
+    return lo;
+}
+
+}  // namespace
+}  // namespace lamps
