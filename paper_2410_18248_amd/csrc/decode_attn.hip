@@ -466,25 +466,31 @@ __global__ __launch_bounds__(64 * kMergeShares) void decode_merge_balanced(const
     int4 rec = make_int4(0, 0, 0, 0);                  // lane i: the record of share base + i
     if (lane < kMergeShares && base + lane < shares) rec = a.share_info[base + lane];
     const unsigned owners = (unsigned)__ballot(rec.w & kShareOwner);
-    const int n = __popc(owners);                      // ranges that start here
-    if (n == 0) return;                                // uniform over the workgroup, like everything but `part`
-    const bool any_long = __any((rec.w & kShareOwner) && rec.z - (base + lane) >= 8);   // more than one round of loads
-    const int parts = any_long ? kMergeShares / n : 1, part = wv / n;
-    unsigned left = owners;
-    for (int k = wv % n; k > 0; --k) left &= left - 1;
-    const int own = __ffs((int)left) - 1;              // this wave's range: the (wv % n)th of them
+    if (owners == 0) return;                           // uniform over the workgroup, like everything but `own` and `part`
+    // Ranges of up to 8 pieces, one round of loads, are the work of the wave of their first share; nothing is
+    // divided for them (the divisions below are 1 of the 6 us of a launch that has no use for them).
+    const bool any_long = __any((rec.w & kShareOwner) && rec.z - (base + lane) >= 8);
+    int own = wv, n = 1, parts = 1, part = 0;
+    if (any_long) {
+        n = __popc(owners);                            // ranges that start here
+        parts = kMergeShares / n;
+        part = wv / n;
+        unsigned left = owners;
+        for (int k = wv % n; k > 0; --k) left &= left - 1;
+        own = __ffs((int)left) - 1;                    // this wave's range: the (wv % n)th of them
+    } else if (!(owners >> wv & 1)) {
+        return;
+    }
     const int r = __builtin_amdgcn_readlane(rec.x, own), hc = __builtin_amdgcn_readlane(rec.y, own);
     const int w_first = base + own, w_last = __builtin_amdgcn_readlane(rec.z, own);
     const int first_slot = (__builtin_amdgcn_readlane(rec.w, own) & kShareSlot1) ? 1 : 0;
-    const int D = a.head_dim;
-    const int G = a.num_q_heads / a.num_kv_heads;
+    const int D = a.head_dim, log2_D = __builtin_ctz(D);   // (a power of two)
     const int GH = a.heads_per_pass;
-    const int passes = G / GH;
     const int idx = blockIdx.y * 128 + 2 * lane;       // the lane's two outputs: same head, d even
     const bool live = idx < GH * D;
-    const int h = live ? idx / D : 0, d = live ? idx % D : 0;
+    const int h = live ? idx >> log2_D : 0, d = live ? idx & (D - 1) : 0;
     float M = kLowest, L = 0.0f, A0 = 0.0f, A1 = 0.0f;
-    const int each = (w_last - w_first + parts) / parts;
+    const int each = any_long ? (w_last - w_first + parts) / parts : 8;
     const int w_end = min(w_last + 1, w_first + (part + 1) * each);
     if (part < parts)
         for (int w = w_first + part * each; w < w_end; w += 8)
@@ -505,7 +511,8 @@ __global__ __launch_bounds__(64 * kMergeShares) void decode_merge_balanced(const
         }
     }
     if (live) {
-        const size_t at = ((size_t)r * a.num_q_heads + (hc / passes) * G + (hc % passes) * GH + h) * D + d;
+        // (a group's heads follow each other, pass by pass: kv head and pass times GH is the first of this one)
+        const size_t at = ((size_t)r * a.num_q_heads + hc * GH + h) * D + d;
         store_out<BF16>(a.out, at, L > 0.0f ? A0 / L : 0.0f);
         store_out<BF16>(a.out, at + 1, L > 0.0f ? A1 / L : 0.0f);
     }

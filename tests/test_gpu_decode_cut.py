@@ -1,0 +1,31 @@
+"""lamps_decode_attn: the merge of ranges of up to eight pieces beside longer ones, against the fp64 oracle."""
+import numpy as np
+import pytest
+
+import lamps_workloads as W
+import oracle
+from rig import Rig, to_f64, tol
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(geom_of, ctx, running):
+    blocks = [(c + 15) // 16 for c in ctx]
+    geom = geom_of(sum(blocks) + 4, max(max(blocks), 1))
+    rig = Rig(geom, len(ctx))
+    table, _ = W.deal_block_table(W.permutation(6, geom.num_blocks), ctx, geom)
+    K, V = zip(*[W.logical_kv(20 + 17 * r, geom, c) for r, c in enumerate(ctx)])
+    rig.page_requests(0, table, K, V)
+    q = W.queries(9, geom, len(ctx))
+    got = to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0))
+    again = to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0))
+    on = np.asarray(running, dtype=bool)
+    assert np.abs(got[on] - oracle.decode_attn(q, K, V, ctx, running)[on]).max() <= tol(geom)
+    assert (got[~on] == 7.0).all() and np.array_equal(got, again)
+    rig.close()
+
+
+@pytest.mark.parametrize("ctx", [[4000] + [30] * 40, [200] * 20 + [2500], [5000, 400, 300, 12, 900] * 3])
+@pytest.mark.parametrize("dtype,H,Hkv,D", [("bf16", 8, 8, 64), ("bf16", 8, 2, 128), ("f32", 8, 4, 64), ("bf16", 32, 1, 64)])
+def test_short_and_long_piece_lists(dtype, H, Hkv, D, ctx):
+    _check(lambda nb, mb: W.Geometry(1, H, Hkv, D, 16, nb, mb, dtype), ctx, [1] * len(ctx))
