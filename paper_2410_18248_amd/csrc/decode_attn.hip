@@ -203,35 +203,50 @@ template <typename R, bool TOGETHER>
 __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
 {
     constexpr int D = R::D;
-    // below, a chunk is GT tokens, and a wave loads one of them, or two, at a time
-    const int GT = R::CT == R::GT || a.whole_chunks ? R::CT : R::GT, log2_whole = GT == R::CT ? 0 : 1;
     extern __shared__ int prefix[];                   // then pieces[] (balanced_ints), and, TOGETHER, [wave][head][D + 2] floats
-    __shared__ int wave_total[kWaves], wave_longest[kWaves];
+    __shared__ int wave_total[2][kWaves], wave_longest[kWaves];
 
     const int B = a.batch;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int per = (B + kThreads - 1) / kThreads;   // consecutive requests per thread
-    int mine = 0, longest = 0;
+    constexpr bool kCut = R::CT != R::GT;            // (else chunk and cut are one)
+    int parts = 0, wholes = 0, longest = 0;          // of this thread's requests, in GT and in CT tokens
     for (int i = 0; i < per; ++i) {
         const int r = tid * per + i;
         if (r < B) {
-            const int n = chunks_of(a, r, GT);
-            mine += n;
+            const int n = chunks_of(a, r, R::GT);
+            parts += n;
+            if (kCut) wholes += (n + 1) >> 1;
             longest = max(longest, n);
         }
     }
     longest = wave_max_to(longest);
-    const int incl = wave_scan(mine);                 // inclusive scan inside the wave
+    const int parts_to = wave_scan(parts), wholes_to = kCut ? wave_scan(wholes) : 0;   // inclusive, inside the wave
     if (lane == 63) {
-        wave_total[wv] = incl;
+        wave_total[0][wv] = parts_to;
+        wave_total[1][wv] = wholes_to;
         wave_longest[wv] = longest;
     }
     __syncthreads();
+    int T_whole = 0;
 #pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) longest = max(longest, wave_longest[ww]);
-    int run = incl - mine;
+    for (int ww = 0; ww < kWaves; ++ww) {
+        longest = max(longest, wave_longest[ww]);
+        T_whole += wave_total[1][ww];
+    }
+    // Below, a chunk is GT tokens, and a wave loads one of them, or two, at a time.  Cutting by the smaller ones evens
+    // launches out whose shares are a chunk or less; it costs a half-empty load where a range is cut, which is
+    // all that is left where shares are longer.  By halves / whole: 40 fp32 requests of 60 to 200 tokens, 32 / 16 heads
+    // of 128 (1.3 chunks a share, 2 layers) 51 / 54 us; 100 of 60 to 90, 16 heads of 256 (1.8, 3 layers) 100 / 96;
+    // 34 of 202 to 532 (2.9) 136 / 129; 110 of 28 to 161 on 40 heads of 128 (3.2) 118 / 116.
+    const long long shares = (long long)gridDim.x * (TOGETHER ? 1 : kWaves);
+    const bool whole_chunks = kCut && 2LL * T_whole * (a.num_kv_heads * a.passes) >= 3 * shares;
+    const int GT = whole_chunks ? R::CT : R::GT, log2_whole = kCut && !whole_chunks ? 1 : 0;
+    if (whole_chunks) longest = (longest + 1) >> 1;
+    const int mine = whole_chunks ? wholes : parts;
+    int run = (whole_chunks ? wholes_to : parts_to) - mine;
 #pragma unroll
-    for (int ww = 0; ww < kWaves - 1; ++ww) run += ww < wv ? wave_total[ww] : 0;
+    for (int ww = 0; ww < kWaves - 1; ++ww) run += ww < wv ? wave_total[whole_chunks][ww] : 0;
     if (tid == 0) prefix[0] = 0;
     if (per == 1) {
         if (tid < B) prefix[tid + 1] = run + mine;
@@ -280,11 +295,11 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     if (wanted < P && B <= kThreads) {
         int *pieces = prefix + B + 1;                 // before request r, of one head
         const int n = (mine + (1 << log2_share_chunks) - 1) >> log2_share_chunks, n_to = wave_scan(n);
-        if (lane == 63) wave_total[wv] = n_to;
+        if (lane == 63) wave_total[0][wv] = n_to;
         __syncthreads();
         int before = n_to - n;
 #pragma unroll
-        for (int ww = 0; ww < kWaves - 1; ++ww) before += ww < wv ? wave_total[ww] : 0;
+        for (int ww = 0; ww < kWaves - 1; ++ww) before += ww < wv ? wave_total[0][ww] : 0;
         if (tid < B) pieces[tid + 1] = before + n;
         if (tid == 0) pieces[0] = 0;
         __syncthreads();
@@ -560,11 +575,6 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
     const int HC = a.num_q_heads / a.heads_per_pass;
     const int P = wgs * (TOGETHER ? 1 : kWaves);
     DecodeArgs b = a;
-    // Cutting by half-chunks evens small launches out (4 layers of 8 requests of 20 to 159 tokens, 16
-    // heads of 256: 57 us, by whole chunks 64), and costs a half-empty load where a range is cut, which is
-    // all that is left where a share is several ranges long (512 short requests on 40 heads, 40 layers:
-    // 14.70 ms, by whole chunks 14.62).
-    b.whole_chunks = (long long)a.batch * HC >= 2LL * P;
     b.share_gcd = b.share_inv = b.share_period = 0;                    // shares in launch order
     if (wgs % 8 == 0) {                               // whole rounds over the XCDs: ranked shares
         int g = HC, t = P;

@@ -29,7 +29,6 @@ struct DecodeArgs {
     // balanced: which share a wavefront takes (filled in by launch_decode): 0 = in launch
     // order, else gcd(head passes, shares) and the inverse of passes / gcd modulo shares / gcd
     int32_t share_gcd, share_inv, share_period;   // (period: shares / gcd)
-    int32_t whole_chunks;     // balanced: ranges are cut between whole chunks only (filled in by launch_decode)
 };
 
 // Query heads of one kv group that share a pass over K/V for this geometry

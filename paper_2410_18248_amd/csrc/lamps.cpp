@@ -174,7 +174,7 @@ void fill_geometry(const lamps_config &cfg, const Derived &d, lamps::DecodeArgs 
     a.heads_per_pass = lamps::decode_heads_per_pass(a.bf16, a.head_dim, a.num_q_heads / a.num_kv_heads);
     a.passes = a.num_q_heads / a.num_kv_heads / a.heads_per_pass;
     a.scale_log2e = d.scale_log2e;
-    a.share_gcd = a.share_inv = a.share_period = a.whole_chunks = 0;
+    a.share_gcd = a.share_inv = a.share_period = 0;
 }
 
 void fill_decode_args(lamps_ctx *c, lamps::DecodeArgs *pa, int32_t layer, int32_t batch, const void *q,

@@ -1,4 +1,6 @@
-"""lamps_decode_attn: the merge of ranges of up to eight pieces beside longer ones, against the fp64 oracle."""
+"""lamps_decode_attn about the line between cutting ranges by half-chunks and by whole ones (chunks of 32 tokens in
+halves of 16, 8 heads of 64: one and a half chunks per resident wave), with lengths that end in either half of
+a chunk, against the fp64 oracle; and the merge of ranges of up to eight pieces beside longer ones."""
 import numpy as np
 import pytest
 
@@ -23,6 +25,14 @@ def _check(geom_of, ctx, running):
     assert np.abs(got[on] - oracle.decode_attn(q, K, V, ctx, running)[on]).max() <= tol(geom)
     assert (got[~on] == 7.0).all() and np.array_equal(got, again)
     rig.close()
+
+
+@pytest.mark.parametrize("n", [60, 140, 144, 145, 150])
+def test_cuts_on_both_sides_of_the_line(n):
+    rng = np.random.RandomState(n)
+    ctx = [int(x) for x in rng.randint(225, 257, n)]                  # 8 chunks each, 15 or 16 halves
+    _check(lambda nb, mb: W.Geometry(1, 8, 8, 64, 16, nb, mb, "bf16"), ctx, [1] * n)
+    _check(lambda nb, mb: W.Geometry(1, 8, 8, 64, 16, nb, mb, "bf16"), ctx[:n - 3] + [0, 1, 17], [int(r % 9 != 4) for r in range(n)])
 
 
 @pytest.mark.parametrize("ctx", [[4000] + [30] * 40, [200] * 20 + [2500], [5000, 400, 300, 12, 900] * 3])
