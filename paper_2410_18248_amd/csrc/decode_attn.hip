@@ -542,29 +542,29 @@ size_t balanced_lds(int batch, int heads_per_pass)
     return balanced_ints(batch) * sizeof(int) + (TOGETHER ? (size_t)kWaves * heads_per_pass * (R::D + 2) * sizeof(float) : 0);
 }
 
-// Workgroups the chip holds at once for decode_balanced<R, TOGETHER>, per device (asked once per device and
-// instantiation; every thread that asks computes the same).
+// Workgroups the chip holds at once for a decode_balanced<R, TOGETHER> launch: what the kernel's registers allow,
+// asked once per device and instantiation (a later call may be under capture; every thread that asks gets the
+// same), and what the launch's own LDS does.
 template <typename R, bool TOGETHER>
 hipError_t resident_workgroups(const DecodeArgs &a, int *out)
 {
-    static std::atomic<int> resident_on[kMaxDevices];
+    static std::atomic<int> by_registers[kMaxDevices], cus_of[kMaxDevices];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    int resident = resident_on[dev].load(std::memory_order_relaxed);
-    if (resident == 0) {
-        int cus = 0, per_cu = 0;
+    int cus = cus_of[dev].load(std::memory_order_relaxed), per_cu = by_registers[dev].load(std::memory_order_relaxed);
+    if (cus == 0 || per_cu == 0) {
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_balanced<R, TOGETHER>, kThreads,
-                                                             balanced_lds<R, false>(a.max_batch, 1));
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, decode_balanced<R, TOGETHER>, kThreads, 0);
         if (e != hipSuccess) return e;
         if (cus < 1 || per_cu < 1) return hipErrorInvalidValue;
-        resident = cus * per_cu;
-        resident_on[dev].store(resident, std::memory_order_relaxed);
+        cus_of[dev].store(cus, std::memory_order_relaxed);
+        by_registers[dev].store(per_cu, std::memory_order_relaxed);
     }
-    *out = resident;
+    constexpr size_t kLds = (size_t)160 << 10, kStep = 2048;   // of a gfx950 CU; no allocation step is larger
+    const size_t lds = (balanced_lds<R, TOGETHER>(a.batch, a.heads_per_pass) + 256 + kStep - 1) / kStep * kStep;
+    *out = cus * min(per_cu, (int)(kLds / lds));      // (never none: 32 KiB for 8 192 requests, 66 for 16 heads of 256 together)
     return hipSuccess;
 }
 
@@ -620,7 +620,7 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     }
     // balanced: as many workgroups as the chip holds at once for this kernel (fewer
     // if the partial slots of that many wave shares would not fit behind a.partials)
-    int resident = 0, together = 0;                   // (both asked for at once: a later call may be under capture)
+    int resident = 0, together = 0;                   // (both asked for at once, for the calls under capture)
     hipError_t e = resident_workgroups<R, false>(a, &resident);
     if (e == hipSuccess) e = resident_workgroups<R, true>(a, &together);
     if (e != hipSuccess) return e;

@@ -20,7 +20,7 @@ struct DecodeArgs {
     size_t partial_capacity;  // bytes behind partials (balanced: bounds the number of shares)
     int4 *share_info;         // balanced: [shares + 1] what each share leaves to the merge kernel
     void *out;                // [batch][H][D]
-    int32_t batch, max_batch, layer, num_layers, num_q_heads, num_kv_heads, head_dim;
+    int32_t batch, layer, num_layers, num_q_heads, num_kv_heads, head_dim;
     int32_t block_size, log2_block_size, max_blocks, num_blocks, part_tokens, max_parts;
     int32_t bf16;             // 0: fp32 storage, 1: bf16 storage
     int32_t heads_per_pass;   // query heads of a kv group that share one pass over K/V

@@ -159,7 +159,6 @@ namespace {
 void fill_geometry(const lamps_config &cfg, const Derived &d, lamps::DecodeArgs *pa)
 {
     lamps::DecodeArgs &a = *pa;
-    a.max_batch = cfg.max_batch;
     a.num_layers = cfg.num_layers;
     a.num_q_heads = cfg.num_q_heads;
     a.num_kv_heads = cfg.num_kv_heads;
