@@ -49,6 +49,13 @@
  *     eagerly on the device, a caller may record them into a HIP graph by stream
  *     capture and replay a whole decode iteration.  The swap calls use events
  *     and copies on the side streams and are not meant for capture.
+ *   - The decode and prefill kernels of one context share its workspace
+ *     (lamps_workspace_bytes): all of its lamps_decode_attn and
+ *     lamps_prefill_attn work, eager and replayed, must run in one order -- on
+ *     the compute stream, or on other streams behind one another by events.  A
+ *     replay beside a call or another replay of the same context overwrites
+ *     its partial results and gives wrong rows, with no error.  (Two contexts
+ *     with a workspace each may overlap.)
  *
  * KV pool layout (part of the ABI, so swap images can be checked byte by byte)
  *   Keys and values live in two pools of identical size
@@ -306,7 +313,10 @@ int lamps_kv_append_tokens(lamps_ctx *ctx, int32_t layer, int32_t n_req, int32_t
  * must already be in the cache):
  *   out[n][h][:] = softmax(q[n][h] . K_r[0..p]^T * scale) . V_r[0..p],  p the position of row n.
  * q, out: device, [total_tokens][H][d_h] dtype, 16-byte aligned.  fp32 accumulation, bf16 output
- * rounded to nearest even, results independent of block placement.
+ * rounded to nearest even, results bit-reproducible for fixed arguments and independent of block
+ * placement.  (Long contexts under few new tokens are cut into runs, in the workspace, and where
+ * depends on all requests of the call: a request's bf16 rows can differ by their rounding, some
+ * 2e-3 relative, with the requests beside it.)
  * max_new_tokens: an upper bound, known on the host, of the new tokens of any one
  * request (it sizes the launch; 0 = unknown, total_tokens is used; rows of a
  * request beyond a bound that is too small are left unwritten).  bf16 with at
