@@ -10,18 +10,22 @@
 // cut in GT tokens.  Two schemes share
 // the same inner loops:
 //   balanced (default): all chunks of all running requests form one flat
-//     sequence (head outermost, then request, then position); as many
-//     wavefronts as the chip holds at once each take an equal
-//     contiguous share of it, so every wavefront ends within a chunk of the
-//     others however skewed the context lengths are.  A share is at most: the
-//     tail of one (request, head), some whole ones, and the head of another;
+//     sequence (head outermost, then request, then position), cut into shares.
+//     With many ranges, (request, head) pairs, for the chip: as many wavefronts as it
+//     holds at once each take an equal contiguous share, so every wavefront ends within
+//     a chunk of the others however skewed the context lengths are.  With eight resident
+//     waves and more to a range: a share belongs to a workgroup, whose four waves
+//     take a quarter of each of its ranges.  With less work than a chunk per
+//     share: the shares are pieces of one range each.  A share is at most: the
+//     tail of one range, some whole ones, and the head of another;
 //     whole ones are written out directly, the two partial ends go to
-//     per-share slots that a small second kernel merges.
+//     per-share slots that a second kernel merges.
 //   fixed partitions (part_tokens > 0): the context is cut every part_tokens
 //     tokens, one wavefront per (partition, request, kv head) in a dense grid.
-// A wavefront works alone (no LDS, no barrier in the main path): with many short
-// requests there are far more (request, head) ranges than workgroups, and four
-// waves cooperating on each would spend their time in start-up and hand-over.
+// The inner loops of a wavefront use no LDS and no barrier: with many short
+// requests there are far more ranges than workgroups, and four
+// waves cooperating on each would spend their time in start-up and hand-over; where
+// they do cooperate, they meet once per range.
 // Partitions are merged by a separate launch on purpose: a kernel boundary
 // makes the partials visible across the eight XCDs' L2s once, whereas a
 // device-scope fence per workgroup writes back and invalidates an L2 each time.
@@ -280,7 +284,9 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     // chain of dependent loads (a 40 000-token request among 70 short ones, 2 heads: 10 us of
     // attention, 200 us of merge).  Then only as many shares are used as gives each 2, 4 or
     // 8 chunks -- for a longest range of 256, 512, 1024 chunks and more -- and the rest stay
-    // empty.  TOGETHER: a chunk per wave at least, and the rest as for a range a quarter as long.
+    // empty.  TOGETHER: a chunk per wave at least (half of that: 10.6 -> 11.6 us on 3 000 tokens of 8 kv heads, twice: 9.6 ->
+    // 11.7 on 8 plain ones), and the rest as for a range a quarter as long (one range of 20 000 tokens 13.3 us, 16.2
+    // with a chunk per wave; 40 000: 16.0 and 21.2; twice the length costs 19.4 there).
     const int span = longest >> log2_whole;
     const int log2_share_chunks = (TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
                                             : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + log2_whole;
