@@ -204,7 +204,8 @@ unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int 
 // through LDS.  Bound by the fp32 matrix rate on long prompts (each K / V byte from L2 serves 16
 // columns) and by the walk over the positions on short ones, which is why the waves share it:
 // six prompts of 17 to 700 tokens, 8 heads of 64: 27 us with a wavefront per token on the vector ALUs
-// (every K / V byte read once per token), 13 now.
+// (every K / V byte read once per token), 14 now.  At head_dim 128 the register bound is what keeps two
+// workgroups on a CU: one register more than 256 and one CU holds one, for 25 to 75 % of the time.
 // Heads of a group that share a tile: the largest divisor up to 16.
 __host__ __device__ __forceinline__ int f32_tile_heads(int group)
 {
@@ -214,7 +215,7 @@ __host__ __device__ __forceinline__ int f32_tile_heads(int group)
 }
 
 template <int D>
-__global__ __launch_bounds__(kThreads) void prefill_tiles_f32(const PrefillArgs p, const int tiles, const int full_groups)
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 1) void prefill_tiles_f32(const PrefillArgs p, const int tiles, const int full_groups)
 {
     typedef MfmaF32Tile<D> R;
     constexpr int ROW = D + 4;                        // floats; 16-byte aligned, rows in different banks

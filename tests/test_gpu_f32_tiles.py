@@ -66,3 +66,21 @@ def test_values_past_a_token_do_not_reach_it():
     assert np.array_equal(got[~fine & ~np.isnan(ref)], ref[~fine & ~np.isnan(ref)])
     assert np.abs(got[fine] - ref[fine]).max() <= tol(geom)
     rig.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D", [(8, 8, 64), (8, 2, 32), (8, 2, 128)])
+def test_a_chunk_is_summed_in_short_chains(H, Hkv, D):
+    """Sixteen tokens of weight one (the queries are zero) whose values are one 1 and fifteen 2^-24:
+    a chain that holds the 1 drops each 2^-24 it meets after it (half an ulp, ties to even).  Two
+    chains of eight lose at most 7 of them, their sum and the division one each; a chain of sixteen
+    loses up to 15 by itself.  Dim d has its 1 at token d % 16, so every place in a chain is met."""
+    geom, rig, table, K, V, ctx = _rig(H, Hkv, D, 16, [(16, 16)], 5)
+    V[0][:] = 2.0 ** -24
+    for d in range(D):
+        V[0][d % 16, :, d] = 1.0
+    rig.page_requests(0, table, K, V)
+    q = np.zeros((16, H, D), dtype=np.float32)
+    _, got = _prefill(geom, rig, table, ctx, [16], q)
+    want = (1 + 15 * 2.0 ** -24) / 16
+    assert np.abs(got[15] - want).max() * 16 <= 9 * 2.0 ** -24
+    rig.close()
