@@ -346,8 +346,8 @@ constexpr int vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
 // the bf16 weights: a request's output depends on how it is cut, that is on the other requests of the
 // call, by what another order of the same sums gives.
 // Bound by the walk over K / V and the hand-over: a dozen requests with 6 to 58 new tokens on 345 to
-// 2 490 cached, 32 / 8 heads of 128 (50 MB): 63 us for this kernel before, 25 now; one request with 16
-// new on 3 000: 75 us before, 21 now.  (Adding the runs up in a second launch instead is 1-8 us faster
+// 2 490 cached, 32 / 8 heads of 128 (50 MB): 63 us for this kernel before, 24 now; one request with 16
+// new on 3 000: 75 us before, 20 now.  (Adding the runs up in a second launch instead is 1-8 us faster
 // on such a call and 4 us slower on every one that has nothing to add up.)
 constexpr int kSplitSlots = 512;         // two workgroups per CU
 constexpr int kSplitRequests = 64;       // one per lane
@@ -913,8 +913,9 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
     const long long stages = ((long long)p.d.max_blocks * p.d.block_size - 1) / kStage + 1;   // of one request, at most
     p.slots = (int)min((size_t)kSplitSlots, p.d.partial_capacity / split_item_bytes(D, kWaves * kCols)) / 8 * 8;
     // Half the slots must be left to cut into: with more tiles than that the chip is busy anyhow.
-    // (Tiles of 128: a quarter.  They come with many new tokens, most of a prompt, where the causal
-    // half of the items is empty: one prompt of 1 000 on 8 kv heads took 46 us split, 34 not.)
+    // (Tiles of 128: a quarter.  They come with many new tokens, and what such a launch can gain is less: half
+    // a turn of the chip at most.  By a quarter / a half of the slots, 32 / 8 heads of 128: one prompt of 1 000
+    // 29.7 / 30.1 us, 2 of 400 on 1 500 50.1 / 50.8; against it 600 on 1 500, 54 / 47.)
     if (all > p.slots / (kCols == 16 ? 2 : 4) || stages < kSplitStages || all * stages > 0x7fffffff) return hipSuccess;
     p.head_slots = p.slots / Hkv;
     // Two stages per barrier for tiles of 128 as on the plain grid, so that a launch that cuts nothing is as
@@ -930,10 +931,10 @@ hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
 {
     const int G = p.d.num_q_heads / p.d.num_kv_heads;
     // Split launches: tiles of 64 columns leave no wave without work when a request brings a few
-    // tokens (16 new on 3 000 cached, 32 / 8 heads: 32 us against 35 with tiles of 128, one tile's
-    // append + attention; 40 on 1 000, 8 requests: 32 against 36); from 16 such tiles per request on
-    // each K / V byte is read 16 times and more, and tiles of 128 are the better ones (512 new on
-    // 3 000: 67 us against 92).
+    // tokens (append + attention, 32 / 8 heads: 16 new on 3 000 cached 23 us against 26 with tiles of 128; 40 on
+    // 1 000, 8 requests, 30 against 35); from 16 such tiles per request on each K / V byte is read 16 times
+    // and more, and tiles of 128 are the better ones (512 new on 3 000: 53 us against 77; where the line lies
+    // they are not yet: 256 on 3 000 41 and 39, 300 on 2 000 46 and 37).
     bool done = false;
     hipError_t e;
     if (G <= 16 && (kCols == 16 || (long long)p.max_new_tokens * G < 1024))
