@@ -26,16 +26,16 @@ namespace {
 constexpr int kAppendThreads = 256;
 
 // Writes the key and value vectors kn, vn ([H_kv][D]) of one token at cached position t of request r.
-// Called by a whole workgroup; k0 and v0 are what this thread takes of them first, asked for before
-// anything is known of where they go.  A position outside the block-table row, or a block id outside
-// the pool, writes nothing.
+// Called by a whole workgroup; EARLY: k0 and v0 are what this thread takes of them first, asked for
+// before anything is known of where they go.  A position outside the block-table row, or a block id
+// outside the pool, writes nothing.
 template <typename T>
 __device__ __forceinline__ uint4 first_unit(const AppendArgs &a, const T *x)
 {
     const int i = threadIdx.x * (16 / (int)sizeof(T));
     return i < a.num_kv_heads * a.head_dim ? *reinterpret_cast<const uint4 *>(x + i) : make_uint4(0, 0, 0, 0);
 }
-template <typename T, bool TILED>
+template <typename T, bool TILED, bool EARLY>
 __device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t, const T *kn, const T *vn, uint4 k0, uint4 v0)
 {
     const int D = a.head_dim, Hkv = a.num_kv_heads, bs = a.block_size;
@@ -50,7 +50,7 @@ __device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t,
     // both layouts (8 dims of a key are contiguous), values in the plain layout
     constexpr int V16 = 16 / (int)sizeof(T);
     for (int i = threadIdx.x * V16; i < Hkv * D; i += kAppendThreads * V16) {
-        if (i >= kAppendThreads * V16) {
+        if (!EARLY || i >= kAppendThreads * V16) {
             k0 = *reinterpret_cast<const uint4 *>(kn + i);
             v0 = *reinterpret_cast<const uint4 *>(vn + i);
         }
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append(const AppendArgs a)
     const int t = a.ctx_lens[r];
     if (!a.running[r]) return;                        // uniform over the workgroup
     __syncthreads();
-    const bool ok = scatter_token<T, TILED>(a, r, t, kn, vn, k0, v0);
+    const bool ok = scatter_token<T, TILED, true>(a, r, t, kn, vn, k0, v0);
     if (ok && a.advance && threadIdx.x == 0) a.ctx_lens[r] = t + 1;
 }
 
@@ -99,18 +99,21 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append(const AppendArgs a)
 // q_start[r] <= n < q_start[r + 1] and goes to position
 // ctx_lens[r] - (q_start[r + 1] - q_start[r]) + (n - q_start[r]), ctx_lens
 // already counting the new tokens.  One workgroup per token.
-template <typename T, bool TILED>
+// EARLY, the vectors asked for before the request is found, is for rows of more than a unit per thread:
+// 4 prompts of 200, 40 heads of 128, 5.6 us, 5.9 late; with smaller rows most of the threads only wait
+// (4 prompts of 2 000, 8 heads of 64, 8.5 us, 7.9 late; fp32, 8 heads of 128, the largest such row: 5.4 and 5.3).
+template <typename T, bool EARLY>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendArgs a)
 {
     const int n = blockIdx.x;
     const size_t row = (size_t)n * a.num_kv_heads * a.head_dim;
     const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
-    const uint4 k0 = first_unit(a, kn), v0 = first_unit(a, vn);
+    const uint4 none = make_uint4(0, 0, 0, 0), k0 = EARLY ? first_unit(a, kn) : none, v0 = EARLY ? first_unit(a, vn) : none;
     const int r = last_request(a.q_start, a.batch, n, [](int q, int) { return q; });
     const int first = a.q_start[r], count = a.q_start[r + 1] - first;
     if (n >= first + count) return;                   // q_start[batch] is less than the grid
     const int t = a.ctx_lens[r] - count + (n - first);
-    scatter_token<T, TILED>(a, r, t, kn, vn, k0, v0);
+    scatter_token<T, false, EARLY>(a, r, t, kn, vn, k0, v0);
 }
 
 // The same for the tiled layout (bf16), where the 16-byte unit of a value tile is four
@@ -122,12 +125,16 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendA
 // range -- fall back to 16-bit stores.
 // Workgroup w belongs to the last request r with (q_start[r] >> 4) + 2 r <= w: request r
 // touches at most (count >> 4) + 2 sub-tiles, and the keys of consecutive requests are at
-// least that far apart.
+// at least that far apart.
+// (Asking for keys and values together with the table entry is up to 5 % slower: 4 prompts of 200, 16 / 8
+// heads of 256, 4.3 us as it is, 4.5 so.  A few requests are told apart one by one: 7 prompts of 55 to
+// 479 tokens on 2 kv heads of 64 3.4 us, 3.5 by ballots; 16 of 45 to 278 on 8 of 128 6.9 and 6.5.)
 __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const AppendArgs a)
 {
     typedef uint16_t T;
     const int w = blockIdx.x;
-    const int r = last_request(a.q_start, a.batch, w, [](int q, int i) { return (q >> 4) + 2 * i; });
+    const auto sub_start = [](int q, int i) { return (q >> 4) + 2 * i; };
+    const int r = a.batch < kFew ? last_of_few(a.q_start, a.batch, w, sub_start) : last_request(a.q_start, a.batch, w, sub_start);
     const int first = a.q_start[r], count = a.q_start[r + 1] - first;
     const int p0 = a.ctx_lens[r] - count;             // position of the request's first new token
     if (count <= 0 || p0 < 0) return;
@@ -137,46 +144,41 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const A
     const int D = a.head_dim, Hkv = a.num_kv_heads, bs = a.block_size;
     const int lb = (sub * 16) >> a.log2_block_size;
     if (lb >= a.max_blocks) return;
-    const int g = blockIdx.y;                         // kv head
-    const int row = Hkv * D;                          // elements of one token's keys (or values)
-    const T *kn = static_cast<const T *>(a.k_new) + g * D, *vn = static_cast<const T *>(a.v_new) + g * D;
     const int block = a.block_table[(size_t)r * a.max_blocks + lb];
-
-    // What this thread takes first is asked for together with the table entry, whatever that turns out to be.
-    // Keys: (position, 8 dims) -> one 16-byte unit.
-    const int c8 = D / 8, n_keys = (t_hi - t_lo) * c8;
-    auto key_unit = [&](int i) {
-        return *reinterpret_cast<const uint4 *>(kn + (size_t)(first + (t_lo + i / c8 - p0)) * row + i % c8 * 8);
-    };
-    uint4 ku = make_uint4(0, 0, 0, 0);
-    if ((int)threadIdx.x < n_keys) ku = key_unit(threadIdx.x);
-    // Values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16): at
-    // most one per thread.
-    const int vi = threadIdx.x, j = vi & 7, i32 = (vi >> 3) % (D / 32), q = vi / (8 * (D / 32));
-    const int t0 = sub * 16 + 4 * q, d0 = 32 * i32 + 2 * j;   // the quad's first position, the first dim
-    const bool quad = q < 4 && t0 >= t_lo && t0 + 4 <= t_hi;
-    uint32_t lo2[4] = {}, hi2[4] = {};                // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
-    if (quad) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const T *src = vn + (size_t)(first + (t0 + k - p0)) * row + d0;
-            lo2[k] = *reinterpret_cast<const uint32_t *>(src);
-            hi2[k] = *reinterpret_cast<const uint32_t *>(src + 16);
-        }
-    }
-
     if (block < 0 || block >= a.num_blocks) return;
     const size_t tile = (size_t)bs * D;
-    const size_t at = (((size_t)block * a.num_layers + a.layer) * Hkv + g) * tile + (size_t)(((sub * 16) & (bs - 1)) >> 4) * 16 * D;
+    const size_t at = (((size_t)block * a.num_layers + a.layer) * Hkv) * tile + (size_t)(((sub * 16) & (bs - 1)) >> 4) * 16 * D;
     T *kt = static_cast<T *>(a.k_pool) + at;
     T *vt = static_cast<T *>(a.v_pool) + at;
-    for (int i = threadIdx.x; i < n_keys; i += kAppendThreads) {
-        if (i >= kAppendThreads) ku = key_unit(i);
-        *reinterpret_cast<uint4 *>(kt + (size_t)(i % c8 * 16 + ((t_lo + i / c8) & 15)) * 8) = ku;
+    const T *kn = static_cast<const T *>(a.k_new), *vn = static_cast<const T *>(a.v_new);
+    const int row = Hkv * D;                          // elements of one token's keys (or values)
+
+    const int g = blockIdx.y;                         // kv head
+    kt += g * tile; vt += g * tile;
+    kn += g * D; vn += g * D;
+
+    const int c8 = D / 8;                             // keys: (position, 8 dims) -> one 16-byte unit
+    for (int i = threadIdx.x; i < (t_hi - t_lo) * c8; i += kAppendThreads) {
+        const int c = i % c8, t = t_lo + i / c8;
+        *reinterpret_cast<uint4 *>(kt + (size_t)(c * 16 + (t & 15)) * 8) =
+            *reinterpret_cast<const uint4 *>(kn + (size_t)(first + (t - p0)) * row + c * 8);
     }
-    if (q < 4 && t0 + 4 > t_lo && t0 < t_hi) {
+
+    // values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16)
+    for (int i = threadIdx.x; i < 4 * (D / 32) * 8; i += kAppendThreads) {
+        const int j = i & 7, i32 = (i >> 3) % (D / 32), q = i / (8 * (D / 32));
+        const int t0 = sub * 16 + 4 * q;              // the quad's first position
+        if (t0 + 4 <= t_lo || t0 >= t_hi) continue;
+        const int d0 = 32 * i32 + 2 * j;
         T *dst = vt + (size_t)((i32 * 4 + q) * 16 + 2 * j) * 8;   // unit of dim d0; dim d0 + 1's follows
-        if (quad) {
+        if (t0 >= t_lo && t0 + 4 <= t_hi) {
+            uint32_t lo2[4], hi2[4];                  // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const T *src = vn + (size_t)(first + (t0 + k - p0)) * row + d0;
+                lo2[k] = *reinterpret_cast<const uint32_t *>(src);
+                hi2[k] = *reinterpret_cast<const uint32_t *>(src + 16);
+            }
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int sh = 16 * e;
@@ -223,12 +225,17 @@ hipError_t launch_kv_append_tokens(const AppendArgs &a, int total_tokens, int ti
 {
     if (a.batch == 0 || total_tokens == 0) return hipSuccess;
     dim3 grid((unsigned)total_tokens), block(kAppendThreads);
+    const bool early = (size_t)a.num_kv_heads * a.head_dim * (a.bf16 ? 2 : 4) > 16 * kAppendThreads;
     if (a.bf16) {
         if (tiled)
             hipLaunchKernelGGL(kv_append_tokens_tiled, dim3((unsigned)((total_tokens >> 4) + 2 * a.batch), (unsigned)a.num_kv_heads),
                                block, 0, stream, a);
+        else if (early)
+            hipLaunchKernelGGL((kv_append_tokens<uint16_t, true>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((kv_append_tokens<uint16_t, false>), grid, block, 0, stream, a);
+    } else if (early) {
+        hipLaunchKernelGGL((kv_append_tokens<float, true>), grid, block, 0, stream, a);
     } else {
         hipLaunchKernelGGL((kv_append_tokens<float, false>), grid, block, 0, stream, a);
     }

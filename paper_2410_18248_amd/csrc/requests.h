@@ -24,5 +24,18 @@ __device__ __forceinline__ int last_request(const int32_t *q_start, int batch, i
     return lo;
 }
 
+// The same one by one, by scalar loads, which come sooner: for a few requests.
+constexpr int kFew = 16;
+template <typename Key>
+__device__ __forceinline__ int last_of_few(const int32_t *q_start, int batch, int x, Key key)
+{
+    int lo = 0, hi = batch;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (key(q_start[mid], mid) <= x) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 }  // namespace
 }  // namespace lamps

@@ -42,3 +42,11 @@ def test_tokens_reach_their_requests(dtype, H, Hkv, D, n_req):
     got_k, got_v = rig.host_pools()
     assert got_k.tobytes() == kp.tobytes() and got_v.tobytes() == vp.tobytes()
     rig.close()
+
+
+# around the number of requests that are told apart one by one, and around the size of a row whose
+# vectors are asked for early (4 KiB)
+@pytest.mark.parametrize("dtype,H,Hkv,D,n_req", [("bf16", 4, 2, 128, 15), ("bf16", 4, 2, 128, 16), ("bf16", 4, 1, 64, 17), ("bf16", 32, 32, 64, 5),
+                                                 ("bf16", 33, 33, 64, 20), ("bf16", 16, 16, 256, 14), ("f32", 8, 8, 128, 9), ("f32", 9, 9, 128, 66)])
+def test_few_requests_and_long_rows(dtype, H, Hkv, D, n_req):
+    test_tokens_reach_their_requests(dtype, H, Hkv, D, n_req)
