@@ -190,7 +190,14 @@ unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int 
     *full_groups = (int)full;
     // the tiles of all requests are at most this many; a quarter fewer workgroups pay for finding them
     const long long most = heads * ((long long)p.total_tokens / WT + p.d.batch);
-    if ((by_start || p.d.batch <= 64 * kRagged) && most + most / 4 + spare < grid) {
+    // With a number of heads that is no multiple of 8 a pair's tiles, numbered so, lie on several XCDs and each
+    // fetches the pair's K / V.  That does not pay where the chip holds the full grid at once, nor for short
+    // walks, which leave no long tail to fill (2 kv heads of 128, 8 heads, append + attention: 16 prompts of 45 to
+    // 278 tokens 17.7 us together, 18.9 apart; 100 of 10 to 200 32.4 and 34.7; but 24 of 16 to 700 49 and 38, and
+    // with 40 of 45 to 278 on 1 000 cached it is 54.4 and 53.8, with heads of 64 45 and 39).
+    const bool short_walks = p.max_new_tokens < 320 && (long long)p.d.max_blocks * p.d.block_size < 640;
+    const bool together = !by_start && p.d.head_dim < 256 && heads % 8 != 0 && (grid <= 512 || short_walks);
+    if (!together && (by_start || p.d.batch <= 64 * kRagged) && most + most / 4 + spare < grid) {
         grid = most;
         *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
     }

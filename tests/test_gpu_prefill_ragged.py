@@ -35,6 +35,14 @@ def test_ragged_batches(H, Hkv, D, n_req, most, cached):
     _check(H, Hkv, D, new, cached, rng)
 
 
+# the same for head counts that are no multiple of 8 where the full grid is larger than the chip and the
+# longest request long enough for workgroups to be started for the tiles there are only, and just too short
+@pytest.mark.parametrize("H,Hkv,D,n_req,most,cached", [(4, 4, 128, 24, 900, 0), (6, 3, 64, 64, 400, 10), (2, 1, 64, 256, 320, 3),
+                                                       (2, 1, 64, 256, 319, 3), (32, 1, 64, 20, 330, 5), (4, 2, 128, 70, 100, 640)])
+def test_ragged_batches_of_few_heads(H, Hkv, D, n_req, most, cached):
+    test_ragged_batches(H, Hkv, D, n_req, most, cached)
+
+
 #  launches that fit the chip at once, where half of the pairs take their tiles the other way round (4 and 8
 #  tiles a pair), or not, as the second turn begins inside a pair's tiles (5, 12 and 7)
 @pytest.mark.parametrize("H,Hkv,D,n_req,most,cached", [(8, 8, 64, 8, 640, 0), (8, 8, 64, 5, 1500, 0), (8, 8, 256, 5, 440, 70),
