@@ -7,6 +7,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 
 namespace lamps {
@@ -411,41 +413,27 @@ struct MfmaReducer {
         const char *vp = static_cast<const char *>(a.v_pool) + head_off + lane * 16;
 
         // Software pipeline: the loads of chunk ch + 1 are issued before chunk ch is
-        // consumed, and the block-table entry of chunk ch + 2 is fetched with them,
-        // so a wave always has a sub-tile of K and V in flight while it computes.
-        auto entry = [&](int c) -> int {
-            return c < n_chunks ? table[(t_begin + c * CT) >> a.log2_block_size] : 0;
-        };
+        // consumed, and the block-table entries of the two chunks behind it with them,
+        // so a wave always has a sub-tile of K and V in flight while it computes.  Nothing on
+        // the way is conditional: behind a load that may or may not have been issued the compiler
+        // waits for the loads of the next chunk before it touches the present one.  (So it did: 200 requests of 100 to
+        // 4 000 tokens, 8 / 2 heads of 64, 28.0 -> 26.8 us; 32 of 100 to 4 000, 16 / 4 heads of 256, 31.3 -> 30.3; 19 of
+        // 4 096 to 32 768, 32 / 8 of 128, 202.7 -> 200.8.)
+        auto entry = [&](int c) -> int { return table[(t_begin + min(c, n_chunks - 1) * CT) >> a.log2_block_size]; };
         auto issue = [&](int c, int block, uint4 (&kx)[NK], uint4 (&vx)[NS]) {
-            // sub-tile (t % block_size) / 16 of the block's tile: 16 * D elements each
+            // sub-tile (t % block_size) / 16 of the block's tile: 16 * D elements each.  A table entry
+            // that does not name a block of the pool is the caller's mistake; it must not become a wild
+            // read: the pool's last block is read instead, and the row it belongs to is meaningless
             const int t = t_begin + c * CT;
-            const size_t off = (size_t)block * block_stride +
+            const size_t off = (size_t)min((unsigned)block, (unsigned)a.num_blocks - 1) * block_stride +
                                (size_t)((t & (a.block_size - 1)) >> 4) * (16 * D * 2);
-            // (wave-uniform) a table entry that does not name a block of the pool is the caller's
-            // mistake; it must not become a wild read: the sub-tile counts as zeros and the row it
-            // belongs to is meaningless
-            if ((unsigned)block < (unsigned)a.num_blocks) {
 #pragma unroll
-                for (int i = 0; i < NK; ++i) kx[i] = load_stream16(kp + off + i * 1024);
+            for (int i = 0; i < NK; ++i) kx[i] = load_stream16(kp + off + i * 1024);
 #pragma unroll
-                for (int i = 0; i < NS; ++i) vx[i] = load_stream16(vp + off + i * 1024);
-            } else {
-#pragma unroll
-                for (int i = 0; i < NK; ++i) kx[i] = make_uint4(0, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < NS; ++i) vx[i] = make_uint4(0, 0, 0, 0);
-            }
+            for (int i = 0; i < NS; ++i) vx[i] = load_stream16(vp + off + i * 1024);
         };
-        uint4 kx[NK], vx[NS], kn[NK], vn[NS];
-        int ch = 0;
-        int pb1 = entry(1);
-        if (n_chunks > 0) issue(0, entry(0), kx, vx);
-        while (ch < n_chunks) {
-            const int t0 = t_begin + ch * CT;
-            const int pb2 = entry(ch + 2);
-            if (ch + 1 < n_chunks) issue(ch + 1, pb1, kn, vn);
-            pb1 = pb2;
-
+        auto consume = [&](int t0, uint4 (&kx)[NK], uint4 (&vx)[NS], auto last) {
+            __builtin_amdgcn_sched_barrier(0);     // (the loads above stay above what waits for the ones before them)
             f32x4 s = {0.f, 0.f, 0.f, 0.f};        // tokens t0 + 4 qd + e, head j
 #pragma unroll
             for (int i = 0; i < NK; ++i)
@@ -454,7 +442,7 @@ struct MfmaReducer {
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] *= a.scale_log2e;
 
-            if (t0 + CT > t_end) {                 // ragged tail: slots at or past ctx_len never count
+            if (last && t0 + CT > t_end) {         // ragged tail: slots at or past ctx_len never count
                 const int valid = min(4, max(0, t_end - (t0 + 4 * qd)));   // of this lane's 4 tokens
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -504,11 +492,33 @@ struct MfmaReducer {
                 o[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1.v, ph.v, o[2 * i + 1], 0, 0, 0);
                 o[2 * i + 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1.v, pl.v, o[2 * i + 1], 0, 0, 0);
             }
-            ++ch;
-#pragma unroll
-            for (int i = 0; i < NK; ++i) kx[i] = kn[i];
-#pragma unroll
-            for (int i = 0; i < NS; ++i) vx[i] = vn[i];
+        };
+        if (n_chunks > 0) {
+            uint4 ka[NK], va[NS], kb[NK], vb[NS];
+            int ch = 0, e1, e2;
+            if ((n_chunks & 1) == 0) {             // the last chunk is to be one that `ka` holds
+                const int e0 = entry(0);
+                e1 = entry(1);
+                issue(0, e0, kb, vb);
+                issue(1, e1, ka, va);
+                e1 = entry(2);
+                e2 = entry(3);
+                consume(t_begin, kb, vb, std::false_type{});
+                ch = 1;
+            } else {
+                issue(0, entry(0), ka, va);
+                e1 = entry(1);
+                e2 = entry(2);
+            }
+            for (; ch + 1 < n_chunks; ch += 2) {
+                issue(ch + 1, e1, kb, vb);
+                e1 = entry(ch + 3);
+                consume(t_begin + ch * CT, ka, va, std::false_type{});
+                issue(ch + 2, e2, ka, va);
+                e2 = entry(ch + 4);
+                consume(t_begin + (ch + 1) * CT, kb, vb, std::false_type{});
+            }
+            consume(t_begin + ch * CT, ka, va, std::true_type{});
         }
 
         // the weight sum was kept per token group: add the four groups of a head
@@ -550,7 +560,8 @@ struct MfmaF32Tile {
     };
 
     // Reduces cached positions [t_begin, t_end) of request r, kv head g, taking every `stride`-th
-    // chunk of 16; t_begin is a multiple of 16.  q: the lane's column's row (nullptr: no column), of
+    // chunk of 16 (two at least: then only a wave's last chunk can hold positions that some column does not
+    // see, limits being at most 15 apart); t_begin is a multiple of 16.  q: the lane's column's row (nullptr: no column), of
     // which positions at or past `limit` do not count; every column sees the positions before min_limit.
     static __device__ __forceinline__ void reduce(const DecodeArgs &a, int r, int g, const float *q, int limit, int min_limit,
                                                   int t_begin, int t_end, int stride, State &st)
@@ -575,41 +586,25 @@ struct MfmaF32Tile {
         const float *kp = static_cast<const float *>(a.k_pool) + head_off + j * D + 4 * qd;
         const float *vp = static_cast<const float *>(a.v_pool) + head_off + 4 * qd * D + VW * j;
 
-        // As in MfmaReducer: chunk c + 1 is asked for before chunk c is consumed, the table entry of
-        // chunk c + 2 with it.
-        auto entry = [&](int c) -> int {
-            return c < n_chunks ? table[(t_begin + c * CT * stride) >> a.log2_block_size] : 0;
-        };
+        // As in MfmaReducer: chunk c + 1 is asked for before chunk c is consumed, the table entries of the
+        // two behind it with it, and nothing on the way is conditional.  (With conditional loads each chunk
+        // waited for the loads of the next: one prompt of 1 000 tokens, 8 heads of 64, append included, 28.2 -> 24.8 us;
+        // 4 x 8 to 32 new on 1 000 to 3 000 cached 41.4 -> 31.0; 3 of 600 on 32 / 8 heads of 128 152.6 -> 130.3.)
+        auto entry = [&](int c) -> int { return table[(t_begin + min(c, n_chunks - 1) * CT * stride) >> a.log2_block_size]; };
         auto issue = [&](int c, int block, f32x4 (&kx)[NK], vvec (&vx)[4][NC]) {
             const int t = t_begin + c * CT * stride;
-            const size_t off = (size_t)block * block_stride + (size_t)(t & (a.block_size - 1)) * D;
-            // (wave-uniform) an entry that names no block of the pool counts as zeros
-            if ((unsigned)block < (unsigned)a.num_blocks) {
+            // (an entry that names no block of the pool is the caller's mistake: it reads the last block)
+            const size_t off = (size_t)min((unsigned)block, (unsigned)a.num_blocks - 1) * block_stride +
+                               (size_t)(t & (a.block_size - 1)) * D;
 #pragma unroll
-                for (int i = 0; i < NK; ++i) kx[i] = *reinterpret_cast<const f32x4 *>(kp + off + 16 * i);
+            for (int i = 0; i < NK; ++i) kx[i] = *reinterpret_cast<const f32x4 *>(kp + off + 16 * i);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = *reinterpret_cast<const vvec *>(vp + off + e * D + 16 * VW * c2);
-            } else {
-#pragma unroll
-                for (int i = 0; i < NK; ++i) kx[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = vvec{};
-            }
+                for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = *reinterpret_cast<const vvec *>(vp + off + e * D + 16 * VW * c2);
         };
-        f32x4 kx[NK], kn[NK];
-        vvec vx[4][NC], vn[4][NC];
-        int pb1 = entry(1);
-        if (n_chunks > 0) issue(0, entry(0), kx, vx);
-        for (int ch = 0; ch < n_chunks; ++ch) {
-            const int t0 = t_begin + ch * CT * stride;
-            const int pb2 = entry(ch + 2);
-            if (ch + 1 < n_chunks) issue(ch + 1, pb1, kn, vn);
-            pb1 = pb2;
-
+        auto consume = [&](int t0, f32x4 (&kx)[NK], vvec (&vx)[4][NC], auto last) {
+            __builtin_amdgcn_sched_barrier(0);        // (the loads above stay above what waits for the ones before them)
             // tokens t0 + 4 qd + e of the lane's column; eight chains: no MFMA waits for the one before
             // it, and the sums are short (their error stays that of the vector ALUs' pairwise ones)
             f32x4 p8[8];
@@ -627,7 +622,7 @@ struct MfmaF32Tile {
             for (int e = 0; e < 4; ++e)
                 s[e] = (((p8[0][e] + p8[1][e]) + (p8[2][e] + p8[3][e])) + ((p8[4][e] + p8[5][e]) + (p8[6][e] + p8[7][e]))) * a.scale_log2e;
             bool wild = false;                        // uniform: a value that not every column sees is no finite number
-            if (t0 + CT > min_limit || t0 + CT > t_end) {   // uniform: some column does not see the whole chunk
+            if (last && (t0 + CT > min_limit || t0 + CT > t_end)) {   // uniform: some column does not see the whole chunk
                 const int seen = min(limit, t_end) - (t0 + 4 * qd);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -697,12 +692,32 @@ struct MfmaF32Tile {
                         for (int e = 0; e < 4; ++e) st.o[c][v][e] = fmaf(st.o[c][v][e], sc, kept[e]);
                     }
             }
-#pragma unroll
-            for (int i = 0; i < NK; ++i) kx[i] = kn[i];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int c2 = 0; c2 < NC; ++c2) vx[e][c2] = vn[e][c2];
+        };
+        if (n_chunks > 0) {
+            f32x4 ka[NK], kb[NK];
+            vvec va[4][NC], vb[4][NC];
+            const int step = CT * stride;
+            const bool even = (n_chunks & 1) == 0;
+            int ch = 0, e0 = entry(0), e1 = entry(1), e2 = entry(2);
+            if (even) {                               // the last chunk is to be one that `ka` holds
+                issue(0, e0, kb, vb);
+                issue(1, e1, ka, va);
+                e1 = e2;
+                e2 = entry(3);
+                consume(t_begin, kb, vb, std::false_type{});
+                ch = 1;
+            } else {
+                issue(0, e0, ka, va);
+            }
+            for (; ch + 1 < n_chunks; ch += 2) {
+                issue(ch + 1, e1, kb, vb);
+                e1 = entry(ch + 3);
+                consume(t_begin + ch * step, ka, va, std::false_type{});
+                issue(ch + 2, e2, ka, va);
+                e2 = entry(ch + 4);
+                consume(t_begin + (ch + 1) * step, kb, vb, std::false_type{});
+            }
+            consume(t_begin + ch * step, ka, va, std::true_type{});
         }
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
