@@ -184,6 +184,7 @@ __device__ __forceinline__ void merge_state(float &m, float &l, float (&acc)[VEC
 // Plain pool layout, GH query heads of the group per pass (GH == 1 for bf16).
 template <bool BF16, int LPT, int GH, int NH>
 struct ValuReducer {
+    static constexpr int kMostPerCu = 8;              // workgroups of a decode launch: as many as fit
     static constexpr bool kBF16 = BF16;
     static constexpr int VEC = BF16 ? 8 : 4;          // elements per 16-byte load
     static constexpr int D = LPT * VEC;
@@ -373,6 +374,10 @@ struct ValuReducer {
 // sub-tile is the max over the four token groups (two shuffles).
 template <int DIM>
 struct MfmaReducer {
+    // Workgroups of a decode launch on a CU.  At head_dim 128 three fit, and two are the better ones: more shares,
+    // so more pieces and shorter ones, for a stream that two keep at the memory's rate (230 of 256 requests of 32
+    // to 8 192 tokens, 32 / 8 heads: 246 us with three, 240 with two; 64 of 50 to 300: 23.3 and 19.3).
+    static constexpr int kMostPerCu = DIM == 128 ? 2 : 8;
     static constexpr bool kBF16 = true;
     static constexpr int D = DIM;
     static constexpr int CT = 16, GT = 16;            // tokens per chunk = one sub-tile
@@ -417,8 +422,8 @@ struct MfmaReducer {
         // so a wave always has a sub-tile of K and V in flight while it computes.  Nothing on
         // the way is conditional: behind a load that may or may not have been issued the compiler
         // waits for the loads of the next chunk before it touches the present one.  (So it did: 200 requests of 100 to
-        // 4 000 tokens, 8 / 2 heads of 64, 28.0 -> 26.8 us; 32 of 100 to 4 000, 16 / 4 heads of 256, 31.3 -> 30.3; 19 of
-        // 4 096 to 32 768, 32 / 8 of 128, 202.7 -> 200.8.)
+        // 4 000 tokens, 8 / 2 heads of 64, 28.0 -> 26.8 us; 32 of 100 to 4 000, 16 / 4 heads of 256, 31.3 -> 28.4, with
+        // the accumulators in ordinary registers; 19 of 4 096 to 32 768, 32 / 8 of 128, 202.7 -> 199.7.)
         auto entry = [&](int c) -> int { return table[(t_begin + min(c, n_chunks - 1) * CT) >> a.log2_block_size]; };
         auto issue = [&](int c, int block, uint4 (&kx)[NK], uint4 (&vx)[NS]) {
             // sub-tile (t % block_size) / 16 of the block's tile: 16 * D elements each.  A table entry

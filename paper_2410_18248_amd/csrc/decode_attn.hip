@@ -570,7 +570,7 @@ hipError_t resident_workgroups(const DecodeArgs &a, int *out)
     }
     constexpr size_t kLds = (size_t)160 << 10, kStep = 2048;   // of a gfx950 CU; no allocation step is larger
     const size_t lds = (balanced_lds<R, TOGETHER>(a.batch, a.heads_per_pass) + 256 + kStep - 1) / kStep * kStep;
-    *out = cus * min(per_cu, (int)(kLds / lds));      // (never none: 32 KiB for 8 192 requests, 66 for 16 heads of 256 together)
+    *out = cus * min(min(per_cu, R::kMostPerCu), (int)(kLds / lds));      // (never none: 32 KiB for 8 192 requests, 66 for 16 heads of 256 together)
     return hipSuccess;
 }
 
