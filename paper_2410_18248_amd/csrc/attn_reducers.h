@@ -119,12 +119,36 @@ __device__ __forceinline__ void store_out(void *out, size_t i, float o)
         static_cast<float *>(out)[i] = o;
 }
 
-__device__ __forceinline__ void store_partial(float *pp, int D, int d, float M, float L, float A)
+// N consecutive dims, d and up, of one head's row.  Rows of partials are 8-byte aligned.
+template <int N>
+__device__ __forceinline__ void store_partial(float *pp, int D, int d, float M, float L, const float (&A)[N])
 {
-    pp[d] = A;
-    if (d == 0) {
-        pp[D] = M;
-        pp[D + 1] = L;
+#pragma unroll
+    for (int e = 0; e < N; e += 2) *reinterpret_cast<float2 *>(pp + d + e) = make_float2(A[e], A[e + 1]);
+    if (d == 0) *reinterpret_cast<float2 *>(pp + D) = make_float2(M, L);
+}
+// Element i and up of `out`, divided by L (zeros if that is none).  wide: out is 16-byte aligned (i is a multiple
+// of N).
+template <bool BF16, int N>
+__device__ __forceinline__ void store_out(void *out, size_t i, bool wide, float L, const float (&A)[N])
+{
+    float o[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) o[e] = L > 0.0f ? A[e] / L : 0.0f;
+    if (!wide) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) store_out<BF16>(out, i + e, o[e]);
+    } else if constexpr (BF16) {
+        uint32_t w[N / 2];
+#pragma unroll
+        for (int e = 0; e < N; e += 2) w[e / 2] = pack_bf16(o[e], o[e + 1]);
+        uint16_t *at = static_cast<uint16_t *>(out) + i;
+        if constexpr (N == 2) *reinterpret_cast<uint32_t *>(at) = w[0];
+        if constexpr (N == 4) *reinterpret_cast<uint2 *>(at) = make_uint2(w[0], w[1]);
+        if constexpr (N == 8) *reinterpret_cast<uint4 *>(at) = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; e += 2) *reinterpret_cast<float2 *>(static_cast<float *>(out) + i + e) = make_float2(o[e], o[e + 1]);
     }
 }
 
@@ -184,7 +208,7 @@ __device__ __forceinline__ void merge_state(float &m, float &l, float (&acc)[VEC
 // Plain pool layout, GH query heads of the group per pass (GH == 1 for bf16).
 template <bool BF16, int LPT, int GH, int NH>
 struct ValuReducer {
-    static constexpr int kMostPerCu = 8;              // workgroups of a decode launch: as many as fit
+    static constexpr int kLeastPerCu = 4, kMostPerCu = 8;   // workgroups of a decode launch: as many as fit
     static constexpr bool kBF16 = BF16;
     static constexpr int VEC = BF16 ? 8 : 4;          // elements per 16-byte load
     static constexpr int D = LPT * VEC;
@@ -198,8 +222,8 @@ struct ValuReducer {
 
     // One wavefront reduces cached positions [t_begin, t_end) of request r (kv
     // head g, query heads h0 .. h0+GH-1), chunk after chunk, then calls
-    // sink(h, d, M, L, A) once for every (head, dim): M = running max (log2
-    // domain), L = sum of weights, A = weighted sum of V[:, d].  t_begin is a
+    // sink(h, d, M, L, A) for every head and run of VEC dims: M = running max (log2
+    // domain), L = sum of weights, A[] = weighted sums of V[:, d ..].  t_begin is a
     // multiple of GT.  No barrier, no LDS: waves of a workgroup are independent.
     // q is row `qrow` of a.q ([rows][H][D]); the block table row is r (decode: the same).
     template <typename Sink>
@@ -354,9 +378,7 @@ struct ValuReducer {
 
         if (row == 0) {
 #pragma unroll
-            for (int h = 0; h < GH; ++h)
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) sink(h, col * VEC + e, m[h], l[h], acc[h][e]);
+            for (int h = 0; h < GH; ++h) sink(h, col * VEC, m[h], l[h], acc[h]);
         }
     }
 };
@@ -377,7 +399,7 @@ struct MfmaReducer {
     // Workgroups of a decode launch on a CU.  At head_dim 128 three fit, and two are the better ones: more shares,
     // so more pieces and shorter ones, for a stream that two keep at the memory's rate (230 of 256 requests of 32
     // to 8 192 tokens, 32 / 8 heads: 246 us with three, 240 with two; 64 of 50 to 300: 23.3 and 19.3).
-    static constexpr int kMostPerCu = DIM == 128 ? 2 : 8;
+    static constexpr int kLeastPerCu = DIM >= 256 ? 1 : DIM == 128 ? 2 : 4, kMostPerCu = DIM == 128 ? 2 : 8;
     static constexpr bool kBF16 = true;
     static constexpr int D = DIM;
     static constexpr int CT = 16, GT = 16;            // tokens per chunk = one sub-tile
@@ -532,9 +554,10 @@ struct MfmaReducer {
 
         if (j < heads) {
 #pragma unroll
-            for (int sidx = 0; sidx < 2 * NS; ++sidx)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sink(j, 16 * sidx + 4 * qd + e, m, l, o[sidx][e]);
+            for (int sidx = 0; sidx < 2 * NS; ++sidx) {
+                const float A[4] = {o[sidx][0], o[sidx][1], o[sidx][2], o[sidx][3]};
+                sink(j, 16 * sidx + 4 * qd, m, l, A);
+            }
         }
     }
 };

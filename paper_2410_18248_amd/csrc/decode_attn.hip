@@ -15,8 +15,8 @@
 //     holds at once each take an equal contiguous share, so every wavefront ends within
 //     a chunk of the others however skewed the context lengths are.  With eight resident
 //     waves and more to a range: a share belongs to a workgroup, whose four waves
-//     take a quarter of each of its ranges.  With less work than a chunk per
-//     share: the shares are pieces of one range each.  A share is at most: the
+//     take a quarter of each of its ranges.  With few chunks to a
+//     share: the shares are pieces of one range each, if there are enough.  A share is at most: the
 //     tail of one range, some whole ones, and the head of another;
 //     whole ones are written out directly, the two partial ends go to
 //     per-share slots that a second kernel merges.
@@ -49,10 +49,12 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "attn_reducers.h"
 #include "internal.h"
 #include "lamps.h"
+#include "prefill_split.h"
 
 namespace lamps {
 namespace {
@@ -91,9 +93,10 @@ __global__ __launch_bounds__(kThreads) void decode_partial(const DecodeArgs a)
     const int h0 = g * G + (hc % passes) * GH;
     const size_t rh0 = (size_t)r * a.num_q_heads + h0;
 
-    R::run(a, r, (size_t)r, g, h0, GH, t_begin, t_end, [&](int h, int d, float M, float L, float A) {
+    const bool wide = ((uintptr_t)a.out & 15) == 0;
+    R::run(a, r, (size_t)r, g, h0, GH, t_begin, t_end, [&](int h, int d, float M, float L, const auto &A) {
         if (n_parts == 1)
-            store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+            store_out<R::kBF16>(a.out, (rh0 + h) * D + d, wide, L, A);
         else
             store_partial(a.partials + ((rh0 + h) * a.max_parts + part) * (D + 2), D, d, M, L, A);
     });
@@ -161,27 +164,53 @@ __device__ __forceinline__ int share_of(long long x, long long total, int P)
     return (int)((double)((x + 1) * P - 1) / (double)total);
 }
 
+constexpr int kLaneBatch = 64;           // requests of a batch that a wave holds one per lane
+constexpr int kPieceMost = 64;           // chunks of a piece: where shares are longer, they straddle ranges
+
 // Chunks a running request contributes per (kv head, pass): an empty context
 // still gets one (empty) chunk so that its zero row is written.
-__device__ __forceinline__ int chunks_of(const DecodeArgs &a, int r, int GT)
+__device__ __forceinline__ int chunks_of(int running, int C, int GT) { return running ? max(1, (C + GT - 1) / GT) : 0; }
+// Mask and length of a request, asked for together.
+__device__ __forceinline__ int2 request_of(const DecodeArgs &a, int r)
 {
     const int running = a.running[r];
     int C = a.ctx_lens[r];
-    asm volatile("" : "+v"(C));                       // asked for together with the mask, not after it
-    C = min(C, a.max_blocks * a.block_size);
-    return running ? max(1, (C + GT - 1) / GT) : 0;
+    asm volatile("" : "+v"(C));                       // (not one after the other)
+    return make_int2(running, min(C, a.max_blocks * a.block_size));
 }
 
-// Ints of a balanced launch's dynamic LDS: the chunk prefix, and that of the pieces of a small launch.
+// The flat chunk sequence of a launch as a wave holds it: the chunks before each request and of it, per head / pass, and
+// its length.  Batches of up to 64: a request per lane.  Up to 256: four per lane, which write them to LDS (every wave
+// the same, so no wave waits for another).  Larger ones: their prefix in LDS, by all waves of a workgroup.
+struct Request {
+    int before, count, ctx;
+};
+struct Sequence {
+    const int *prefix;                                // LDS
+    const DecodeArgs *a;
+    Request mine;                                     // of request `lane`
+    __device__ __forceinline__ Request operator[](int r) const
+    {
+        if (a->batch <= kLaneBatch)
+            return Request{__builtin_amdgcn_readlane(mine.before, r), __builtin_amdgcn_readlane(mine.count, r),
+                           __builtin_amdgcn_readlane(mine.ctx, r)};
+        if (a->batch <= 4 * kLaneBatch) {
+            const int4 x = reinterpret_cast<const int4 *>(prefix)[r];
+            return Request{__builtin_amdgcn_readfirstlane(x.x), __builtin_amdgcn_readfirstlane(x.y), __builtin_amdgcn_readfirstlane(x.z)};
+        }
+        const int before = __builtin_amdgcn_readfirstlane(prefix[r]);
+        return Request{before, __builtin_amdgcn_readfirstlane(prefix[r + 1]) - before, ctx_len(*a, r)};
+    }
+};
+// Ints of it in a launch's dynamic LDS.
 __host__ __device__ __forceinline__ int balanced_ints(int batch)
 {
-    return ((batch + 1) * (batch <= kThreads ? 2 : 1) + 3) & ~3;
+    return batch <= kLaneBatch ? 0 : batch <= 4 * kLaneBatch ? 16 * kLaneBatch : (batch + 1 + 3) & ~3;
 }
 
 // gridDim.x * 4 wavefronts, each an equal contiguous share of the flat chunk
-// sequence ordered (kv head / pass, request, chunk).  prefix[] (dynamic LDS,
-// batch + 1 ints) holds the running chunk count per request; every workgroup
-// computes it for itself from ctx_lens / running (a few hundred loads that hit
+// sequence ordered (kv head / pass, request, chunk).  Every wave (of batches above 64: every workgroup, through the
+// prefix in dynamic LDS) works the sequence out for itself from ctx_lens / running (loads that hit
 // in L2), which costs less than a dependent launch.
 //
 // Which share a wavefront takes: with the heads outermost, the shares that read
@@ -193,9 +222,9 @@ __host__ __device__ __forceinline__ int balanced_ints(int batch)
 // 100 GB and more this is worth several per cent; with small pools it is neutral.
 //
 // Small launches are bound by the way to the first K / V byte: mask and lengths are asked for
-// together, scans are DPP adds, divisions 32 bits wide, and the cut is by half-chunks, so that no
-// wave has twice another's work.  One request of 1 999 tokens, both launches: 13.2 -> 10.3 us (2.6 of
-// the 6.3 us of this kernel pass before its first range, 4.0 before).
+// together, scans are DPP adds, nothing waits at a barrier, divisions are by reciprocal or 32 bits wide, lengths
+// come out of registers or LDS, and the cut is by half-chunks, so that no wave has twice another's work.  One
+// request of 1 999 tokens, both launches: 13.2 -> 10.3 us with half of that, 9.85 -> 9.05 with the rest.
 //
 // TOGETHER: a share belongs to a workgroup, whose four waves take a quarter of each of its ranges
 // and add the quarters up in LDS.  For launches with few ranges for the waves (a few requests, or
@@ -204,81 +233,28 @@ __host__ __device__ __forceinline__ int balanced_ints(int batch)
 // 128, 40.8 -> 33.0 us; 19 of 32 requests of 4 096 to 32 768 tokens, 32 / 8 heads, 209.7 -> 205.3; one
 // request of 1 999 tokens 14.5 -> 13.2.
 template <typename R, bool TOGETHER>
-__global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
+__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(const DecodeArgs a)
 {
     constexpr int D = R::D;
-    extern __shared__ int prefix[];                   // then pieces[] (balanced_ints), and, TOGETHER, [wave][head][D + 2] floats
+    extern __shared__ __align__(16) int prefix[];     // balanced_ints; then, TOGETHER, [wave][head][D + 2] floats
     __shared__ int wave_total[2][kWaves], wave_longest[kWaves];
 
     const int B = a.batch;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int per = (B + kThreads - 1) / kThreads;   // consecutive requests per thread
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr bool kCut = R::CT != R::GT;            // (else chunk and cut are one)
-    int parts = 0, wholes = 0, longest = 0;          // of this thread's requests, in GT and in CT tokens
-    for (int i = 0; i < per; ++i) {
-        const int r = tid * per + i;
-        if (r < B) {
-            const int n = chunks_of(a, r, R::GT);
-            parts += n;
-            if (kCut) wholes += (n + 1) >> 1;
-            longest = max(longest, n);
-        }
-    }
-    longest = wave_max_to(longest);
-    const int parts_to = wave_scan(parts), wholes_to = kCut ? wave_scan(wholes) : 0;   // inclusive, inside the wave
-    if (lane == 63) {
-        wave_total[0][wv] = parts_to;
-        wave_total[1][wv] = wholes_to;
-        wave_longest[wv] = longest;
-    }
-    __syncthreads();
-    int T_whole = 0;
-#pragma unroll
-    for (int ww = 0; ww < kWaves; ++ww) {
-        longest = max(longest, wave_longest[ww]);
-        T_whole += wave_total[1][ww];
-    }
+    const int GH = a.heads_per_pass;
+    const int passes = a.passes;
+    const int HC = a.num_kv_heads * passes;
+    constexpr int kOwnShares = TOGETHER ? 1 : kWaves;  // of a workgroup
+    const int sub = TOGETHER ? 0 : wv;
+    int P = gridDim.x * kOwnShares;
+    int share = blockIdx.x * kOwnShares + sub;
     // Below, a chunk is GT tokens, and a wave loads one of them, or two, at a time.  Cutting by the smaller ones evens
     // launches out whose shares are a chunk or less; it costs a half-empty load where a range is cut, which is
     // all that is left where shares are longer.  By halves / whole: 40 fp32 requests of 60 to 200 tokens, 32 / 16 heads
     // of 128 (1.3 chunks a share, 2 layers) 51 / 54 us; 100 of 60 to 90, 16 heads of 256 (1.8, 3 layers) 100 / 96;
     // 34 of 202 to 532 (2.9) 136 / 129; 110 of 28 to 161 on 40 heads of 128 (3.2) 118 / 116.
-    const long long shares = (long long)gridDim.x * (TOGETHER ? 1 : kWaves);
-    const bool whole_chunks = kCut && 2LL * T_whole * (a.num_kv_heads * a.passes) >= 3 * shares;
-    const int GT = whole_chunks ? R::CT : R::GT, log2_whole = kCut && !whole_chunks ? 1 : 0;
-    if (whole_chunks) longest = (longest + 1) >> 1;
-    const int mine = whole_chunks ? wholes : parts;
-    int run = (whole_chunks ? wholes_to : parts_to) - mine;
-#pragma unroll
-    for (int ww = 0; ww < kWaves - 1; ++ww) run += ww < wv ? wave_total[whole_chunks][ww] : 0;
-    if (tid == 0) prefix[0] = 0;
-    if (per == 1) {
-        if (tid < B) prefix[tid + 1] = run + mine;
-    } else {
-        for (int i = 0; i < per; ++i) {
-            const int r = tid * per + i;
-            if (r < B) {
-                run += chunks_of(a, r, GT);
-                prefix[r + 1] = run;
-            }
-        }
-    }
-    __syncthreads();
-
-    const int GH = a.heads_per_pass;
-    const int passes = a.passes;
-    const int HC = a.num_kv_heads * passes;
-    // (values that are the same in every lane are told so: the compiler cannot see it
-    // through LDS and the shuffles, and would keep the range arithmetic in vector registers)
-    const int T = __builtin_amdgcn_readfirstlane(prefix[B]);   // chunks per head / pass
-    const long long total = (long long)HC * T;
-    longest = __builtin_amdgcn_readfirstlane(longest);
-    // from here on every wave is on its own (TOGETHER: every workgroup, and its waves alike); the one
-    // barrier pair below is for all or none
-    constexpr int kOwnShares = TOGETHER ? 1 : kWaves;  // of a workgroup
-    const int sub = TOGETHER ? 0 : __builtin_amdgcn_readfirstlane(wv);
-    int P = gridDim.x * kOwnShares;
-    int share = blockIdx.x * kOwnShares + sub;
+    const auto by_whole = [&](int wholes) { return kCut && 2LL * wholes * HC >= 3LL * P; };
     // A launch with little work and a long range in it: equal shares over all wavefronts would
     // cut that range into hundreds of pieces of a chunk each, and the merge of one range is a
     // chain of dependent loads (a 40 000-token request among 70 short ones, 2 heads: 10 us of
@@ -287,52 +263,174 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
     // empty.  TOGETHER: a chunk per wave at least (half of that: 10.6 -> 11.6 us on 3 000 tokens of 8 kv heads, twice: 9.6 ->
     // 11.7 on 8 plain ones), and the rest as for a range a quarter as long (one range of 20 000 tokens 13.3 us, 16.2
     // with a chunk per wave; 40 000: 16.0 and 21.2; twice the length costs 19.4 there).
-    const int span = longest >> log2_whole;
-    const int log2_share_chunks = (TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
-                                            : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0) + log2_whole;
-    const long long wanted = (total + (1 << log2_share_chunks) - 1) >> log2_share_chunks;
-    // A launch with less work than that for every share is bound by latency, and a share that straddles
-    // two ranges is two chains of dependent loads (3.5 us each) behind each other: its shares are pieces
-    // of one range each, if there are enough of them.  Both launches, straddling -> pieces: 4 layers of 8
-    // requests of 20 to 159 tokens, 16 heads of 256, append included, 72 -> 57 us; 4 requests of 20 to 40
-    // tokens, 32 / 8 heads, 9.2 -> 7.8.
-    long long x_begin = -1, x_end = 0;
-    int last_share = 0;                               // of the range that x_begin is in
-    if (wanted < P && B <= kThreads) {
-        int *pieces = prefix + B + 1;                 // before request r, of one head
-        const int n = (mine + (1 << log2_share_chunks) - 1) >> log2_share_chunks, n_to = wave_scan(n);
-        if (lane == 63) wave_total[0][wv] = n_to;
-        __syncthreads();
-        int before = n_to - n;
+    const auto least_share = [&](int span) {          // log2, in whole chunks
+        return TOGETHER ? (span >= 4096 ? 5 : span >= 2048 ? 4 : span >= 1024 ? 3 : 2)
+                        : span >= 1024 ? 3 : span >= 512 ? 2 : span >= 256 ? 1 : 0;
+    };
+    // A piece may have so many chunks more than an even cut, less than what a share that straddles two ranges loses: a chunk
+    // of a wave, but none where that is 32 tokens (32 requests of 100 to 900 tokens, 32 plain heads of 128: 37.0 us
+    // without, 39.6 with one more; 60 of 20 to 9 000, 8 / 2 heads of 64: 18.8 us without, 14.5; 250 of 20 to 500, by workgroups,
+    // 17.0 with a quarter of a chunk, 12.3).
+    const auto piece_slack = [](bool whole_chunks) { return TOGETHER ? (whole_chunks ? 1 : kWaves) : (whole_chunks ? 0 : 1); };
+    const auto empty_share = [&](int which) {
+        if (lane == 0) a.share_info[which] = make_int4(0, 0, 0, kShareEmpty);
+    };
+    Sequence seq{prefix, &a, {0, 0, 0}};
+    int GT, T, least;                                 // tokens of a chunk; chunks per head / pass; least chunks of a share
+    // A share that straddles two ranges is two chains of dependent loads (2.3 to 3.5 us each) behind each other, and
+    // the launch ends with the last of them.  Where shares are a few chunks, they are pieces of one range each, if
+    // there are enough shares for the pieces of about the size of an even cut.  Both launches, straddling -> pieces (as for
+    // the last three, they were before only where a share had less than a chunk): 4 layers of 8 requests of 20 to 159 tokens,
+    // 16 heads of 256, append included, 72 -> 57 us; 24 fp32 requests of 17 to 2 500, 32 / 8 heads, 32.9 -> 30.2;
+    // 4 layers of 16 of 70 to 914, 40 heads, with the append 112.9 -> 106; 64 of 50 to 300, 32 / 8 heads, 19.7 -> 15.3.
+    int r = 0, hc = 0, last_share = -1;               // the first range's request, head / pass; its last share, if known
+    long long x = -1, x_end = 0;                      // this share's part of the sequence
+    // Batches of up to 64 * K requests, K consecutive ones per lane; every wave by itself, no barrier in front of the
+    // first byte.  False: the share is empty, and marked so.
+    const auto plan = [&](auto per_lane) {
+        constexpr int K = per_lane;
+        int n[K], parts = 0, wholes = 0, longest = 0;
+        int2 q[K];
 #pragma unroll
-        for (int ww = 0; ww < kWaves - 1; ++ww) before += ww < wv ? wave_total[0][ww] : 0;
-        if (tid < B) pieces[tid + 1] = before + n;
-        if (tid == 0) pieces[0] = 0;
-        __syncthreads();
-        const int all = __builtin_amdgcn_readfirstlane(pieces[B]);
-        if ((long long)all * HC <= P) {
-            if (share >= all * HC) {
-                if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
-                return;
-            }
-            const int head = share / all, at = share - head * all;
-            int lo = 0, hi = B;                       // the last request with pieces[r] <= at
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (pieces[mid] <= at) lo = mid; else hi = mid;
-            }
-            const int nr = prefix[lo + 1] - prefix[lo], np = pieces[lo + 1] - pieces[lo], k = at - pieces[lo];
-            const int each = (nr + np - 1) / np;
-            x_begin = (long long)head * T + prefix[lo] + k * each;
-            x_end = min(x_begin + each, (long long)head * T + prefix[lo + 1]);
-            last_share = share - k + np - 1;
+        for (int k = 0; k < K; ++k) {
+            q[k] = make_int2(0, 0);
+            if (K * lane + k < B) q[k] = request_of(a, K * lane + k);
         }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            n[k] = chunks_of(q[k].x, q[k].y, R::GT);
+            wholes += (n[k] + 1) >> 1;
+        }
+        const bool whole_chunks = kCut && by_whole(__builtin_amdgcn_readlane(wave_scan(wholes), 63));
+        const int log2_whole = kCut && !whole_chunks ? 1 : 0;
+        GT = whole_chunks ? R::CT : R::GT;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (whole_chunks) n[k] = (n[k] + 1) >> 1;
+            parts += n[k];
+            longest = max(longest, n[k]);
+        }
+        const int upto = wave_scan(parts);
+        longest = __builtin_amdgcn_readlane(wave_max_to(longest), 63);
+        T = __builtin_amdgcn_readlane(upto, 63);
+        if constexpr (K == 1) {
+            seq.mine = Request{upto - parts, parts, q[0].y};
+        } else {
+            int before = upto - parts;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                reinterpret_cast<int4 *>(prefix)[K * lane + k] = make_int4(before, n[k], q[k].y, 0);
+                before += n[k];
+            }
+        }
+        least = 1 << (least_share(longest >> log2_whole) + log2_whole);
+        // the smallest size that gives no more pieces than shares, if it is about that of an even cut
+        const long long even = (T * (long long)HC + P - 1) / P;
+        int size = max(least, (int)min(even, (long long)kPieceMost));
+        if (even <= kPieceMost && longest < split::kMostDividend / 2)
+            for (int more = piece_slack(whole_chunks); more >= 0; --more, ++size) {
+                int np[K], all_np = 0;
+#pragma unroll
+                for (int k = 0; k < K; ++k) all_np += np[k] = split::small_div(n[k] + size - 1, size);
+                const int np_to = wave_scan(all_np), all = __builtin_amdgcn_readlane(np_to, 63), N = all * HC;
+                if (N > P) continue;
+                // Pieces by position, a position's heads next to each other, an eighth of them to each XCD (workgroups
+                // are dealt to those in turn); share numbers go by head, for the second kernel.
+                int rank = share, idle = share;
+                if (a.share_gcd > 0) {
+                    const int xcd = blockIdx.x & 7, local = (blockIdx.x >> 3) * kOwnShares + sub, eighth = (N + 7) >> 3;
+                    const int mine = min(max(N - xcd * eighth, 0), eighth);
+                    rank = local < mine ? xcd * eighth + local : N;
+                    idle = N + xcd * (P >> 3) - min(N, xcd * eighth) + local - mine;
+                }
+                if (rank >= N) {
+                    empty_share(idle);
+                    return false;
+                }
+                int at = split::small_div(rank, HC);
+                hc = rank - at * HC;
+                share = hc * all + at;
+                // the request: the first whose pieces end behind `at`
+                const int l = __popcll(__ballot(np_to <= at));
+                at -= __builtin_amdgcn_readlane(np_to - all_np, l);
+                int of = __builtin_amdgcn_readlane(np[0], l), k = 0, base = __builtin_amdgcn_readlane(upto - parts, l);
+                int nr = __builtin_amdgcn_readlane(n[0], l);
+#pragma unroll
+                for (int j = 1; j < K; ++j)
+                    if (k == j - 1 && at >= of) {
+                        at -= of;
+                        base += nr;
+                        k = j;
+                        of = __builtin_amdgcn_readlane(np[j], l);
+                        nr = __builtin_amdgcn_readlane(n[j], l);
+                    }
+                r = K * l + k;
+                const int each = split::small_div(nr + of - 1, of);
+                x = (long long)hc * T + base + at * each;
+                x_end = (long long)hc * T + base + min((at + 1) * each, nr);
+                last_share = share - at + of - 1;
+                break;
+            }
+        return true;
+    };
+    if (B <= kLaneBatch) {
+        if (!plan(std::integral_constant<int, 1>{})) return;
+    } else if (B <= 4 * kLaneBatch) {
+        if (!plan(std::integral_constant<int, 4>{})) return;
+    } else {
+        const int per = (B + kThreads - 1) / kThreads;   // consecutive requests per thread
+        int parts = 0, wholes = 0, longest = 0;          // of this thread's requests, in GT and in CT tokens
+        for (int i = 0; i < per; ++i)
+            if (tid * per + i < B) {
+                const int2 q = request_of(a, tid * per + i);
+                const int n = chunks_of(q.x, q.y, R::GT);
+                parts += n;
+                if (kCut) wholes += (n + 1) >> 1;
+                longest = max(longest, n);
+            }
+        longest = wave_max_to(longest);
+        const int parts_to = wave_scan(parts), wholes_to = kCut ? wave_scan(wholes) : 0;   // inclusive, inside the wave
+        if (lane == 63) {
+            wave_total[0][wv] = parts_to;
+            wave_total[1][wv] = wholes_to;
+            wave_longest[wv] = longest;
+        }
+        __syncthreads();
+        int T_whole = 0;
+#pragma unroll
+        for (int ww = 0; ww < kWaves; ++ww) {
+            longest = max(longest, wave_longest[ww]);
+            T_whole += wave_total[1][ww];
+        }
+        const bool whole_chunks = by_whole(T_whole);
+        const int log2_whole = kCut && !whole_chunks ? 1 : 0;
+        GT = whole_chunks ? R::CT : R::GT;
+        if (whole_chunks) longest = (longest + 1) >> 1;
+        int run = (whole_chunks ? wholes_to - wholes : parts_to - parts);
+#pragma unroll
+        for (int ww = 0; ww < kWaves - 1; ++ww) run += ww < wv ? wave_total[whole_chunks][ww] : 0;
+        if (tid == 0) prefix[0] = 0;
+        for (int i = 0; i < per; ++i) {
+            const int q = tid * per + i;
+            if (q < B) {
+                const int2 x = request_of(a, q);
+                run += chunks_of(x.x, x.y, GT);
+                prefix[q + 1] = run;
+            }
+        }
+        __syncthreads();
+        // (values that are the same in every lane are told so: the compiler cannot see it
+        // through LDS and the shuffles, and would keep the range arithmetic in vector registers)
+        T = __builtin_amdgcn_readfirstlane(prefix[B]);
+        least = 1 << (__builtin_amdgcn_readfirstlane(least_share(longest >> log2_whole)) + log2_whole);
     }
-    if (x_begin < 0) {
+    const long long total = (long long)HC * T;
+    if (x < 0) {
+        const long long wanted = (total + least - 1) / least;
         if (wanted < P) {
             P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
             if (share >= P) {
-                if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
+                empty_share(share);
                 return;
             }
         } else if (a.share_gcd > 0) {
@@ -343,36 +441,37 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
             const unsigned turn = (unsigned)rank / (unsigned)a.share_gcd, tie = (unsigned)rank - turn * (unsigned)a.share_gcd;
             share = (int)(turn * (unsigned)a.share_inv % (unsigned)a.share_period + tie * (unsigned)a.share_period);   // < kMaxShares^2
         }
-        x_begin = share_begin(share, total, P);
+        x = share_begin(share, total, P);
         x_end = share_begin(share + 1, total, P);
-        last_share = -1;                              // worked out where it is needed
+        if (x >= x_end) {
+            empty_share(share);
+            return;
+        }
+        // request that holds position x of its head: the last r that begins at or before it
+        hc = __builtin_amdgcn_readfirstlane(fits32(total) ? (int)((unsigned)x / (unsigned)T) : (int)(x / T));
+        const int first_pos = (int)(x - (long long)hc * T);
+        if (B <= kLaneBatch) {
+            r = __popcll(__ballot(seq.mine.before + seq.mine.count <= first_pos));
+        } else {
+            int lo = 0, hi = B;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (prefix[B <= 4 * kLaneBatch ? 4 * mid : mid] <= first_pos) lo = mid; else hi = mid;
+            }
+            r = __builtin_amdgcn_readfirstlane(lo);
+        }
     }
     // What the merge kernel needs to know about this share: whether it is empty,
     // and the (request, head) range it starts but does not finish, if any (only
     // its last range can be one): request, head/pass, last share of the range,
     // and the slot this share's piece went to.
     int4 owned = make_int4(0, 0, 0, 0);
-    if (x_begin >= x_end) {
-        if (lane == 0) a.share_info[share] = make_int4(0, 0, 0, kShareEmpty);
-        return;
-    }
-
-    // request that holds position x_begin of its head: the last r with prefix[r] <= it
-    const int first_hc = fits32(total) ? (int)((unsigned)x_begin / (unsigned)T) : (int)(x_begin / T);
-    const int first_pos = (int)(x_begin - (long long)first_hc * T);
-    int lo = 0, hi = B;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= first_pos) lo = mid; else hi = mid;
-    }
-    int r = __builtin_amdgcn_readfirstlane(lo), hc = __builtin_amdgcn_readfirstlane(first_hc);
-    long long x = x_begin;
-    while (x < x_end) {
-        const int base = __builtin_amdgcn_readfirstlane(prefix[r]);
-        const int nr = __builtin_amdgcn_readfirstlane(prefix[r + 1]) - base;   // > 0 here
+    const bool wide = ((uintptr_t)a.out & 15) == 0;
+    Request at = seq[r];
+    for (const long long x_begin = x; x < x_end;) {
+        const int base = at.before, nr = at.count, C = at.ctx;   // nr > 0 here
         const int c0 = (int)(x - (long long)hc * T) - base;
         const int len = (int)min((long long)(nr - c0), x_end - x);
-        const int C = ctx_len(a, r);
         int g = hc, h0 = hc * GH;                     // (GH == G, or a pass over part of the group)
         if (passes > 1) g = hc / passes;
         const bool whole = (c0 == 0 && len == nr);
@@ -381,34 +480,40 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
         const size_t rh0 = (size_t)r * a.num_q_heads + h0;
         if constexpr (TOGETHER) {
             float *part = reinterpret_cast<float *>(prefix) + balanced_ints(B);
-            const int each = (len + kWaves - 1) / kWaves, from = min(len, each * __builtin_amdgcn_readfirstlane(wv));
-            float *mine = part + (size_t)__builtin_amdgcn_readfirstlane(wv) * GH * (D + 2);
+            const int each = (len + kWaves - 1) / kWaves, from = min(len, each * wv);
+            float *mine = part + (size_t)wv * GH * (D + 2);
             R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * GT, min(C, (c0 + min(len, from + each)) * GT),
-                   [&](int h, int d, float M, float L, float A) { store_partial(mine + h * (D + 2), D, d, M, L, A); });
+                   [&](int h, int d, float M, float L, const auto &A) { store_partial(mine + h * (D + 2), D, d, M, L, A); });
             __syncthreads();
-            for (int i = tid; i < GH * D; i += kThreads) {
+            for (int i = 2 * tid; i < GH * D; i += 2 * kThreads) {
                 const int h = i / D, d = i % D;
                 const float *x = part + h * (D + 2);
-                float M = kLowest, L = 0.0f, A = 0.0f;
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) M = fmaxf(M, x[w * GH * (D + 2) + D]);
+                float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
+                float2 ml[kWaves];
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) {
-                    const float f = fast_exp2(x[w * GH * (D + 2) + D] - M);
-                    L += x[w * GH * (D + 2) + D + 1] * f;
-                    A += x[w * GH * (D + 2) + d] * f;
+                    ml[w] = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + D);
+                    M = fmaxf(M, ml[w].x);
+                }
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) {
+                    const float f = fast_exp2(ml[w].x - M);
+                    const float2 o = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + d);
+                    L += ml[w].y * f;
+                    A[0] += o.x * f;
+                    A[1] += o.y * f;
                 }
                 if (whole)
-                    store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+                    store_out<R::kBF16>(a.out, (rh0 + h) * D + d, wide, L, A);
                 else
                     store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
             }
             __syncthreads();                          // before the next range's parts
         } else {
             R::run(a, r, (size_t)r, g, h0, GH, c0 * GT, min(C, (c0 + len) * GT),
-                   [&](int h, int d, float M, float L, float A) {
+                   [&](int h, int d, float M, float L, const auto &A) {
                        if (whole)
-                           store_out<R::kBF16>(a.out, (rh0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+                           store_out<R::kBF16>(a.out, (rh0 + h) * D + d, wide, L, A);
                        else
                            store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
                    });
@@ -417,13 +522,14 @@ __global__ __launch_bounds__(kThreads) void decode_balanced(const DecodeArgs a)
             owned = make_int4(r, hc, last_share >= 0 ? last_share : share_of(x + nr - 1, total, P),
                               kShareOwner | (x == x_begin ? 0 : kShareSlot1));
         x += len;
-        if (c0 + len == nr) {                         // request finished: next one with work,
+        if (c0 + len == nr && x < x_end) {            // request finished: next one with work,
             do {                                      // after the last one the next head's first
                 if (++r == B) {
                     r = 0;
                     ++hc;
                 }
-            } while (prefix[r + 1] == prefix[r]);
+                at = seq[r];
+            } while (at.count == 0);
         }
     }
     if (TOGETHER ? tid == 0 : lane == 0) a.share_info[share] = owned;

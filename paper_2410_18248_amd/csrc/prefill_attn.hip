@@ -54,8 +54,9 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
     const int g = hc / passes;
     const int h0 = g * G + (hc % passes) * GH;
     const size_t row0 = (size_t)n * a.num_q_heads + h0;
-    R::run(a, r, (size_t)n, g, h0, GH, 0, max(t_end, 0), [&](int h, int d, float M, float L, float A) {
-        store_out<R::kBF16>(a.out, (row0 + h) * D + d, L > 0.0f ? A / L : 0.0f);
+    const bool wide = ((uintptr_t)a.out & 15) == 0;
+    R::run(a, r, (size_t)n, g, h0, GH, 0, max(t_end, 0), [&](int h, int d, float, float L, const auto &A) {
+        store_out<R::kBF16>(a.out, (row0 + h) * D + d, wide, L, A);
     });
 }
 

@@ -40,6 +40,7 @@ __host__ __device__ inline float reciprocal(float x)
 #endif
 }
 
+constexpr int kMostDividend = 1 << 19;
 // a / b for 0 <= a < 2^19, 0 < b < 2^19: (a + 1/2) / b is at least 1 / 2 b away from a whole number, and
 // two roundings and a reciprocal one unit off move it by less.  (A general division is 30 instructions
 // in front of the first byte of every workgroup.)
