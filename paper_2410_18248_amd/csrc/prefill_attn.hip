@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
 // full_groups >= 0: a grid of (request, head) pairs x tiles, tiles being the most any request has.
 // All tiles of one pair run on one XCD (workgroups are dealt to the 8 XCDs round-robin in launch
 // order), so its K/V stream is fetched into one L2 and shared there; consecutive heads go to
-// different XCDs; the longest tiles of a pair start first.  That holds for the pairs that fill whole
+// different XCDs; the longest tiles of a pair, or of the pairs that go abreast (p.slots of them), start first.  That holds for the pairs that fill whole
 // groups of 8; the (pair, tile) items of the remaining 1..7 pairs are dealt round-robin over all
 // XCDs instead of leaving some of them empty.
 //
@@ -91,8 +91,15 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
         const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
         int pair, t;
         if (slot < full_groups * tiles) {
-            pair = xcd + 8 * (slot / tiles);
-            t = slot % tiles;
+            const int abreast = p.slots;
+            if (abreast <= 1) {
+                pair = xcd + 8 * (slot / tiles);
+                t = slot % tiles;
+            } else {
+                const int first = slot / (abreast * tiles) * abreast, n = min(abreast, full_groups - first);
+                t = (slot - first * tiles) / n;
+                pair = xcd + 8 * (slot - first * tiles - t * n + first);
+            }
             // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
             // second turn begins with a pair, its pairs start with their short tiles, so that a CU has
             // a long and a short one: 4 prompts of 512 on 16 heads of 256, append included, 41.2 -> 37.6
@@ -182,9 +189,27 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     // mistake: nothing is read or written for it
     return at.ctx >= at.n_new && at.ctx <= a.max_blocks * a.block_size;
 }
+// Pairs of an XCD (of the `groups` it has) whose tiles are dealt together, the longest of all of them first.  One pair after
+// the other, a launch ends with the long tiles of its last pairs while most of the chip has nothing left; all together,
+// their K / V streams no longer share an L2.  So they go together in even parts of up to 20 MB (head size 256, whose tiles of 64
+// columns read each byte twice as often: 10), as the table row bounds it; not where the chip holds the launch at once, nor under long contexts, whose tiles are about
+// equally long (30 requests of 20 to 100 new on 100 to 800 cached, 32 / 8 heads: 39.5 us, 46.1 abreast), nor where many
+// workgroups have no tile (6 fp32 prompts of 20 to 428 tokens: 14.5 us, 15.4: those that have one land on half of the CUs).
+// us, append included, one by one / in parts of 4 / 8 or 10 / all: 4 prompts of 1 000, 32 heads of 128 (16 pairs an XCD, 8 MB) 100.9 /
+// 84.6 / 80.7 / 79.0; 4 of 2 048, 40 heads (20 MB) 302 / 271 / 276 / 264; 4 of 4 096 (40 MB) 884 / 830 / 840 / 914; one (5 pairs)
+// 255 / 271 (the last one alone) / - / 214; 8 of 500 on 4 000 cached, 32 heads (72 MB) 343 / 340 / 344 / 396; 8 of 1 900, 8 heads of
+// 64, 76.0 / 71.3 / 60.9; 4 of 4 000, 16 heads of 256 (32 MB), 715 / 729 (in parts of 2: 714) / 758; 4 of 2 000 238 / 222 / 226.
+int pairs_abreast(const PrefillArgs &p, long long grid, long long most, int groups)
+{
+    const long long row = (long long)p.d.max_blocks * p.d.block_size;
+    if (grid <= 512 || groups < 2 || grid > most + most / 4 || 6LL * p.max_new_tokens < row) return 1;
+    const long long pair = row * p.d.head_dim * (p.d.bf16 ? 4 : 8), all = pair * groups;
+    const long long part = (p.d.head_dim >= 256 ? 10LL : 20LL) << 20, parts = min((all + part - 1) / part, (long long)groups);
+    return (int)((groups + parts - 1) / parts);
+}
 // The grid for it and what place() needs to know; 0: too large.  `spare`: workgroups without a tile that
 // cost less than finding one's place among the tiles there are.
-unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int *full_groups)
+unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int *full_groups)
 {
     const long long pairs = heads * p.d.batch, full = pairs / 8, rest = pairs % 8;
     long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
@@ -202,6 +227,7 @@ unsigned place_grid(const PrefillArgs &p, long long heads, long long tiles, int 
         grid = most;
         *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
     }
+    p.slots = *full_groups >= 0 ? pairs_abreast(p, grid, most, (int)full) : 1;
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
 }
 
@@ -278,7 +304,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 1) void prefill_tiles_f32(
 }
 
 template <int D>
-hipError_t launch_tiles_f32(const PrefillArgs &p, hipStream_t s)
+hipError_t launch_tiles_f32(PrefillArgs p, hipStream_t s)
 {
     const int GH = f32_tile_heads(p.d.num_q_heads / p.d.num_kv_heads), TW = 16 / GH;
     const long long tiles = (p.max_new_tokens + TW - 1) / TW;
@@ -935,7 +961,7 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
 }
 
 template <int D, bool TILED, int kCols = kMaxCols>
-hipError_t launch_mfma_prefill(const PrefillArgs &p, hipStream_t s)
+hipError_t launch_mfma_prefill(PrefillArgs p, hipStream_t s)
 {
     const int G = p.d.num_q_heads / p.d.num_kv_heads;
     // Split launches: tiles of 64 columns leave no wave without work when a request brings a few
