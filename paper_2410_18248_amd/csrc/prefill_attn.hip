@@ -444,8 +444,7 @@ __device__ __forceinline__ Run locate(const PrefillArgs &p, int tiles, int WT)
 // Memory of a split launch behind DecodeArgs::partials, per item: the unnormalised outputs of each
 // block of 16 columns as its wave holds them, [pair of registers][lane] -- whole lines, written and
 // read by 512 contiguous bytes per instruction (by column, in pieces of 8 bytes, the hand-over of a
-// tile took 25 us) --, the columns' (reference, sum), and the arrival count of the tile whose
-// first item it is.
+// tile took 25 us) --, the columns' (reference, sum), and a flag that they are there.
 constexpr size_t split_item_bytes(int D, int columns) { return (size_t)columns * (D + 2) * sizeof(float) + sizeof(uint64_t); }
 
 // The hand-over between the runs of a tile goes through memory that every XCD sees alike:
@@ -461,18 +460,46 @@ __device__ __forceinline__ float2 get_shared(const float *p)
     return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT));
 }
-// Reports one run of `total` at the tile's count; true for the last.  A count is (tag, reports so
-// far); the tag is the launch's own, so whatever the memory held before counts as none, and the last
-// report takes the tag away again (a graph replays its launches with the same tag).
-__device__ __forceinline__ bool report_run(uint64_t *count, uint64_t tag, int total)
+// Reports one run of a tile of `total` runs, whose words are `stride` apart from `first` on; true for the last.  By a whole wave.
+// The words count only with the launch's own tag, so whatever the memory held before is nothing, and are taken away by the
+// last run, for the launch may be replayed with the same tag.
+//
+// MANY: for tiles of 64 columns (contexts under wider ones are cut into few runs).  Up to four runs are counted in the first
+// word, (tag, reports so far), by compare-and-swap: each failure is another run's report.  More of them, that end together,
+// would take a round trip each (2 new tokens on 8 000 cached, 32 / 8 heads: 33.4 us, 24.4 with flags; 16 on 3 000 25.5 and 24.1; with
+// flags for all, a dozen responses 30.3, 29.6 so): there each run sets its own word, waits until that has arrived, and looks at
+// the others.  The last to arrive finds them all; of those that do at the same time the one that takes the first word away
+// is the one.
+template <bool MANY>
+__device__ __forceinline__ bool report_run(uint64_t *first, int stride, int mine, int total, uint64_t tag)
 {
-    uint64_t old = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (;;) {                                        // (each failure is another run's report: at most total)
-        const int n = (old >> 16) == tag ? (int)(old & 0xFFFF) + 1 : 1;
-        const uint64_t want = n == total ? 0 : (tag << 16) + (uint64_t)n;
-        if (__hip_atomic_compare_exchange_strong(count, &old, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return n == total;
+    const int lane = threadIdx.x & 63;
+    int last = 0;
+    if (!MANY || total <= 4) {
+        if (lane == 0) {
+            uint64_t old = 0;                         // (a guess, most often right for the first)
+            for (;;) {
+                const int n = (old >> 16) == tag ? (int)(old & 0xFFFF) + 1 : 1;
+                const uint64_t want = n == total ? 0 : (tag << 16) + (uint64_t)n;
+                if (__hip_atomic_compare_exchange_strong(first, &old, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                    last = n == total;
+                    break;
+                }
+            }
+        }
+    } else {
+        if (lane == 0) __hip_atomic_store(first + (size_t)mine * stride, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(vmcnt(0));
+        bool all = true;
+        for (int k = lane; k < total; k += 64)
+            all = all && __hip_atomic_load(first + (size_t)k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+        if (__all(all)) {
+            if (lane == 0) last = __hip_atomic_exchange(first, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+            for (int k = lane; k < total; k += 64)
+                if (k > 0) __hip_atomic_store(first + (size_t)k * stride, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
+    return __builtin_amdgcn_readfirstlane(last) != 0;
 }
 
 // The kernels of narrow tiles: more than two workgroups to a CU.
@@ -861,7 +888,7 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     if (SPLIT && n_runs > 1) {
         constexpr int kAll = kWaves * kCols;          // columns of an item
         float *out = a.partials, *stats = out + (size_t)p.slots * kAll * D;
-        uint64_t *count = reinterpret_cast<uint64_t *>(stats + (size_t)p.slots * kAll * 2);
+        uint64_t *flags = reinterpret_cast<uint64_t *>(stats + (size_t)p.slots * kAll * 2);
         if (wave_maxpos >= 0) {                       // uniform: the wave has columns
 #pragma unroll
             for (int b = 0; b < kColBlocks; ++b) {
@@ -875,53 +902,81 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
         __builtin_amdgcn_s_waitcnt(vmcnt(0));
         __syncthreads();                              // the workgroup's stores have arrived, and its LDS is free
         int *is_last = reinterpret_cast<int *>(lds);
-        if (tid == 0) *is_last = report_run(count + first_item, p.tag, n_runs);
+        if (wv == 0) {
+            const bool all = report_run<(kCols <= 16)>(flags + first_item, item_stride, (item - first_item) / item_stride, n_runs, p.tag);
+            if (lane == 0) *is_last = all;
+        }
         __syncthreads();
         if (!*is_last) return;
-        // the runs in order, whichever workgroup this is: bit-reproducible
-#pragma unroll
-        for (int b = 0; b < kColBlocks; ++b) {
-            if (wave_maxpos < 0) break;               // uniform: the wave has no columns
-            const size_t at0 = (size_t)first_item * (kAll / 16) + wv * kColBlocks + b, step = (size_t)item_stride * (kAll / 16);
-            constexpr int N = D >= 256 ? 2 : 4;       // runs whose loads are in flight together
+        // The runs in order, whichever workgroup this is: bit-reproducible.  The waves share the blocks of 16 columns that
+        // the tile has, by halves of their dims from head size 128 on, and ask for eight runs at a time: an API response's few tokens fill one or
+        // two blocks, and a wave alone on each took two trips of 50 KB and more at the rate one wave gets (12 requests with 6
+        // to 58 new tokens on 345 to 2 490 cached, 32 / 8 heads of 128, with the append: 30.3 us, 29.6 so; one of 300
+        // on 2 000 46.7 and 39.1).
+        int me = lane;
+        if constexpr (D >= 256) asm volatile("" : "+v"(me));   // (worked out here, not kept over the loop: it spills as it is)
+        const int j = me & 15, qd = me >> 4;
+        constexpr int PARTS = D >= 128 ? 2 : 1, HS = NS / PARTS, N = D >= 256 ? 2 : 8;   // slabs of a unit of work; runs whose loads are in flight together
+        const int blocks = (min(WT, n_new - tile * WT) + TW - 1) / TW * kColBlocks;
+#pragma unroll 1
+        for (int u = wv; u < PARTS * blocks; u += kWaves) {
+            const int block = u / PARTS, half = u % PARTS;
+            const size_t at0 = (size_t)first_item * (kAll / 16) + block, step = (size_t)item_stride * (kAll / 16);
             float M = kLowest, L = 0.0f;
-            f32x4 A[NS];
+            f32x4 A[HS];
 #pragma unroll
-            for (int s = 0; s < NS; ++s) A[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int s = 0; s < HS; ++s) A[s] = f32x4{0.f, 0.f, 0.f, 0.f};
             for (int k0 = 0; k0 < n_runs; k0 += N) {
-                float2 ml[N], x[N][2 * NS];
+                float2 ml[N], x[N][2 * HS];
 #pragma unroll
                 for (int k = 0; k < N; ++k) {
                     const size_t at = at0 + min(k0 + k, n_runs - 1) * step;
+                    if (k > 0 && k0 + k >= n_runs) {  // uniform
+                        ml[k] = make_float2(kLowest, 0.0f);
+#pragma unroll
+                        for (int s = 0; s < 2 * HS; ++s) x[k][s] = make_float2(0.0f, 0.0f);
+                        continue;
+                    }
                     ml[k] = get_shared(stats + (at * 16 + j) * 2);
 #pragma unroll
-                    for (int s = 0; s < 2 * NS; ++s) x[k][s] = get_shared(out + at * 16 * D + s * 128 + 2 * lane);
+                    for (int s = 0; s < 2 * HS; ++s) x[k][s] = get_shared(out + at * 16 * D + (half * 2 * HS + s) * 128 + 2 * me);
                 }
                 float Mn = M;
 #pragma unroll
-                for (int k = 0; k < N; ++k) Mn = fmaxf(Mn, ml[k].x);   // (the last run once more changes nothing)
+                for (int k = 0; k < N; ++k) Mn = fmaxf(Mn, ml[k].x);
                 const float f0 = fast_exp2(M - Mn);
                 M = Mn;
                 L *= f0;
 #pragma unroll
-                for (int s = 0; s < NS; ++s)
+                for (int s = 0; s < HS; ++s)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) A[s][e] *= f0;
 #pragma unroll
                 for (int k = 0; k < N; ++k) {
-                    const float f = k0 + k < n_runs ? fast_exp2(ml[k].x - M) : 0.0f;
+                    const float f = fast_exp2(ml[k].x - M);
                     L += ml[k].y * f;
 #pragma unroll
-                    for (int s = 0; s < 2 * NS; ++s) {
+                    for (int s = 0; s < 2 * HS; ++s) {
                         A[s >> 1][2 * (s & 1)] += x[k][s].x * f;
                         A[s >> 1][2 * (s & 1) + 1] += x[k][s].y * f;
                     }
                 }
             }
-            l[b][0] = L;
+            // column j of the block: as above, for the wave whose block it was
+            const int c = block % kColBlocks * 16 + j, t = c / G, tok = tile * WT + block / kColBlocks * TW + t;
+            if (c < TW * G && tok < n_new) {
+                const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+                uint16_t *dst = static_cast<uint16_t *>(a.out) + ((size_t)(first + tok) * a.num_q_heads + g * G + c - t * G) * D;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) o[b][s] = A[s];
+                for (int s = 0; s < HS; ++s) {
+                    uint2 w;
+                    w.x = pack_bf16(A[s][0] * inv, A[s][1] * inv);
+                    w.y = pack_bf16(A[s][2] * inv, A[s][3] * inv);
+                    *reinterpret_cast<uint2 *>(dst + 16 * (half * HS + s) + 4 * qd) = w;
+                }
+            }
         }
+        return;
     }
 #pragma unroll
     for (int b = 0; b < kColBlocks; ++b) {
