@@ -327,7 +327,7 @@ hipError_t launch_tiles_f32(PrefillArgs p, hipStream_t s)
 // 32 cached positions cost 2 D/32 + D/16 + 1 MFMAs (16x16x32) per 16 columns.
 //
 // One workgroup = one (request, kv head, tile of new tokens); its four waves each
-// own kCols = 32 columns (kCols / G tokens x G heads) as blocks of 16.  K and V
+// own kCols = 32 columns (16 in launches of few rounds, and at head_dim 256; kCols / G tokens x G heads) as blocks of 16.  K and V
 // are streamed 32 positions at a time through LDS: while stage s is consumed,
 // stage s + 1 arrives in the other of two LDS buffers, straight from the pools (loads
 // that write LDS directly: no registers, no LDS-write instructions), one barrier
