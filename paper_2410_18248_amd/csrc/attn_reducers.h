@@ -616,8 +616,8 @@ struct MfmaF32Tile {
 
         // As in MfmaReducer: chunk c + 1 is asked for before chunk c is consumed, the table entries of the
         // two behind it with it, and nothing on the way is conditional.  (With conditional loads each chunk
-        // waited for the loads of the next: one prompt of 1 000 tokens, 8 heads of 64, append included, 28.2 -> 24.8 us;
-        // 4 x 8 to 32 new on 1 000 to 3 000 cached 41.4 -> 31.0; 3 of 600 on 32 / 8 heads of 128 152.6 -> 130.3.)
+        // waited for the loads of the next: one prompt of 1 000 tokens, 8 heads of 64, append included, 28.2 -> 24.6 us;
+        // 4 x 8 to 32 new on 1 000 to 3 000 cached 41.4 -> 30.7; 3 of 600 on 32 / 8 heads of 128 152.6 -> 125, in the order of now.)
         auto entry = [&](int c) -> int { return table[(t_begin + min(c, n_chunks - 1) * CT * stride) >> a.log2_block_size]; };
         auto issue = [&](int c, int block, f32x4 (&kx)[NK], vvec (&vx)[4][NC]) {
             const int t = t_begin + c * CT * stride;
@@ -726,16 +726,20 @@ struct MfmaF32Tile {
             vvec va[4][NC], vb[4][NC];
             const int step = CT * stride;
             const bool even = (n_chunks & 1) == 0;
-            int ch = 0, e0 = entry(0), e1 = entry(1), e2 = entry(2);
+            int ch = 0, e1, e2;
             if (even) {                               // the last chunk is to be one that `ka` holds
+                const int e0 = entry(0);
+                e1 = entry(1);
                 issue(0, e0, kb, vb);
                 issue(1, e1, ka, va);
-                e1 = e2;
+                e1 = entry(2);
                 e2 = entry(3);
                 consume(t_begin, kb, vb, std::false_type{});
                 ch = 1;
             } else {
-                issue(0, e0, ka, va);
+                issue(0, entry(0), ka, va);
+                e1 = entry(1);
+                e2 = entry(2);
             }
             for (; ch + 1 < n_chunks; ch += 2) {
                 issue(ch + 1, e1, kb, vb);
