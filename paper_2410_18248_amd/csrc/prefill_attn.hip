@@ -488,8 +488,10 @@ __device__ __forceinline__ bool report_run(uint64_t *first, int stride, int mine
             }
         }
     } else {
-        if (lane == 0) __hip_atomic_store(first + (size_t)mine * stride, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __builtin_amdgcn_s_waitcnt(vmcnt(0));
+        if (lane == 0) {                              // (an exchange: what it returns has been where all XCDs look)
+            const uint64_t was = __hip_atomic_exchange(first + (size_t)mine * stride, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("" ::"v"((uint32_t)was) : "memory");
+        }
         bool all = true;
         for (int k = lane; k < total; k += 64)
             all = all && __hip_atomic_load(first + (size_t)k * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
