@@ -170,13 +170,29 @@ constexpr int kPieceMost = 64;           // chunks of a piece: where shares are 
 // Chunks a running request contributes per (kv head, pass): an empty context
 // still gets one (empty) chunk so that its zero row is written.
 __device__ __forceinline__ int chunks_of(int running, int C, int GT) { return running ? max(1, (C + GT - 1) / GT) : 0; }
-// Mask and length of a request, asked for together.
+// Masks and lengths of K requests from r on, asked for together and not one behind the other: no load is conditional, and
+// nothing is looked at before the last of them has been asked for.  Those past the batch do not run.  (Four round trips, one for
+// each request of a lane, and one: 256 requests of 16 to 80 tokens, 8 heads of 64, 13.9 and 13.3 us; 180 on 40 heads of 128 36.5 and 35.7.)
+template <int K>
+__device__ __forceinline__ void requests_of(const DecodeArgs &a, int r, int2 (&q)[K])
+{
+    int running[K], C[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = min(r + k, a.batch - 1);
+        running[k] = a.running[i];
+        C[k] = a.ctx_lens[i];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(running[k]), "+v"(C[k]));
+#pragma unroll
+    for (int k = 0; k < K; ++k) q[k] = make_int2(r + k < a.batch ? running[k] : 0, min(C[k], a.max_blocks * a.block_size));
+}
 __device__ __forceinline__ int2 request_of(const DecodeArgs &a, int r)
 {
-    const int running = a.running[r];
-    int C = a.ctx_lens[r];
-    asm volatile("" : "+v"(C));                       // (not one after the other)
-    return make_int2(running, min(C, a.max_blocks * a.block_size));
+    int2 q[1];
+    requests_of(a, r, q);
+    return q[0];
 }
 
 // The flat chunk sequence of a launch as a wave holds it: the chunks before each request and of it, per head / pass, and
@@ -291,11 +307,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         constexpr int K = per_lane;
         int n[K], parts = 0, wholes = 0, longest = 0;
         int2 q[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            q[k] = make_int2(0, 0);
-            if (K * lane + k < B) q[k] = request_of(a, K * lane + k);
-        }
+        requests_of(a, K * lane, q);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             n[k] = chunks_of(q[k].x, q[k].y, R::GT);

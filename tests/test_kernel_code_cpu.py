@@ -1,0 +1,54 @@
+"""What the compiler made of the kernels, from the instructions of the built library, for what neither a result nor the
+metadata shows: which loads are in flight together."""
+import os
+import re
+import subprocess
+import tempfile
+
+import pytest
+
+import paper_2410_18248_amd as P
+from paper_2410_18248_amd import build
+from test_kernel_resources_cpu import _code_objects, _metadata
+
+OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "llvm", "bin", "llvm-objdump")
+
+
+@pytest.fixture(scope="module")
+def balanced():
+    """name -> instructions of the kernels of balanced decode launches"""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump beside hipcc")
+    out = {}
+    for co in _code_objects(open(P.lib_path(), "rb").read()):
+        if not any("decode_balanced" in k[".name"] for k in _metadata(co)):
+            continue
+        with tempfile.NamedTemporaryFile(suffix=".o") as f:
+            f.write(co)
+            f.flush()
+            text = subprocess.check_output([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", f.name], text=True)
+        name = None
+        for line in text.split("\n"):
+            m = re.match(r".*<(\S+)>:", line)
+            if m:
+                name = m.group(1)
+                out[name] = []
+            elif name and line.strip():
+                out[name].append(line.split("//")[0].strip())
+    out = {n: x for n, x in out.items() if "decode_balanced" in n and "merge" not in n}
+    assert len(out) == 30
+    return out
+
+
+def test_requests_of_a_lane_are_asked_for_together(balanced):
+    """Batches of 65 to 256 are planned by waves that hold four requests per lane: eight loads, masks (bytes) and
+    lengths, and one wait."""
+    for name, code in balanced.items():
+        runs, n = [], 0
+        for x in code:
+            if x.startswith("global_load_ubyte"):
+                n += 1
+            elif x.startswith("s_waitcnt") and "vmcnt" in x:
+                runs.append(n)
+                n = 0
+        assert max(runs) >= 4, (name, sorted(runs)[-3:])
