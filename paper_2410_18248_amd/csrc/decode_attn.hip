@@ -169,7 +169,7 @@ constexpr int kPieceMost = 64;           // chunks of a piece: where shares are 
 
 // Chunks a running request contributes per (kv head, pass): an empty context
 // still gets one (empty) chunk so that its zero row is written.
-__device__ __forceinline__ int chunks_of(int running, int C, int GT) { return running ? max(1, (C + GT - 1) / GT) : 0; }
+__device__ __forceinline__ int chunks_of(int running, int C, int GT) { return running ? max(1, (C + GT - 1) >> __builtin_ctz(GT)) : 0; }
 // Masks and lengths of K requests from r on, asked for together and not one behind the other: no load is conditional, and
 // nothing is looked at before the last of them has been asked for.  Those past the batch do not run.  (Four round trips, one for
 // each request of a lane, and one: 256 requests of 16 to 80 tokens, 8 heads of 64, 13.9 and 13.3 us; 180 on 40 heads of 128 36.5 and 35.7.)
@@ -211,8 +211,9 @@ struct Sequence {
             return Request{__builtin_amdgcn_readlane(mine.before, r), __builtin_amdgcn_readlane(mine.count, r),
                            __builtin_amdgcn_readlane(mine.ctx, r)};
         if (a->batch <= 4 * kLaneBatch) {
-            const int4 x = reinterpret_cast<const int4 *>(prefix)[r];
-            return Request{__builtin_amdgcn_readfirstlane(x.x), __builtin_amdgcn_readfirstlane(x.y), __builtin_amdgcn_readfirstlane(x.z)};
+            const int2 x = reinterpret_cast<const int2 *>(prefix)[r];
+            const int before = __builtin_amdgcn_readfirstlane(x.x);
+            return Request{before, __builtin_amdgcn_readfirstlane(prefix[2 * r + 2]) - before, __builtin_amdgcn_readfirstlane(x.y)};
         }
         const int before = __builtin_amdgcn_readfirstlane(prefix[r]);
         return Request{before, __builtin_amdgcn_readfirstlane(prefix[r + 1]) - before, ctx_len(*a, r)};
@@ -221,11 +222,11 @@ struct Sequence {
 // Ints of it in a launch's dynamic LDS.
 __host__ __device__ __forceinline__ int balanced_ints(int batch)
 {
-    return batch <= kLaneBatch ? 0 : batch <= 4 * kLaneBatch ? 16 * kLaneBatch : (batch + 1 + 3) & ~3;
+    return batch <= kLaneBatch ? 0 : batch <= 4 * kLaneBatch ? 8 * kLaneBatch + 4 : (batch + 1 + 3) & ~3;
 }
 
 // gridDim.x * 4 wavefronts, each an equal contiguous share of the flat chunk
-// sequence ordered (kv head / pass, request, chunk).  Every wave (of batches above 64: every workgroup, through the
+// sequence ordered (kv head / pass, request, chunk).  Every wave (of batches above 256: every workgroup, through the
 // prefix in dynamic LDS) works the sequence out for itself from ctx_lens / running (loads that hit
 // in L2), which costs less than a dependent launch.
 //
@@ -238,7 +239,7 @@ __host__ __device__ __forceinline__ int balanced_ints(int batch)
 // 100 GB and more this is worth several per cent; with small pools it is neutral.
 //
 // Small launches are bound by the way to the first K / V byte: mask and lengths are asked for
-// together, scans are DPP adds, nothing waits at a barrier, divisions are by reciprocal or 32 bits wide, lengths
+// together, scans are DPP adds, nothing waits at a barrier, divisions are by reciprocal or 32 bits wide (beyond 2^31 chunks 64), lengths
 // come out of registers or LDS, and the cut is by half-chunks, so that no wave has twice another's work.  One
 // request of 1 999 tokens, both launches: 13.2 -> 10.3 us with half of that, 9.85 -> 9.05 with the rest.
 //
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         if (lane == 0) a.share_info[which] = make_int4(0, 0, 0, kShareEmpty);
     };
     Sequence seq{prefix, &a, {0, 0, 0}};
-    int GT, T, least;                                 // tokens of a chunk; chunks per head / pass; least chunks of a share
+    int GT, T, log2_least;                            // tokens of a chunk; chunks per head / pass; least chunks of a share
     // A share that straddles two ranges is two chains of dependent loads (2.3 to 3.5 us each) behind each other, and
     // the launch ends with the last of them.  Where shares are a few chunks, they are pieces of one range each, if
     // there are enough shares for the pieces of about the size of an even cut.  Both launches, straddling -> pieces (as for
@@ -302,7 +303,12 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
     int r = 0, hc = 0, last_share = -1;               // the first range's request, head / pass; its last share, if known
     long long x = -1, x_end = 0;                      // this share's part of the sequence
     // Batches of up to 64 * K requests, K consecutive ones per lane; every wave by itself, no barrier in front of the
-    // first byte.  False: the share is empty, and marked so.
+    // first byte.  False: the share is empty, and marked so.  All the waves of a SIMD issue it, four to six of them, so its
+    // length is time: where it ends in straddling shares all the same, it must not take longer than the barriers and the
+    // one request per thread of larger batches.  (So it did, with a 64-bit division, a scan for every size that might
+    // fit, entries of 16 bytes and a binary search through them.  By barriers / so / as it is, us: 250 requests of 100 to 1 500
+    // tokens on 8 heads of 64 52.9 / 54.4 / 52.4; 150 of 16 to 80 on 32 heads of 128 27.3 / 27.9 / 26.7; 100 of 50 to 400 on 16 of 256
+    // 59.1 / 59.4 / 58.4; 250 fp32 ones of 100 to 1 500 on 8 heads of 32 51.0 / 51.9 / 51.1.)
     const auto plan = [&](auto per_lane) {
         constexpr int K = per_lane;
         int n[K], parts = 0, wholes = 0, longest = 0;
@@ -311,78 +317,106 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             n[k] = chunks_of(q[k].x, q[k].y, R::GT);
-            wholes += (n[k] + 1) >> 1;
-        }
-        const bool whole_chunks = kCut && by_whole(__builtin_amdgcn_readlane(wave_scan(wholes), 63));
-        const int log2_whole = kCut && !whole_chunks ? 1 : 0;
-        GT = whole_chunks ? R::CT : R::GT;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (whole_chunks) n[k] = (n[k] + 1) >> 1;
             parts += n[k];
+            wholes += (n[k] + 1) >> 1;
             longest = max(longest, n[k]);
         }
-        const int upto = wave_scan(parts);
+        int upto = wave_scan(parts);
+        const int upto_whole = kCut ? wave_scan(wholes) : 0;
         longest = __builtin_amdgcn_readlane(wave_max_to(longest), 63);
+        const bool whole_chunks = kCut && by_whole(__builtin_amdgcn_readlane(upto_whole, 63));
+        const int log2_whole = kCut && !whole_chunks ? 1 : 0;
+        GT = whole_chunks ? R::CT : R::GT;
+        if (whole_chunks) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) n[k] = (n[k] + 1) >> 1;
+            parts = wholes;
+            upto = upto_whole;
+            longest = (longest + 1) >> 1;
+        }
         T = __builtin_amdgcn_readlane(upto, 63);
-        if constexpr (K == 1) {
-            seq.mine = Request{upto - parts, parts, q[0].y};
-        } else {
+        seq.mine = Request{upto - parts, parts, q[0].y};
+        if constexpr (K > 1) {
             int before = upto - parts;
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                reinterpret_cast<int4 *>(prefix)[K * lane + k] = make_int4(before, n[k], q[k].y, 0);
-                before += n[k];
+            for (int k = 0; k < K; k += 2) {
+                reinterpret_cast<int4 *>(prefix)[(K * lane + k) / 2] = make_int4(before, q[k].y, before + n[k], q[k + 1].y);
+                before += n[k] + n[k + 1];
             }
+            if (lane == 63) prefix[8 * kLaneBatch] = T;
         }
-        least = 1 << (least_share(longest >> log2_whole) + log2_whole);
-        // the smallest size that gives no more pieces than shares, if it is about that of an even cut
-        const long long even = (T * (long long)HC + P - 1) / P;
-        int size = max(least, (int)min(even, (long long)kPieceMost));
-        if (even <= kPieceMost && longest < split::kMostDividend / 2)
-            for (int more = piece_slack(whole_chunks); more >= 0; --more, ++size) {
-                int np[K], all_np = 0;
+        log2_least = least_share(longest >> log2_whole) + log2_whole;
+        const long long chunks = (long long)T * HC;
+        if (chunks > (long long)kPieceMost * P || longest >= split::kMostDividend / 2) return true;
+        // The smallest size that gives no more pieces than shares, if it is about that of an even cut.  The lane's pieces of the
+        // first size, and from bit 16 on those of the last (together at most T / even + 256 of each): where not even those
+        // fit, the launch has lost one scan and no more.
+        const auto pieces = [&](int k, int size) { return split::small_div(n[k] + size - 1, size); };
+        int size = max(1 << log2_least, (int)((unsigned)(chunks + P - 1) / (unsigned)P));
+        const int most = size + piece_slack(whole_chunks);
+        int on = longest > most;
 #pragma unroll
-                for (int k = 0; k < K; ++k) all_np += np[k] = split::small_div(n[k] + size - 1, size);
-                const int np_to = wave_scan(all_np), all = __builtin_amdgcn_readlane(np_to, 63), N = all * HC;
-                if (N > P) continue;
-                // Pieces by position, a position's heads next to each other, an eighth of them to each XCD (workgroups
-                // are dealt to those in turn); share numbers go by head, for the second kernel.
-                int rank = share, idle = share;
-                if (a.share_gcd > 0) {
-                    const int xcd = blockIdx.x & 7, local = (blockIdx.x >> 3) * kOwnShares + sub, eighth = (N + 7) >> 3;
-                    const int mine = min(max(N - xcd * eighth, 0), eighth);
-                    rank = local < mine ? xcd * eighth + local : N;
-                    idle = N + xcd * (P >> 3) - min(N, xcd * eighth) + local - mine;
-                }
-                if (rank >= N) {
-                    empty_share(idle);
-                    return false;
-                }
-                int at = split::small_div(rank, HC);
-                hc = rank - at * HC;
-                share = hc * all + at;
-                // the request: the first whose pieces end behind `at`
-                const int l = __popcll(__ballot(np_to <= at));
-                at -= __builtin_amdgcn_readlane(np_to - all_np, l);
-                int of = __builtin_amdgcn_readlane(np[0], l), k = 0, base = __builtin_amdgcn_readlane(upto - parts, l);
-                int nr = __builtin_amdgcn_readlane(n[0], l);
+        for (int k = 0; k < K; ++k) on += __popcll(__ballot(n[k] > 0));
+        if (on * HC > P) return true;                 // a piece per request that runs, and one more, do not fit
+        int both = 0;
 #pragma unroll
-                for (int j = 1; j < K; ++j)
-                    if (k == j - 1 && at >= of) {
-                        at -= of;
-                        base += nr;
-                        k = j;
-                        of = __builtin_amdgcn_readlane(np[j], l);
-                        nr = __builtin_amdgcn_readlane(n[j], l);
-                    }
-                r = K * l + k;
-                const int each = split::small_div(nr + of - 1, of);
-                x = (long long)hc * T + base + at * each;
-                x_end = (long long)hc * T + base + min((at + 1) * each, nr);
-                last_share = share - at + of - 1;
-                break;
+        for (int k = 0; k < K; ++k) both += pieces(k, most) << 16;
+        if (most > size) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) both += pieces(k, size);
+        } else {
+            both |= (unsigned)both >> 16;
+        }
+        const int both_to = wave_scan(both), both_all = __builtin_amdgcn_readlane(both_to, 63);
+        if ((both_all >> 16) * HC > P) return true;
+        int own = both & 0xFFFF, upto_own = both_to & 0xFFFF, all = both_all & 0xFFFF;
+        while (all * HC > P) {                        // (`most` is the last)
+            ++size;
+            own = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) own += pieces(k, size);
+            upto_own = wave_scan(own);
+            all = __builtin_amdgcn_readlane(upto_own, 63);
+        }
+        int np[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) np[k] = pieces(k, size);
+        const int N = all * HC;
+        // Pieces by position, a position's heads next to each other, an eighth of them to each XCD (workgroups
+        // are dealt to those in turn); share numbers go by head, for the second kernel.
+        int rank = share, idle = share;
+        if (a.share_gcd > 0) {
+            const int xcd = blockIdx.x & 7, local = (blockIdx.x >> 3) * kOwnShares + sub, eighth = (N + 7) >> 3;
+            const int mine = min(max(N - xcd * eighth, 0), eighth);
+            rank = local < mine ? xcd * eighth + local : N;
+            idle = N + xcd * (P >> 3) - min(N, xcd * eighth) + local - mine;
+        }
+        if (rank >= N) {
+            empty_share(idle);
+            return false;
+        }
+        int at = split::small_div(rank, HC);
+        hc = rank - at * HC;
+        share = hc * all + at;
+        // the request: the first whose pieces end behind `at`
+        const int l = __popcll(__ballot(upto_own <= at));
+        at -= __builtin_amdgcn_readlane(upto_own - own, l);
+        int of = __builtin_amdgcn_readlane(np[0], l), k = 0, base = __builtin_amdgcn_readlane(upto - parts, l);
+        int nr = __builtin_amdgcn_readlane(n[0], l);
+#pragma unroll
+        for (int j = 1; j < K; ++j)
+            if (k == j - 1 && at >= of) {
+                at -= of;
+                base += nr;
+                k = j;
+                of = __builtin_amdgcn_readlane(np[j], l);
+                nr = __builtin_amdgcn_readlane(n[j], l);
             }
+        r = K * l + k;
+        const int each = split::small_div(nr + of - 1, of);
+        x = (long long)hc * T + base + at * each;
+        x_end = (long long)hc * T + base + min((at + 1) * each, nr);
+        last_share = share - at + of - 1;
         return true;
     };
     if (B <= kLaneBatch) {
@@ -434,11 +468,11 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         // (values that are the same in every lane are told so: the compiler cannot see it
         // through LDS and the shuffles, and would keep the range arithmetic in vector registers)
         T = __builtin_amdgcn_readfirstlane(prefix[B]);
-        least = 1 << (__builtin_amdgcn_readfirstlane(least_share(longest >> log2_whole)) + log2_whole);
+        log2_least = __builtin_amdgcn_readfirstlane(least_share(longest >> log2_whole)) + log2_whole;
     }
     const long long total = (long long)HC * T;
     if (x < 0) {
-        const long long wanted = (total + least - 1) / least;
+        const long long wanted = (total + (1 << log2_least) - 1) >> log2_least;
         if (wanted < P) {
             P = __builtin_amdgcn_readfirstlane(max(1, (int)wanted));
             if (share >= P) {
@@ -462,13 +496,17 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         // request that holds position x of its head: the last r that begins at or before it
         hc = __builtin_amdgcn_readfirstlane(fits32(total) ? (int)((unsigned)x / (unsigned)T) : (int)(x / T));
         const int first_pos = (int)(x - (long long)hc * T);
-        if (B <= kLaneBatch) {
+        if (B <= 4 * kLaneBatch) {
             r = __popcll(__ballot(seq.mine.before + seq.mine.count <= first_pos));
+            if (B > kLaneBatch) {                     // of four
+                const int *of = prefix + 8 * r;
+                r = 4 * r + __builtin_amdgcn_readfirstlane((of[2] <= first_pos) + (of[4] <= first_pos) + (of[6] <= first_pos));
+            }
         } else {
             int lo = 0, hi = B;
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
-                if (prefix[B <= 4 * kLaneBatch ? 4 * mid : mid] <= first_pos) lo = mid; else hi = mid;
+                if (prefix[mid] <= first_pos) lo = mid; else hi = mid;
             }
             r = __builtin_amdgcn_readfirstlane(lo);
         }

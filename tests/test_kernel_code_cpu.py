@@ -52,3 +52,10 @@ def test_requests_of_a_lane_are_asked_for_together(balanced):
                 runs.append(n)
                 n = 0
         assert max(runs) >= 4, (name, sorted(runs)[-3:])
+
+
+def test_the_plan_divides_by_32_bits(balanced):
+    """General 64-bit divisions (2^64 as a float is a constant of each) are 120 instructions in front of the first byte:
+    only the four for sequences of 2^31 chunks and more (two ends of a share, its range, and a range's last share)."""
+    for name, code in balanced.items():
+        assert sum("0x5f7ffffc" in x for x in code) <= 4, name
