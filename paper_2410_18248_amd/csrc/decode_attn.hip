@@ -195,21 +195,20 @@ __device__ __forceinline__ int2 request_of(const DecodeArgs &a, int r)
     return q[0];
 }
 
-// The flat chunk sequence of a launch as a wave holds it: the chunks before each request and of it, per head / pass, and
-// its length.  Batches of up to 64: a request per lane.  Up to 256: four per lane, which write them to LDS (every wave
-// the same, so no wave waits for another).  Larger ones: their prefix in LDS, by all waves of a workgroup.
+// The flat chunk sequence of a launch in LDS: the chunks before each request, per head / pass, and its length.  Batches of up
+// to 256: pairs of the two, and the chunks of all behind them, written by every wave (each the same, so no wave waits for
+// another).  Not kept in registers, one request per lane, for batches of up to 64: two registers through the loop took a
+// workgroup off a CU with fp32 heads of 32 (250 requests of 100 to 1 500 tokens on 8 / 2 of them, by workgroups: 26.5 us with four,
+// 21.7 with five).  Larger batches: the prefix alone, by all waves of a workgroup.
 struct Request {
     int before, count, ctx;
 };
 struct Sequence {
     const int *prefix;                                // LDS
     const DecodeArgs *a;
-    Request mine;                                     // of request `lane`
+    int upto;                                         // chunks up to and of the lane's requests
     __device__ __forceinline__ Request operator[](int r) const
     {
-        if (a->batch <= kLaneBatch)
-            return Request{__builtin_amdgcn_readlane(mine.before, r), __builtin_amdgcn_readlane(mine.count, r),
-                           __builtin_amdgcn_readlane(mine.ctx, r)};
         if (a->batch <= 4 * kLaneBatch) {
             const int2 x = reinterpret_cast<const int2 *>(prefix)[r];
             const int before = __builtin_amdgcn_readfirstlane(x.x);
@@ -222,7 +221,7 @@ struct Sequence {
 // Ints of it in a launch's dynamic LDS.
 __host__ __device__ __forceinline__ int balanced_ints(int batch)
 {
-    return batch <= kLaneBatch ? 0 : batch <= 4 * kLaneBatch ? 8 * kLaneBatch + 4 : (batch + 1 + 3) & ~3;
+    return batch <= 4 * kLaneBatch ? (batch <= kLaneBatch ? 2 : 8) * kLaneBatch + 4 : (batch + 1 + 3) & ~3;
 }
 
 // gridDim.x * 4 wavefronts, each an equal contiguous share of the flat chunk
@@ -240,7 +239,7 @@ __host__ __device__ __forceinline__ int balanced_ints(int batch)
 //
 // Small launches are bound by the way to the first K / V byte: mask and lengths are asked for
 // together, scans are DPP adds, nothing waits at a barrier, divisions are by reciprocal or 32 bits wide (beyond 2^31 chunks 64), lengths
-// come out of registers or LDS, and the cut is by half-chunks, so that no wave has twice another's work.  One
+// come out of LDS, and the cut is by half-chunks, so that no wave has twice another's work.  One
 // request of 1 999 tokens, both launches: 13.2 -> 10.3 us with half of that, 9.85 -> 9.05 with the rest.
 //
 // TOGETHER: a share belongs to a workgroup, whose four waves take a quarter of each of its ranges
@@ -292,7 +291,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
     const auto empty_share = [&](int which) {
         if (lane == 0) a.share_info[which] = make_int4(0, 0, 0, kShareEmpty);
     };
-    Sequence seq{prefix, &a, {0, 0, 0}};
+    Sequence seq{prefix, &a, 0};
     int GT, T, log2_least;                            // tokens of a chunk; chunks per head / pass; least chunks of a share
     // A share that straddles two ranges is two chains of dependent loads (2.3 to 3.5 us each) behind each other, and
     // the launch ends with the last of them.  Where shares are a few chunks, they are pieces of one range each, if
@@ -335,16 +334,18 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
             longest = (longest + 1) >> 1;
         }
         T = __builtin_amdgcn_readlane(upto, 63);
-        seq.mine = Request{upto - parts, parts, q[0].y};
-        if constexpr (K > 1) {
-            int before = upto - parts;
+        seq.upto = upto;
+        int before = upto - parts;
+        if constexpr (K == 1) {
+            reinterpret_cast<int2 *>(prefix)[lane] = make_int2(before, q[0].y);
+        } else {
 #pragma unroll
             for (int k = 0; k < K; k += 2) {
                 reinterpret_cast<int4 *>(prefix)[(K * lane + k) / 2] = make_int4(before, q[k].y, before + n[k], q[k + 1].y);
                 before += n[k] + n[k + 1];
             }
-            if (lane == 63) prefix[8 * kLaneBatch] = T;
         }
+        if (lane == 63) prefix[2 * K * kLaneBatch] = T;
         log2_least = least_share(longest >> log2_whole) + log2_whole;
         const long long chunks = (long long)T * HC;
         if (chunks > (long long)kPieceMost * P || longest >= split::kMostDividend / 2) return true;
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         hc = __builtin_amdgcn_readfirstlane(fits32(total) ? (int)((unsigned)x / (unsigned)T) : (int)(x / T));
         const int first_pos = (int)(x - (long long)hc * T);
         if (B <= 4 * kLaneBatch) {
-            r = __popcll(__ballot(seq.mine.before + seq.mine.count <= first_pos));
+            r = __popcll(__ballot(seq.upto <= first_pos));
             if (B > kLaneBatch) {                     // of four
                 const int *of = prefix + 8 * r;
                 r = 4 * r + __builtin_amdgcn_readfirstlane((of[2] <= first_pos) + (of[4] <= first_pos) + (of[6] <= first_pos));

@@ -81,3 +81,17 @@ def test_prefill_workgroups_per_cu(kernels):
     for name, k in kernels.items():
         if "prefill_tiles_f32" in name:
             assert _workgroups(k) >= 2, name
+
+
+def test_decode_workgroups_per_cu(kernels):
+    """A launch is as wide as the chip holds of it: what the loops of the plain-layout reducers need, and no less for the
+    plan in front of them."""
+    least = {"Lb1ELi8ELi1ELi2EEELb0": 6, "Lb1ELi8ELi1ELi2EEELb1": 5, "Lb0ELi8ELi1ELi2EEELb0": 7, "Lb0ELi8ELi1ELi2EEELb1": 6,
+             "Lb0ELi8ELi2ELi2EEELb0": 5, "Lb0ELi8ELi2ELi2EEELb1": 5, "Lb0ELi8ELi4ELi1EEELb0": 5, "Lb0ELi8ELi4ELi1EEELb1": 5}
+    seen = 0
+    for name, k in kernels.items():
+        m = re.search(r"decode_balanced.*ValuReducerI(\w+?)EEEvNS", name)
+        if m:
+            assert _workgroups(k) >= least.get(m.group(1), 4), (name, k[".vgpr_count"])
+            seen += m.group(1) in least
+    assert seen == len(least)
