@@ -165,7 +165,7 @@ __device__ __forceinline__ int share_of(long long x, long long total, int P)
 }
 
 constexpr int kLaneBatch = 64;           // requests of a batch that a wave holds one per lane
-constexpr int kPieceMost = 64;           // chunks of a piece: where shares are longer, they straddle ranges
+constexpr int kPieceMost = 64;           // chunks of a piece
 
 // Chunks a running request contributes per (kv head, pass): an empty context
 // still gets one (empty) chunk so that its zero row is written.
@@ -288,6 +288,11 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
     // without, 39.6 with one more; 60 of 20 to 9 000, 8 / 2 heads of 64: 18.8 us without, 14.5; 250 of 20 to 500, by workgroups,
     // 17.0 with a quarter of a chunk, 12.3).
     const auto piece_slack = [](bool whole_chunks) { return TOGETHER ? (whole_chunks ? 1 : kWaves) : (whole_chunks ? 0 : 1); };
+    // Chunks of a piece at most: where shares are longer, they straddle ranges.  By waves and 32 tokens at a time the chip is
+    // bound by memory before that, and a piece longer than an even cut is what the launch ends with (straddling / pieces, us: 167 fp32
+    // requests of 596 to 775, 8 heads of 32, 4.1 chunks a share, pieces of 5, 45.3 / 46.9; 108 of 691 to 899 on 8 of 64, 5.3 and 6,
+    // 61.6 / 62.9; 18 of 1 010 to 1 313 on 32 of 128, 5.3 and 6, 62.7 / 62.3; 61 of 96 to 387 on 16 of 256, 3.5 and 4, 46.8 / 46.2).
+    const auto piece_most = [](bool whole_chunks) { return !TOGETHER && whole_chunks ? 4 : kPieceMost; };
     const auto empty_share = [&](int which) {
         if (lane == 0) a.share_info[which] = make_int4(0, 0, 0, kShareEmpty);
     };
@@ -348,7 +353,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
         if (lane == 63) prefix[2 * K * kLaneBatch] = T;
         log2_least = least_share(longest >> log2_whole) + log2_whole;
         const long long chunks = (long long)T * HC;
-        if (chunks > (long long)kPieceMost * P || longest >= split::kMostDividend / 2) return true;
+        if (chunks > (long long)piece_most(whole_chunks) * P || longest >= split::kMostDividend / 2) return true;
         // The smallest size that gives no more pieces than shares, if it is about that of an even cut.  The lane's pieces of the
         // first size, and from bit 16 on those of the last (together at most T / even + 256 of each): where not even those
         // fit, the launch has lost one scan and no more.

@@ -55,3 +55,9 @@ def test_sizes_of_pieces(n):
 @pytest.mark.parametrize("B", [3, 150])
 def test_out_at_any_element(H, Hkv, D, dtype, B):
     _check(H, Hkv, D, dtype, [5 + 3 * r for r in range(B)], [1] * B, shift=1)
+
+
+@pytest.mark.parametrize("n", [31, 34])
+def test_by_waves_in_whole_chunks(n):
+    """Shares of up to four chunks of 32 tokens, which are pieces, and of more, which straddle."""
+    _check(24, 24, 64, "bf16", [16 * n - r % 7 for r in range(64)], [1] * 64)
