@@ -10,6 +10,7 @@
 
 #include "attn_reducers.h"
 #include "internal.h"
+#include "prefill_rules.h"
 #include "prefill_split.h"
 #include "requests.h"
 
@@ -96,9 +97,9 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
                 pair = xcd + 8 * (slot / tiles);
                 t = slot % tiles;
             } else {
-                const int first = slot / (abreast * tiles) * abreast, n = min(abreast, full_groups - first);
-                t = (slot - first * tiles) / n;
-                pair = xcd + 8 * (slot - first * tiles - t * n + first);
+                const rules::Turn at = rules::abreast_at(slot, tiles, full_groups, abreast);
+                t = at.t;
+                pair = xcd + 8 * at.pair;
             }
             // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
             // second turn begins with a pair, its pairs start with their short tiles, so that a CU has

@@ -1,0 +1,63 @@
+"""In which order the tiles of a prefill launch start (csrc/prefill_rules.h, compiled here for the host)."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = """
+#include "prefill_rules.h"
+using namespace lamps;
+extern "C" {
+void c_turn(int slot, int tiles, int pairs, int abreast, int *out)
+{
+    const rules::Turn at = rules::abreast_at(slot, tiles, pairs, abreast);
+    out[0] = at.pair; out[1] = at.t;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    so = str(d / "rules.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2410_18248_amd", "csrc"),
+                           str(d / "rules.cpp"), "-o", so])
+    return ctypes.CDLL(so)
+
+
+def _turns(lib, tiles, pairs, abreast):
+    out = (ctypes.c_int * 2)()
+    for slot in range(tiles * pairs):
+        lib.c_turn(slot, tiles, pairs, abreast, out)
+        yield slot, out[0], out[1]
+
+
+def test_every_tile_has_one_workgroup(lib):
+    rng = random.Random(5)
+    for _ in range(200):
+        tiles, pairs = rng.choice([1, 2, 3, 5, 17, 130]), rng.choice([2, 3, 4, 5, 7, 8, 16, 23, 115])
+        abreast = rng.randint(2, pairs)
+        turns = [(p, t) for _, p, t in _turns(lib, tiles, pairs, abreast)]
+        assert sorted(turns) == [(p, t) for p in range(pairs) for t in range(tiles)]
+        for first in range(0, pairs, abreast):           # part by part, the longest tiles first
+            part = [t for p, t in turns[first * tiles:(first + abreast) * tiles]]
+            assert part == sorted(part)
+
+
+@pytest.mark.parametrize("lengths", [[125, 118, 104, 94], [63, 47], [62, 60, 57, 55, 54, 52, 50, 47], [31, 16] * 4,
+                                     [20, 18, 15, 12, 10, 9] * 2, [100, 20, 20, 20], [50, 41, 33, 30, 28, 27, 90]])
+def test_work_is_even_over_shader_engines(lib, lengths):
+    """An XCD's workgroups go to its four shader engines in turn.  Pairs of different lengths (in tiles, whose work
+    grows with their place), all abreast: each engine's share of it."""
+    tiles = max(lengths)
+    work = [0, 0, 0, 0]
+    for slot, pair, t in _turns(lib, tiles, len(lengths), len(lengths)):
+        place = tiles - 1 - t
+        if place < lengths[pair]:
+            work[slot % 4] += place + 1
+    assert max(work) <= 1.06 * sum(work) / 4, work
