@@ -203,7 +203,7 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
 int pairs_abreast(const PrefillArgs &p, long long grid, long long most, int groups)
 {
     const long long row = (long long)p.d.max_blocks * p.d.block_size;
-    if (grid <= 512 || groups < 2 || grid > most + most / 4 || 6LL * p.max_new_tokens < row) return 1;
+    if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > most + most / 4 || 6LL * p.max_new_tokens < row) return 1;
     const long long pair = row * p.d.head_dim * (p.d.bf16 ? 4 : 8), all = pair * groups;
     const long long part = (p.d.head_dim >= 256 ? 10LL : 20LL) << 20, parts = min((all + part - 1) / part, (long long)groups);
     return (int)((groups + parts - 1) / parts);

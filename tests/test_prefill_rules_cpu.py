@@ -61,3 +61,21 @@ def test_work_is_even_over_shader_engines(lib, lengths):
         if place < lengths[pair]:
             work[slot % 4] += place + 1
     assert max(work) <= 1.06 * sum(work) / 4, work
+
+
+def test_the_largest_launches(lib):
+    """Places of the last slots there may be, which a reciprocal has to find exactly."""
+    rng = random.Random(6)
+    out = (ctypes.c_int * 2)()
+    for _ in range(3000):
+        slots = rng.randint(1 << 18, (1 << 19) - 1)
+        pairs = rng.choice([2, 3, 7, 64, 115, 600])
+        tiles = slots // pairs
+        abreast = rng.randint(2, pairs)
+        slot = rng.randint(0, tiles * pairs - 1)
+        if rng.random() < 0.5:
+            slot = min(tiles * pairs - 1, slot // abreast * abreast + rng.choice([-1, 0]) % abreast)
+        lib.c_turn(slot, tiles, pairs, abreast, out)
+        first = slot // (abreast * tiles) * abreast
+        n = min(abreast, pairs - first)
+        assert out[1] == (slot - first * tiles) // n and first <= out[0] < first + n
