@@ -858,6 +858,9 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     constexpr bool kLean = (D >= 256 && kCols <= 16) || (kSmall<D, kCols, GRP, SPLIT> && D == 128);
     if (!kLean) read_k(lds);
     const int n_groups = (n_stages + GRP - 1) / GRP;
+    // This kernel's loop (1 252 bytes) is 4 % slower where its first instruction lies across a fetch of 32 bytes; so its first one begins such
+    // a line (28 bytes behind this; 10 prompts' responses of 16 to 64 on 300 to 1 000 cached, 32 / 8 heads of 64, 14.5 us, 15.4 across).
+    if constexpr (D == 64 && TILED && kCols == 16 && GRP == 1 && !SPLIT) asm volatile(".p2align 6\n\t.fill 9, 4, 0xbf800000");
     for (int grp = grp0; grp < n_groups; ++grp) {
         char *cur = lds + ((grp - grp0) & (NB - 1)) * GSTAGE, *nxt = lds + ((grp - grp0 + 1) & (NB - 1)) * GSTAGE;
         if ((grp + 1) * GRP * kStage > valid_end) {   // the group holds the last stage: uniform
@@ -1023,28 +1026,6 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
     return hipGetLastError();
 }
 
-// Tiles of 64 columns (16 per wave, a stage at a time) instead of 128: three (head size 128, grouped heads) or four workgroups and more
-// to a CU, finer grain, half the columns that a short prompt leaves unused -- but each K / V byte read from LDS for half as
-// many products.  They are the better ones while a launch is bound by the way to each tile's first bytes, not by the matrix
-// cores, that is for a few rounds of the chip.  `wide`: tiles of 128 there are at most.  us with the append, 128 / 64 columns:
-// plain heads of 128: 24 prompts of 16 to 700 on 40 heads (wide 1 880) 69.1 / 65.9; 4 of 50 to 150 on 32 (160) 12.4 / 10.5; one of
-// 1 000 (288) 36.7 / 29.8; 20 of 16 to 64 new on 200 to 1 000 cached (832) 47.2 / 44.5; against it 30 of 16 to 700 on 40 (2 900)
-// 122.6 / 124.5, one of 3 000 on 32 (768) 108 / 116, 3 of 600 to 1 200 (768) 54.3 / 56.9, 30 of 2 to 8 new on 64 to 1 000 (992) 35.9 /
-// 38.0, 4 of 500 on 2 000 (640) 104 / 114.  32 / 8 heads: 30 of 16 to 120 (690) 25.8 / 21.9; 20 of 16 to 64 on 200 to 1 000 (360)
-// 41.4 / 33.4; one of 1 000 (264) 35.3 / 28.4; 12 of 100 to 1 200 (1 456) 82.4 / 84.1; 9 of 89 to 1 490 (1 200) 78 / 98.  Heads of
-// 64: one of 8 192 on 8 (520) 148 / 122; 12 of 100 to 1 200 (470) 30.4 / 25.3; 8 / 2 heads, 30 of 20 to 100 on 100 to 800 24.8 /
-// 20.4; 4 of 4 096 on 8 (1 056) 107 / 117; 32 heads, 4 of 2 048 (2 176) 118 / 131.
-bool narrow_tiles(const PrefillArgs &p, int head_dim, bool tiled, int WT)
-{
-    const long long wide = (long long)p.d.num_kv_heads * ((long long)p.total_tokens / WT + p.d.batch);
-    const long long row = (long long)p.d.max_blocks * p.d.block_size;
-    const int most = p.max_new_tokens;
-    const bool prompts = row <= 2LL * most;           // (else what is cached may be most of a walk)
-    if (head_dim == 64) return wide <= (prompts && most <= 1200 ? 1200 : 600);
-    if (prompts) return wide <= 400 || (most <= 800 && wide <= (tiled ? 800 : 2400));
-    return most < 384 && wide <= (tiled ? 800 : 900);
-}
-
 template <int D, bool TILED, int kCols = kMaxCols>
 hipError_t launch_mfma_prefill(PrefillArgs p, hipStream_t s)
 {
@@ -1067,7 +1048,8 @@ hipError_t launch_mfma_prefill(PrefillArgs p, hipStream_t s)
     const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, false, 0, &full);
     if (grid == 0) return hipErrorInvalidValue;
     if constexpr (kCols == kMaxCols && D <= 128) {
-        if (G <= 16 && narrow_tiles(p, D, TILED, WT)) {
+        const long long row = (long long)p.d.max_blocks * p.d.block_size;
+        if (rules::narrow_tiles({p.d.num_kv_heads, G, D, p.d.batch, p.total_tokens, p.max_new_tokens, row}, TILED)) {
             const int WT16 = kWaves * (16 / G);
             const long long tiles16 = (p.max_new_tokens + WT16 - 1) / WT16;
             const unsigned grid16 = place_grid(p, p.d.num_kv_heads, tiles16, WT16, false, 0, &full);

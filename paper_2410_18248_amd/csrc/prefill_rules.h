@@ -1,5 +1,5 @@
-// In which order the tiles of a prefill launch that splits no context start: the arithmetic alone, the same on the host
-// (where a test walks through it) and in the kernel.
+// How wide the tiles of a prefill launch that splits no context are, and in which order they start: the arithmetic alone, the
+// same on the host (where a test walks through it) and in the kernel.
 #pragma once
 #include "prefill_split.h"
 
@@ -24,6 +24,45 @@ __host__ __device__ inline Turn abreast_at(int slot, int tiles, int pairs, int a
     const int shift = n & 1 ? 0 : n & 2 ? t >> 1 & 1 : t & 3;
     const int k = slot - first * tiles - t * n + shift;
     return {first + (k < n ? k : k - n), t};
+}
+
+// Tiles of 64 columns (16 per wave, a stage at a time) instead of 128: three (head size 128, grouped heads) or four workgroups and more
+// to a CU, finer grain, half the columns that a short prompt leaves unused -- but each K / V byte read from LDS for half as
+// many products.  They are the better ones while a launch is bound by the way to each tile's first bytes, not by the matrix
+// cores, that is for a few rounds of the chip.  `wide`: tiles of 128 there are at most.  us with the append, 128 / 64 columns:
+// plain heads of 128: 24 prompts of 16 to 700 on 40 heads (wide 1 880) 69.1 / 65.9; 4 of 50 to 150 on 32 (160) 12.4 / 10.5; one of
+// 1 000 (288) 36.7 / 29.8; 20 of 16 to 64 new on 200 to 1 000 cached (832) 47.2 / 44.5; against it 30 of 16 to 700 on 40 (2 900)
+// 122.6 / 124.5, one of 3 000 on 32 (768) 108 / 116, 3 of 600 to 1 200 (768) 54.3 / 56.9, 30 of 2 to 8 new on 64 to 1 000 (992) 35.9 /
+// 38.0, 4 of 500 on 2 000 (640) 104 / 114.  32 / 8 heads: 30 of 16 to 120 (690) 25.8 / 21.9; 20 of 16 to 64 on 200 to 1 000 (360)
+// 41.4 / 33.4; one of 1 000 (264) 35.3 / 28.4; 12 of 100 to 1 200 (1 456) 82.4 / 84.1; 9 of 89 to 1 490 (1 200) 78 / 98.  Heads of
+// 64: one of 8 192 on 8 (520) 148 / 122; 12 of 100 to 1 200 (470) 30.4 / 25.3; 8 / 2 heads, 30 of 20 to 100 on 100 to 800 24.8 /
+// 20.4; 4 of 4 096 on 8 (1 056) 107 / 117; 32 heads, 4 of 2 048 (2 176) 118 / 131.
+// The lines lie between those.  And: a wave of 16 columns should hold half the tokens that one of 32 does; with groups of 6, 9
+// and 10 it holds a third to two fifths, and only small launches are better off (attention alone: one of 1 000, 40 / 4 heads (336) 32.2 / 26.4;
+// 3 of 300 to 600 there (460) 23.0 / 26.7; 4 of 100 to 300 on 300 to 1 000 (308) 40.3 / 52.8; 24 / 4 heads, 3 of 300 to 600 (308) 22.3 / 19.4).  Over
+// cached positions, past a small launch, narrow tiles are better where wide ones would be half empty (32 / 8 heads: 60 of 4 to 64 on 300
+// to 1 000 (760) 56.7 / 40.8, 10 of 100 to 250 there (496) 40.2 / 45.2; 32 plain heads: 20 of 4 to 64 on 1 000 to 2 000 (704) 101 / 88, 10 of 100 to
+// 250 there (736) 82 / 85, on 300 to 1 000 51 / 47).  Grouped heads of 64, prompts
+// long on average: 32 of 200 to 500 on 8 / 2 (766) 16.9 / 17.5, 6 of 1 000 on 16 / 8 (792) 24.9 / 27.6; short: 24 of 16 to 700 there (728) 18.9 / 15.3, 16 of
+// 154 to 272 on 32 / 8 (936) 16.4 / 14.1.
+//
+// The length of the contexts is known to the host as that of a row of the block table, their bound: rows longer than twice
+// the most new tokens count as mostly cached.  A caller whose rows are as long as its longest possible request gets the lines for those.
+struct Launch {
+    int kv_heads, group, head_dim, batch, total, most;   // total, most: new tokens
+    long long row;                       // positions
+};
+inline bool narrow_tiles(const Launch &l, bool tiled)
+{
+    if (l.group > 16) return false;
+    const int wt = 4 * (32 / l.group);   // new tokens of a wide tile
+    const long long wide = (long long)l.kv_heads * (l.total / wt + l.batch);
+    const bool prompts = l.row <= 2LL * l.most;
+    if (2 * (16 / l.group) < 32 / l.group) return prompts ? wide <= 400 : l.most < 384 && wide <= 250;
+    if (l.head_dim == 64) return wide <= (prompts && l.most <= 1200 ? (tiled && l.total > 300LL * l.batch ? 700 : 1200) : 600);
+    if (prompts) return wide <= 400 || (l.most <= 800 && wide <= (tiled ? 800 : 2400));
+    const bool half_empty = tiled ? l.most <= 2 * wt : l.most <= wt || l.row <= 1280;
+    return l.most < 384 && wide <= (!half_empty ? 400 : tiled ? 800 : 900);
 }
 
 }  // namespace rules

@@ -37,3 +37,9 @@ def test_rows(H, Hkv, D, B, most):
         rig.compute.synchronize()
         assert np.abs(to_f64(out) - want).max() <= tol(geom)
     rig.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D", [(12, 2, 128), (18, 2, 64), (20, 2, 128)])
+@pytest.mark.parametrize("B,most", [(5, 150), (36, 129)])
+def test_groups_that_leave_columns_empty(H, Hkv, D, B, most):
+    test_rows(H, Hkv, D, B, most)

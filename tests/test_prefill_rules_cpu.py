@@ -1,4 +1,4 @@
-"""In which order the tiles of a prefill launch start (csrc/prefill_rules.h, compiled here for the host)."""
+"""How wide the tiles of a prefill launch are and in which order they start (csrc/prefill_rules.h, compiled here for the host)."""
 import ctypes
 import os
 import random
@@ -15,6 +15,10 @@ void c_turn(int slot, int tiles, int pairs, int abreast, int *out)
 {
     const rules::Turn at = rules::abreast_at(slot, tiles, pairs, abreast);
     out[0] = at.pair; out[1] = at.t;
+}
+int c_narrow(int kv_heads, int group, int dim, int batch, int total, int most, long long row, int tiled)
+{
+    return rules::narrow_tiles({kv_heads, group, dim, batch, total, most, row}, tiled);
 }
 }
 """
@@ -79,3 +83,45 @@ def test_the_largest_launches(lib):
         first = slot // (abreast * tiles) * abreast
         n = min(abreast, pairs - first)
         assert out[1] == (slot - first * tiles) // n and first <= out[0] < first + n
+
+
+@pytest.mark.parametrize("H,Hkv,D,batch,total,most,row,narrow", [
+    # half the tokens in half the columns
+    (40, 40, 128, 24, 2950, 683, 688, True),             # an iteration's prompts
+    (32, 32, 128, 1, 1000, 1000, 1008, True),
+    (32, 32, 128, 4, 16000, 4000, 4000, False),
+    (32, 8, 128, 4, 16384, 4096, 4096, False),
+    (32, 8, 128, 1, 1000, 1000, 1008, True),
+    (12, 4, 128, 6, 1200, 300, 1300, True),              # groups of 3, 5, 7
+    (20, 4, 128, 6, 1200, 300, 1300, True),
+    (28, 4, 128, 1, 1000, 1000, 1008, True),
+    # fewer than that: groups of 6, 9 and 10
+    (24, 4, 128, 3, 1350, 600, 608, True),
+    (48, 8, 128, 6, 1200, 300, 1300, False),
+    (36, 4, 128, 3, 1350, 600, 608, False),
+    (40, 4, 128, 4, 800, 300, 1300, False),
+    (40, 4, 128, 1, 1000, 1000, 1008, True),
+    (36, 4, 64, 30, 1700, 120, 128, False),
+    (36, 4, 64, 1, 300, 300, 304, True),
+    # cached positions: tiles half empty, and full ones
+    (32, 8, 128, 60, 1100, 64, 1040, True),
+    (32, 8, 128, 10, 1750, 250, 1250, False),
+    (32, 8, 128, 4, 800, 300, 2300, True),
+    (32, 32, 128, 20, 640, 64, 2064, True),
+    (32, 32, 128, 10, 1750, 250, 2250, False),
+    (32, 32, 128, 10, 1750, 250, 1250, True),
+    # grouped heads of 64
+    (8, 2, 64, 60, 8736, 250, 256, True),
+    (8, 2, 64, 32, 11232, 500, 512, False),
+    (16, 8, 64, 6, 6000, 1000, 1008, False),
+    (16, 8, 64, 24, 4290, 683, 688, True),
+    (32, 8, 64, 16, 3376, 272, 272, True),
+    (8, 8, 64, 32, 11200, 500, 512, True),
+    # a row as long as the longest possible request
+    (40, 40, 128, 24, 2950, 683, 32768, False),
+    (64, 2, 128, 4, 400, 100, 112, False),               # groups above 16: no tiles of 64 columns
+])
+def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
+    """On both sides of each line, launches that were measured."""
+    row = ctypes.c_longlong(row)
+    assert lib.c_narrow(Hkv, H // Hkv, D, batch, total, most, row, H > Hkv) == narrow
