@@ -190,24 +190,6 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     // mistake: nothing is read or written for it
     return at.ctx >= at.n_new && at.ctx <= a.max_blocks * a.block_size;
 }
-// Pairs of an XCD (of the `groups` it has) whose tiles are dealt together, the longest of all of them first.  One pair after
-// the other, a launch ends with the long tiles of its last pairs while most of the chip has nothing left; all together,
-// their K / V streams no longer share an L2.  So they go together in even parts of up to 20 MB (head size 256, whose tiles of 64
-// columns read each byte twice as often: 10), as the table row bounds it; not where the chip holds the launch at once, nor under long contexts, whose tiles are about
-// equally long (30 requests of 20 to 100 new on 100 to 800 cached, 32 / 8 heads: 39.5 us, 46.1 abreast), nor where many
-// workgroups have no tile (6 fp32 prompts of 20 to 428 tokens: 14.5 us, 15.4: those that have one land on half of the CUs).
-// us, append included, one by one / in parts of 4 / 8 or 10 / all: 4 prompts of 1 000, 32 heads of 128 (16 pairs an XCD, 8 MB) 100.9 /
-// 84.6 / 80.7 / 79.0; 4 of 2 048, 40 heads (20 MB) 302 / 271 / 276 / 264; 4 of 4 096 (40 MB) 884 / 830 / 840 / 914; one (5 pairs)
-// 255 / 271 (the last one alone) / - / 214; 8 of 500 on 4 000 cached, 32 heads (72 MB) 343 / 340 / 344 / 396; 8 of 1 900, 8 heads of
-// 64, 76.0 / 71.3 / 60.9; 4 of 4 000, 16 heads of 256 (32 MB), 715 / 729 (in parts of 2: 714) / 758; 4 of 2 000 238 / 222 / 226.
-int pairs_abreast(const PrefillArgs &p, long long grid, long long most, int groups)
-{
-    const long long row = (long long)p.d.max_blocks * p.d.block_size;
-    if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > most + most / 4 || 6LL * p.max_new_tokens < row) return 1;
-    const long long pair = row * p.d.head_dim * (p.d.bf16 ? 4 : 8), all = pair * groups;
-    const long long part = (p.d.head_dim >= 256 ? 10LL : 20LL) << 20, parts = min((all + part - 1) / part, (long long)groups);
-    return (int)((groups + parts - 1) / parts);
-}
 // The grid for it and what place() needs to know; 0: too large.  `spare`: workgroups without a tile that
 // cost less than finding one's place among the tiles there are.
 unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int *full_groups)
@@ -228,7 +210,9 @@ unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bo
         grid = most;
         *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
     }
-    p.slots = *full_groups >= 0 ? pairs_abreast(p, grid, most, (int)full) : 1;
+    const rules::Launch launch = {p.d.num_kv_heads, p.d.num_q_heads / p.d.num_kv_heads, p.d.head_dim, p.d.batch, p.total_tokens,
+                                  p.max_new_tokens, (long long)p.d.max_blocks * p.d.block_size};
+    p.slots = *full_groups >= 0 ? rules::pairs_abreast(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full) : 1;
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
 }
 

@@ -6,13 +6,18 @@
 namespace lamps {
 namespace rules {
 
+struct Launch {
+    int kv_heads, group, head_dim, batch, total, most;   // total, most: new tokens
+    long long row;                       // positions
+};
+
 struct Turn {
     int pair, t;                         // of the pairs of an XCD; tiles behind the longest
 };
 // The place of an XCD's slot-th workgroup, of `pairs` x `tiles`, where `abreast` pairs go together: the longest tiles of all
-// of them, the next ones, and so on.  The pairs of a level begin with another one every other level: an XCD's
-// workgroups go to its four shader engines in turn, and where a level has as many pairs as that, or a multiple, each engine
-// would get the tiles of the same requests all along and the launch end with the engine that has the longest (us, without /
+// of them, the next ones, and so on.  Which pair a level begins with changes from level to level: an XCD's workgroups go to
+// its four shader engines in turn, and where a level has four pairs or a multiple (an even number: every other level), each
+// engine would get the tiles of the same requests all along, and the launch end with the one that has the longest (us, without /
 // with: 4 prompts of 1 500 to 2 000, 32 / 8 heads of 128, one pair of each on an XCD, 142 / 115, of 3 000 to 4 000 468 / 400; 8 of
 // 1 500 to 2 000 on 32 / 4 heads 256 / 223; 16 of 154 to 272 there 31.3 / 27.0; equal lengths level).  Divisions by reciprocal, for there are at
 // most kMostDividend slots: two general ones are in front of the first byte of launches that take 6 us (30 fp32 prompts of 52 to 62
@@ -24,6 +29,31 @@ __host__ __device__ inline Turn abreast_at(int slot, int tiles, int pairs, int a
     const int shift = n & 1 ? 0 : n & 2 ? t >> 1 & 1 : t & 3;
     const int k = slot - first * tiles - t * n + shift;
     return {first + (k < n ? k : k - n), t};
+}
+
+// Pairs of an XCD (of the `groups` it has) whose tiles are dealt together, the longest of all of them first.  One pair after
+// the other, a launch ends with the long tiles of its last pairs while most of the chip has nothing left; all together,
+// their K / V streams no longer share an L2.  So they go together in even parts of up to 20 MB (head size 256, whose tiles of 64
+// columns read each byte twice as often: 10), as the table row bounds it; not where the chip holds the launch at once, nor where many
+// workgroups have no tile (6 fp32 prompts of 20 to 428 tokens: 14.5 us, 15.4: those that have one land on half of the CUs).
+// us, append included, one by one / in parts of 4 / 8 or 10 / all: 4 prompts of 1 000, 32 heads of 128 (16 pairs an XCD, 8 MB) 100.9 /
+// 84.6 / 80.7 / 79.0; 4 of 2 048, 40 heads (20 MB) 302 / 271 / 276 / 264; 4 of 4 096 (40 MB) 884 / 830 / 840 / 914; one (5 pairs)
+// 255 / 271 (the last one alone) / - / 214; 8 of 500 on 4 000 cached, 32 heads (72 MB) 343 / 340 / 344 / 396; 8 of 1 900, 8 heads of
+// 64, 76.0 / 71.3 / 60.9; 4 of 4 000, 16 heads of 256 (32 MB), 715 / 729 (in parts of 2: 714) / 758; 4 of 2 000 238 / 222 / 226.
+// Nor over cached positions, at most as many as are new as the row bounds it: there a tile's place says less of its length, and the
+// last tiles of the longest contexts end the launch (attention alone, one by one / abreast: 16 requests of 500 on 675 to 2 250, 8 fp32 heads of
+// 64, 251 / 322; 10 of 200 on 270 to 900, 32 heads of 128, 44.7 / 51.1; 16 of 500 on 450 to 1 500, 32 / 8 heads, 189 / 215; 10 of 500 on 225 to
+// 750, 32 / 4 heads 78 / 85, 32 heads 104 / 100) -- but if a request has only a few tiles and many have fewer: the workgroups without one
+// would be all through the launch (10 of 100 to 250 on 340 to 1 125, 32 heads of 128, 58.3 / 47.3; 16 there, heads of 64, 46.1 / 34.0).
+// grid: pairs x tiles; there_are: tiles the requests can have, at most.  Bytes of a cached element, keys and values.
+inline int pairs_abreast(const Launch &l, int bytes, long long tiles, long long grid, long long there_are, int groups)
+{
+    if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > there_are + there_are / 4) return 1;
+    const bool ragged = tiles <= 4 && 5LL * l.most * l.batch >= 6LL * l.total;
+    if (l.row > (ragged ? 6LL : 2LL) * l.most) return 1;
+    const long long pair = l.row * l.head_dim * bytes, all = pair * groups;
+    const long long part = (l.head_dim >= 256 ? 10LL : 20LL) << 20, most = (all + part - 1) / part, parts = most < groups ? most : groups;
+    return (int)((groups + parts - 1) / parts);
 }
 
 // Tiles of 64 columns (16 per wave, a stage at a time) instead of 128: three (head size 128, grouped heads) or four workgroups and more
@@ -48,10 +78,6 @@ __host__ __device__ inline Turn abreast_at(int slot, int tiles, int pairs, int a
 //
 // The length of the contexts is known to the host as that of a row of the block table, their bound: rows longer than twice
 // the most new tokens count as mostly cached.  A caller whose rows are as long as its longest possible request gets the lines for those.
-struct Launch {
-    int kv_heads, group, head_dim, batch, total, most;   // total, most: new tokens
-    long long row;                       // positions
-};
 inline bool narrow_tiles(const Launch &l, bool tiled)
 {
     if (l.group > 16) return false;

@@ -1,5 +1,6 @@
 """lamps_prefill_attn where a launch is several times what the chip holds and the (request, head) pairs of an XCD go abreast:
-all together, in parts of which the last is smaller, with pairs left over that fill no group of 8; rows against the fp64 oracle."""
+all together, in parts of which the last is smaller, with pairs left over that fill no group of 8, and where they go one by one for
+all that; rows against the fp64 oracle.  Which of these a launch does is asserted on the CPU (test_prefill_rules_cpu.py)."""
 import numpy as np
 import pytest
 import torch
@@ -12,10 +13,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,Hkv,D,dtype,row,reqs", [
-    (40, 40, 64, "bf16", 640, [(300, 300), (320, 317), (290, 290), (305, 301), (310, 310)]),   # 25 groups, one part
-    (18, 9, 64, "bf16", 2048, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over
-    (32, 8, 256, "bf16", 4096, [(700, 700), (690, 688), (700, 695)]),                         # 3 groups in parts of 2 and 1
-    (16, 16, 256, "bf16", 6144, [(1030, 1030), (1024, 1024)]),                                # 4 groups in parts of 1
+    (40, 40, 64, "bf16", 640, [(300, 300), (320, 317), (290, 290), (305, 301), (310, 310)]),   # 25 groups, one by one
+    (18, 9, 64, "bf16", 2048, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over, one by one (rows mostly cached)
+    (32, 8, 256, "bf16", 4096, [(700, 700), (690, 688), (700, 695)]),                         # 3 groups, one by one
+    (16, 16, 256, "bf16", 6144, [(1030, 1030), (1024, 1024)]),                                # 4 groups, one by one
     (9, 9, 64, "f32", 512, [(400, 400), (390, 390), (410, 401)]),
 ])
 def test_rows(H, Hkv, D, dtype, row, reqs):
@@ -35,3 +36,13 @@ def test_rows(H, Hkv, D, dtype, row, reqs):
     rig.compute.synchronize()
     assert np.abs(to_f64(out) - oracle.prefill_attn(q, K, V, q_start, ctx, threads=8)).max() <= tol(geom)
     rig.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D,dtype,row,reqs", [
+    (40, 40, 64, "bf16", 608, [(300, 300), (320, 317), (290, 290), (305, 301), (310, 310)]),   # 25 groups, one part
+    (18, 9, 64, "bf16", 1200, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over, one part
+    (8, 8, 256, "bf16", 3584, [(1800, 1800), (1790, 1785), (1300, 1290)]),                    # 3 groups in parts of 2 and 1
+    (32, 32, 128, "bf16", 1100, [(200 + 90 * r, 130 + 12 * r) for r in range(10)]),           # few tiles, 40 groups in two parts
+])
+def test_parts(H, Hkv, D, dtype, row, reqs):
+    test_rows(H, Hkv, D, dtype, row, reqs)

@@ -16,6 +16,12 @@ void c_turn(int slot, int tiles, int pairs, int abreast, int *out)
     const rules::Turn at = rules::abreast_at(slot, tiles, pairs, abreast);
     out[0] = at.pair; out[1] = at.t;
 }
+int c_abreast(int heads, int dim, int batch, int total, int most, long long row, int bytes, int wt)
+{
+    const long long pairs = (long long)heads * batch, tiles = (most + wt - 1) / wt;
+    return rules::pairs_abreast({heads, 1, dim, batch, total, most, row}, bytes, tiles, pairs / 8 * 8 * tiles + (pairs % 8 * tiles + 7) / 8 * 8,
+                                heads * ((long long)total / wt + batch), (int)(pairs / 8));
+}
 int c_narrow(int kv_heads, int group, int dim, int batch, int total, int most, long long row, int tiled)
 {
     return rules::narrow_tiles({kv_heads, group, dim, batch, total, most, row}, tiled);
@@ -125,3 +131,39 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
     """On both sides of each line, launches that were measured."""
     row = ctypes.c_longlong(row)
     assert lib.c_narrow(Hkv, H // Hkv, D, batch, total, most, row, H > Hkv) == narrow
+
+
+@pytest.mark.parametrize("heads,D,batch,total,most,row,bytes,wt,abreast", [
+    # the launches whose rows are compared on the GPU
+    (40, 64, 5, 1518, 310, 640, 4, 128, 1),
+    (40, 64, 5, 1518, 310, 608, 4, 128, 25),
+    (9, 64, 3, 1790, 610, 2048, 4, 32, 1),
+    (8, 256, 3, 2083, 700, 4096, 4, 16, 1),
+    (16, 256, 2, 2054, 1030, 6144, 4, 64, 1),
+    (9, 64, 3, 1190, 401, 512, 8, 16, 3),
+    (9, 64, 3, 1790, 610, 1200, 4, 32, 3),
+    (8, 256, 3, 4875, 1800, 3584, 4, 64, 2),
+    (32, 128, 10, 1840, 238, 1100, 4, 128, 20),
+    # heads of 128, 128 columns: all of the groups of an XCD, parts of 20 MB, one by one where a pair has as much
+    (32, 128, 4, 4000, 1000, 1008, 4, 128, 16),
+    (40, 128, 4, 8192, 2048, 2048, 4, 128, 20),
+    (32, 128, 4, 16384, 4096, 4096, 4, 128, 8),
+    (16, 128, 1, 40000, 40000, 40000, 4, 128, 1),
+    (8, 256, 3, 2100, 700, 4096, 4, 16, 1),              # a row of 4 096: mostly cached
+    (8, 256, 3, 2100, 700, 1400, 4, 16, 3),
+    (16, 256, 2, 4100, 2050, 4096, 4, 64, 2),            # parts of 10 MB: two, of the four groups
+    (16, 256, 2, 12000, 6000, 6016, 4, 64, 2),           # three
+    (16, 256, 2, 24000, 12000, 12000, 4, 64, 1),         # more than four, so four of one each
+    # where the chip holds the launch at once, or many workgroups have no tile
+    (32, 128, 2, 1000, 500, 512, 4, 128, 1),
+    (32, 128, 24, 4200, 4000, 4000, 4, 128, 1),
+    # cached positions: more than new ones, and few tiles of which many requests have fewer
+    (32, 128, 10, 2000, 200, 1100, 4, 128, 1),
+    (32, 128, 10, 1750, 250, 1375, 4, 128, 20),
+    (32, 128, 10, 1750, 250, 1520, 4, 128, 1),
+    (8, 64, 16, 8000, 500, 2750, 8, 16, 1),
+    (8, 64, 16, 8000, 500, 750, 8, 16, 16),
+])
+def test_pairs_abreast(lib, heads, D, batch, total, most, row, bytes, wt, abreast):
+    row = ctypes.c_longlong(row)
+    assert lib.c_abreast(heads, D, batch, total, most, row, bytes, wt) == abreast
