@@ -842,9 +842,10 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     constexpr bool kLean = (D >= 256 && kCols <= 16) || (kSmall<D, kCols, GRP, SPLIT> && D == 128);
     if (!kLean) read_k(lds);
     const int n_groups = (n_stages + GRP - 1) / GRP;
-    // This kernel's loop (1 252 bytes) is 4 % slower where its first instruction lies across a fetch of 32 bytes; so its first one begins such
-    // a line (28 bytes behind this; 10 prompts' responses of 16 to 64 on 300 to 1 000 cached, 32 / 8 heads of 64, 14.5 us, 15.4 across).
-    if constexpr (D == 64 && TILED && kCols == 16 && GRP == 1 && !SPLIT) asm volatile(".p2align 6\n\t.fill 9, 4, 0xbf800000");
+    // Instructions are fetched by 32 bytes.  Where in such a line the loops of narrow tiles of heads of 64 begin (20 bytes behind this,
+    // grouped ones 28) is up to 6 % of their time, least at 4: 10 requests' 16 to 64 on 300 to 1 000 cached, 32 / 8 heads, 13.1 us to
+    // 14.1; one prompt of 2 000 on 8 plain heads 27.2 to 29.3.
+    if constexpr (D == 64 && kCols == 16 && GRP == 1 && !SPLIT) asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(TILED ? 2 : 4));
     for (int grp = grp0; grp < n_groups; ++grp) {
         char *cur = lds + ((grp - grp0) & (NB - 1)) * GSTAGE, *nxt = lds + ((grp - grp0 + 1) & (NB - 1)) * GSTAGE;
         if ((grp + 1) * GRP * kStage > valid_end) {   // the group holds the last stage: uniform

@@ -14,28 +14,35 @@ from test_kernel_resources_cpu import _code_objects, _metadata
 OBJDUMP = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "llvm", "bin", "llvm-objdump")
 
 
-@pytest.fixture(scope="module")
-def balanced():
-    """name -> instructions of the kernels of balanced decode launches"""
+def _code(part):
+    """name -> (address, instruction) of the kernels whose code object has one with `part` in its name"""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump beside hipcc")
     out = {}
     for co in _code_objects(open(P.lib_path(), "rb").read()):
-        if not any("decode_balanced" in k[".name"] for k in _metadata(co)):
+        if not any(part in k[".name"] for k in _metadata(co)):
             continue
         with tempfile.NamedTemporaryFile(suffix=".o") as f:
             f.write(co)
             f.flush()
-            text = subprocess.check_output([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", f.name], text=True)
+            text = subprocess.check_output([OBJDUMP, "-d", "--no-show-raw-insn", f.name], text=True)
         name = None
         for line in text.split("\n"):
-            m = re.match(r".*<(\S+)>:", line)
+            m = re.match(r"([0-9a-f]+) <(\S+)>:", line)
             if m:
-                name = m.group(1)
+                name, start = m.group(2), int(m.group(1), 16)
                 out[name] = []
-            elif name and line.strip():
-                out[name].append(line.split("//")[0].strip())
-    out = {n: x for n, x in out.items() if "decode_balanced" in n and "merge" not in n}
+                continue
+            m = re.match(r"\s+(.*\S)\s*// *([0-9A-F]+):(.*)", line)
+            if name and m:
+                out[name].append((int(m.group(2), 16) - start, m.group(1) + m.group(3)))
+    return {n: x for n, x in out.items() if part in n}
+
+
+@pytest.fixture(scope="module")
+def balanced():
+    """name -> instructions of the kernels of balanced decode launches"""
+    out = {n: [i for _, i in x] for n, x in _code("decode_balanced").items() if "merge" not in n}
     assert len(out) == 30
     return out
 
@@ -59,3 +66,20 @@ def test_the_plan_divides_by_32_bits(balanced):
     only the four for sequences of 2^31 chunks and more (two ends of a share, its range, and a range's last share)."""
     for name, code in balanced.items():
         assert sum("0x5f7ffffc" in x for x in code) <= 4, name
+
+
+def test_where_loops_begin_in_a_fetch():
+    """The loops of narrow tiles of heads of 64, whose time goes by that: the last backward branch over more than 600 bytes."""
+    seen = 0
+    for name, code in _code("prefill_mfma").items():
+        m = re.search(r"prefill_mfmaILi64ELb(\d)ELi16ELi1ELb0E", name)
+        if not m:
+            continue
+        begin = None
+        for at, x in code:
+            t = re.match(r"s_c?branch.*<\S+\+0x([0-9a-f]+)>", x)
+            if t and int(t.group(1), 16) < at - 600:
+                begin = int(t.group(1), 16)
+        assert begin % 32 == 4, (name, begin % 32)
+        seen += 1
+    assert seen == 2
