@@ -89,32 +89,17 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     const DecodeArgs &a = p.d;
     if (full_groups >= 0) {
         const int pairs = heads * a.batch;
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        int pair, t;
-        if (slot < full_groups * tiles) {
-            const int abreast = p.slots;
-            if (abreast <= 1) {
-                pair = xcd + 8 * (slot / tiles);
-                t = slot % tiles;
-            } else {
-                const rules::Turn at = rules::abreast_at(slot, tiles, full_groups, abreast);
-                t = at.t;
-                pair = xcd + 8 * at.pair;
-            }
-            // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
-            // second turn begins with a pair, its pairs start with their short tiles, so that a CU has
-            // a long and a short one: 4 prompts of 512 on 16 heads of 256, append included, 41.2 -> 37.6
-            // us, 2 of 1 000 54.6 -> 49.3; fp32, 2 of 512 on 8 heads of 64, 17.0 -> 12.8, 2 of 256 on 16 of 128,
-            // 19.6 -> 15.2.  (Beginning inside a pair's tiles: 2 % slower than without.)  Not where a CU holds
-            // one workgroup: the second turn then waits for the first, and has to begin with its long tiles
-            // (4 prompts of 512, 32 / 4 heads of 256: 55.3 us, 42.3 in order).
-            if (two_per_cu && gridDim.x <= 512 && 32 % tiles == 0 && (slot & 32)) t = tiles - 1 - t;
-        } else {
-            const int rest = pairs - 8 * full_groups;    // 1..7 here: the grid has no such slots otherwise
-            const int i = (slot - full_groups * tiles) * 8 + xcd;
-            pair = 8 * full_groups + i % rest;
-            t = i / rest;
-        }
+        const rules::Turn turn = rules::deal(blockIdx.x, pairs, full_groups, tiles, p.slots);
+        const int pair = turn.pair;
+        int t = turn.t;
+        // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
+        // second turn begins with a pair, its pairs start with their short tiles, so that a CU has
+        // a long and a short one: 4 prompts of 512 on 16 heads of 256, append included, 41.2 -> 37.6
+        // us, 2 of 1 000 54.6 -> 49.3; fp32, 2 of 512 on 8 heads of 64, 17.0 -> 12.8, 2 of 256 on 16 of 128,
+        // 19.6 -> 15.2.  (Beginning inside a pair's tiles: 2 % slower than without.)  Not where a CU holds
+        // one workgroup: the second turn then waits for the first, and has to begin with its long tiles
+        // (4 prompts of 512, 32 / 4 heads of 256: 55.3 us, 42.3 in order).
+        if (two_per_cu && gridDim.x <= 512 && 32 % tiles == 0 && turn.slot >= 0 && (turn.slot & 32)) t = tiles - 1 - t;
         if (t >= tiles) return false;
         at.tile = tiles - 1 - t;
         at.r = pair / heads;

@@ -12,7 +12,7 @@ struct Launch {
 };
 
 struct Turn {
-    int pair, t;                         // of the pairs of an XCD; tiles behind the longest
+    int pair, t, slot;                   // t: tiles behind the longest
 };
 // The place of an XCD's slot-th workgroup, of `pairs` x `tiles`, where `abreast` pairs go together: the longest tiles of all
 // of them, the next ones, and so on.  Which pair a level begins with changes from level to level: an XCD's workgroups go to
@@ -28,7 +28,23 @@ __host__ __device__ inline Turn abreast_at(int slot, int tiles, int pairs, int a
     const int t = split::small_div(slot - first * tiles, n);
     const int shift = n & 1 ? 0 : n & 2 ? t >> 1 & 1 : t & 3;
     const int k = slot - first * tiles - t * n + shift;
-    return {first + (k < n ? k : k - n), t};
+    return {first + (k < n ? k : k - n), t, slot};
+}
+// A workgroup's pair and tile in a grid of `pairs` x `tiles`: groups of 8 pairs, one on each XCD, whose place among those is `slot`; the
+// pairs left over, -1, are dealt round-robin over the XCDs -- in front of pairs that go abreast, which end with their short
+// tiles (behind them, us attention alone, one by one / abreast / in front: 9 prompts of 599 to 665 on 32 / 4 heads of 128 62.3 / 65.6 / 54.5; 9 of
+// 1 714 to 1 769 on 8 / 2 heads of 64 58.6 / 60.7 / 43.8; 7 of 1 000 on 20 heads of 128 83.5 / 81.2 / 63.3).
+__host__ __device__ inline Turn deal(int block, int pairs, int groups, int tiles, int abreast)
+{
+    const int xcd = block & 7, rest = pairs - 8 * groups, ahead = abreast > 1 ? (rest * tiles + 7) >> 3 : 0;
+    const int slot = (block >> 3) - ahead;
+    if (slot >= 0 && slot < groups * tiles) {
+        if (abreast <= 1) return {xcd + 8 * (slot / tiles), slot % tiles, slot};
+        const Turn turn = abreast_at(slot, tiles, groups, abreast);
+        return {xcd + 8 * turn.pair, turn.t, slot};
+    }
+    const int i = (abreast > 1 ? block >> 3 : slot - groups * tiles) * 8 + xcd;   // (rest is 1..7: the grid has no such slots otherwise)
+    return {8 * groups + i % rest, i / rest, -1};
 }
 
 // Pairs of an XCD (of the `groups` it has) whose tiles are dealt together, the longest of all of them first.  One pair after

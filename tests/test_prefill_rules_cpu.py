@@ -16,6 +16,11 @@ void c_turn(int slot, int tiles, int pairs, int abreast, int *out)
     const rules::Turn at = rules::abreast_at(slot, tiles, pairs, abreast);
     out[0] = at.pair; out[1] = at.t;
 }
+void c_deal(int block, int pairs, int tiles, int abreast, int *out)
+{
+    const rules::Turn at = rules::deal(block, pairs, pairs / 8, tiles, abreast);
+    out[0] = at.pair; out[1] = at.t;
+}
 int c_abreast(int heads, int dim, int batch, int total, int most, long long row, int bytes, int wt)
 {
     const long long pairs = (long long)heads * batch, tiles = (most + wt - 1) / wt;
@@ -167,3 +172,30 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
 def test_pairs_abreast(lib, heads, D, batch, total, most, row, bytes, wt, abreast):
     row = ctypes.c_longlong(row)
     assert lib.c_abreast(heads, D, batch, total, most, row, bytes, wt) == abreast
+
+
+def test_pairs_left_over(lib):
+    """Whole grids: every tile has one workgroup, eight pairs to a group, and the pairs that fill no group come in front of those
+    that go abreast and behind those that do not."""
+    out = (ctypes.c_int * 2)()
+    for pairs, tiles in ((18, 27), (36, 42), (28, 8), (17, 5), (9, 3), (15, 130), (16, 7), (23, 1)):
+        groups, rest = pairs // 8, pairs % 8
+        spare = (rest * tiles + 7) // 8
+        for abreast in sorted({1, 2, groups}):
+            if abreast > groups:
+                continue
+            seen = {}
+            for block in range(8 * (groups * tiles + spare)):
+                lib.c_deal(block, pairs, tiles, abreast, out)
+                if out[1] < tiles:
+                    assert (out[0], out[1]) not in seen
+                    seen[out[0], out[1]] = block
+                    if out[0] < 8 * groups:
+                        assert out[0] % 8 == block % 8
+                else:
+                    assert out[0] >= 8 * groups
+            assert len(seen) == pairs * tiles
+            left = [b for (p, _), b in seen.items() if p >= 8 * groups]
+            others = [b for (p, _), b in seen.items() if p < 8 * groups]
+            if rest:
+                assert max(left) < min(others) if abreast > 1 else min(left) > max(others)
