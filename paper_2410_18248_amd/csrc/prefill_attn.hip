@@ -195,7 +195,7 @@ unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bo
         grid = most;
         *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
     }
-    const rules::Launch launch = {p.d.num_kv_heads, p.d.num_q_heads / p.d.num_kv_heads, p.d.head_dim, p.d.batch, p.total_tokens,
+    const rules::Launch launch = {(int)heads, p.d.num_q_heads / p.d.num_kv_heads, p.d.head_dim, p.d.batch, p.total_tokens,
                                   p.max_new_tokens, (long long)p.d.max_blocks * p.d.block_size};
     p.slots = *full_groups >= 0 ? rules::pairs_abreast(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full) : 1;
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;

@@ -7,7 +7,7 @@ namespace lamps {
 namespace rules {
 
 struct Launch {
-    int kv_heads, group, head_dim, batch, total, most;   // total, most: new tokens
+    int heads, group, head_dim, batch, total, most;   // heads: kv heads, of fp32 tiles passes over them; total, most: new tokens
     long long row;                       // positions
 };
 
@@ -56,17 +56,22 @@ __host__ __device__ inline Turn deal(int block, int pairs, int groups, int tiles
 // 84.6 / 80.7 / 79.0; 4 of 2 048, 40 heads (20 MB) 302 / 271 / 276 / 264; 4 of 4 096 (40 MB) 884 / 830 / 840 / 914; one (5 pairs)
 // 255 / 271 (the last one alone) / - / 214; 8 of 500 on 4 000 cached, 32 heads (72 MB) 343 / 340 / 344 / 396; 8 of 1 900, 8 heads of
 // 64, 76.0 / 71.3 / 60.9; 4 of 4 000, 16 heads of 256 (32 MB), 715 / 729 (in parts of 2: 714) / 758; 4 of 2 000 238 / 222 / 226.
-// Nor over cached positions, at most as many as are new as the row bounds it: there a tile's place says less of its length, and the
-// last tiles of the longest contexts end the launch (attention alone, one by one / abreast: 16 requests of 500 on 675 to 2 250, 8 fp32 heads of
-// 64, 251 / 322; 10 of 200 on 270 to 900, 32 heads of 128, 44.7 / 51.1; 16 of 500 on 450 to 1 500, 32 / 8 heads, 189 / 215; 10 of 500 on 225 to
-// 750, 32 / 4 heads 78 / 85, 32 heads 104 / 100) -- but if a request has only a few tiles and many have fewer: the workgroups without one
-// would be all through the launch (10 of 100 to 250 on 340 to 1 125, 32 heads of 128, 58.3 / 47.3; 16 there, heads of 64, 46.1 / 34.0).
+// Nor over cached positions, as the row bounds them, of more than twice what is new, of as much where a pair's neighbours are another request's:
+// there a tile's place says less of its length, and the last tiles of the longest contexts end the launch (attention alone, one
+// by one / abreast: 16 requests of 500 on 675 to 2 250, 8 fp32 heads of 64, 251 / 322; 10 of 200 on 270 to 900, 32 heads of 128, 47.4 / 52.1; 16 of
+// 500 on 450 to 1 500, 32 / 8 heads, 188 / 213; 10 of 500 on 225 to 750 there 87 / 82, 32 / 4 heads 81 / 88) -- but if a request has only
+// a few tiles and many have fewer: the workgroups without one would be all through the launch (10 of 100 to 250 on 340 to 1 125,
+// 32 heads of 128, 58.3 / 47.3; 16 there, heads of 64, 46.1 / 34.0).
+// Nor up to three tiles of requests that have about as many each: there is next to no tail to fill, and one by one a pair's tiles read
+// its K / V at the same time (27 prompts of 300 to 362, 32 heads of 128, 80.7 / 93.3; 16 of 200 there, row of 300, 34.7 / 36.2; but 4 tiles, 16 of
+// 500, 115 / 103).
 // grid: pairs x tiles; there_are: tiles the requests can have, at most.  Bytes of a cached element, keys and values.
 inline int pairs_abreast(const Launch &l, int bytes, long long tiles, long long grid, long long there_are, int groups)
 {
     if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > there_are + there_are / 4) return 1;
-    const bool ragged = tiles <= 4 && 5LL * l.most * l.batch >= 6LL * l.total;
-    if (l.row > (ragged ? 6LL : 2LL) * l.most) return 1;
+    const bool ragged = tiles <= 4 && 20LL * l.most * l.batch >= 27LL * l.total;
+    if (!ragged && (tiles <= 3 || l.row > (l.heads % 8 == 0 ? 3LL : 2LL) * l.most)) return 1;
+    if (l.row > 6LL * l.most) return 1;
     const long long pair = l.row * l.head_dim * bytes, all = pair * groups;
     const long long part = (l.head_dim >= 256 ? 10LL : 20LL) << 20, most = (all + part - 1) / part, parts = most < groups ? most : groups;
     return (int)((groups + parts - 1) / parts);
@@ -98,7 +103,7 @@ inline bool narrow_tiles(const Launch &l, bool tiled)
 {
     if (l.group > 16) return false;
     const int wt = 4 * (32 / l.group);   // new tokens of a wide tile
-    const long long wide = (long long)l.kv_heads * (l.total / wt + l.batch);
+    const long long wide = (long long)l.heads * (l.total / wt + l.batch);
     const bool prompts = l.row <= 2LL * l.most;
     if (2 * (16 / l.group) < 32 / l.group) return prompts ? wide <= 400 : l.most < 384 && wide <= 250;
     if (l.head_dim == 64) return wide <= (prompts && l.most <= 1200 ? (tiled && l.total > 300LL * l.batch ? 700 : 1200) : 600);

@@ -141,14 +141,15 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
 @pytest.mark.parametrize("heads,D,batch,total,most,row,bytes,wt,abreast", [
     # the launches whose rows are compared on the GPU
     (40, 64, 5, 1518, 310, 640, 4, 128, 1),
-    (40, 64, 5, 1518, 310, 608, 4, 128, 25),
+    (40, 64, 5, 1518, 310, 608, 4, 128, 1),
+    (40, 64, 5, 2148, 501, 608, 4, 128, 25),
     (9, 64, 3, 1790, 610, 2048, 4, 32, 1),
     (8, 256, 3, 2083, 700, 4096, 4, 16, 1),
     (16, 256, 2, 2054, 1030, 6144, 4, 64, 1),
     (9, 64, 3, 1190, 401, 512, 8, 16, 3),
     (9, 64, 3, 1790, 610, 1200, 4, 32, 3),
     (8, 256, 3, 4875, 1800, 3584, 4, 64, 2),
-    (32, 128, 10, 1840, 238, 1100, 4, 128, 20),
+    (32, 128, 10, 1478, 250, 1100, 4, 128, 20),
     # heads of 128, 128 columns: all of the groups of an XCD, parts of 20 MB, one by one where a pair has as much
     (32, 128, 4, 4000, 1000, 1008, 4, 128, 16),
     (40, 128, 4, 8192, 2048, 2048, 4, 128, 20),
@@ -162,11 +163,18 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
     # where the chip holds the launch at once, or many workgroups have no tile
     (32, 128, 2, 1000, 500, 512, 4, 128, 1),
     (32, 128, 24, 4200, 4000, 4000, 4, 128, 1),
-    # cached positions: more than new ones, and few tiles of which many requests have fewer
+    # few tiles, as many for every request
+    (32, 128, 27, 8937, 362, 368, 4, 128, 1),
+    (32, 128, 16, 8000, 500, 512, 4, 128, 64),
+    (32, 128, 60, 10500, 250, 256, 4, 128, 120),
+    # cached positions: twice the new ones and more, as many on heads that share an XCD, and few tiles of which many requests have fewer
     (32, 128, 10, 2000, 200, 1100, 4, 128, 1),
     (32, 128, 10, 1750, 250, 1375, 4, 128, 20),
     (32, 128, 10, 1750, 250, 1520, 4, 128, 1),
     (8, 64, 16, 8000, 500, 2750, 8, 16, 1),
+    (8, 128, 10, 5000, 500, 1250, 4, 32, 10),
+    (4, 128, 10, 5000, 500, 1250, 4, 16, 1),
+    (4, 128, 10, 5000, 500, 900, 4, 16, 5),
     (8, 64, 16, 8000, 500, 750, 8, 16, 16),
 ])
 def test_pairs_abreast(lib, heads, D, batch, total, most, row, bytes, wt, abreast):
