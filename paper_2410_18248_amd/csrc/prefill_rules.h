@@ -97,6 +97,11 @@ inline int pairs_abreast(const Launch &l, int bytes, long long tiles, long long 
 // long on average: 32 of 200 to 500 on 8 / 2 (766) 16.9 / 17.5, 6 of 1 000 on 16 / 8 (792) 24.9 / 27.6; short: 24 of 16 to 700 there (728) 18.9 / 15.3, 16 of
 // 154 to 272 on 32 / 8 (936) 16.4 / 14.1.
 //
+// Plain heads of 128, prompts long on average: 12 of 512 on 32 (1 920) 62.1 / 66.8, 14 of 300 to 362 on 40 (1 960) 58.5 / 64.0, 10 of 400 to 600 on 32 (1 536)
+// 55.1 / 51.0; short: 50 of 20 to 128 on 32 (2 272) 28.4 / 25.3.  17 of 31 to 124 on 650 to 2 239 on 32 (860) 100 / 111, 20 of 1 to 5 on 143 to 1 553 on 40 (800)
+// 57.3 / 60.4.  32 plain heads of 64: 30 of 2 to 8 on 1 000 to 2 000 (990) 87 / 72; 10 of 100 to 250 on 300 to 1 000
+// (704) 31.3 / 28.5.
+//
 // The length of the contexts is known to the host as that of a row of the block table, their bound: rows longer than twice
 // the most new tokens count as mostly cached.  A caller whose rows are as long as its longest possible request gets the lines for those.
 inline bool narrow_tiles(const Launch &l, bool tiled)
@@ -106,10 +111,13 @@ inline bool narrow_tiles(const Launch &l, bool tiled)
     const long long wide = (long long)l.heads * (l.total / wt + l.batch);
     const bool prompts = l.row <= 2LL * l.most;
     if (2 * (16 / l.group) < 32 / l.group) return prompts ? wide <= 400 : l.most < 384 && wide <= 250;
-    if (l.head_dim == 64) return wide <= (prompts && l.most <= 1200 ? (tiled && l.total > 300LL * l.batch ? 700 : 1200) : 600);
-    if (prompts) return wide <= 400 || (l.most <= 800 && wide <= (tiled ? 800 : 2400));
-    const bool half_empty = tiled ? l.most <= 2 * wt : l.most <= wt || l.row <= 1280;
-    return l.most < 384 && wide <= (!half_empty ? 400 : tiled ? 800 : 900);
+    if (l.head_dim == 64) {
+        if (!prompts) return wide <= (tiled ? 600 : 1100);
+        return wide <= (l.most > 1200 ? 600 : tiled && l.total > 300LL * l.batch ? 700 : 1200);
+    }
+    if (prompts) return wide <= 400 || (l.most <= 800 && wide <= (tiled ? 800 : l.total > 220LL * l.batch ? 1850 : 2400));
+    const bool half_empty = tiled ? l.most <= 2 * wt : 2LL * l.total <= (long long)wt * l.batch || l.row <= 1280;
+    return l.most < 384 && wide <= (!half_empty ? 400 : tiled ? 800 : 780);
 }
 
 }  // namespace rules

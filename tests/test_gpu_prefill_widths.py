@@ -28,7 +28,7 @@ def test_rows(H, Hkv, D, B, most):
     q = W.queries(13, geom, sum(new))
     q_start = np.concatenate([[0], np.cumsum(new)]).astype(np.int32)
     want = oracle.prefill_attn(q, K, V, q_start, ctx, threads=8)
-    for known in (most, 0):                             # the most new tokens known to the caller, or not
+    for known in (max(new), 0):                         # the most new tokens known to the caller, or not
         out = torch.full(q.shape, 7.0, device=rig.dev, dtype=rig.tdtype)
         with torch.cuda.stream(rig.compute):
             rig.lamps.prefill_attn(0, B, sum(new), n2t(q, rig.dev), torch.as_tensor(q_start, device=rig.dev),

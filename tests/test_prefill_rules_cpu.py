@@ -106,6 +106,10 @@ def test_the_largest_launches(lib):
     (12, 4, 128, 6, 1200, 300, 1300, True),              # groups of 3, 5, 7
     (20, 4, 128, 6, 1200, 300, 1300, True),
     (28, 4, 128, 1, 1000, 1000, 1008, True),
+    (32, 32, 128, 10, 4984, 600, 608, True),             # long on average, and short
+    (32, 32, 128, 12, 6144, 512, 512, False),
+    (40, 40, 128, 14, 4578, 362, 368, False),
+    (32, 32, 128, 50, 2690, 128, 128, True),
     # fewer than that: groups of 6, 9 and 10
     (24, 4, 128, 3, 1350, 600, 608, True),
     (48, 8, 128, 6, 1200, 300, 1300, False),
@@ -118,8 +122,10 @@ def test_the_largest_launches(lib):
     (32, 8, 128, 60, 1100, 64, 1040, True),
     (32, 8, 128, 10, 1750, 250, 1250, False),
     (32, 8, 128, 4, 800, 300, 2300, True),
-    (32, 32, 128, 20, 640, 64, 2064, True),
+    (32, 32, 128, 20, 340, 64, 2064, True),
     (32, 32, 128, 10, 1750, 250, 2250, False),
+    (32, 32, 128, 17, 1260, 124, 2363, False),
+    (40, 40, 128, 20, 55, 5, 1568, False),
     (32, 32, 128, 10, 1750, 250, 1250, True),
     # grouped heads of 64
     (8, 2, 64, 60, 8736, 250, 256, True),
@@ -128,6 +134,10 @@ def test_the_largest_launches(lib):
     (16, 8, 64, 24, 4290, 683, 688, True),
     (32, 8, 64, 16, 3376, 272, 272, True),
     (8, 8, 64, 32, 11200, 500, 512, True),
+    (32, 8, 64, 20, 680, 64, 2064, True),
+    (32, 8, 64, 60, 1700, 64, 2064, False),
+    (32, 32, 64, 30, 150, 8, 2008, True),
+    (32, 32, 64, 60, 300, 8, 2008, False),
     # a row as long as the longest possible request
     (40, 40, 128, 24, 2950, 683, 32768, False),
     (64, 2, 128, 4, 400, 100, 112, False),               # groups above 16: no tiles of 64 columns
