@@ -885,73 +885,88 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
         __syncthreads();
         if (!*is_last) return;
         // The runs in order, whichever workgroup this is: bit-reproducible.  The waves share the blocks of 16 columns that
-        // the tile has, by halves of their dims from head size 128 on, and ask for eight runs at a time: an API response's few tokens fill one or
-        // two blocks, and a wave alone on each took two trips of 50 KB and more at the rate one wave gets (12 requests with 6
-        // to 58 new tokens on 345 to 2 490 cached, 32 / 8 heads of 128, with the append: 30.3 us, 29.6 so; one of 300
-        // on 2 000 46.7 and 39.1).
+        // the tile has: at head size 128 by halves of their dims, eight runs at a time, if that leaves no wave two units of work (an
+        // API response's few tokens fill one or two blocks, and a wave alone on each took two trips of 50 KB and more at the rate one wave
+        // gets); otherwise whole and four at a time.  Attention alone, a wave to a block / by halves always / so: 12 requests' 4 to 64 on
+        // 300 to 3 000, 32 / 8 heads of 128, 24.4 / 23.8 / 23.2 us; one of 300 on 2 000 43.3 / 35.9 / 35.2; 3 of 17 to 69 on 74 to 1 529 17.8 / 18.3 /
+        // 17.3; 2 of 100 on 1 500, 40 heads, 33.4 / 33.3 / 30.6.
         int me = lane;
         if constexpr (D >= 256) asm volatile("" : "+v"(me));   // (worked out here, not kept over the loop: it spills as it is)
         const int j = me & 15, qd = me >> 4;
-        constexpr int PARTS = D >= 128 ? 2 : 1, HS = NS / PARTS, N = D >= 256 ? 2 : 8;   // slabs of a unit of work; runs whose loads are in flight together
         const int blocks = (min(WT, n_new - tile * WT) + TW - 1) / TW * kColBlocks;
+        const auto add_up = [&](auto parts, auto runs) {   // parts of a block's dims; runs whose loads are in flight together
+            constexpr int PARTS = parts, HS = NS / PARTS, N = runs;
 #pragma unroll 1
-        for (int u = wv; u < PARTS * blocks; u += kWaves) {
-            const int block = u / PARTS, half = u % PARTS;
-            const size_t at0 = (size_t)first_item * (kAll / 16) + block, step = (size_t)item_stride * (kAll / 16);
-            float M = kLowest, L = 0.0f;
-            f32x4 A[HS];
+            for (int u = wv; u < PARTS * blocks; u += kWaves) {
+                const int block = u / PARTS, half = u % PARTS;
+                const size_t at0 = (size_t)first_item * (kAll / 16) + block, step = (size_t)item_stride * (kAll / 16);
+                float M = kLowest, L = 0.0f;
+                f32x4 A[HS];
 #pragma unroll
-            for (int s = 0; s < HS; ++s) A[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (int k0 = 0; k0 < n_runs; k0 += N) {
-                float2 ml[N], x[N][2 * HS];
+                for (int s = 0; s < HS; ++s) A[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int k0 = 0; k0 < n_runs; k0 += N) {
+                    float2 ml[N], x[N][2 * HS];
 #pragma unroll
-                for (int k = 0; k < N; ++k) {
-                    const size_t at = at0 + min(k0 + k, n_runs - 1) * step;
-                    if (k > 0 && k0 + k >= n_runs) {  // uniform
-                        ml[k] = make_float2(kLowest, 0.0f);
+                    for (int k = 0; k < N; ++k) {
+                        const size_t at = at0 + min(k0 + k, n_runs - 1) * step;
+                        if (k > 0 && k0 + k >= n_runs) {  // uniform
+                            ml[k] = make_float2(kLowest, 0.0f);
 #pragma unroll
-                        for (int s = 0; s < 2 * HS; ++s) x[k][s] = make_float2(0.0f, 0.0f);
-                        continue;
+                            for (int s = 0; s < 2 * HS; ++s) x[k][s] = make_float2(0.0f, 0.0f);
+                            continue;
+                        }
+                        ml[k] = get_shared(stats + (at * 16 + j) * 2);
+#pragma unroll
+                        for (int s = 0; s < 2 * HS; ++s) x[k][s] = get_shared(out + at * 16 * D + (half * 2 * HS + s) * 128 + 2 * me);
                     }
-                    ml[k] = get_shared(stats + (at * 16 + j) * 2);
+                    float Mn = M;
 #pragma unroll
-                    for (int s = 0; s < 2 * HS; ++s) x[k][s] = get_shared(out + at * 16 * D + (half * 2 * HS + s) * 128 + 2 * me);
+                    for (int k = 0; k < N; ++k) Mn = fmaxf(Mn, ml[k].x);
+                    const float f0 = fast_exp2(M - Mn);
+                    M = Mn;
+                    L *= f0;
+#pragma unroll
+                    for (int s = 0; s < HS; ++s)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) A[s][e] *= f0;
+#pragma unroll
+                    for (int k = 0; k < N; ++k) {
+                        const float f = fast_exp2(ml[k].x - M);
+                        L += ml[k].y * f;
+#pragma unroll
+                        for (int s = 0; s < 2 * HS; ++s) {
+                            A[s >> 1][2 * (s & 1)] += x[k][s].x * f;
+                            A[s >> 1][2 * (s & 1) + 1] += x[k][s].y * f;
+                        }
+                    }
                 }
-                float Mn = M;
+                // column j of the block: as above, for the wave whose block it was
+                const int c = block % kColBlocks * 16 + j, t = c / G, tok = tile * WT + block / kColBlocks * TW + t;
+                if (c < TW * G && tok < n_new) {
+                    const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+                    uint16_t *dst = static_cast<uint16_t *>(a.out) + ((size_t)(first + tok) * a.num_q_heads + g * G + c - t * G) * D;
 #pragma unroll
-                for (int k = 0; k < N; ++k) Mn = fmaxf(Mn, ml[k].x);
-                const float f0 = fast_exp2(M - Mn);
-                M = Mn;
-                L *= f0;
-#pragma unroll
-                for (int s = 0; s < HS; ++s)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) A[s][e] *= f0;
-#pragma unroll
-                for (int k = 0; k < N; ++k) {
-                    const float f = fast_exp2(ml[k].x - M);
-                    L += ml[k].y * f;
-#pragma unroll
-                    for (int s = 0; s < 2 * HS; ++s) {
-                        A[s >> 1][2 * (s & 1)] += x[k][s].x * f;
-                        A[s >> 1][2 * (s & 1) + 1] += x[k][s].y * f;
+                    for (int s = 0; s < HS; ++s) {
+                        uint2 w;
+                        w.x = pack_bf16(A[s][0] * inv, A[s][1] * inv);
+                        w.y = pack_bf16(A[s][2] * inv, A[s][3] * inv);
+                        *reinterpret_cast<uint2 *>(dst + 16 * (half * HS + s) + 4 * qd) = w;
                     }
                 }
             }
-            // column j of the block: as above, for the wave whose block it was
-            const int c = block % kColBlocks * 16 + j, t = c / G, tok = tile * WT + block / kColBlocks * TW + t;
-            if (c < TW * G && tok < n_new) {
-                const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-                uint16_t *dst = static_cast<uint16_t *>(a.out) + ((size_t)(first + tok) * a.num_q_heads + g * G + c - t * G) * D;
-#pragma unroll
-                for (int s = 0; s < HS; ++s) {
-                    uint2 w;
-                    w.x = pack_bf16(A[s][0] * inv, A[s][1] * inv);
-                    w.y = pack_bf16(A[s][2] * inv, A[s][3] * inv);
-                    *reinterpret_cast<uint2 *>(dst + 16 * (half * HS + s) + 4 * qd) = w;
-                }
-            }
-        }
+        };
+        using one = std::integral_constant<int, 1>;
+        using two = std::integral_constant<int, 2>;
+        using four = std::integral_constant<int, 4>;
+        using eight = std::integral_constant<int, 8>;
+        if constexpr (D >= 256)
+            add_up(two{}, two{});
+        else if constexpr (D < 128)
+            add_up(one{}, four{});
+        else if (2 * blocks <= kWaves)
+            add_up(two{}, eight{});
+        else
+            add_up(one{}, four{});
         return;
     }
 #pragma unroll

@@ -16,3 +16,9 @@ pytestmark = pytest.mark.gpu
 ])
 def test_many_runs(H, Hkv, D, bs, reqs):
     split.test_split_contexts(H, Hkv, D, bs, reqs)
+
+
+@pytest.mark.parametrize("reqs", [[(5000, 57)], [(5000, 9), (700, 11)], [(1500, 16), (1400, 13), (900, 5)]])
+def test_blocks_of_a_tile(reqs):
+    """Tiles with one to four blocks of 16 columns: added up by halves of their dims, or whole; few runs and many."""
+    split.test_split_contexts(8, 2, 128, 16, reqs)
