@@ -396,9 +396,10 @@ struct ValuReducer {
 // sub-tile is the max over the four token groups (two shuffles).
 template <int DIM>
 struct MfmaReducer {
-    // Workgroups of a decode launch on a CU.  At head_dim 128 three fit, and two are the better ones: more shares,
-    // so more pieces and shorter ones, for a stream that two keep at the memory's rate (230 of 256 requests of 32
-    // to 8 192 tokens, 32 / 8 heads: 246 us with three, 240 with two; 64 of 50 to 300: 23.3 and 19.3).
+    // Workgroups of a decode launch on a CU.  At head_dim 128 three fit, and two are the better ones: fewer shares, so
+    // fewer pieces and shorter merges, for a stream that two keep at the memory's rate, and a plan that two waves of a
+    // SIMD issue in front of the first byte, not three (three / two, 32 / 8 heads: 230 requests of 32 to 8 192 tokens 212.6 / 206.7 us;
+    // 256 of 16 to 80 20.2 / 16.6; 64 of 50 to 300 17.6 / 14.9; one of 30 000 28.2 / 27.5; of 59 batches tried, 3 are up to 7 % faster with three).
     static constexpr int kLeastPerCu = DIM >= 256 ? 1 : DIM == 128 ? 2 : 4, kMostPerCu = DIM == 128 ? 2 : 8;
     static constexpr bool kBF16 = true;
     static constexpr int D = DIM;
