@@ -82,7 +82,8 @@ struct PrefillArgs {
     int32_t max_new_tokens;      // upper bound of q_start[r + 1] - q_start[r]
     int32_t force_rows;          // use the one-wavefront-per-token kernel whatever the geometry
     int32_t slots, head_slots;   // workgroups of a launch that splits the contexts, of a kv head; of another, slots: the
-                                 // (request, head) pairs that go abreast (filled in by launch_prefill)
+                                 // (request, head) pairs that go abreast, 0 if the contexts decide (filled in by launch_prefill)
+    int32_t longest, part;       // then: rules::Together
     uint64_t tag;                // of this call, 48 bits, nonzero: no other call of the process has it
 };
 // Enqueues attention for the new tokens of every request over its paged cache, each token over

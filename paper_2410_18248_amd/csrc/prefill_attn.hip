@@ -70,7 +70,8 @@ __global__ __launch_bounds__(kThreads) void prefill_rows(const PrefillArgs p)
 // full_groups >= 0: a grid of (request, head) pairs x tiles, tiles being the most any request has.
 // All tiles of one pair run on one XCD (workgroups are dealt to the 8 XCDs round-robin in launch
 // order), so its K/V stream is fetched into one L2 and shared there; consecutive heads go to
-// different XCDs; the longest tiles of a pair, or of the pairs that go abreast (p.slots of them), start first.  That holds for the pairs that fill whole
+// different XCDs; the longest tiles of a pair, or of the pairs that go abreast (p.slots of them, or
+// as the contexts say), start first.  That holds for the pairs that fill whole
 // groups of 8; the (pair, tile) items of the remaining 1..7 pairs are dealt round-robin over all
 // XCDs instead of leaving some of them empty.
 //
@@ -92,7 +93,13 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     const DecodeArgs &a = p.d;
     if (full_groups >= 0) {
         const int pairs = heads * a.batch;
-        const rules::Turn turn = rules::deal(blockIdx.x, pairs, full_groups, tiles, p.slots);
+        int abreast = p.slots;
+        if (abreast == 0) {
+            const int lane = threadIdx.x & 63;
+            const int longest = __builtin_amdgcn_readlane(wave_max_to(lane < a.batch ? a.ctx_lens[lane] : 0), 63);
+            abreast = rules::pairs_abreast({p.longest, p.part}, longest, full_groups);
+        }
+        const rules::Turn turn = rules::deal(blockIdx.x, pairs, full_groups, tiles, abreast);
         const int pair = turn.pair;
         int t = turn.t;
         // Where all run at once, two to a CU (the 32 CUs of an XCD are dealt to in turn), and the
@@ -200,7 +207,13 @@ unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bo
     }
     const rules::Launch launch = {(int)heads, p.d.num_q_heads / p.d.num_kv_heads, p.d.head_dim, p.d.batch, p.total_tokens,
                                   p.max_new_tokens, (long long)p.d.max_blocks * p.d.block_size};
-    p.slots = *full_groups >= 0 ? rules::pairs_abreast(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full) : 1;
+    p.slots = 1;
+    if (*full_groups >= 0) {
+        const rules::Together w = rules::together(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full);
+        p.longest = w.longest;
+        p.part = w.part;
+        if (w.longest > 0) p.slots = launch.row <= w.longest ? rules::pairs_abreast(w, (int)launch.row, (int)full) : p.d.batch <= 64 && launch.most >= 128 ? 0 : 1;
+    }
     return tiles < 1 || grid > 0x7fffffffLL ? 0u : (unsigned)grid;
 }
 

@@ -50,13 +50,13 @@ __host__ __device__ inline Turn deal(int block, int pairs, int groups, int tiles
 // Pairs of an XCD (of the `groups` it has) whose tiles are dealt together, the longest of all of them first.  One pair after
 // the other, a launch ends with the long tiles of its last pairs while most of the chip has nothing left; all together,
 // their K / V streams no longer share an L2.  So they go together in even parts of up to 20 MB (head size 256, whose tiles of 64
-// columns read each byte twice as often: 10), as the table row bounds it; not where the chip holds the launch at once, nor where many
+// columns read each byte twice as often: 10), for the longest context; not where the chip holds the launch at once, nor where many
 // workgroups have no tile (6 fp32 prompts of 20 to 428 tokens: 14.5 us, 15.4: those that have one land on half of the CUs).
 // us, append included, one by one / in parts of 4 / 8 or 10 / all: 4 prompts of 1 000, 32 heads of 128 (16 pairs an XCD, 8 MB) 100.9 /
 // 84.6 / 80.7 / 79.0; 4 of 2 048, 40 heads (20 MB) 302 / 271 / 276 / 264; 4 of 4 096 (40 MB) 884 / 830 / 840 / 914; one (5 pairs)
 // 255 / 271 (the last one alone) / - / 214; 8 of 500 on 4 000 cached, 32 heads (72 MB) 343 / 340 / 344 / 396; 8 of 1 900, 8 heads of
 // 64, 76.0 / 71.3 / 60.9; 4 of 4 000, 16 heads of 256 (32 MB), 715 / 729 (in parts of 2: 714) / 758; 4 of 2 000 238 / 222 / 226.
-// Nor over cached positions, as the row bounds them, of more than twice what is new, of as much where a pair's neighbours are another request's:
+// Nor over cached positions of more than twice what is new, of as much where a pair's neighbours are another request's:
 // there a tile's place says less of its length, and the last tiles of the longest contexts end the launch (attention alone, one
 // by one / abreast: 16 requests of 500 on 675 to 2 250, 8 fp32 heads of 64, 251 / 322; 10 of 200 on 270 to 900, 32 heads of 128, 47.4 / 52.1; 16 of
 // 500 on 450 to 1 500, 32 / 8 heads, 188 / 213; 10 of 500 on 225 to 750 there 87 / 82, 32 / 4 heads 81 / 88) -- but if a request has only
@@ -65,16 +65,32 @@ __host__ __device__ inline Turn deal(int block, int pairs, int groups, int tiles
 // Nor up to three tiles of requests that have about as many each: there is next to no tail to fill, and one by one a pair's tiles read
 // its K / V at the same time (27 prompts of 300 to 362, 32 heads of 128, 80.7 / 93.3; 16 of 200 there, row of 300, 34.7 / 36.2; but 4 tiles, 16 of
 // 500, 115 / 103).
-// grid: pairs x tiles; there_are: tiles the requests can have, at most.  Bytes of a cached element, keys and values.
-inline int pairs_abreast(const Launch &l, int bytes, long long tiles, long long grid, long long there_are, int groups)
+// The host knows the longest context by its bound, the length of a table row.  Where that rules nothing out it decides; where it does, a
+// server's rows may be as long as its longest possible request, and the workgroups look at the contexts themselves (a load per lane, so up
+// to 64 requests; 0.2 to 0.5 us in front of everything, so from 128 new tokens on).  Row of 4 096, by the row / by the contexts: 4 prompts of 1 000 on 32
+// heads 99.4 / 79.0; row of 32 768: 4 of 2 048 on 40 heads 302 / 269, one of 4 096 256 / 216, 8 of 1 900 on 8 heads of 64 80.6 / 64.6; contexts that rule it
+// out level.
+struct Together {
+    int longest;                         // pairs go abreast over contexts up to this long, in positions; 0: not at all
+    int part;                            // in parts of this many positions of all of an XCD's pairs
+};
+// grid: pairs x tiles; there_are: tiles the requests can have, at most.  bytes: of a cached element, keys and values.
+inline Together together(const Launch &l, int bytes, long long tiles, long long grid, long long there_are, int groups)
 {
-    if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > there_are + there_are / 4) return 1;
+    if (grid <= 512 || grid >= 8LL * split::kMostDividend || groups < 2 || grid > there_are + there_are / 4) return {0, 1};
     const bool ragged = tiles <= 4 && 20LL * l.most * l.batch >= 27LL * l.total;
-    if (!ragged && (tiles <= 3 || l.row > (l.heads % 8 == 0 ? 3LL : 2LL) * l.most)) return 1;
-    if (l.row > 6LL * l.most) return 1;
-    const long long pair = l.row * l.head_dim * bytes, all = pair * groups;
-    const long long part = (l.head_dim >= 256 ? 10LL : 20LL) << 20, most = (all + part - 1) / part, parts = most < groups ? most : groups;
-    return (int)((groups + parts - 1) / parts);
+    if (!ragged && tiles <= 3) return {0, 1};
+    const long long longest = (ragged ? 6LL : l.heads % 8 == 0 ? 3LL : 2LL) * l.most, top = 1 << 30;
+    const long long part = ((l.head_dim >= 256 ? 10LL : 20LL) << 20) / ((long long)l.head_dim * bytes * groups);
+    return {(int)(longest < top ? longest : top), part < 1 ? 1 : (int)part};
+}
+// The pairs that go abreast, of `groups`, over contexts up to `longest`.
+__host__ __device__ inline int pairs_abreast(const Together &w, int longest, int groups)
+{
+    if (longest > w.longest) return 1;
+    if (longest <= w.part) return groups;
+    const unsigned parts = ((unsigned)longest + w.part - 1) / w.part;
+    return parts < (unsigned)groups ? (groups + parts - 1) / parts : 1;
 }
 
 // Tiles of 64 columns (16 per wave, a stage at a time) instead of 128: three (head size 128, grouped heads) or four workgroups and more

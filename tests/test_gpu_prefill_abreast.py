@@ -14,9 +14,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("H,Hkv,D,dtype,row,reqs", [
     (40, 40, 64, "bf16", 640, [(300, 300), (320, 317), (290, 290), (305, 301), (310, 310)]),   # 25 groups, one by one
-    (18, 9, 64, "bf16", 2048, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over, one by one (rows mostly cached)
-    (32, 8, 256, "bf16", 4096, [(700, 700), (690, 688), (700, 695)]),                         # 3 groups, one by one
-    (16, 16, 256, "bf16", 6144, [(1030, 1030), (1024, 1024)]),                                # 4 groups, one by one
+    (18, 9, 64, "bf16", 2048, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over, one part (the contexts decide)
+    (32, 8, 256, "bf16", 4096, [(700, 700), (690, 688), (700, 695)]),                         # 3 groups, one part (the contexts decide)
+    (16, 16, 256, "bf16", 6144, [(1030, 1030), (1024, 1024)]),                                # 4 groups, one part (the contexts decide)
     (9, 9, 64, "f32", 512, [(400, 400), (390, 390), (410, 401)]),
 ])
 def test_rows(H, Hkv, D, dtype, row, reqs):
@@ -45,4 +45,16 @@ def test_rows(H, Hkv, D, dtype, row, reqs):
     (32, 32, 128, "bf16", 1100, [(200 + 90 * r, 250 if r == 4 else 100 + 8 * r) for r in range(10)]),           # few tiles, 40 groups in two parts
 ])
 def test_parts(H, Hkv, D, dtype, row, reqs):
+    test_rows(H, Hkv, D, dtype, row, reqs)
+
+
+@pytest.mark.parametrize("H,Hkv,D,dtype,row,reqs", [
+    (18, 9, 64, "bf16", 8192, [(600, 600), (590, 580), (610, 610)]),                          # 3 groups, 3 pairs left over, one part
+    (18, 9, 64, "bf16", 8192, [(600, 600), (1190, 580), (1830, 610)]),                        # a context of three times the new tokens: one by one
+    (8, 8, 256, "bf16", 8192, [(3500, 1800), (1790, 1785), (1300, 1290)]),                    # in parts of 2 and 1
+    (9, 9, 64, "f32", 4096, [(400, 400), (390, 390), (410, 401)]),
+    (8, 8, 64, "f32", 8192, [(130 + 3 * r, 130 - r // 2) for r in range(64)]),                     # a request per lane
+])
+def test_contexts_decide(H, Hkv, D, dtype, row, reqs):
+    """A table row that rules nothing in: the workgroups look at the contexts themselves."""
     test_rows(H, Hkv, D, dtype, row, reqs)

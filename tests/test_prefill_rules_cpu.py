@@ -24,8 +24,9 @@ void c_deal(int block, int pairs, int tiles, int abreast, int *out)
 int c_abreast(int heads, int dim, int batch, int total, int most, long long row, int bytes, int wt)
 {
     const long long pairs = (long long)heads * batch, tiles = (most + wt - 1) / wt;
-    return rules::pairs_abreast({heads, 1, dim, batch, total, most, row}, bytes, tiles, pairs / 8 * 8 * tiles + (pairs % 8 * tiles + 7) / 8 * 8,
-                                heads * ((long long)total / wt + batch), (int)(pairs / 8));
+    const rules::Together w = rules::together({heads, 1, dim, batch, total, most, 0}, bytes, tiles,
+                                              pairs / 8 * 8 * tiles + (pairs % 8 * tiles + 7) / 8 * 8, heads * ((long long)total / wt + batch), (int)(pairs / 8));
+    return rules::pairs_abreast(w, (int)row, (int)(pairs / 8));
 }
 int c_narrow(int kv_heads, int group, int dim, int batch, int total, int most, long long row, int tiled)
 {
@@ -149,7 +150,7 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
 
 
 @pytest.mark.parametrize("heads,D,batch,total,most,row,bytes,wt,abreast", [
-    # the launches whose rows are compared on the GPU
+    # the launches whose rows are compared on the GPU, over their contexts and (test_contexts_decide) over long ones
     (40, 64, 5, 1518, 310, 640, 4, 128, 1),
     (40, 64, 5, 1518, 310, 608, 4, 128, 1),
     (40, 64, 5, 2148, 501, 608, 4, 128, 25),
@@ -160,6 +161,13 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
     (9, 64, 3, 1790, 610, 1200, 4, 32, 3),
     (8, 256, 3, 4875, 1800, 3584, 4, 64, 2),
     (32, 128, 10, 1478, 250, 1100, 4, 128, 20),
+    (9, 64, 3, 1790, 610, 610, 4, 32, 3),
+    (9, 64, 3, 1790, 610, 1830, 4, 32, 1),
+    (8, 256, 3, 2083, 700, 700, 4, 16, 3),
+    (16, 256, 2, 2054, 1030, 1030, 4, 64, 4),
+    (8, 256, 3, 4875, 1800, 3500, 4, 64, 2),
+    (9, 64, 3, 1191, 401, 410, 8, 16, 3),
+    (8, 64, 64, 7328, 130, 319, 8, 16, 64),
     # heads of 128, 128 columns: all of the groups of an XCD, parts of 20 MB, one by one where a pair has as much
     (32, 128, 4, 4000, 1000, 1008, 4, 128, 16),
     (40, 128, 4, 8192, 2048, 2048, 4, 128, 20),
@@ -188,6 +196,7 @@ def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
     (8, 64, 16, 8000, 500, 750, 8, 16, 16),
 ])
 def test_pairs_abreast(lib, heads, D, batch, total, most, row, bytes, wt, abreast):
+    """row: the longest context, or its bound."""
     row = ctypes.c_longlong(row)
     assert lib.c_abreast(heads, D, batch, total, most, row, bytes, wt) == abreast
 
