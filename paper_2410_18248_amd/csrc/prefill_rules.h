@@ -96,27 +96,24 @@ __host__ __device__ inline int pairs_abreast(const Together &w, int longest, int
 // Tiles of 64 columns (16 per wave, a stage at a time) instead of 128: three (head size 128, grouped heads) or four workgroups and more
 // to a CU, finer grain, half the columns that a short prompt leaves unused -- but each K / V byte read from LDS for half as
 // many products.  They are the better ones while a launch is bound by the way to each tile's first bytes, not by the matrix
-// cores, that is for a few rounds of the chip.  `wide`: tiles of 128 there are at most.  us with the append, 128 / 64 columns:
-// plain heads of 128: 24 prompts of 16 to 700 on 40 heads (wide 1 880) 69.1 / 65.9; 4 of 50 to 150 on 32 (160) 12.4 / 10.5; one of
-// 1 000 (288) 36.7 / 29.8; 20 of 16 to 64 new on 200 to 1 000 cached (832) 47.2 / 44.5; against it 30 of 16 to 700 on 40 (2 900)
-// 122.6 / 124.5, one of 3 000 on 32 (768) 108 / 116, 3 of 600 to 1 200 (768) 54.3 / 56.9, 30 of 2 to 8 new on 64 to 1 000 (992) 35.9 /
-// 38.0, 4 of 500 on 2 000 (640) 104 / 114.  32 / 8 heads: 30 of 16 to 120 (690) 25.8 / 21.9; 20 of 16 to 64 on 200 to 1 000 (360)
-// 41.4 / 33.4; one of 1 000 (264) 35.3 / 28.4; 12 of 100 to 1 200 (1 456) 82.4 / 84.1; 9 of 89 to 1 490 (1 200) 78 / 98.  Heads of
-// 64: one of 8 192 on 8 (520) 148 / 122; 12 of 100 to 1 200 (470) 30.4 / 25.3; 8 / 2 heads, 30 of 20 to 100 on 100 to 800 24.8 /
-// 20.4; 4 of 4 096 on 8 (1 056) 107 / 117; 32 heads, 4 of 2 048 (2 176) 118 / 131.
-// The lines lie between those.  And: a wave of 16 columns should hold half the tokens that one of 32 does; with groups of 6, 9
-// and 10 it holds a third to two fifths, and only small launches are better off (attention alone: one of 1 000, 40 / 4 heads (336) 32.2 / 26.4;
-// 3 of 300 to 600 there (460) 23.0 / 26.7; 4 of 100 to 300 on 300 to 1 000 (308) 40.3 / 52.8; 24 / 4 heads, 3 of 300 to 600 (308) 22.3 / 19.4).  Over
-// cached positions, past a small launch, narrow tiles are better where wide ones would be half empty (32 / 8 heads: 60 of 4 to 64 on 300
-// to 1 000 (760) 56.7 / 40.8, 10 of 100 to 250 there (496) 40.2 / 45.2; 32 plain heads: 20 of 4 to 64 on 1 000 to 2 000 (704) 101 / 88, 10 of 100 to
-// 250 there (736) 82 / 85, on 300 to 1 000 51 / 47).  Grouped heads of 64, prompts
-// long on average: 32 of 200 to 500 on 8 / 2 (766) 16.9 / 17.5, 6 of 1 000 on 16 / 8 (792) 24.9 / 27.6; short: 24 of 16 to 700 there (728) 18.9 / 15.3, 16 of
-// 154 to 272 on 32 / 8 (936) 16.4 / 14.1.
-//
-// Plain heads of 128, prompts long on average: 12 of 512 on 32 (1 920) 62.1 / 66.8, 14 of 300 to 362 on 40 (1 960) 58.5 / 64.0, 10 of 400 to 600 on 32 (1 536)
-// 55.1 / 51.0; short: 50 of 20 to 128 on 32 (2 272) 28.4 / 25.3.  17 of 31 to 124 on 650 to 2 239 on 32 (860) 100 / 111, 20 of 1 to 5 on 143 to 1 553 on 40 (800)
-// 57.3 / 60.4.  32 plain heads of 64: 30 of 2 to 8 on 1 000 to 2 000 (990) 87 / 72; 10 of 100 to 250 on 300 to 1 000
-// (704) 31.3 / 28.5.
+// cores, that is up to so many tiles of 128 (`wide`, at most), the more the shorter the prompts.  The lines are drawn through 1 050 random
+// launches timed both ways (1 to 250 requests, groups of 1 to 16, 1 to 5 600 new tokens, up to 6 000 cached), where the mean over
+// a range of `wide` comes near level; time of narrow tiles over wide ones, attention alone, below a line / above it:
+//   prompts of 130 on average   plain heads of 128 0.57 (5 800), of 64 0.81 (4 100) / 1.17; grouped, of 128 0.89 (5 800), of 64 0.94 (4 100)
+//      of 220                   plain 128 0.93 (2 000), 64 0.85 (2 000) / 1.17; grouped 128 0.95 (2 900) / 1.0, 64 0.94 (1 450) / 1.0 to 1.06
+//      of 700                   plain 128 0.90 (1 450) / 1.08 (12 of 512), 64 0.91 (2 000) / 1.13; grouped 128 0.93 (1 250) / 1.04, 64 0.9 (900) / 1.0 to 1.1
+//      longer                   plain 128 0.94 (1 000) / 1.03 to 1.10, 64 0.97 (1 400) / 1.0; grouped 128 0.89 (500) / 1.03, 64 0.86 (500) / 1.0 to 1.08
+//   up to 8 new on cached       plain 128 1.02 to 1.06 (800 to 1 000)
+//   new on up to 1 500 cached   heads of 128 0.95 (900) / 0.99, of 64 0.93 (1 100) / 0.97
+//   on more, an average request's up to half a wide tile   128 0.95 (700) / 0.99, 64 0.94 (800); up to a tile 0.96 (500) / 1.02, 0.94 (800)
+//      up to five               128 0.94 (720) / 1.0, 64 0.93 (720) / 0.96 to 1.04
+//      more                     128 0.95 (360) / 1.02 and up to 1.3, 64 0.93 (500) / 1.02
+// Single launches scatter by 0.1 about the mean (how the tiles fill the last round): over cached positions, below the lines, one in fourteen is
+// 5 % and more slower with narrow tiles, up to 24 % (15 of 64 to 128 on 1 000 to 2 000, 32 / 4 heads), above them up to 40 % (21 of 12 to 128 on 1 500 to
+// 2 500, 32 heads of 64), so the lines over long contexts stay at 800 or 900 also where the mean is still 0.95; nothing the host knows tells them.
+// A wave of 16 columns should hold half the tokens that one of 32 does; with groups of 6 it holds two fifths, of 9 and 10 a third, and
+// fewer launches are better off (6: prompts of up to 400 0.94 (1 800), longer 0.92 (400) / 1.17, cached 0.94 (400) / 1.10; 9 and 10: 0.89 (300) /
+// 0.9 to 1.1, longer 1.2 to 1.5; cached 0.79 (200) / 0.9 to 1.3).
 //
 // The length of the contexts is known to the host as that of a row of the block table, their bound: rows longer than twice
 // the most new tokens count as mostly cached.  A caller whose rows are as long as its longest possible request gets the lines for those.
@@ -125,15 +122,20 @@ inline bool narrow_tiles(const Launch &l, bool tiled)
     if (l.group > 16) return false;
     const int wt = 4 * (32 / l.group);   // new tokens of a wide tile
     const long long wide = (long long)l.heads * (l.total / wt + l.batch);
-    const bool prompts = l.row <= 2LL * l.most;
-    if (2 * (16 / l.group) < 32 / l.group) return prompts ? wide <= 400 : l.most < 384 && wide <= 250;
-    if (l.head_dim == 64) {
-        if (!prompts) return wide <= (tiled ? 600 : 1100);
-        return wide <= (l.most > 1200 ? 600 : tiled && l.total > 300LL * l.batch ? 700 : 1200);
+    const bool prompts = l.row <= 2LL * l.most, d64 = l.head_dim == 64;
+    auto average_to = [&l](long long n) { return l.total <= n * l.batch; };
+    if (2 * (16 / l.group) < 32 / l.group) {
+        if (l.group == 6) return wide <= (l.most > 400 ? (prompts ? 500 : 250) : prompts ? 1800 : 500);
+        return wide <= (prompts ? 400 : 250) && (prompts || l.most < 384);
     }
-    if (prompts) return wide <= 400 || (l.most <= 800 && wide <= (tiled ? 800 : l.total > 220LL * l.batch ? 1850 : 2400));
-    const bool half_empty = tiled ? l.most <= 2 * wt : 2LL * l.total <= (long long)wt * l.batch || l.row <= 1280;
-    return l.most < 384 && wide <= (!half_empty ? 400 : tiled ? 800 : 780);
+    if (!prompts && !tiled && !d64 && average_to(8)) return wide <= 400;
+    if (!prompts && l.row <= 1500) return wide <= (d64 ? 1100 : 900);
+    if (!prompts && average_to(5 * wt)) return wide <= (d64 || tiled ? 800 : 900) && (wide <= 600 || d64 || average_to(wt / 2) || !average_to(wt));
+    if (!prompts) return wide <= (d64 ? 600 : 400);
+    if (average_to(130)) return wide <= (d64 && !tiled ? 4500 : 6000);
+    if (average_to(220)) return wide <= (tiled ? (d64 ? 1800 : 3200) : d64 ? 2400 : 2800);
+    if (average_to(700)) return wide <= (tiled ? (d64 ? 1000 : 1300) : d64 ? 2100 : 1800);
+    return wide <= (tiled ? 600 : d64 ? 1400 : 1100);
 }
 
 }  // namespace rules

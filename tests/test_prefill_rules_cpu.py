@@ -98,53 +98,63 @@ def test_the_largest_launches(lib):
 
 
 @pytest.mark.parametrize("H,Hkv,D,batch,total,most,row,narrow", [
-    # half the tokens in half the columns
-    (40, 40, 128, 24, 2950, 683, 688, True),             # an iteration's prompts
-    (32, 32, 128, 1, 1000, 1000, 1008, True),
-    (32, 32, 128, 4, 16000, 4000, 4000, False),
-    (32, 8, 128, 4, 16384, 4096, 4096, False),
-    (32, 8, 128, 1, 1000, 1000, 1008, True),
-    (12, 4, 128, 6, 1200, 300, 1300, True),              # groups of 3, 5, 7
-    (20, 4, 128, 6, 1200, 300, 1300, True),
-    (28, 4, 128, 1, 1000, 1000, 1008, True),
-    (32, 32, 128, 10, 4984, 600, 608, True),             # long on average, and short
+    # prompts, by their length on average
+    (40, 40, 128, 24, 2950, 683, 688, True),             # an iteration's
+    (32, 32, 128, 50, 2690, 128, 128, True),
+    (32, 32, 128, 90, 11520, 250, 256, True),
+    (32, 32, 128, 100, 13000, 250, 256, False),
+    (8, 8, 64, 32, 11200, 500, 512, True),
+    (32, 32, 64, 70, 9000, 250, 256, True),
+    (32, 32, 64, 80, 10000, 250, 256, False),
+    (32, 32, 128, 10, 4984, 600, 608, True),
     (32, 32, 128, 12, 6144, 512, 512, False),
     (40, 40, 128, 14, 4578, 362, 368, False),
-    (32, 32, 128, 50, 2690, 128, 128, True),
-    # fewer than that: groups of 6, 9 and 10
+    (32, 32, 128, 1, 1000, 1000, 1008, True),
+    (32, 32, 128, 4, 16000, 4000, 4000, False),
+    (32, 8, 128, 1, 1000, 1000, 1008, True),
+    (32, 8, 128, 4, 16384, 4096, 4096, False),
+    (8, 2, 64, 60, 8736, 250, 256, True),
+    (8, 2, 64, 32, 11232, 500, 512, True),
+    (16, 8, 64, 6, 6000, 1000, 1008, False),
+    (16, 8, 64, 24, 4290, 683, 688, True),
+    (32, 8, 64, 16, 3376, 272, 272, True),
+    # half the tokens in half the columns: groups of 3, 5, 7; fewer: of 6, 9 and 10
+    (12, 4, 128, 6, 1200, 300, 1300, True),
+    (20, 4, 128, 6, 1200, 300, 1300, True),
+    (28, 4, 128, 1, 1000, 1000, 1008, True),
     (24, 4, 128, 3, 1350, 600, 608, True),
     (48, 8, 128, 6, 1200, 300, 1300, False),
+    (24, 4, 128, 20, 4000, 300, 304, True),
+    (24, 4, 128, 6, 3600, 700, 704, False),
     (36, 4, 128, 3, 1350, 600, 608, False),
     (40, 4, 128, 4, 800, 300, 1300, False),
     (40, 4, 128, 1, 1000, 1000, 1008, True),
     (36, 4, 64, 30, 1700, 120, 128, False),
     (36, 4, 64, 1, 300, 300, 304, True),
-    # cached positions: tiles half empty, and full ones
+    # cached positions: short rows, few new tokens to a tile of 128, more
     (32, 8, 128, 60, 1100, 64, 1040, True),
-    (32, 8, 128, 10, 1750, 250, 1250, False),
+    (32, 8, 128, 10, 1750, 250, 1250, True),
     (32, 8, 128, 4, 800, 300, 2300, True),
+    (32, 8, 128, 10, 1750, 250, 2250, False),
+    (32, 8, 128, 40, 1360, 64, 2064, True),
     (32, 32, 128, 20, 340, 64, 2064, True),
-    (32, 32, 128, 10, 1750, 250, 2250, False),
+    (32, 32, 128, 10, 1750, 250, 2250, True),
     (32, 32, 128, 17, 1260, 124, 2363, False),
-    (40, 40, 128, 20, 55, 5, 1568, False),
     (32, 32, 128, 10, 1750, 250, 1250, True),
-    # grouped heads of 64
-    (8, 2, 64, 60, 8736, 250, 256, True),
-    (8, 2, 64, 32, 11232, 500, 512, False),
-    (16, 8, 64, 6, 6000, 1000, 1008, False),
-    (16, 8, 64, 24, 4290, 683, 688, True),
-    (32, 8, 64, 16, 3376, 272, 272, True),
-    (8, 8, 64, 32, 11200, 500, 512, True),
+    (40, 40, 128, 20, 55, 5, 1568, False),               # a few tokens each
+    (32, 32, 128, 30, 150, 8, 1008, False),
     (32, 8, 64, 20, 680, 64, 2064, True),
-    (32, 8, 64, 60, 1700, 64, 2064, False),
-    (32, 32, 64, 30, 150, 8, 2008, True),
-    (32, 32, 64, 60, 300, 8, 2008, False),
+    (32, 8, 64, 50, 1400, 64, 2064, True),
+    (32, 8, 64, 80, 2700, 64, 2064, False),
+    (32, 32, 64, 24, 120, 8, 2008, True),
+    (32, 32, 64, 30, 150, 8, 2008, False),
     # a row as long as the longest possible request
     (40, 40, 128, 24, 2950, 683, 32768, False),
+    (32, 8, 128, 1, 1000, 1000, 32768, True),
     (64, 2, 128, 4, 400, 100, 112, False),               # groups above 16: no tiles of 64 columns
 ])
 def test_width_of_tiles(lib, H, Hkv, D, batch, total, most, row, narrow):
-    """On both sides of each line, launches that were measured."""
+    """On both sides of the lines."""
     row = ctypes.c_longlong(row)
     assert lib.c_narrow(Hkv, H // Hkv, D, batch, total, most, row, H > Hkv) == narrow
 
