@@ -97,7 +97,7 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
         if (abreast == 0) {
             const int lane = threadIdx.x & 63;
             const int longest = __builtin_amdgcn_readlane(wave_max_to(lane < a.batch ? a.ctx_lens[lane] : 0), 63);
-            abreast = rules::pairs_abreast({p.longest, p.part}, longest, full_groups);
+            abreast = __builtin_amdgcn_readfirstlane(rules::pairs_abreast({p.longest, p.part}, longest, full_groups));
         }
         const rules::Turn turn = rules::deal(blockIdx.x, pairs, full_groups, tiles, abreast);
         const int pair = turn.pair;
