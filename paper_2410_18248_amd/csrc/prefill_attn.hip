@@ -186,8 +186,8 @@ __device__ __forceinline__ bool place(const PrefillArgs &p, int heads, int tiles
     return at.ctx >= at.n_new && at.ctx <= a.max_blocks * a.block_size;
 }
 // The grid for it and what place() needs to know; 0: too large.  `spare`: workgroups without a tile that
-// cost less than finding one's place among the tiles there are.
-unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int *full_groups)
+// cost less than finding one's place among the tiles there are.  `chip`: workgroups it holds at once.
+unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bool by_start, int spare, int chip, int *full_groups)
 {
     const long long pairs = heads * p.d.batch, full = pairs / 8, rest = pairs % 8;
     long long grid = full * tiles * 8 + (rest * tiles + 7) / 8 * 8;
@@ -200,7 +200,7 @@ unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bo
     // 278 tokens 17.7 us together, 18.9 apart; 100 of 10 to 200 32.4 and 34.7; but 24 of 16 to 700 49 and 38, and
     // with 40 of 45 to 278 on 1 000 cached it is 54.4 and 53.8, with heads of 64 45 and 39).
     const bool short_walks = p.max_new_tokens < 320 && (long long)p.d.max_blocks * p.d.block_size < 640;
-    const bool together = !by_start && p.d.head_dim < 256 && heads % 8 != 0 && (grid <= 512 || short_walks);
+    const bool together = !by_start && p.d.head_dim < 256 && heads % 8 != 0 && (grid <= chip || short_walks);
     if (!together && (by_start || p.d.batch <= 64 * kRagged) && most + most / 4 + spare < grid) {
         grid = most;
         *full_groups = p.d.batch <= 64 * kRagged ? -1 : kByStart;
@@ -209,7 +209,7 @@ unsigned place_grid(PrefillArgs &p, long long heads, long long tiles, int WT, bo
                                   p.max_new_tokens, (long long)p.d.max_blocks * p.d.block_size};
     p.slots = 1;
     if (*full_groups >= 0) {
-        const rules::Together w = rules::together(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full);
+        const rules::Together w = rules::together(launch, p.d.bf16 ? 4 : 8, tiles, grid, most, (int)full, chip);
         p.longest = w.longest;
         p.part = w.part;
         if (w.longest > 0) p.slots = launch.row <= w.longest ? rules::pairs_abreast(w, (int)launch.row, (int)full) : p.d.batch <= 64 && launch.most >= 128 ? 0 : 1;
@@ -299,7 +299,7 @@ hipError_t launch_tiles_f32(PrefillArgs p, hipStream_t s)
     // 8 heads of 64 (768 workgroups, 400 tiles), 10.2 us on the full grid, 11.8 ragged; 12 of 8 to 300, 16 / 2
     // heads (3 600 and 1 000), 25.5 and 15.4.  The full grid alone grew with requests x tokens where the most
     // new tokens are not known: 64 prompts of 100, 32 / 8 heads of 128, 1 200 us, 203 so.
-    const unsigned grid = place_grid(p, p.d.num_q_heads / GH, tiles, TW, true, 1024, &full);
+    const unsigned grid = place_grid(p, p.d.num_q_heads / GH, tiles, TW, true, 1024, 512, &full);
     if (grid == 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prefill_tiles_f32<D>, dim3(grid), dim3(kThreads), 0, s, p, (int)tiles, full);
     return hipGetLastError();
@@ -1001,6 +1001,8 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     }
 }
 
+#include "prefill_teams.h"
+
 // The split launch if it is the right one for the sizes; *done says whether it was.
 template <int D, bool TILED, int kCols>
 hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
@@ -1027,6 +1029,19 @@ hipError_t launch_split_prefill(PrefillArgs p, hipStream_t s, bool *done)
     return hipGetLastError();
 }
 
+template <int D, bool TILED, int kCB>
+hipError_t launch_teams(PrefillArgs p, hipStream_t s)
+{
+    constexpr int kLds = 128 << 10;
+    const int WT = 8 * (16 * kCB / (p.d.num_q_heads / p.d.num_kv_heads));
+    const long long tiles = (p.max_new_tokens + WT - 1) / WT;
+    int full = 0;
+    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, false, 0, 256, &full);
+    if (grid == 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((prefill_teams<D, TILED, kCB>), dim3(grid), dim3(512), kLds, s, p, (int)tiles, full);
+    return hipGetLastError();
+}
+
 template <int D, bool TILED, int kCols = kMaxCols>
 hipError_t launch_mfma_prefill(PrefillArgs p, hipStream_t s)
 {
@@ -1046,14 +1061,18 @@ hipError_t launch_mfma_prefill(PrefillArgs p, hipStream_t s)
     const int WT = kWaves * (kCols / G);
     const long long tiles = (p.max_new_tokens + WT - 1) / WT;
     int full = 0;
-    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, false, 0, &full);
+    if constexpr (D >= 128) {
+        const rules::Launch launch = {p.d.num_kv_heads, G, D, p.d.batch, p.total_tokens, p.max_new_tokens, (long long)p.d.max_blocks * p.d.block_size};
+        if (rules::teams(launch)) return launch_teams<D, TILED, D == 128 ? 2 : 1>(p, s);
+    }
+    const unsigned grid = place_grid(p, p.d.num_kv_heads, tiles, WT, false, 0, 512, &full);
     if (grid == 0) return hipErrorInvalidValue;
     if constexpr (kCols == kMaxCols && D <= 128) {
         const long long row = (long long)p.d.max_blocks * p.d.block_size;
         if (rules::narrow_tiles({p.d.num_kv_heads, G, D, p.d.batch, p.total_tokens, p.max_new_tokens, row}, TILED)) {
             const int WT16 = kWaves * (16 / G);
             const long long tiles16 = (p.max_new_tokens + WT16 - 1) / WT16;
-            const unsigned grid16 = place_grid(p, p.d.num_kv_heads, tiles16, WT16, false, 0, &full);
+            const unsigned grid16 = place_grid(p, p.d.num_kv_heads, tiles16, WT16, false, 0, 512, &full);
             if (grid16 == 0) return hipErrorInvalidValue;
             hipLaunchKernelGGL((prefill_mfma<D, TILED, 16, 1, false>), dim3(grid16), dim3(kThreads), 0, s, p, (int)tiles16, full);
             return hipGetLastError();

@@ -25,8 +25,12 @@ int c_abreast(int heads, int dim, int batch, int total, int most, long long row,
 {
     const long long pairs = (long long)heads * batch, tiles = (most + wt - 1) / wt;
     const rules::Together w = rules::together({heads, 1, dim, batch, total, most, 0}, bytes, tiles,
-                                              pairs / 8 * 8 * tiles + (pairs % 8 * tiles + 7) / 8 * 8, heads * ((long long)total / wt + batch), (int)(pairs / 8));
+                                              pairs / 8 * 8 * tiles + (pairs % 8 * tiles + 7) / 8 * 8, heads * ((long long)total / wt + batch), (int)(pairs / 8), 512);
     return rules::pairs_abreast(w, (int)row, (int)(pairs / 8));
+}
+int c_teams(int kv_heads, int group, int dim, int batch, int total, int most, long long row)
+{
+    return rules::teams({kv_heads, group, dim, batch, total, most, row});
 }
 int c_narrow(int kv_heads, int group, int dim, int batch, int total, int most, long long row, int tiled)
 {
@@ -236,3 +240,26 @@ def test_pairs_left_over(lib):
             others = [b for (p, _), b in seen.items() if p < 8 * groups]
             if rest:
                 assert max(left) < min(others) if abreast > 1 else min(left) > max(others)
+
+
+@pytest.mark.parametrize("H,Hkv,D,batch,total,most,row,two_teams", [
+    (32, 8, 128, 4, 16384, 4096, 4096, True),
+    (32, 8, 128, 4, 4000, 1000, 1008, True),
+    (32, 8, 128, 1, 1000, 1000, 1008, False),
+    (32, 4, 128, 41, 5371, 131, 144, False),              # short walks
+    (28, 4, 128, 20, 1750, 103, 592, False),
+    (32, 32, 128, 4, 16000, 4000, 4000, True),
+    (32, 32, 128, 4, 4000, 1000, 1008, False),
+    (40, 40, 128, 24, 2950, 683, 688, False),
+    (32, 32, 128, 16, 4000, 250, 2256, True),             # full tiles
+    (16, 16, 128, 25, 7150, 336, 1008, False),            # half-empty ones
+    (32, 8, 128, 4, 2048, 512, 2560, True),
+    (16, 16, 256, 4, 2048, 512, 2560, True),
+    (16, 16, 256, 1, 700, 700, 704, False),
+    (16, 4, 256, 2, 40, 30, 48, True),                    # grouped heads of 256
+    (32, 1, 256, 4, 4096, 1024, 1024, False),             # more heads than a wave has columns
+    (64, 2, 128, 4, 4096, 1024, 1024, True),
+])
+def test_two_teams(lib, H, Hkv, D, batch, total, most, row, two_teams):
+    lib.c_teams.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong]
+    assert lib.c_teams(Hkv, H // Hkv, D, batch, total, most, row) == two_teams
