@@ -490,6 +490,24 @@ __device__ __forceinline__ bool report_run(uint64_t *first, int stride, int mine
     return __builtin_amdgcn_readfirstlane(last) != 0;
 }
 
+// Stores a column's N slabs of 16 outputs, those of quarter qd being 4 qd .. of each.  Odd and even quarters exchange halves of
+// two slabs, so that a lane stores 16 bytes and an instruction 64 of a row: by 8 and 32, 24 prompts of 16 to 700 tokens on 40 heads took
+// 42.0 us, 39.2 so; 12 of 100 to 700 on 32 / 8 heads 30.4 and 27.5.  By a whole wave.
+template <int N, typename Slabs>
+__device__ __forceinline__ void store_column(uint16_t *dst, int qd, bool mine, float inv, const Slabs &o)
+{
+    static_assert(N % 2 == 0, "slabs go in pairs");
+#pragma unroll
+    for (int s = 0; s < N; s += 2) {
+        uint32_t w[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w[k] = pack_bf16(o[s + (k >> 1)][2 * (k & 1)] * inv, o[s + (k >> 1)][2 * (k & 1) + 1] * inv);
+        const auto x0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
+        const auto x1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
+        if (mine) *reinterpret_cast<uint4 *>(dst + 16 * (s + (qd & 1)) + 8 * (qd >> 1)) = make_uint4(x0[0], x1[0], x0[1], x1[1]);
+    }
+}
+
 // The kernels of narrow tiles: more than two workgroups to a CU.
 template <int D, int kCols, int GRP, bool SPLIT>
 constexpr bool kSmall = D <= 128 && kCols <= 16 && GRP == 1 && !SPLIT;
@@ -843,10 +861,10 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     constexpr bool kLean = (D >= 256 && kCols <= 16) || (kSmall<D, kCols, GRP, SPLIT> && D == 128);
     if (!kLean) read_k(lds);
     const int n_groups = (n_stages + GRP - 1) / GRP;
-    // Instructions are fetched by 32 bytes.  Where in such a line the loops of narrow tiles of heads of 64 begin (20 bytes behind this,
+    // Instructions are fetched by 32 bytes.  Where in such a line the loops of narrow tiles of heads of 64 begin (16 bytes behind this,
     // grouped ones 28) is up to 6 % of their time, least at 4: 10 requests' 16 to 64 on 300 to 1 000 cached, 32 / 8 heads, 13.1 us to
     // 14.1; one prompt of 2 000 on 8 plain heads 27.2 to 29.3.
-    if constexpr (D == 64 && kCols == 16 && GRP == 1 && !SPLIT) asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(TILED ? 2 : 4));
+    if constexpr (D == 64 && kCols == 16 && GRP == 1 && !SPLIT) asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(TILED ? 2 : 5));
     for (int grp = grp0; grp < n_groups; ++grp) {
         char *cur = lds + ((grp - grp0) & (NB - 1)) * GSTAGE, *nxt = lds + ((grp - grp0 + 1) & (NB - 1)) * GSTAGE;
         if ((grp + 1) * GRP * kStage > valid_end) {   // the group holds the last stage: uniform
@@ -958,17 +976,10 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
                 }
                 // column j of the block: as above, for the wave whose block it was
                 const int c = block % kColBlocks * 16 + j, t = c / G, tok = tile * WT + block / kColBlocks * TW + t;
-                if (c < TW * G && tok < n_new) {
-                    const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-                    uint16_t *dst = static_cast<uint16_t *>(a.out) + ((size_t)(first + tok) * a.num_q_heads + g * G + c - t * G) * D;
-#pragma unroll
-                    for (int s = 0; s < HS; ++s) {
-                        uint2 w;
-                        w.x = pack_bf16(A[s][0] * inv, A[s][1] * inv);
-                        w.y = pack_bf16(A[s][2] * inv, A[s][3] * inv);
-                        *reinterpret_cast<uint2 *>(dst + 16 * (half * HS + s) + 4 * qd) = w;
-                    }
-                }
+                const bool mine = c < TW * G && tok < n_new;
+                const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+                store_column<HS>(static_cast<uint16_t *>(a.out) + ((size_t)(first + (mine ? tok : 0)) * a.num_q_heads + g * G + (mine ? c - t * G : 0)) * D + 16 * half * HS,
+                                 qd, mine, inv, A);
             }
         };
         using one = std::integral_constant<int, 1>;
@@ -987,17 +998,8 @@ __global__ __launch_bounds__(kThreads, (D >= 256 && kCols <= 16) ? 2 : (kSmall<D
     }
 #pragma unroll
     for (int b = 0; b < kColBlocks; ++b) {
-        if (pos[b] < 0) continue;
         const float lt = l[b][0];
-        const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        uint16_t *dst = static_cast<uint16_t *>(a.out) + orow[b];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            uint2 w;
-            w.x = pack_bf16(o[b][s][0] * inv, o[b][s][1] * inv);
-            w.y = pack_bf16(o[b][s][2] * inv, o[b][s][3] * inv);
-            *reinterpret_cast<uint2 *>(dst + 16 * s + 4 * qd) = w;
-        }
+        store_column<NS>(static_cast<uint16_t *>(a.out) + orow[b], qd, pos[b] >= 0, lt > 0.0f ? 1.0f / lt : 0.0f, o[b]);
     }
 }
 

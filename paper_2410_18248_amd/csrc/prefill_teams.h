@@ -357,16 +357,6 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
 #pragma unroll
     for (int b = 0; b < kCB; ++b) {
         const float lt = l[b][0];
-        const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        uint16_t *dst = static_cast<uint16_t *>(a.out) + orow[b];
-#pragma unroll
-        for (int s = 0; s < NS; s += 2) {            // lanes of odd and even quarters exchange pieces: 16 bytes a lane
-            uint32_t w[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) w[k] = pack_bf16(o[b][s + (k >> 1)][2 * (k & 1)] * inv, o[b][s + (k >> 1)][2 * (k & 1) + 1] * inv);
-            const auto x0 = __builtin_amdgcn_permlane16_swap(w[0], w[2], false, false);
-            const auto x1 = __builtin_amdgcn_permlane16_swap(w[1], w[3], false, false);
-            if (pos[b] >= 0) *reinterpret_cast<uint4 *>(dst + 16 * (s + (qd & 1)) + 8 * (qd >> 1)) = make_uint4(x0[0], x1[0], x0[1], x1[1]);
-        }
+        store_column<NS>(static_cast<uint16_t *>(a.out) + orow[b], qd, pos[b] >= 0, lt > 0.0f ? 1.0f / lt : 0.0f, o[b]);
     }
 }
