@@ -591,6 +591,115 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
     if (TOGETHER ? tid == 0 : lane == 0) a.share_info[share] = owned;
 }
 
+// ---------------------------------------------------------------- whole ranges
+
+// W waves of a workgroup take a whole range, one (request, kv head / pass), each a stretch of its chunks, and add their states up in LDS:
+// no plan, no pieces and no second launch.  For launches of ranges that are short, or short against the work of the chip; lengths are on the
+// device, so the host goes by the bound of a table row (whole_form).  Bound by latency -- length, table entries, K / V, and at the end the
+// sum -- where the launch is small, otherwise by memory as decode_balanced is.  Both ways, us: one request of 200 tokens, 32 / 8 heads of 128,
+// 7.0 / 4.4; 64 of 50 to 300 on 32 / 8 14.8 / 8.9; 40 of 16 to 130 on 40 plain heads 14.1 / 9.6; 200 of 20 to 250 on 32 / 8 20.6 / 12.9.
+// SORTED: the longest contexts first, where the workgroups come in several rounds and ranges are long enough for the last of
+// them to show (0.15 of a launch of 7 us, for every wave finds the place of its own).
+template <typename R, int W, bool SORTED>
+__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_whole(const DecodeArgs a)
+{
+    constexpr int D = R::D, kPer = kWaves / W;   // ranges of a workgroup
+    constexpr bool kCut = R::CT != R::GT;
+    extern __shared__ __align__(16) float parts[];    // [range][wave][head][D + 2]
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int GH = a.heads_per_pass, passes = a.passes, HC = a.num_kv_heads * passes;
+    const int of = wv / W, sub = wv % W;
+    const int item = blockIdx.x * kPer + of;
+    int nth = __builtin_amdgcn_readfirstlane(item / HC);
+    const int hc = item - nth * HC;
+    int r = nth, C;
+    bool on = true;
+    if constexpr (SORTED) {
+        // the request with the nth longest context (of those that run; ties by place): its bits from the highest on
+        int2 q[4];
+        requests_of(a, 4 * lane, q);
+        unsigned key[4], top = 0;
+        unsigned long long in[4];
+        int running = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            key[k] = q[k].x ? (unsigned)max(q[k].y, 0) + 1 : 0;
+            top = max(top, key[k]);
+            in[k] = __ballot(key[k] > 0);
+            running += __popcll(in[k]);
+        }
+        if (nth >= running) return;
+        top = (unsigned)__builtin_amdgcn_readlane(wave_max_to((int)top), 63);
+        for (int bit = 31 - __builtin_clz(top); bit >= 0; --bit) {
+            unsigned long long set[4];
+            int n = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                set[k] = in[k] & __ballot(key[k] >> bit & 1);
+                n += __popcll(set[k]);
+            }
+            const bool have = nth < n;
+            if (!have) nth -= n;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) in[k] = have ? set[k] : in[k] & ~set[k];
+        }
+        // the nth of those that are left
+        C = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int n = __popcll(in[k]);
+            if (nth >= 0 && nth < n) {
+                unsigned long long left = in[k];
+                for (; nth > 0; --nth) left &= left - 1;
+                const int l = __ffsll((long long)left) - 1;
+                r = 4 * l + k;
+                C = __builtin_amdgcn_readlane(q[k].y, l);
+                nth = -1;
+            } else if (nth >= 0) {
+                nth -= n;
+            }
+        }
+    } else {
+        const int2 q = request_of(a, r);              // (past the batch: does not run)
+        on = __builtin_amdgcn_readfirstlane(q.x) != 0;
+        C = __builtin_amdgcn_readfirstlane(q.y);
+        if (kPer == 1 && !on) return;                 // (else the workgroup's other range may)
+    }
+    const int n = chunks_of(1, C, R::GT);
+    const int g = passes > 1 ? hc / passes : hc, h0 = hc * GH;
+    int each = (n + W - 1) / W;
+    if (kCut && each >= 2) each = (each + 1) & ~1;    // (by whole chunks)
+    const int from = min(n, each * sub);
+    float *x0 = parts + (size_t)of * W * GH * (D + 2);
+    const size_t rh0 = (size_t)r * a.num_q_heads + h0;
+    if (on)
+        R::run(a, r, (size_t)r, g, h0, GH, from * R::GT, min(C, min(n, from + each) * R::GT), [&](int h, int d, float M, float L, const auto &A) {
+            store_partial(x0 + (size_t)(sub * GH + h) * (D + 2), D, d, M, L, A);
+        });
+    __syncthreads();
+    if (!on) return;
+    for (int i = 2 * (64 * sub + lane); i < GH * D; i += 128 * W) {
+        const int h = i / D, d = i % D;
+        const float *x = x0 + h * (D + 2);
+        float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
+        float2 ml[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            ml[w] = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + D);
+            M = fmaxf(M, ml[w].x);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float f = fast_exp2(ml[w].x - M);
+            const float2 o = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + d);
+            L += ml[w].y * f;
+            A[0] += o.x * f;
+            A[1] += o.y * f;
+        }
+        store_out<R::kBF16>(a.out, (rh0 + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
+    }
+}
+
 // N pieces of a split range (first, first + 1, ... in slot order; at most cnt of them), their loads
 // in flight together, folded into the running (M, L, A0, A1) of the lane's two outputs.
 template <int N>
@@ -768,6 +877,48 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
     return hipGetLastError();
 }
 
+// Whether ranges go whole, and how, by the most there can be of them and the longest there can be, a table row, in rounds: the chunks
+// one of four waves walks through.  The lines are drawn through 500 random launches (1 to 256 requests, bf16 and fp32, contexts of a tenth to all of
+// a row) timed with each form; time over that of decode_balanced and its second launch:
+//   vector path, up to 2 rounds        0.63 to 0.72; from 1 024 ranges on by two waves 0.70 (2 048: 0.80; by four 0.85)
+//      to 3                            0.67 to 0.88
+//      to 4                            128 ranges and more 0.81 to 0.84 (fewer 0.98)
+//      to 6                            256 and more 0.92 to 0.95 (fewer 1.03 to 1.18)
+//      to 8                            768 and more 0.95, from 1 024 on sorted 0.88 (0.92 as they come; 512 0.95, but up to 1.1; fewer 1.0 to 1.5)
+//      to 12                           1 024 and more, sorted, 0.88 to 0.98 (512 0.94 to 1.0)
+//      to 24                           2 048 and more, sorted, 0.96 (1 280, 32 requests of 60 to 3 000 tokens, 1.10)
+//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on
+//      to 24                           512 and more, sorted, 0.83 to 0.92 (fewer 1.01 to 1.18)
+// Longer rows: level at best (64 requests of 60 to 6 000 tokens, 40 heads, 1.01), and one long context among short ones would be walked by
+// four waves.
+enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeSorted };
+template <typename R>
+WholeForm whole_form(const DecodeArgs &a, int HC)
+{
+    const long long ranges = (long long)a.batch * HC, row = (long long)a.max_blocks * a.block_size;
+    // (a row of more blocks than there are is no bound of contexts to go by)
+    if (ranges > 0x7fffffff / kThreads || a.max_blocks > a.num_blocks) return kNotWhole;
+    const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
+    const WholeForm sorted = a.batch <= 4 * kLaneBatch ? kWholeSorted : kNotWhole;
+    if (decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads)) {
+        if (rounds_to(3)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
+        if (rounds_to(12)) return ranges >= 1024 && !rounds_to(6) ? sorted : kWholePlain;
+        return rounds_to(24) && ranges >= 512 ? sorted : kNotWhole;
+    }
+    if (rounds_to(2)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
+    if (rounds_to(8) && ranges < 1024) return rounds_to(3) || ranges >= (rounds_to(4) ? 128 : rounds_to(6) ? 256 : 768) ? kWholePlain : kNotWhole;
+    if (rounds_to(6)) return kWholePlain;
+    return ranges >= 1024 && (rounds_to(12) || (rounds_to(24) && ranges >= 2048)) ? sorted : kNotWhole;
+}
+template <typename R, int W, bool SORTED>
+hipError_t launch_whole(const DecodeArgs &a, int HC, hipStream_t s)
+{
+    constexpr int kPer = kWaves / W;                  // ranges of a workgroup
+    hipLaunchKernelGGL((decode_whole<R, W, SORTED>), dim3((unsigned)(((long long)a.batch * HC + kPer - 1) / kPer)), dim3(kThreads),
+                       (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a);
+    return hipGetLastError();
+}
+
 // demand != nullptr: nothing is launched; *demand receives the bytes of partial slots the
 // balanced launch would use with every resident wavefront taking a share.
 template <typename R>
@@ -800,6 +951,12 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     const size_t fit = min((size_t)kMaxShares, a.partial_capacity / per_share);
     const int wgs = min(resident, (int)(fit / kWaves));
     if (wgs < 1) return hipErrorInvalidValue;
+    switch (whole_form<R>(a, HC)) {
+    case kWholeTiny: return launch_whole<R, 2, false>(a, HC, s);
+    case kWholePlain: return launch_whole<R, kWaves, false>(a, HC, s);
+    case kWholeSorted: return launch_whole<R, kWaves, true>(a, HC, s);
+    case kNotWhole: break;
+    }
     // With eight waves and more to a range (if every request runs) they are better off together; with
     // six (16 requests of 60 to 1 500 tokens, 40 heads) the barriers cost 4 % more than they save.
     constexpr int kTogetherWaves = 8;

@@ -1,0 +1,92 @@
+"""lamps_decode_attn where workgroups take whole ranges, and on the other side of that line: rows of few and of many rounds of chunks, few
+ranges and many, two waves to a range, four, and four with the longest contexts first; contexts around a chunk and at the end of the
+row, paused and empty requests, equal lengths, against the fp64 oracle; a call that is replayed from a HIP graph with other lengths."""
+import numpy as np
+import pytest
+import torch
+
+import lamps_workloads as W
+import oracle
+from rig import Rig, n2t, to_f64, tol
+
+pytestmark = pytest.mark.gpu
+
+GEOMS = [("bf16", 8, 8, 64, 16), ("bf16", 6, 6, 128, 32), ("bf16", 2, 2, 256, 16), ("bf16", 16, 4, 64, 16), ("bf16", 16, 2, 128, 32),
+         ("bf16", 32, 1, 128, 16), ("bf16", 10, 2, 256, 16), ("f32", 4, 4, 32, 16), ("f32", 6, 3, 64, 16), ("f32", 16, 2, 128, 32)]
+
+
+def _check(dtype, H, Hkv, D, bs, batch, row, seed):
+    rng = np.random.RandomState(seed)
+    edges = [e for e in (0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 257, row - 17, row - 1, row) if 0 <= e <= row]
+    ctx = [int(x) for x in rng.choice(edges, batch)]
+    ctx[0] = row
+    ctx[batch // 2] = 0 if batch > 2 else ctx[batch // 2]
+    running = [0 if batch > 1 and r % 6 == 1 else 1 for r in range(batch)]
+    blocks = [(c + bs - 1) // bs for c in ctx]
+    geom = W.Geometry(1, H, Hkv, D, bs, sum(blocks) + 4, (row + bs - 1) // bs, dtype)
+    rig = Rig(geom, batch)
+    table, _ = W.deal_block_table(W.permutation(3, geom.num_blocks), ctx, geom)
+    K, V = zip(*[W.logical_kv(70 + 17 * r, geom, c) for r, c in enumerate(ctx)])
+    rig.page_requests(0, table, K, V)
+    q = W.queries(6, geom, batch)
+    got = to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0))
+    ref = oracle.decode_attn(q, K, V, ctx, running)
+    on = np.asarray(running, dtype=bool)
+    assert np.abs(got[on] - ref[on]).max() <= tol(geom), ctx
+    assert (got[~on] == 7.0).all()
+    assert np.array_equal(got, to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0)))
+    rig.close()
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs", GEOMS)
+def test_few_ranges(dtype, H, Hkv, D, bs):
+    """Rows of one to thirteen rounds."""
+    for batch, row in ((1, 16), (1, 100), (3, 130), (7, 260), (9, 400), (12, 520), (4, 800)):
+        _check(dtype, H, Hkv, D, bs, batch, row, batch + row)
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
+    ("bf16", 8, 8, 64, 16, 130, 200), ("bf16", 8, 8, 64, 16, 300, 60), ("bf16", 32, 32, 128, 16, 33, 256), ("bf16", 32, 32, 128, 16, 33, 257),
+    ("bf16", 32, 32, 128, 16, 34, 800), ("bf16", 32, 32, 128, 16, 65, 1600), ("bf16", 16, 8, 128, 16, 129, 190), ("bf16", 16, 8, 128, 16, 128, 400),
+    ("bf16", 16, 8, 128, 16, 66, 1500), ("bf16", 16, 8, 64, 32, 257, 400), ("f32", 8, 8, 64, 16, 129, 600), ("f32", 12, 12, 32, 16, 100, 120),
+])
+def test_many_ranges(dtype, H, Hkv, D, bs, batch, row):
+    _check(dtype, H, Hkv, D, bs, batch, row, 5)
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100)])
+def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
+    """The same graph over contexts that grow, shrink and trade places: order and stretches are worked out in the launch."""
+    rng = np.random.RandomState(9)
+    geom = W.Geometry(1, H, Hkv, D, 16, batch * ((row + 15) // 16) + 4, (row + 15) // 16, dtype)
+    rig = Rig(geom, batch)
+    full = [row] * batch
+    table, _ = W.deal_block_table(W.permutation(3, geom.num_blocks), full, geom)
+    K, V = zip(*[W.logical_kv(70 + 17 * r, geom, row) for r in range(batch)])
+    rig.page_requests(0, table, K, V)
+    q = W.queries(6, geom, batch)
+    dq, dt = n2t(q, rig.dev), torch.as_tensor(table, device=rig.dev)
+    dc = torch.zeros(batch, dtype=torch.int32, device=rig.dev)
+    dm = torch.ones(batch, dtype=torch.uint8, device=rig.dev)
+    out = torch.zeros(q.shape, device=rig.dev, dtype=rig.tdtype)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(rig.compute):
+        rig.lamps.decode_attn(0, batch, dq, dt, dc, dm, out)
+    rig.compute.synchronize()
+    with torch.cuda.graph(graph, stream=rig.compute):
+        rig.lamps.decode_attn(0, batch, dq, dt, dc, dm, out)
+    for turn in range(3):
+        ctx = [int(x) for x in rng.randint(0, row + 1, batch)]
+        mask = [int(x) for x in rng.rand(batch) < 0.8]
+        mask[0] = 1
+        dc.copy_(torch.as_tensor(np.asarray(ctx, dtype=np.int32)))
+        dm.copy_(torch.as_tensor(np.asarray(mask, dtype=np.uint8)))
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        on = np.asarray(mask, dtype=bool)
+        ref = oracle.decode_attn(q, [k[:c] for k, c in zip(K, ctx)], [v[:c] for v, c in zip(V, ctx)], ctx, mask)
+        assert np.abs(to_f64(out)[on] - ref[on]).max() <= tol(geom)
+        assert (to_f64(out)[~on] == 0.0).all()
+    rig.close()
