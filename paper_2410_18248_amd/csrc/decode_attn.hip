@@ -601,9 +601,9 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
 // SORTED: the longest contexts first, where the workgroups come in several rounds and ranges are long enough for the last of
 // them to show (0.15 of a launch of 7 us, for every wave finds the place of its own).
 template <typename R, int W, bool SORTED>
-__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_whole(const DecodeArgs a)
+__global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) void decode_whole(const DecodeArgs a)
 {
-    constexpr int D = R::D, kPer = kWaves / W;   // ranges of a workgroup
+    constexpr int D = R::D, kPer = W > kWaves ? 1 : kWaves / W;   // ranges of a workgroup
     constexpr bool kCut = R::CT != R::GT;
     extern __shared__ __align__(16) float parts[];    // [range][wave][head][D + 2]
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -882,16 +882,18 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
 // a row) timed with each form; time over that of decode_balanced and its second launch:
 //   vector path, up to 2 rounds        0.63 to 0.72; from 1 024 ranges on by two waves 0.70 (2 048: 0.80; by four 0.85)
 //      to 3                            0.67 to 0.88
-//      to 4                            128 ranges and more 0.81 to 0.84 (fewer 0.98)
+//      to 4                            256 ranges and more 0.81 to 0.86, fewer by eight waves 0.84 to 0.91 (by four 0.98)
 //      to 6                            256 and more 0.92 to 0.95 (fewer 1.03 to 1.18)
 //      to 8                            768 and more 0.95, from 1 024 on sorted 0.88 (0.92 as they come; 512 0.95, but up to 1.1; fewer 1.0 to 1.5)
 //      to 12                           1 024 and more, sorted, 0.88 to 0.98 (512 0.94 to 1.0)
 //      to 24                           2 048 and more, sorted, 0.96 (1 280, 32 requests of 60 to 3 000 tokens, 1.10)
-//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on
+//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on;
+//                                      from 8 on with fewer than 256 by eight waves (0.80 to 0.94, by four 0.82 to 0.95)
+//      to 16                           64 to 512 by eight waves, 0.78 to 0.96 (fewer 1.12)
 //      to 24                           512 and more, sorted, 0.83 to 0.92 (fewer 1.01 to 1.18)
 // Longer rows: level at best (64 requests of 60 to 6 000 tokens, 40 heads, 1.01), and one long context among short ones would be walked by
 // four waves.
-enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeSorted };
+enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeEight, kWholeSorted };
 template <typename R>
 WholeForm whole_form(const DecodeArgs &a, int HC)
 {
@@ -899,13 +901,16 @@ WholeForm whole_form(const DecodeArgs &a, int HC)
     // (a row of more blocks than there are is no bound of contexts to go by)
     if (ranges > 0x7fffffff / kThreads || a.max_blocks > a.num_blocks) return kNotWhole;
     const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
+    const bool eight = 8 * a.heads_per_pass * (R::D + 2) * sizeof(float) <= (80u << 10);   // of the LDS: two workgroups to a CU
     const WholeForm sorted = a.batch <= 4 * kLaneBatch ? kWholeSorted : kNotWhole;
     if (decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads)) {
         if (rounds_to(3)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
-        if (rounds_to(12)) return ranges >= 1024 && !rounds_to(6) ? sorted : kWholePlain;
+        if (rounds_to(12)) return ranges >= 1024 && !rounds_to(6) ? sorted : ranges < 256 && eight && !rounds_to(8) ? kWholeEight : kWholePlain;
+        if (rounds_to(16) && ranges >= 64 && ranges < 512 && eight) return kWholeEight;
         return rounds_to(24) && ranges >= 512 ? sorted : kNotWhole;
     }
     if (rounds_to(2)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
+    if (rounds_to(4) && !rounds_to(3) && ranges < 256 && eight) return kWholeEight;
     if (rounds_to(8) && ranges < 1024) return rounds_to(3) || ranges >= (rounds_to(4) ? 128 : rounds_to(6) ? 256 : 768) ? kWholePlain : kNotWhole;
     if (rounds_to(6)) return kWholePlain;
     return ranges >= 1024 && (rounds_to(12) || (rounds_to(24) && ranges >= 2048)) ? sorted : kNotWhole;
@@ -913,9 +918,9 @@ WholeForm whole_form(const DecodeArgs &a, int HC)
 template <typename R, int W, bool SORTED>
 hipError_t launch_whole(const DecodeArgs &a, int HC, hipStream_t s)
 {
-    constexpr int kPer = kWaves / W;                  // ranges of a workgroup
-    hipLaunchKernelGGL((decode_whole<R, W, SORTED>), dim3((unsigned)(((long long)a.batch * HC + kPer - 1) / kPer)), dim3(kThreads),
-                       (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a);
+    constexpr int kPer = W > kWaves ? 1 : kWaves / W, kAll = kPer * W;   // ranges and waves of a workgroup
+    hipLaunchKernelGGL((decode_whole<R, W, SORTED>), dim3((unsigned)(((long long)a.batch * HC + kPer - 1) / kPer)), dim3(64 * kAll),
+                       (size_t)kAll * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a);
     return hipGetLastError();
 }
 
@@ -954,6 +959,7 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     switch (whole_form<R>(a, HC)) {
     case kWholeTiny: return launch_whole<R, 2, false>(a, HC, s);
     case kWholePlain: return launch_whole<R, kWaves, false>(a, HC, s);
+    case kWholeEight: return launch_whole<R, 8, false>(a, HC, s);
     case kWholeSorted: return launch_whole<R, kWaves, true>(a, HC, s);
     case kNotWhole: break;
     }
