@@ -67,10 +67,11 @@ struct AppendArgs {
     const int32_t *q_start;      // [batch + 1] (token form): first new-token row of each request
     int32_t batch, layer, num_layers, num_kv_heads, head_dim, block_size, log2_block_size;
     int32_t max_blocks, num_blocks, bf16, advance;
+    int32_t slices;              // workgroups of a request (decode form; filled in by launch_kv_append)
 };
 
 // Enqueues the append of one new position per running request in one layer.
-hipError_t launch_kv_append(const AppendArgs &a, int tiled, hipStream_t stream);
+hipError_t launch_kv_append(AppendArgs a, int tiled, hipStream_t stream);
 // Enqueues the append of total_tokens new tokens, q_start[r + 1] - q_start[r] of them at the end
 // of request r's context.
 hipError_t launch_kv_append_tokens(const AppendArgs &a, int total_tokens, int tiled, hipStream_t stream);

@@ -10,7 +10,7 @@
 // kernels read (plain or tiled, see lamps.h).  Requests outside the running
 // batch (Algorithm 1) append nothing.
 //
-// One workgroup per request (decode) or per token (many tokens at once).  In
+// One workgroup per request (decode; several of a long row) or per token (many tokens at once).  In
 // the decode form all threads read the request's context length, meet at a
 // barrier, then scatter; with `advance` thread 0 stores length + 1 after the
 // barrier, so nobody can read the new value.  A position outside the
@@ -26,17 +26,17 @@ namespace {
 constexpr int kAppendThreads = 256;
 
 // Writes the key and value vectors kn, vn ([H_kv][D]) of one token at cached position t of request r.
-// Called by a whole workgroup; EARLY: k0 and v0 are what this thread takes of them first, asked for
-// before anything is known of where they go.  A position outside the block-table row, or a block id
+// Called by the workgroups of a token, of which this is number `slice` of `slices`; EARLY: k0 and v0 are what this thread
+// takes of them first, asked for before anything is known of where they go.  A position outside the block-table row, or a block id
 // outside the pool, writes nothing.
 template <typename T>
-__device__ __forceinline__ uint4 first_unit(const AppendArgs &a, const T *x)
+__device__ __forceinline__ uint4 first_unit(const AppendArgs &a, const T *x, int slice)
 {
-    const int i = threadIdx.x * (16 / (int)sizeof(T));
+    const int i = (slice * kAppendThreads + threadIdx.x) * (16 / (int)sizeof(T));
     return i < a.num_kv_heads * a.head_dim ? *reinterpret_cast<const uint4 *>(x + i) : make_uint4(0, 0, 0, 0);
 }
 template <typename T, bool TILED, bool EARLY>
-__device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t, const T *kn, const T *vn, uint4 k0, uint4 v0)
+__device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t, const T *kn, const T *vn, uint4 k0, uint4 v0, int slice, int slices)
 {
     const int D = a.head_dim, Hkv = a.num_kv_heads, bs = a.block_size;
     const int lb = t >> a.log2_block_size, slot = t & (bs - 1);
@@ -49,8 +49,9 @@ __device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t,
     // 16 bytes at a time wherever 16 bytes of a vector stay together in the tile: keys in
     // both layouts (8 dims of a key are contiguous), values in the plain layout
     constexpr int V16 = 16 / (int)sizeof(T);
-    for (int i = threadIdx.x * V16; i < Hkv * D; i += kAppendThreads * V16) {
-        if (!EARLY || i >= kAppendThreads * V16) {
+    const int step = slices * kAppendThreads * V16;
+    for (int i = (slice * kAppendThreads + threadIdx.x) * V16; i < Hkv * D; i += step) {
+        if (!EARLY || i >= step) {
             k0 = *reinterpret_cast<const uint4 *>(kn + i);
             v0 = *reinterpret_cast<const uint4 *>(vn + i);
         }
@@ -79,18 +80,20 @@ __device__ __forceinline__ bool scatter_token(const AppendArgs &a, int r, int t,
 
 // Bound by the round trips in front of the stores: mask, length and the vectors are asked for
 // together, then the table entry.  4 layers of append + decode for 16 requests on 40 heads of 128:
-// 116.7 us with each asked for when the one before had come, 113.8 now.
+// 116.7 us with each asked for when the one before had come, 113.8 then; with a unit per thread in place of two and a half one
+// after the other (4 layers of 16 requests, ranges cut: 106.4 -> 104.2; of 16 up to 600 tokens, 87.0 -> 85.3; where a workgroup takes a request level).
 template <typename T, bool TILED>
 __global__ __launch_bounds__(kAppendThreads) void kv_append(const AppendArgs a)
 {
     const int r = blockIdx.x;
     const size_t row = (size_t)r * a.num_kv_heads * a.head_dim;
     const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
-    const uint4 k0 = first_unit(a, kn), v0 = first_unit(a, vn);
+    const int slice = blockIdx.y, slices = a.slices;
+    const uint4 k0 = first_unit(a, kn, slice), v0 = first_unit(a, vn, slice);
     const int t = a.ctx_lens[r];
     if (!a.running[r]) return;                        // uniform over the workgroup
     __syncthreads();
-    const bool ok = scatter_token<T, TILED, true>(a, r, t, kn, vn, k0, v0);
+    const bool ok = scatter_token<T, TILED, true>(a, r, t, kn, vn, k0, v0, slice, slices);
     if (ok && a.advance && threadIdx.x == 0) a.ctx_lens[r] = t + 1;
 }
 
@@ -108,12 +111,12 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendA
     const int n = blockIdx.x;
     const size_t row = (size_t)n * a.num_kv_heads * a.head_dim;
     const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
-    const uint4 none = make_uint4(0, 0, 0, 0), k0 = EARLY ? first_unit(a, kn) : none, v0 = EARLY ? first_unit(a, vn) : none;
+    const uint4 none = make_uint4(0, 0, 0, 0), k0 = EARLY ? first_unit(a, kn, 0) : none, v0 = EARLY ? first_unit(a, vn, 0) : none;
     const int r = last_request(a.q_start, a.batch, n, [](int q, int) { return q; });
     const int first = a.q_start[r], count = a.q_start[r + 1] - first;
     if (n >= first + count) return;                   // q_start[batch] is less than the grid
     const int t = a.ctx_lens[r] - count + (n - first);
-    scatter_token<T, false, EARLY>(a, r, t, kn, vn, k0, v0);
+    scatter_token<T, false, EARLY>(a, r, t, kn, vn, k0, v0, 0, 1);
 }
 
 // The same for the tiled layout (bf16), where the 16-byte unit of a value tile is four
@@ -206,10 +209,14 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const A
 
 }  // namespace
 
-hipError_t launch_kv_append(const AppendArgs &a, int tiled, hipStream_t stream)
+hipError_t launch_kv_append(AppendArgs a, int tiled, hipStream_t stream)
 {
     if (a.batch == 0) return hipSuccess;
-    dim3 grid((unsigned)a.batch), block(kAppendThreads);
+    // A unit per thread, by as many workgroups as that takes of a request -- except where the call advances the lengths, which the
+    // request's other workgroups may have yet to read.
+    const int unit = 16 / (a.bf16 ? 2 : 4);
+    a.slices = a.advance ? 1 : (a.num_kv_heads * a.head_dim + kAppendThreads * unit - 1) / (kAppendThreads * unit);
+    dim3 grid((unsigned)a.batch, (unsigned)a.slices), block(kAppendThreads);
     if (a.bf16) {
         if (tiled)
             hipLaunchKernelGGL((kv_append<uint16_t, true>), grid, block, 0, stream, a);
