@@ -609,7 +609,10 @@ __global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) voi
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int GH = a.heads_per_pass, passes = a.passes, HC = a.num_kv_heads * passes;
     const int of = wv / W, sub = wv % W;
-    const int item = blockIdx.x * kPer + of;
+    int item = blockIdx.x * kPer + of;
+    // Every other 256 of them, one to a CU, the other way round: where the chip holds all at once a CU else has the longest of each
+    // 256 (as they come / so, us: 4 layers of 32 requests of 60 to 1 500 tokens, 32 heads, 202 / 195; 128 of those on 32 / 8 heads 45.1 / 43.2).
+    if (SORTED && (item & 256) && (item | 255) < a.batch * HC) item ^= 255;
     int nth = __builtin_amdgcn_readfirstlane(item / HC);
     const int hc = item - nth * HC;
     int r = nth, C;
