@@ -593,6 +593,46 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
 
 // ---------------------------------------------------------------- whole ranges
 
+// Chunks c0 .. c1 - 1 of a range by W waves of a workgroup, a stretch each, whose states are added up through x0 ([wave][head][D + 2], LDS)
+// and given to out(first head's row, head, dim, M, L, two outputs).  `on`: false for waves that only keep others company at the barrier.
+template <typename R, int W, typename Out>
+__device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int sub, int r, int hc, int c0, int c1, int C, bool on, Out out)
+{
+    constexpr int D = R::D;
+    constexpr bool kCut = R::CT != R::GT;
+    const int lane = threadIdx.x & 63, GH = a.heads_per_pass, passes = a.passes;
+    const int g = passes > 1 ? hc / passes : hc, h0 = hc * GH, n = c1 - c0;
+    int each = (n + W - 1) / W;
+    if (kCut && each >= 2) each = (each + 1) & ~1;    // (by whole chunks)
+    const int from = min(n, each * sub);
+    const size_t rh0 = (size_t)r * a.num_q_heads + h0;
+    if (on)
+        R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * R::GT, min(C, (c0 + min(n, from + each)) * R::GT),
+               [&](int h, int d, float M, float L, const auto &A) { store_partial(x0 + (size_t)(sub * GH + h) * (D + 2), D, d, M, L, A); });
+    __syncthreads();
+    if (!on) return;
+    for (int i = 2 * (64 * sub + lane); i < GH * D; i += 128 * W) {
+        const int h = i / D, d = i % D;
+        const float *x = x0 + h * (D + 2);
+        float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
+        float2 ml[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            ml[w] = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + D);
+            M = fmaxf(M, ml[w].x);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float f = fast_exp2(ml[w].x - M);
+            const float2 o = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + d);
+            L += ml[w].y * f;
+            A[0] += o.x * f;
+            A[1] += o.y * f;
+        }
+        out(rh0, h, d, M, L, A);
+    }
+}
+
 // W waves of a workgroup take a whole range, one (request, kv head / pass), each a stretch of its chunks, and add their states up in LDS:
 // no plan, no pieces and no second launch.  For launches of ranges that are short, or short against the work of the chip; lengths are on the
 // device, so the host goes by the bound of a table row (whole_form).  Bound by latency -- length, table entries, K / V, and at the end the
@@ -604,7 +644,6 @@ template <typename R, int W, bool SORTED>
 __global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) void decode_whole(const DecodeArgs a)
 {
     constexpr int D = R::D, kPer = W > kWaves ? 1 : kWaves / W;   // ranges of a workgroup
-    constexpr bool kCut = R::CT != R::GT;
     extern __shared__ __align__(16) float parts[];    // [range][wave][head][D + 2]
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int GH = a.heads_per_pass, passes = a.passes, HC = a.num_kv_heads * passes;
@@ -669,38 +708,98 @@ __global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) voi
         if (kPer == 1 && !on) return;                 // (else the workgroup's other range may)
     }
     const int n = chunks_of(1, C, R::GT);
-    const int g = passes > 1 ? hc / passes : hc, h0 = hc * GH;
-    int each = (n + W - 1) / W;
-    if (kCut && each >= 2) each = (each + 1) & ~1;    // (by whole chunks)
-    const int from = min(n, each * sub);
     float *x0 = parts + (size_t)of * W * GH * (D + 2);
-    const size_t rh0 = (size_t)r * a.num_q_heads + h0;
-    if (on)
-        R::run(a, r, (size_t)r, g, h0, GH, from * R::GT, min(C, min(n, from + each) * R::GT), [&](int h, int d, float M, float L, const auto &A) {
-            store_partial(x0 + (size_t)(sub * GH + h) * (D + 2), D, d, M, L, A);
-        });
-    __syncthreads();
-    if (!on) return;
-    for (int i = 2 * (64 * sub + lane); i < GH * D; i += 128 * W) {
-        const int h = i / D, d = i % D;
-        const float *x = x0 + h * (D + 2);
-        float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
-        float2 ml[W];
+    stretches<R, W>(a, x0, sub, r, hc, 0, n, C, on, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
+        store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
+    });
+}
+
+// The same with a range cut into up to `cuts` parts, a workgroup each, of at least a chunk per wave; the parts of a range are
+// added up by a second launch, which works them out from the lengths as this one does.  How many parts there can be is the
+// host's, so neither launch has a plan or records of shares in front of its first byte: one request of 1 999 tokens, 32 / 8 heads, 9.3 -> 7.2 us
+// (5.2 + 3.7 -> 4.3 + 2.8), one of 4 000 on 8 plain heads of 64 9.0 -> 7.8.
+template <typename R, int W>
+__device__ __forceinline__ int part_chunks(int n, int cuts)
+{
+    constexpr int kChunk = R::CT / R::GT;
+    return max(W * kChunk, ((n + cuts - 1) / cuts + kChunk - 1) / kChunk * kChunk);
+}
+template <typename R>
+__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const DecodeArgs a, const int cuts)
+{
+    constexpr int D = R::D;
+    extern __shared__ __align__(16) float parts[];    // [wave][head][D + 2]
+    const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes, ranges = a.batch * HC;
+    const int part = __builtin_amdgcn_readfirstlane(blockIdx.x / ranges), range = blockIdx.x - part * ranges;
+    const int r = __builtin_amdgcn_readfirstlane(range / HC), hc = range - r * HC;
+    const int2 q = request_of(a, r);
+    if (!__builtin_amdgcn_readfirstlane(q.x)) return;
+    const int C = __builtin_amdgcn_readfirstlane(q.y), n = chunks_of(1, C, R::GT);
+    const int each = part_chunks<R, kWaves>(n, cuts), c0 = part * each;
+    if (c0 >= n) return;
+    const bool all = each >= n;
+    float *slot = a.partials + ((size_t)range * cuts + part) * GH * (D + 2);
+    stretches<R, kWaves>(a, parts, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r, hc, c0, min(n, c0 + each), C, true,
+                         [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
+                             if (all)
+                                 store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
+                             else
+                                 store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
+                         });
+}
+
+// Adds the parts of a range up: 128 (head, dim) outputs a workgroup, two per lane, its waves every eighth part.  One round trip: the parts there
+// can be are asked for together with the length that says how many there are.
+constexpr int kPartWaves = 8, kMostCuts = 64;
+template <typename R>
+__global__ __launch_bounds__(64 * kPartWaves) void decode_merge_parts(const DecodeArgs a, const int cuts)
+{
+    constexpr int D = R::D, N = kMostCuts / kPartWaves;
+    __shared__ float4 sums[kPartWaves][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
+    const int range = blockIdx.x, r = range / HC, hc = range - r * HC;
+    const int idx = min((int)blockIdx.y * 128 + 2 * lane, GH * D - 2), h = idx / D, d = idx % D;
+    const int running = a.running[r], length = a.ctx_lens[r];
+    float2 ml[N], ao[N];
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            ml[w] = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + D);
-            M = fmaxf(M, ml[w].x);
+    for (int k = 0; k < N; ++k) {
+        const int part = wv + kPartWaves * k;
+        ml[k] = make_float2(kLowest, 0.0f);
+        ao[k] = make_float2(0.0f, 0.0f);
+        if (part < cuts) {                            // uniform
+            const float2 *x = reinterpret_cast<const float2 *>(a.partials + (((size_t)range * cuts + part) * GH + h) * (D + 2));
+            ml[k] = x[D / 2];
+            ao[k] = x[d / 2];
         }
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const float f = fast_exp2(ml[w].x - M);
-            const float2 o = *reinterpret_cast<const float2 *>(x + w * GH * (D + 2) + d);
-            L += ml[w].y * f;
-            A[0] += o.x * f;
-            A[1] += o.y * f;
-        }
-        store_out<R::kBF16>(a.out, (rh0 + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
     }
+    if (!running) return;                             // uniform
+    const int C = min(length, a.max_blocks * a.block_size), n = chunks_of(1, C, R::GT), each = part_chunks<R, kWaves>(n, cuts);
+    if (each >= n) return;                            // written already
+    float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        if ((wv + kPartWaves * k) * each >= n) break;
+        const float Mn = fmaxf(M, ml[k].x), f0 = fast_exp2(M - Mn), f = fast_exp2(ml[k].x - Mn);
+        L = L * f0 + ml[k].y * f;
+        A[0] = A[0] * f0 + ao[k].x * f;
+        A[1] = A[1] * f0 + ao[k].y * f;
+        M = Mn;
+    }
+    sums[wv][lane] = make_float4(M, L, A[0], A[1]);
+    __syncthreads();
+    if (wv > 0) return;
+#pragma unroll
+    for (int k = 1; k < kPartWaves; ++k) {
+        const float4 o = sums[k][lane];
+        const float Mn = fmaxf(M, o.x), f0 = fast_exp2(M - Mn), f = fast_exp2(o.x - Mn);
+        L = L * f0 + o.y * f;
+        A[0] = A[0] * f0 + o.z * f;
+        A[1] = A[1] * f0 + o.w * f;
+        M = Mn;
+    }
+    if (blockIdx.y * 128 + 2 * lane < GH * D)
+        store_out<R::kBF16>(a.out, ((size_t)r * a.num_q_heads + hc * GH + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
 }
 
 // N pieces of a split range (first, first + 1, ... in slot order; at most cnt of them), their loads
@@ -918,6 +1017,42 @@ WholeForm whole_form(const DecodeArgs &a, int HC)
     if (rounds_to(6)) return kWholePlain;
     return ranges >= 1024 && (rounds_to(12) || (rounds_to(24) && ranges >= 2048)) ? sorted : kNotWhole;
 }
+// Parts that ranges are cut into at most, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
+// records of decode_balanced are a third of the time.  Workgroups in all 256, or 512 where rows are long for them: the same 400 random launches of
+// up to 400 ranges, time over the other forms' with 256 / 512 / 1 024:
+//   vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 / 0.89, more 0.93 / 0.87 / 0.87
+//      16 to 32               4 to 16 rounds 0.85 / 0.86 / 0.90, to 128 0.98 / 0.89 / 0.93, more 1.10 / 0.98 / 1.01
+//      32 to 64               4 to 32 rounds 0.92 / 0.87 / 0.90, to 128 1.14 / 0.96 / 0.96, more 1.40 / 1.06 / 1.0
+//      64 to 128              4 to 32 rounds 1.1 / 0.95 / 0.95, more 1.6 and up / 1.1 and up / 1.02 and up;  more ranges 1.1 and up
+//   matrix path, fewer than 32 ranges, 8 to 128 rounds 0.79 / 0.84 / 0.86 (fewer 1.1), more 0.88 / 0.89 / 0.92
+//      32 to 64               8 to 128 rounds 0.89 / 0.89 / 0.96, more 0.98 / 0.97 / 1.03
+//      64 to 128              16 to 32 rounds 0.91 / 0.87 / 0.91 (else 1.0 and up);  more ranges 1.0 and up
+template <typename R>
+int cuts_of(const DecodeArgs &a, int HC)
+{
+    const long long ranges = (long long)a.batch * HC, row = (long long)a.max_blocks * a.block_size;
+    if (ranges >= 128 || a.max_blocks > a.num_blocks) return 0;
+    const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
+    const bool matrix = decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads);
+    // (the more ranges, the more a long one among short ones costs: it has its parts and no others; 5 of 1 306 to 13 065 tokens on 8 heads of
+    // 64 1.1, 4 of 131 to 4 390 on 32 / 8 fp32 heads 1.15)
+    const int most = matrix ? (ranges < 32 ? 400 : ranges < 64 ? 128 : 32) : ranges < 16 ? 400 : ranges < 32 ? 64 : ranges < 64 ? 32 : 16;
+    const int least = matrix ? (ranges >= 64 ? 16 : R::D < 128 ? 12 : 8) : 4;
+    if (rounds_to(least) || !rounds_to(most)) return 0;
+    const bool few = matrix ? ranges < 64 && rounds_to(128) : ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
+    const int cuts = min(kMostCuts, (few ? 256 : 512) / (int)ranges);
+    return (size_t)ranges * cuts * a.heads_per_pass * (R::D + 2) * sizeof(float) <= a.partial_capacity ? cuts : 0;
+}
+template <typename R>
+hipError_t launch_parts(const DecodeArgs &a, int HC, int cuts, hipStream_t s)
+{
+    const int ranges = a.batch * HC;
+    hipLaunchKernelGGL(decode_parts<R>, dim3(ranges * cuts), dim3(kThreads), (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a, cuts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(decode_merge_parts<R>, dim3(ranges, (a.heads_per_pass * a.head_dim + 127) / 128), dim3(64 * kPartWaves), 0, s, a, cuts);
+    return hipGetLastError();
+}
 template <typename R, int W, bool SORTED>
 hipError_t launch_whole(const DecodeArgs &a, int HC, hipStream_t s)
 {
@@ -959,6 +1094,8 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     const size_t fit = min((size_t)kMaxShares, a.partial_capacity / per_share);
     const int wgs = min(resident, (int)(fit / kWaves));
     if (wgs < 1) return hipErrorInvalidValue;
+    const int cuts = cuts_of<R>(a, HC);
+    if (cuts > 0) return launch_parts<R>(a, HC, cuts, s);
     switch (whole_form<R>(a, HC)) {
     case kWholeTiny: return launch_whole<R, 2, false>(a, HC, s);
     case kWholePlain: return launch_whole<R, kWaves, false>(a, HC, s);

@@ -1,6 +1,6 @@
-"""lamps_decode_attn where workgroups take whole ranges, and on the other side of that line: rows of few and of many rounds of chunks, few
-ranges and many, two waves to a range, four, and four with the longest contexts first; contexts around a chunk and at the end of the
-row, paused and empty requests, equal lengths, against the fp64 oracle; a call that is replayed from a HIP graph with other lengths."""
+"""lamps_decode_attn where workgroups take whole ranges, or ranges in parts, and on the other side of those lines: rows of few and of many rounds of
+chunks, few ranges and many, two waves to a range, four, eight, and four with the longest contexts first; contexts around a chunk, a part and at
+the end of the row, paused and empty requests, equal lengths, against the fp64 oracle; a call that is replayed from a HIP graph with other lengths."""
 import numpy as np
 import pytest
 import torch
@@ -29,6 +29,7 @@ def _check(dtype, H, Hkv, D, bs, batch, row, seed):
     K, V = zip(*[W.logical_kv(70 + 17 * r, geom, c) for r, c in enumerate(ctx)])
     rig.page_requests(0, table, K, V)
     q = W.queries(6, geom, batch)
+    rig.workspace.fill_(255)                             # NaN where no part writes
     got = to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0))
     ref = oracle.decode_attn(q, K, V, ctx, running)
     on = np.asarray(running, dtype=bool)
@@ -45,6 +46,13 @@ def test_few_ranges(dtype, H, Hkv, D, bs):
         _check(dtype, H, Hkv, D, bs, batch, row, batch + row)
 
 
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs", GEOMS)
+def test_parts(dtype, H, Hkv, D, bs):
+    """Few ranges of longer rows."""
+    for batch, row in ((1, 600), (1, 3001), (3, 1040), (4, 2080), (6, 1300)):
+        _check(dtype, H, Hkv, D, bs, batch, row, batch + row)
+
+
 @pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
     ("bf16", 8, 8, 64, 16, 130, 200), ("bf16", 8, 8, 64, 16, 300, 60), ("bf16", 32, 32, 128, 16, 33, 256), ("bf16", 32, 32, 128, 16, 33, 257),
     ("bf16", 32, 32, 128, 16, 34, 800), ("bf16", 32, 32, 128, 16, 65, 1600), ("bf16", 16, 8, 128, 16, 129, 190), ("bf16", 16, 8, 128, 16, 128, 400),
@@ -54,7 +62,7 @@ def test_many_ranges(dtype, H, Hkv, D, bs, batch, row):
     _check(dtype, H, Hkv, D, bs, batch, row, 5)
 
 
-@pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100)])
+@pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100)])
 def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
     """The same graph over contexts that grow, shrink and trade places: order and stretches are worked out in the launch."""
     rng = np.random.RandomState(9)
