@@ -143,11 +143,11 @@ inline bool narrow_tiles(const Launch &l, bool tiled)
 // random launches timed both ways (1 to 48 requests, groups of 1 to 8, 24 to 6 000 new tokens, up to 6 000 cached), where the mean
 // over a range of tiles (`all`, at most) comes near level; time over that of the other kernels, attention alone, above a line / below it:
 //   prompts of four tiles and more on average   heads of 128 0.94 (400 and more) / 1.01 to 1.13, plain 0.95 / 1.09; plain heads of 256 0.92 (250) / 1.05
-//      of two to four       heads of 128 0.94 (1 500) / 1.02 to 1.18, plain 0.99 / 1.08; plain heads of 256 0.88 (1 500) / 1.0
+//      of two to four       heads of 128 0.94 (1 500) / 1.02 to 1.18, plain 0.99 to 1.07 / 1.08; plain heads of 256 0.88 (1 500) / 1.0
 //   on cached positions, four and more          heads of 128 0.90 (250) / 1.14, plain 0.93 / 1.3; plain heads of 256 0.87 / 0.9 to 1.05
 //      two to four          heads of 128 0.92 (250) / 1.06, plain 0.99 (700) / 1.1; plain heads of 256 0.92 / 1.06
 //      four fifths to two   plain heads of 128 0.93 (700) / 1.05; of 256 0.77 (250) / 1.2
-// Not for short walks: grouped heads of 128, prompts of 150 to 200 on average 1.05 to 1.2, of 300 to 400 0.92; 20 of 72 to 103 on 97 to 486 1.24.
+// Not for short walks: grouped heads of 128, prompts of 150 to 200 on average 1.05 to 1.2, of 300 to 430 1.03 to 1.07; 20 of 72 to 103 on 97 to 486 1.24.
 // Grouped heads of 256, whose other kernel holds one workgroup of four waves to a CU: 0.91 throughout (47 launches).
 inline bool teams(const Launch &l)
 {
@@ -157,11 +157,11 @@ inline bool teams(const Launch &l)
     const long long wt = 8 * (columns / l.group), all = l.heads * (l.total / wt + l.batch);
     const bool prompts = l.row <= 2LL * l.most, plain = l.group == 1;
     auto tiles = [&l, wt](int n) { return l.total >= n * wt * l.batch; };   // on average
-    if (prompts ? l.total < 300LL * l.batch : l.row < 600) return false;
+    if (prompts ? l.total < 450LL * l.batch : l.row < 600) return false;
     // few tiles: the average request's leave little of them empty (25 of 235 to 336 on 134 to 672, 16 plain heads of 128, 1.27; 10 of 324 to 464 on 40 1.11)
     const long long average = l.total / l.batch, filled = (average + wt - 1) / wt * wt;
     if (!tiles(4) && 5 * average < 4 * filled) return false;
-    if (prompts) return all >= (tiles(4) ? (l.head_dim >= 256 ? 256 : 400) : tiles(2) ? 1500 : 1LL << 40);
+    if (prompts) return all >= (tiles(4) ? (l.head_dim >= 256 ? 256 : 400) : tiles(2) && (!plain || l.head_dim >= 256) ? 1500 : 1LL << 40);
     if (tiles(4)) return all >= 256;
     if (tiles(2)) return all >= (plain && l.head_dim < 256 ? 700 : 256);
     return plain && all >= (l.head_dim < 256 ? 700 : 256);

@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # heads, block, new tokens, cached.  Tiles of 256 / G tokens (128 / G at 256), 32 / G (16 / G) to a wave
-    (32, 2, 128, 16, [300, 304, 320, 321, 330, 388, 297] * 8, 0),             # 16 to a group: 16 tokens a tile, 2 a wave
-    (56, 8, 128, 16, [300, 301, 319, 340, 333], 0),                                # 7 to a group: 32 a tile, 4 columns of a wave empty
-    (128, 4, 128, 32, [310, 292, 300], 5),                                    # 32 to a group
+    (32, 2, 128, 16, [470, 464, 480, 481, 450, 455, 449], 0),             # 16 to a group: 16 tokens a tile, 2 a wave
+    (56, 8, 128, 16, [470, 451, 449, 460], 0),                                # 7 to a group: 32 a tile, 4 columns of a wave empty
+    (128, 4, 128, 32, [460, 451, 452], 5),                                    # 32 to a group
     (32, 32, 128, 16, [1024, 1023, 1057], 0),                                 # plain
     (40, 40, 128, 32, [255, 256, 240, 250, 256, 251, 256, 249, 256, 225], 700),    # one tile a request, over cached positions
     (32, 32, 256, 16, [512, 545, 497], 0),
