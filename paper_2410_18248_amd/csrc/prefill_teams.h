@@ -290,7 +290,11 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
     eq[2] = lookup(KA);
 #pragma unroll
     for (int i = 0; i < NS; ++i) read_k(lds, i >> 1, i & 1);
-    if (team) barrier();
+    if (team) {
+        // (the first keys are in registers by the end of phase 0: at head size 256 phase 1 asks for others in their place)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        barrier();
+    }
 #pragma unroll
     for (int i = 0; i < NK; ++i) qk(i);
 #pragma unroll

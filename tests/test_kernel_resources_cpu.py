@@ -95,3 +95,12 @@ def test_decode_workgroups_per_cu(kernels):
             assert _workgroups(k) >= least.get(m.group(1), 4), (name, k[".vgpr_count"])
             seen += m.group(1) in least
     assert seen == len(least)
+
+
+def test_teams_have_a_cu_to_themselves_and_no_scratch(kernels):
+    """Two waves of a workgroup to a SIMD; and the waits for the loads of a stage count every load and store, which one to scratch memory
+    between them would be."""
+    seen = [k for name, k in kernels.items() if "prefill_teams" in name]
+    assert len(seen) == 4
+    for k in seen:
+        assert k[".vgpr_count"] <= 256 and k[".private_segment_fixed_size"] == 0, k[".name"]
