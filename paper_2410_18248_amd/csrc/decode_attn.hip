@@ -981,21 +981,28 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
 
 // Whether ranges go whole, and how, by the most there can be of them and the longest there can be, a table row, in rounds: the chunks
 // one of four waves walks through.  The lines are drawn through 500 random launches (1 to 256 requests, bf16 and fp32, contexts of a tenth to all of
-// a row) timed with each form; time over that of decode_balanced and its second launch:
+// a row) timed with each form, and from 256 ranges on through 6 500 more (down to a five-hundredth of a row); time over that of decode_balanced and
+// its second launch:
 //   vector path, up to 2 rounds        0.63 to 0.72; from 1 024 ranges on by two waves 0.70 (2 048: 0.80; by four 0.85)
 //      to 3                            0.67 to 0.88
-//      to 4                            256 ranges and more 0.81 to 0.86, fewer by eight waves 0.84 to 0.91 (by four 0.98)
-//      to 6                            256 and more 0.92 to 0.95 (fewer 1.03 to 1.18)
-//      to 8                            768 and more 0.95, from 1 024 on sorted 0.88 (0.92 as they come; 512 0.95, but up to 1.1; fewer 1.0 to 1.5)
-//      to 12                           1 024 and more, sorted, 0.88 to 0.98 (512 0.94 to 1.0)
-//      to 24                           2 048 and more, sorted, 0.96 (1 280, 32 requests of 60 to 3 000 tokens, 1.10)
-//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on;
-//                                      from 8 on with fewer than 256 by eight waves (0.80 to 0.94, by four 0.82 to 0.95)
-//      to 16                           64 to 512 by eight waves, 0.78 to 0.96 (fewer 1.12)
-//      to 24                           512 and more, sorted, 0.83 to 0.92 (fewer 1.01 to 1.18)
-// Longer rows: level at best (64 requests of 60 to 6 000 tokens, 40 heads, 1.01), and one long context among short ones would be walked by
-// four waves.
-enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeEight, kWholeSorted };
+//      to 4                            256 ranges and more 0.81 to 0.86, fewer by eight waves 0.84 to 0.91 (by four 0.98); from 512 on sorted 0.84 to 0.87
+//      to 6                            256 and more 0.92 to 0.95 (fewer 1.03 to 1.18); from 512 on sorted 0.87 to 0.90 (as they come 0.90 to 0.94)
+//      to 8                            1 024 and more, sorted, 0.91 (as they come 0.97), 512 by eight waves 0.90 to 0.92 (by four the same, but 4 layers of
+//                                      16 requests of 60 to 914 tokens, 40 heads, append included, 110 us against 99; in two launches 103); fewer 1.0 to 1.5
+//      to 12                           512 and more, sorted, by eight waves 0.91 to 0.97 (by four 0.96 up to 768; fewer ranges 0.99 to 1.1)
+//      to 16                           768 and more, sorted, by eight waves 0.92 to 0.96 (512 0.95, with skewed contexts 0.99)
+//      to 24                           1 536 and more, sorted, by eight waves 0.91 to 0.97 (768 0.95, with skewed contexts 1.01)
+//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on (512 and more
+//                                      0.78 to 0.84, as they come 0.83 to 0.85); from 8 on with fewer than 256 by eight waves (0.80 to 0.94, by four 0.82 to 0.95)
+//      to 16                           64 to 256 by eight waves, 0.78 to 0.96 (fewer 1.12)
+//      to 24                           256 to 512, sorted, by eight waves 0.82 to 0.91; more, sorted, by four 0.83 to 0.92 (fewer 1.01 to 1.18)
+//      to 32                           512 and more, sorted, 0.87 to 0.91 (fewer 0.89 to 0.99)
+//      to 48                           1 024 and more, sorted, 0.90 to 0.93 (768 0.92)
+// Longer rows gain as much where the work is even (230 of 256 requests of 32 to 8 192 tokens, 32 / 8 heads, 236 -> 226 us), but one long context among
+// short ones is walked by one workgroup: 256 requests of 200 tokens and one of 8 192 56 -> 99 us, and of 1 500, which the lines let through, 49 ->
+// 40.  Where they cost most: 15 plain requests of 30 tokens and one of 1 500, 40 heads, 15.8 -> 23.8; with the others at 200 24.5 -> 27.7, with two of them long
+// 27.9 -> 29.2.  Therefore eight waves where they are level with four.
+enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeEight, kWholeSorted, kWholeSortedEight };
 template <typename R>
 WholeForm whole_form(const DecodeArgs &a, int HC)
 {
@@ -1004,18 +1011,24 @@ WholeForm whole_form(const DecodeArgs &a, int HC)
     if (ranges > 0x7fffffff / kThreads || a.max_blocks > a.num_blocks) return kNotWhole;
     const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
     const bool eight = 8 * a.heads_per_pass * (R::D + 2) * sizeof(float) <= (80u << 10);   // of the LDS: two workgroups to a CU
-    const WholeForm sorted = a.batch <= 4 * kLaneBatch ? kWholeSorted : kNotWhole;
+    const bool order = a.batch <= 4 * kLaneBatch;     // what a wave can sort
+    const WholeForm sorted = order ? kWholeSorted : kNotWhole, sorted_eight = order && eight ? kWholeSortedEight : kNotWhole;
     if (decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads)) {
         if (rounds_to(3)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
-        if (rounds_to(12)) return ranges >= 1024 && !rounds_to(6) ? sorted : ranges < 256 && eight && !rounds_to(8) ? kWholeEight : kWholePlain;
-        if (rounds_to(16) && ranges >= 64 && ranges < 512 && eight) return kWholeEight;
-        return rounds_to(24) && ranges >= 512 ? sorted : kNotWhole;
+        if (rounds_to(12)) {
+            if (!rounds_to(6) && ranges >= (order ? 512 : 1024)) return sorted;
+            return ranges < 256 && eight && !rounds_to(8) ? kWholeEight : kWholePlain;
+        }
+        if (ranges < (order ? 256 : 512)) return rounds_to(16) && ranges >= 64 && eight ? kWholeEight : kNotWhole;
+        if (ranges < 512) return rounds_to(24) ? sorted_eight : kNotWhole;
+        return rounds_to(ranges < 1024 ? 32 : 48) ? sorted : kNotWhole;
     }
     if (rounds_to(2)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
     if (rounds_to(4) && !rounds_to(3) && ranges < 256 && eight) return kWholeEight;
+    if (rounds_to(8) && !rounds_to(3) && ranges >= 512 && order) return ranges < 1024 && !rounds_to(6) ? sorted_eight : kWholeSorted;
     if (rounds_to(8) && ranges < 1024) return rounds_to(3) || ranges >= (rounds_to(4) ? 128 : rounds_to(6) ? 256 : 768) ? kWholePlain : kNotWhole;
     if (rounds_to(6)) return kWholePlain;
-    return ranges >= 1024 && (rounds_to(12) || (rounds_to(24) && ranges >= 2048)) ? sorted : kNotWhole;
+    return ranges >= (rounds_to(12) ? 512 : rounds_to(16) ? 768 : 1536) && rounds_to(24) ? sorted_eight : kNotWhole;
 }
 // Parts that ranges are cut into at most, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
 // records of decode_balanced are a third of the time.  Workgroups in all 256, or 512 where rows are long for them: the same 400 random launches of
@@ -1101,6 +1114,7 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     case kWholePlain: return launch_whole<R, kWaves, false>(a, HC, s);
     case kWholeEight: return launch_whole<R, 8, false>(a, HC, s);
     case kWholeSorted: return launch_whole<R, kWaves, true>(a, HC, s);
+    case kWholeSortedEight: return launch_whole<R, 8, true>(a, HC, s);
     case kNotWhole: break;
     }
     // With eight waves and more to a range (if every request runs) they are better off together; with
