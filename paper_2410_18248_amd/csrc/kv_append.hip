@@ -105,6 +105,8 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append(const AppendArgs a)
 // EARLY, the vectors asked for before the request is found, is for rows of more than a unit per thread:
 // 4 prompts of 200, 40 heads of 128, 5.6 us, 5.9 late; with smaller rows most of the threads only wait
 // (4 prompts of 2 000, 8 heads of 64, 8.5 us, 7.9 late; fp32, 8 heads of 128, the largest such row: 5.4 and 5.3).
+// The request, the place of its first token and its length come in one round trip (one for the request and one for those: 4 prompts
+// of 2 000 as above 8.6 us, 7.8 so; 6 of 17 to 700, fp32, 3.05 and 2.88; 24 of 16 to 700, 40 heads, level).
 template <typename T, bool EARLY>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendArgs a)
 {
@@ -112,10 +114,9 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendA
     const size_t row = (size_t)n * a.num_kv_heads * a.head_dim;
     const T *kn = static_cast<const T *>(a.k_new) + row, *vn = static_cast<const T *>(a.v_new) + row;
     const uint4 none = make_uint4(0, 0, 0, 0), k0 = EARLY ? first_unit(a, kn, 0) : none, v0 = EARLY ? first_unit(a, vn, 0) : none;
-    const int r = last_request(a.q_start, a.batch, n, [](int q, int) { return q; });
-    const int first = a.q_start[r], count = a.q_start[r + 1] - first;
+    const auto [r, first, count, ctx] = new_tokens_at(a.q_start, a.ctx_lens, a.batch, n, [](int q, int) { return q; });
     if (n >= first + count) return;                   // q_start[batch] is less than the grid
-    const int t = a.ctx_lens[r] - count + (n - first);
+    const int t = ctx - count + (n - first);
     scatter_token<T, false, EARLY>(a, r, t, kn, vn, k0, v0, 0, 1);
 }
 
@@ -129,17 +130,20 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens(const AppendA
 // Workgroup w belongs to the last request r with (q_start[r] >> 4) + 2 r <= w: request r
 // touches at most (count >> 4) + 2 sub-tiles, and the keys of consecutive requests are at
 // at least that far apart.
-// (Asking for keys and values together with the table entry is up to 5 % slower: 4 prompts of 200, 16 / 8
-// heads of 256, 4.3 us as it is, 4.5 so.  A few requests are told apart one by one: 7 prompts of 55 to
-// 479 tokens on 2 kv heads of 64 3.4 us, 3.5 by ballots; 16 of 45 to 278 on 8 of 128 6.9 and 6.5.)
+// A long prompt is bound by memory (5.6 TB/s read + written), short ones by the round trips to it: the request, the table entry, keys and values, all
+// of them asked for before the first is stored.  (Values asked for behind the stores of keys, and a ragged quad's positions one by one behind one
+// another's stores: 12 requests of 6 to 58 tokens, 8 heads of 128, 5.3 us, 3.6 so; 64 prompts of 20 to 200 11.0 and 8.5; 4 of 4 096 28.6 and 28.4.
+// Keys and values asked for together with the table entry were up to 5 % slower: 4 prompts of 200, 16 / 8 heads of 256, 4.3 us as it is, 4.5 so.
+// A few requests are told apart one by one, by scalar loads: 4 prompts of 4 096 28.6, in one trip by lanes 29.5; 12 requests of 6 to 58 0.1 the other way.)
 __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const AppendArgs a)
 {
     typedef uint16_t T;
     const int w = blockIdx.x;
     const auto sub_start = [](int q, int i) { return (q >> 4) + 2 * i; };
-    const int r = a.batch < kFew ? last_of_few(a.q_start, a.batch, w, sub_start) : last_request(a.q_start, a.batch, w, sub_start);
-    const int first = a.q_start[r], count = a.q_start[r + 1] - first;
-    const int p0 = a.ctx_lens[r] - count;             // position of the request's first new token
+    const int few = a.batch < kFew ? last_of_few(a.q_start, a.batch, w, sub_start) : 0;
+    const auto [r, first, count, ctx] = a.batch < kFew ? NewTokens{few, a.q_start[few], a.q_start[few + 1] - a.q_start[few], a.ctx_lens[few]}
+                                                       : new_tokens_at(a.q_start, a.ctx_lens, a.batch, w, sub_start);
+    const int p0 = ctx - count;                       // position of the request's first new token
     if (count <= 0 || p0 < 0) return;
     const int sub = (p0 >> 4) + (w - ((first >> 4) + 2 * r));     // sub-tile of the request's context
     const int t_lo = max(p0, sub * 16), t_hi = min(p0 + count, sub * 16 + 16);
@@ -160,48 +164,54 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_tokens_tiled(const A
     kt += g * tile; vt += g * tile;
     kn += g * D; vn += g * D;
 
-    const int c8 = D / 8;                             // keys: (position, 8 dims) -> one 16-byte unit
-    for (int i = threadIdx.x; i < (t_hi - t_lo) * c8; i += kAppendThreads) {
-        const int c = i % c8, t = t_lo + i / c8;
-        *reinterpret_cast<uint4 *>(kt + (size_t)(c * 16 + (t & 15)) * 8) =
-            *reinterpret_cast<const uint4 *>(kn + (size_t)(first + (t - p0)) * row + c * 8);
-    }
-
-    // values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16)
-    for (int i = threadIdx.x; i < 4 * (D / 32) * 8; i += kAppendThreads) {
-        const int j = i & 7, i32 = (i >> 3) % (D / 32), q = i / (8 * (D / 32));
-        const int t0 = sub * 16 + 4 * q;              // the quad's first position
-        if (t0 + 4 <= t_lo || t0 >= t_hi) continue;
-        const int d0 = 32 * i32 + 2 * j;
-        T *dst = vt + (size_t)((i32 * 4 + q) * 16 + 2 * j) * 8;   // unit of dim d0; dim d0 + 1's follows
-        if (t0 >= t_lo && t0 + 4 <= t_hi) {
-            uint32_t lo2[4], hi2[4];                  // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
+    // Everything is asked for before the first of it is stored.
+    const auto src = [&](const T *x, int t) { return x + (size_t)(first + (t - p0)) * row; };
+    // keys: (position, 8 dims) -> one 16-byte unit, at most two to a thread (heads are 64, 128 or 256 here); eight positions by eight units to
+    // a wave: 128 bytes of a row on one side and of a tile on the other
+    const auto unit = [](int i) { return (i >> 3 & 7) | (i >> 7) << 3; };
+    const auto slot = [](int i) { return (i & 7) | (i >> 3 & 8); };
+    const int i1 = threadIdx.x + kAppendThreads, c0 = unit(threadIdx.x), c1 = unit(i1), s0 = sub * 16 + slot(threadIdx.x), s1 = sub * 16 + slot(i1);
+    const bool key0 = c0 < D / 8 && s0 >= t_lo && s0 < t_hi, key1 = c1 < D / 8 && s1 >= t_lo && s1 < t_hi;
+    uint4 k0 = make_uint4(0, 0, 0, 0), k1 = k0;
+    if (key0) k0 = *reinterpret_cast<const uint4 *>(src(kn, s0) + c0 * 8);
+    if (key1) k1 = *reinterpret_cast<const uint4 *>(src(kn, s1) + c1 * 8);
+    // values: (quad of positions, 32-dim group, dims 2 j, 2 j + 1 of its first 16 and of its last 16), one to a thread at most
+    const int j = threadIdx.x & 7, i32 = (threadIdx.x >> 3) % (D / 32), q = threadIdx.x / (D / 4);
+    const int t0 = sub * 16 + 4 * q;                  // the quad's first position
+    const int d0 = 32 * i32 + 2 * j;
+    const bool some = q < 4 && t0 + 4 > t_lo && t0 < t_hi;
+    uint32_t lo2[4], hi2[4];                          // [position]: dims d0, d0 + 1 and d0 + 16, d0 + 17
+    if (some) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const T *src = vn + (size_t)(first + (t0 + k - p0)) * row + d0;
-                lo2[k] = *reinterpret_cast<const uint32_t *>(src);
-                hi2[k] = *reinterpret_cast<const uint32_t *>(src + 16);
-            }
+        for (int k = 0; k < 4; ++k) {                 // (positions that are not new: the nearest that is)
+            const T *x = src(vn, min(max(t0 + k, t_lo), t_hi - 1)) + d0;
+            lo2[k] = *reinterpret_cast<const uint32_t *>(x);
+            hi2[k] = *reinterpret_cast<const uint32_t *>(x + 16);
+        }
+    }
+    if (key0) *reinterpret_cast<uint4 *>(kt + (size_t)(c0 * 16 + (s0 & 15)) * 8) = k0;
+    if (key1) *reinterpret_cast<uint4 *>(kt + (size_t)(c1 * 16 + (s1 & 15)) * 8) = k1;
+    if (!some) return;
+    T *dst = vt + (size_t)((i32 * 4 + q) * 16 + 2 * j) * 8;       // unit of dim d0; dim d0 + 1's follows
+    if (t0 >= t_lo && t0 + 4 <= t_hi) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int sh = 16 * e;
+            uint4 u;
+            u.x = ((lo2[0] >> sh) & 0xFFFFu) | ((lo2[1] >> sh) << 16);
+            u.y = ((lo2[2] >> sh) & 0xFFFFu) | ((lo2[3] >> sh) << 16);
+            u.z = ((hi2[0] >> sh) & 0xFFFFu) | ((hi2[1] >> sh) << 16);
+            u.w = ((hi2[2] >> sh) & 0xFFFFu) | ((hi2[3] >> sh) << 16);
+            *reinterpret_cast<uint4 *>(dst + e * 8) = u;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (t0 + k < t_lo || t0 + k >= t_hi) continue;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const int sh = 16 * e;
-                uint4 u;
-                u.x = ((lo2[0] >> sh) & 0xFFFFu) | ((lo2[1] >> sh) << 16);
-                u.y = ((lo2[2] >> sh) & 0xFFFFu) | ((lo2[3] >> sh) << 16);
-                u.z = ((hi2[0] >> sh) & 0xFFFFu) | ((hi2[1] >> sh) << 16);
-                u.w = ((hi2[2] >> sh) & 0xFFFFu) | ((hi2[3] >> sh) << 16);
-                *reinterpret_cast<uint4 *>(dst + e * 8) = u;
-            }
-        } else {
-            for (int k = 0; k < 4; ++k) {
-                const int t = t0 + k;
-                if (t < t_lo || t >= t_hi) continue;
-                const T *src = vn + (size_t)(first + (t - p0)) * row + d0;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    dst[e * 8 + k] = src[e];
-                    dst[e * 8 + 4 + k] = src[16 + e];
-                }
+                dst[e * 8 + k] = (T)(lo2[k] >> (16 * e));
+                dst[e * 8 + 4 + k] = (T)(hi2[k] >> (16 * e));
             }
         }
     }

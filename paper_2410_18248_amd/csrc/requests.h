@@ -37,5 +37,26 @@ __device__ __forceinline__ int last_of_few(const int32_t *q_start, int batch, in
     return lo;
 }
 
+// Where a token form's workgroup works: a request, the row of its first new token, how many of them it has, its context's length.
+struct NewTokens {
+    int r, first, count, ctx;
+};
+// That of the last request with key(q_start[r], r) <= x, by every wave.  Up to 64 requests in one round trip: each lane asks for all of one request, and
+// the wave takes its request's out of the registers.
+template <typename Key>
+__device__ __forceinline__ NewTokens new_tokens_at(const int32_t *q_start, const int32_t *ctx_lens, int batch, int x, Key key)
+{
+    if (batch > 64) {
+        const int r = last_request(q_start, batch, x, key), first = q_start[r];
+        return {r, first, q_start[r + 1] - first, ctx_lens[r]};
+    }
+    const int lane = threadIdx.x & 63, i = min(lane, batch - 1);
+    const int first = q_start[i], next = q_start[i + 1], ctx = ctx_lens[i];
+    const unsigned long long le = __ballot(lane < batch && key(first, lane) <= x);
+    const int r = max(0, 63 - __clzll((long long)le));     // (none: clz 64)
+    const int from = __builtin_amdgcn_readlane(first, r);
+    return {r, from, __builtin_amdgcn_readlane(next, r) - from, __builtin_amdgcn_readlane(ctx, r)};
+}
+
 }  // namespace
 }  // namespace lamps
