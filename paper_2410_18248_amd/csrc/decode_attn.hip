@@ -981,7 +981,7 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
 
 // Whether ranges go whole, and how, by the most there can be of them and the longest there can be, a table row, in rounds: the chunks
 // one of four waves walks through.  The lines are drawn through 500 random launches (1 to 256 requests, bf16 and fp32, contexts of a tenth to all of
-// a row) timed with each form, and from 256 ranges on through 6 500 more (down to a five-hundredth of a row); time over that of decode_balanced and
+// a row) timed with each form, and from 256 ranges on through 5 500 more (contexts down to a five-hundredth of a row); time over that of decode_balanced and
 // its second launch:
 //   vector path, up to 2 rounds        0.63 to 0.72; from 1 024 ranges on by two waves 0.70 (2 048: 0.80; by four 0.85)
 //      to 3                            0.67 to 0.88
