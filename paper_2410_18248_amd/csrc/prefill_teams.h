@@ -23,8 +23,9 @@
 // a unit each; 16-byte reads want 8 register swaps (500 cycles) or, with values brought in by 4 bytes such that they lie as operands, three more
 // loads a wave (+3 %).
 //
-// The reference point of the exponentials moves as in prefill_mfma, found after the fact: weights are kept relative to 2^(kSlack - 1)
-// times the largest seen, and one of 2 and more -- a bit of its exponent -- says that the reference has to move.
+// The reference point of the exponentials moves where prefill_mfma's does and to the same value, so that a row has the same bits whichever of the two
+// kernels a call's totals choose.  That it has to is found after the fact, by a weight of 2^kSlack and more: the largest by packed maxima of
+// three (two instructions to eight weights; by packed maxima of two the phase is 5 % longer).
 template <int D, bool TILED, int kCB>
 __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, const int tiles, const int full_groups)
 {
@@ -190,9 +191,11 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
 #pragma unroll
         for (int b = 0; b < kCB; ++b) l[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pw[b], l[b], 0, 0, 0);
     };
-    // Whether one of the weights is 2 or more (or no finite number).
+    // Whether one of the weights is 2^kSlack or more (or no finite number): weights are not negative, so their bits compare as they
+    // do, and as those of fp16 numbers.
+    typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
     auto weigh = [&]() {
-        uint32_t any = 0;
+        uint32_t most = 0;
 #pragma unroll
         for (int b = 0; b < kCB; ++b) {
 #pragma unroll
@@ -201,9 +204,12 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
                 pw[b][4 + e] = (__bf16)fast_exp2(fmaf(sc1[b][e], a.scale_log2e, -m[b]));
             }
             const uint4 u = __builtin_bit_cast(uint4, pw[b]);
-            any |= u.x | u.y | u.z | u.w;
+            uint32_t t;
+            asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(t) : "v"(u.x), "v"(u.y), "v"(u.z));
+            asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(most) : "v"(most), "v"(t), "v"(u.w));
         }
-        return (any & 0x40004000u) != 0;
+        constexpr unsigned short kBelow = ((127 + (int)kSlack) << 7) - 1;   // the bf16 in front of 2^kSlack
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, most), u16x2{kBelow, kBelow})) != 0;
     };
     auto softmax = [&](int t0) {
         if (t0 + kStage - 1 > wave_minpos) {
@@ -224,7 +230,7 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
                 mx *= a.scale_log2e;
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float mn = mx - m[b] >= 1.0f ? mx + (kSlack - 1.0f) : m[b];
+                const float mn = mx - m[b] > kSlack ? mx : m[b];
                 const float f = fast_exp2(m[b] - mn);
                 m[b] = mn;
                 l[b] *= f;

@@ -70,3 +70,33 @@ def test_rows(H, Hkv, D, bs, new, cached):
         torch.cuda.synchronize()
         assert np.array_equal(to_f64(out), got)
     rig.close()
+
+
+@pytest.mark.parametrize("H,Hkv,D,new,cached,double", [
+    (32, 8, 128, [1000, 997, 1001, 1002], 0, 0), (32, 8, 128, [1000, 997, 1001, 1002], 0, 2), (32, 32, 128, [1030, 1025, 1029, 1036], 0, 2),
+    (16, 16, 256, [512, 513, 511, 512], 400, 2),
+])
+def test_a_row_has_the_same_bits_by_either_kernel(H, Hkv, D, new, cached, double):
+    """Together the requests go by two teams of waves, each alone by the kernel of four: a row does not depend on the requests beside it.
+    Queries of N(0, 1), and doubled twice: there the reference point of the exponentials moves in most stages of some wave."""
+    B, ctx = len(new), [n + cached for n in new]
+    geom = W.Geometry(1, H, Hkv, D, 16, sum((c + 15) // 16 for c in ctx) + 4, (max(ctx) + 15) // 16, "bf16")
+    rig = Rig(geom, B)
+    table, _ = W.deal_block_table(W.permutation(7, geom.num_blocks), ctx, geom)
+    g = torch.Generator(rig.dev).manual_seed(4)
+    for pool in (rig.k_pool, rig.v_pool):
+        pool.copy_(torch.randn(pool.shape, generator=g, device=rig.dev))
+    dq = (torch.randn((sum(new), H, D), generator=g, device=rig.dev) * 2 ** double).to(rig.tdtype)
+    out, alone = torch.full_like(dq, 7.0), torch.full_like(dq, 5.0)
+    dt, dc = torch.as_tensor(table, device=rig.dev), torch.as_tensor(np.asarray(ctx, dtype=np.int32), device=rig.dev)
+    first = np.concatenate([[0], np.cumsum(new)]).astype(np.int32)
+    starts = [torch.as_tensor(np.asarray(x, dtype=np.int32), device=rig.dev) for x in [first] + [[0, n] for n in new]]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(rig.compute):
+        rig.lamps.prefill_attn(0, B, sum(new), dq, starts[0], dt, dc, out, max_new_tokens=max(new))
+        for r, n in enumerate(new):
+            rig.lamps.prefill_attn(0, 1, n, dq[first[r]:], starts[1 + r], dt[r:r + 1].contiguous(), dc[r:r + 1].contiguous(), alone[first[r]:],
+                                   max_new_tokens=n)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), alone.view(torch.int16))
+    rig.close()

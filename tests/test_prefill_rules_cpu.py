@@ -259,6 +259,13 @@ def test_pairs_left_over(lib):
     (16, 4, 256, 2, 40, 30, 48, True),                    # grouped heads of 256
     (32, 1, 256, 4, 4096, 1024, 1024, False),             # more heads than a wave has columns
     (64, 2, 128, 4, 4096, 1024, 1024, True),
+    # a request among others and alone, as the test of equal bits has them
+    (32, 8, 128, 4, 4000, 1002, 1008, True),
+    (32, 8, 128, 1, 1002, 1002, 1008, False),
+    (32, 32, 128, 4, 4120, 1036, 1040, True),
+    (32, 32, 128, 1, 1036, 1036, 1040, False),
+    (16, 16, 256, 4, 2048, 513, 928, True),
+    (16, 16, 256, 1, 513, 513, 928, False),
 ])
 def test_two_teams(lib, H, Hkv, D, batch, total, most, row, two_teams):
     lib.c_teams.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong]
