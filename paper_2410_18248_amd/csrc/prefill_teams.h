@@ -25,7 +25,10 @@
 //
 // The reference point of the exponentials moves where prefill_mfma's does and to the same value, so that a row has the same bits whichever of the two
 // kernels a call's totals choose.  That it has to is found after the fact, by a weight of 2^kSlack and more: the largest by packed maxima of
-// three (two instructions to eight weights; by packed maxima of two the phase is 5 % longer).
+// three (two instructions to eight weights; by packed maxima of two the phase is 5 % longer).  A move is far from rare where scores are
+// peaked, and all eight waves wait for it at the barrier; only the block that asks for it is weighed again, and lanes compare without LDS.  4 prompts
+// of 4 096, 32 / 8 heads, us, queries of N(0, 1) / N(0, 16) by prefill_mfma 549 / 579, with the reference looked for in both blocks through LDS
+// 483 / 640, so 482 / 551; 4 of 2 048 on 40 plain heads 207 / 216, 200 / 270, 195 / 229.
 template <int D, bool TILED, int kCB>
 __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, const int tiles, const int full_groups)
 {
@@ -191,25 +194,35 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
 #pragma unroll
         for (int b = 0; b < kCB; ++b) l[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pw[b], l[b], 0, 0, 0);
     };
-    // Whether one of the weights is 2^kSlack or more (or no finite number): weights are not negative, so their bits compare as they
+    // The weights of block b; whether one of them is 2^kSlack or more (or no finite number).  They are not negative, so their bits compare as they
     // do, and as those of fp16 numbers.
     typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
-    auto weigh = [&]() {
-        uint32_t most = 0;
+    auto weigh = [&](int b) {
 #pragma unroll
-        for (int b = 0; b < kCB; ++b) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pw[b][e] = (__bf16)fast_exp2(fmaf(sc0[b][e], a.scale_log2e, -m[b]));
-                pw[b][4 + e] = (__bf16)fast_exp2(fmaf(sc1[b][e], a.scale_log2e, -m[b]));
-            }
-            const uint4 u = __builtin_bit_cast(uint4, pw[b]);
-            uint32_t t;
-            asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(t) : "v"(u.x), "v"(u.y), "v"(u.z));
-            asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(most) : "v"(most), "v"(t), "v"(u.w));
+        for (int e = 0; e < 4; ++e) {
+            pw[b][e] = (__bf16)fast_exp2(fmaf(sc0[b][e], a.scale_log2e, -m[b]));
+            pw[b][4 + e] = (__bf16)fast_exp2(fmaf(sc1[b][e], a.scale_log2e, -m[b]));
         }
+        uint4 u = __builtin_bit_cast(uint4, pw[b]);
+        asm("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));   // (pairs from here on: carried over the branch one by one, they are converted twice)
+        pw[b] = __builtin_bit_cast(bf16x8, u);
+        uint32_t most;
+        asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(most) : "v"(u.x), "v"(u.y), "v"(u.z));
+        asm("v_pk_maximum3_f16 %0, %1, %2, %2" : "=v"(most) : "v"(most), "v"(u.w));
+        return most;
+    };
+    auto over = [](uint32_t most) {
         constexpr unsigned short kBelow = ((127 + (int)kSlack) << 7) - 1;   // the bf16 in front of 2^kSlack
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, most), u16x2{kBelow, kBelow})) != 0;
+        return __any(__builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, most), u16x2{kBelow, kBelow})) != 0);
+    };
+    // the larger of a lane's and the one's whose number differs by 16 (32)
+    auto max16 = [](float x) {
+        const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));
+    };
+    auto max32 = [](float x) {
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));
     };
     auto softmax = [&](int t0) {
         if (t0 + kStage - 1 > wave_minpos) {
@@ -223,14 +236,26 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
                 }
             }
         }
-        if (__any(weigh())) {
+        uint32_t most[kCB], all = 0;
+#pragma unroll
+        for (int b = 0; b < kCB; ++b) {
+            most[b] = weigh(b);
+            if (b == 0) all = most[0];
+            else asm("v_pk_maximum3_f16 %0, %1, %2, %2" : "=v"(all) : "v"(all), "v"(most[b]));
+        }
+        if (over(all)) {
 #pragma unroll
             for (int b = 0; b < kCB; ++b) {
-                float mx = fmaxf(fmaxf(fmaxf(sc0[b][0], sc0[b][1]), fmaxf(sc0[b][2], sc0[b][3])), fmaxf(fmaxf(sc1[b][0], sc1[b][1]), fmaxf(sc1[b][2], sc1[b][3])));
+                if (kCB > 1 && !over(most[b])) continue;
+                float mx = sc0[b][0];                // (as prefill_mfma finds it)
+#pragma unroll
+                for (int e = 1; e < 8; ++e) mx = __builtin_amdgcn_fmed3f(mx, e < 4 ? sc0[b][e & 3] : sc1[b][e & 3], INFINITY);
+                mx = max32(max16(mx));
+                // (there a lane looks first, at the product and the difference rounded once, and then at both rounded)
+                const bool above = fmaf(mx, a.scale_log2e, -m[b]) > kSlack;
                 mx *= a.scale_log2e;
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float mn = mx - m[b] > kSlack ? mx : m[b];
+                asm("" : "+v"(mx));
+                const float mn = above && mx - m[b] > kSlack ? mx : m[b];
                 const float f = fast_exp2(m[b] - mn);
                 m[b] = mn;
                 l[b] *= f;
@@ -238,8 +263,8 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
                 for (int s = 0; s < NS; ++s)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[b][s][e] *= f;
+                weigh(b);
             }
-            weigh();
         }
     };
     auto pin = [&]() { __builtin_amdgcn_sched_barrier(0); };
@@ -332,6 +357,7 @@ __global__ __launch_bounds__(512, 2) void prefill_teams(const PrefillArgs p, con
     softmax_phase();
     barrier();
     for (st = 1; st < wave_stages; ++st) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0), which it is: said again where the compiler sees it, or it waits so among the products
         __builtin_amdgcn_s_setprio(1);
         matrix(st);
         __builtin_amdgcn_s_waitcnt(vmcnt(kBehind));

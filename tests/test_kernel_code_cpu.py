@@ -83,3 +83,19 @@ def test_where_loops_begin_in_a_fetch():
         assert begin % 32 == 4, (name, begin % 32)
         seen += 1
     assert seen == 2
+
+
+def test_teams_move_a_reference_without_lds():
+    """All eight waves wait for the one whose reference point moves, which peaked scores make it do in most stages: lanes compare by register
+    swaps, and inside the loop (from the first s_setprio 1 on) no product waits for the loads of operands behind its own."""
+    seen = 0
+    for name, code in _code("prefill_teams").items():
+        text = [x for _, x in code]
+        assert not any(x.startswith("ds_bpermute") for x in text), name
+        at = next(k for k, x in enumerate(text) if x.startswith("s_setprio 1"))
+        loop = text[at:at + next(k for k, x in enumerate(text[at:]) if x.startswith("s_setprio 0"))]
+        assert sum(x.startswith("v_mfma") for x in loop) >= 32, name
+        waits = [x for x in loop if "lgkmcnt" in x]
+        assert waits and not any("lgkmcnt(0)" in x for x in waits[:len(waits) // 2]), (name, waits)
+        seen += 1
+    assert seen == 4
