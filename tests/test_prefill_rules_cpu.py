@@ -253,6 +253,10 @@ def test_pairs_left_over(lib):
     (40, 40, 128, 24, 2950, 683, 688, False),
     (32, 32, 128, 16, 4000, 250, 2256, True),             # full tiles
     (16, 16, 128, 25, 7150, 336, 1008, False),            # half-empty ones
+    (32, 32, 128, 13, 2928, 321, 2480, False),            # some with a second one
+    (32, 32, 128, 13, 2928, 256, 2480, True),
+    (16, 16, 256, 37, 4148, 134, 1040, False),
+    (16, 16, 256, 37, 4148, 128, 1040, True),
     (32, 8, 128, 4, 2048, 512, 2560, True),
     (16, 16, 256, 4, 2048, 512, 2560, True),
     (16, 16, 256, 1, 700, 700, 704, False),
