@@ -52,6 +52,8 @@
 #include <type_traits>
 
 #include "attn_reducers.h"
+#include "decode_rules.h"
+#include "handover.h"
 #include "internal.h"
 #include "lamps.h"
 #include "prefill_split.h"
@@ -638,80 +640,207 @@ __device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int su
 // device, so the host goes by the bound of a table row (whole_form).  Bound by latency -- length, table entries, K / V, and at the end the
 // sum -- where the launch is small, otherwise by memory as decode_balanced is.  Both ways, us: one request of 200 tokens, 32 / 8 heads of 128,
 // 7.0 / 4.4; 64 of 50 to 300 on 32 / 8 14.8 / 8.9; 40 of 16 to 130 on 40 plain heads 14.1 / 9.6; 200 of 20 to 250 on 32 / 8 20.6 / 12.9.
-// SORTED: the longest contexts first, where the workgroups come in several rounds and ranges are long enough for the last of
-// them to show (0.15 of a launch of 7 us, for every wave finds the place of its own).
-template <typename R, int W, bool SORTED>
+template <typename R, int W>
 __global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) void decode_whole(const DecodeArgs a)
 {
     constexpr int D = R::D, kPer = W > kWaves ? 1 : kWaves / W;   // ranges of a workgroup
     extern __shared__ __align__(16) float parts[];    // [range][wave][head][D + 2]
-    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int GH = a.heads_per_pass, passes = a.passes, HC = a.num_kv_heads * passes;
     const int of = wv / W, sub = wv % W;
-    int item = blockIdx.x * kPer + of;
-    // Every other 256 of them, one to a CU, the other way round: where the chip holds all at once a CU else has the longest of each
-    // 256 (as they come / so, us: 4 layers of 32 requests of 60 to 1 500 tokens, 32 heads, 202 / 195; 128 of those on 32 / 8 heads 45.1 / 43.2).
-    if (SORTED && (item & 256) && (item | 255) < a.batch * HC) item ^= 255;
-    int nth = __builtin_amdgcn_readfirstlane(item / HC);
-    const int hc = item - nth * HC;
-    int r = nth, C;
-    bool on = true;
-    if constexpr (SORTED) {
-        // the request with the nth longest context (of those that run; ties by place): its bits from the highest on
-        int2 q[4];
-        requests_of(a, 4 * lane, q);
-        unsigned key[4], top = 0;
-        unsigned long long in[4];
-        int running = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            key[k] = q[k].x ? (unsigned)max(q[k].y, 0) + 1 : 0;
-            top = max(top, key[k]);
-            in[k] = __ballot(key[k] > 0);
-            running += __popcll(in[k]);
-        }
-        if (nth >= running) return;
-        top = (unsigned)__builtin_amdgcn_readlane(wave_max_to((int)top), 63);
-        for (int bit = 31 - __builtin_clz(top); bit >= 0; --bit) {
-            unsigned long long set[4];
-            int n = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                set[k] = in[k] & __ballot(key[k] >> bit & 1);
-                n += __popcll(set[k]);
-            }
-            const bool have = nth < n;
-            if (!have) nth -= n;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) in[k] = have ? set[k] : in[k] & ~set[k];
-        }
-        // the nth of those that are left
-        C = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int n = __popcll(in[k]);
-            if (nth >= 0 && nth < n) {
-                unsigned long long left = in[k];
-                for (; nth > 0; --nth) left &= left - 1;
-                const int l = __ffsll((long long)left) - 1;
-                r = 4 * l + k;
-                C = __builtin_amdgcn_readlane(q[k].y, l);
-                nth = -1;
-            } else if (nth >= 0) {
-                nth -= n;
-            }
-        }
-    } else {
-        const int2 q = request_of(a, r);              // (past the batch: does not run)
-        on = __builtin_amdgcn_readfirstlane(q.x) != 0;
-        C = __builtin_amdgcn_readfirstlane(q.y);
-        if (kPer == 1 && !on) return;                 // (else the workgroup's other range may)
-    }
+    const int item = blockIdx.x * kPer + of;
+    const int r = __builtin_amdgcn_readfirstlane(item / HC), hc = item - r * HC;
+    const int2 q = request_of(a, r);                  // (past the batch: does not run)
+    const bool on = __builtin_amdgcn_readfirstlane(q.x) != 0;
+    const int C = __builtin_amdgcn_readfirstlane(q.y);
+    if (kPer == 1 && !on) return;                     // (else the workgroup's other range may)
     const int n = chunks_of(1, C, R::GT);
     float *x0 = parts + (size_t)of * W * GH * (D + 2);
     stretches<R, W>(a, x0, sub, r, hc, 0, n, C, on, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
         store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
     });
+}
+
+// Ranges that may be long, in one launch that looks at the lengths itself: those of about the size of an even share go whole to a workgroup, the
+// longest first, and longer ones are cut, each part a workgroup's, in front of them; the last part of a range to arrive adds them up.  No walk
+// is longer than one and a half even shares (or three rounds of chunks), however skewed the batch is and however few of it run; the workgroups that are not needed
+// (`spare` more than there are ranges are launched) leave.  Bound by the memory where the launch is large, else by one walk: request, table entry, two
+// rounds, the sum.  By the plan's two launches / whole ranges by eight waves / so, us, 40 plain heads: 16 requests of 60 to 1 500 tokens 32.5 / 30.3 / 27.3,
+// 15 of 30 and one of 1 500 14.9 / 22.7 / 12.8, 2 of 16 running 15.8 / 23.4 / 14.6; 54 of 144 running, 180 tokens and one of 2 863, 32 heads, 37.2 / 48.4 / 34;
+// 64 of 1 500, 32 / 8 heads, 65.6 / 60.8 / 59.5.  Every wave finds its place: where ranges are less than a round that is most of what it does,
+// and they go as they come (180 requests, 43 tokens and one of 1 231: 55 us sorted, 43 so; 40 by the plan, 94 by eight waves).
+struct CutArgs {
+    uint64_t tag;
+    int spare;
+};
+// What a workgroup of it takes: chunks c0 .. c1 - 1 of a range, which is one of `runs` parts of it (the at'th, `first` the item of the first).
+struct CutItem {
+    int r, hc, C, c0, c1, runs, at, first;
+};
+// Found by every wave for itself, K consecutive requests per lane.  False: nothing.
+template <typename R, int K>
+__device__ __forceinline__ bool cut_item(const DecodeArgs &a, const CutArgs &c, int item, CutItem &it)
+{
+    constexpr int kChunk = R::CT / R::GT, kUnit = kWaves * kChunk;
+    const int lane = threadIdx.x & 63, HC = a.num_kv_heads * a.passes;
+    int2 q[K];
+    requests_of(a, K * lane, q);
+    int n[K], np[K], sum = 0, longest = 0, running = 0, cuts = 0, upto = 0, own = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        n[k] = chunks_of(q[k].x, q[k].y, R::GT);
+        np[k] = 0;
+        sum += n[k];
+        longest = max(longest, n[k]);
+        running += __popcll(__ballot(n[k] > 0));
+    }
+    longest = __builtin_amdgcn_readlane(wave_max_to(longest), 63);
+    const unsigned all = (unsigned)__builtin_amdgcn_readlane(wave_scan(sum), 63) * (unsigned)HC;
+    const rules::CutSize size = rules::cut_size(all, c.spare, kUnit);
+    if (longest > size.worth) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            np[k] = rules::cut_parts(n[k], size);
+            own += np[k];
+            running -= __popcll(__ballot(np[k] > 0));
+        }
+        upto = wave_scan(own);
+        cuts = __builtin_amdgcn_readlane(upto, 63) * HC;
+    }
+    const int total = cuts + running * HC;
+    // Every other 256 of them, one to a CU, the other way round: where the chip holds all at once a CU else has the longest of each
+    // 256 (as they come / so, us: 4 layers of 32 requests of 60 to 1 500 tokens, 32 heads, 202 / 195; 128 of those on 32 / 8 heads 45.1 / 43.2).
+    if ((item & 256) && (item | 255) < total) item ^= 255;
+    if (item >= total) return false;
+    if (item < cuts) {
+        int at = split::small_div(item, HC);
+        it.hc = item - at * HC;
+        const int l = __popcll(__ballot(upto <= at));
+        at -= __builtin_amdgcn_readlane(upto - own, l);
+        int k = 0, of = __builtin_amdgcn_readlane(np[0], l), nr = __builtin_amdgcn_readlane(n[0], l);
+        it.C = __builtin_amdgcn_readlane(q[0].y, l);
+#pragma unroll
+        for (int j = 1; j < K; ++j)
+            if (k == j - 1 && at >= of) {
+                at -= of;
+                k = j;
+                of = __builtin_amdgcn_readlane(np[j], l);
+                nr = __builtin_amdgcn_readlane(n[j], l);
+                it.C = __builtin_amdgcn_readlane(q[j].y, l);
+            }
+        it.r = K * l + k;
+        const int each = rules::cut_each(nr, of, kChunk);
+        it.runs = split::small_div(nr + each - 1, each);
+        it.at = at;
+        it.first = item - at * HC;
+        it.c0 = at * each;
+        it.c1 = min(nr, it.c0 + each);
+        return it.at < it.runs;
+    }
+    // the request with the nth longest context (of those that run and are not cut; ties by place): its bits from the highest on
+    int nth = split::small_div(item - cuts, HC);
+    it.hc = item - cuts - nth * HC;
+    unsigned key[K], top = 0;
+    unsigned long long in[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        key[k] = np[k] == 0 ? (unsigned)n[k] : 0;
+        top = max(top, key[k]);
+        in[k] = __ballot(key[k] > 0);
+    }
+    if (all >= (unsigned)total * kUnit) {
+        top = (unsigned)min(longest, size.worth);
+        for (int bit = 31 - __builtin_clz(top); bit >= 0; --bit) {
+            unsigned long long set[K];
+            int m = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                set[k] = in[k] & __ballot(key[k] >> bit & 1);
+                m += __popcll(set[k]);
+            }
+            const bool have = nth < m;
+            if (!have) nth -= m;
+#pragma unroll
+            for (int k = 0; k < K; ++k) in[k] = have ? set[k] : in[k] & ~set[k];
+        }
+    }
+    it.r = it.C = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int m = __popcll(in[k]);
+        if (nth >= 0 && nth < m) {
+            // (the lane with nth of them in front of it)
+            const unsigned long long mine = __ballot((in[k] >> lane & 1) && __builtin_amdgcn_mbcnt_hi((unsigned)(in[k] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)in[k], 0)) == (unsigned)nth);
+            const int l = __ffsll((long long)mine) - 1;
+            it.r = K * l + k;
+            it.C = __builtin_amdgcn_readlane(q[k].y, l);
+            nth = -1;
+        } else if (nth >= 0) {
+            nth -= m;
+        }
+    }
+    it.c0 = 0;
+    it.c1 = chunks_of(1, it.C, R::GT);
+    it.runs = 1;
+    it.at = it.first = 0;
+    return true;
+}
+
+template <typename R>
+__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_cut(const DecodeArgs a, const CutArgs c)
+{
+    constexpr int D = R::D;
+    extern __shared__ __align__(16) float parts[];    // [wave][head][D + 2]
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
+    CutItem it;
+    if (a.batch <= kLaneBatch ? !cut_item<R, 1>(a, c, blockIdx.x, it) : !cut_item<R, 4>(a, c, blockIdx.x, it)) return;
+    const size_t slot = (size_t)GH * (D + 2);
+    const bool wide = ((uintptr_t)a.out & 15) == 0;
+    float *mine = a.partials + (size_t)(it.first + it.at * HC) * slot;
+    stretches<R, kWaves>(a, parts, wv, it.r, it.hc, it.c0, it.c1, it.C, true, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
+        if (it.runs == 1) {
+            store_out<R::kBF16>(a.out, (rh + h) * D + d, wide, L, A);
+        } else {
+            put_shared(mine + h * (D + 2) + d, A[0], A[1]);
+            if (d == 0) put_shared(mine + h * (D + 2) + D, M, L);
+        }
+    });
+    if (it.runs == 1) return;
+    uint64_t *flags = reinterpret_cast<uint64_t *>(a.partials + gridDim.x * slot);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    int *is_last = reinterpret_cast<int *>(parts);
+    if (wv == 0) {
+        const bool last = report_run<true>(flags + it.first, HC, it.at, it.runs, c.tag);
+        if (lane == 0) *is_last = last;
+    }
+    __syncthreads();
+    if (!*is_last) return;
+    for (int i = 2 * (64 * wv + lane); i < GH * D; i += 128 * kWaves) {
+        const int h = i / D, d = i % D;
+        const float *x = a.partials + (size_t)it.first * slot + h * (D + 2);
+        float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
+        for (int p0 = 0; p0 < it.runs; p0 += 8) {
+            float2 ml[8], o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float *y = x + (size_t)min(p0 + j, it.runs - 1) * HC * slot;
+                ml[j] = get_shared(y + D);
+                o[j] = get_shared(y + d);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (p0 + j >= it.runs) break;
+                const float Mn = fmaxf(M, ml[j].x), f0 = fast_exp2(M - Mn), f = fast_exp2(ml[j].x - Mn);
+                L = L * f0 + ml[j].y * f;
+                A[0] = A[0] * f0 + o[j].x * f;
+                A[1] = A[1] * f0 + o[j].y * f;
+                M = Mn;
+            }
+        }
+        store_out<R::kBF16>(a.out, ((size_t)it.r * a.num_q_heads + it.hc * GH + h) * D + d, wide, L, A);
+    }
 }
 
 // The same with a range cut into up to `cuts` parts, a workgroup each, of at least a chunk per wave; the parts of a range are
@@ -750,11 +879,11 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const D
 
 // Adds the parts of a range up: 128 (head, dim) outputs a workgroup, two per lane, its waves every eighth part.  One round trip: the parts there
 // can be are asked for together with the length that says how many there are.
-constexpr int kPartWaves = 8, kMostCuts = 64;
+constexpr int kPartWaves = 8;
 template <typename R>
 __global__ __launch_bounds__(64 * kPartWaves) void decode_merge_parts(const DecodeArgs a, const int cuts)
 {
-    constexpr int D = R::D, N = kMostCuts / kPartWaves;
+    constexpr int D = R::D, N = rules::kMostCuts / kPartWaves;
     __shared__ float4 sums[kPartWaves][64];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
@@ -979,83 +1108,6 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
     return hipGetLastError();
 }
 
-// Whether ranges go whole, and how, by the most there can be of them and the longest there can be, a table row, in rounds: the chunks
-// one of four waves walks through.  The lines are drawn through 500 random launches (1 to 256 requests, bf16 and fp32, contexts of a tenth to all of
-// a row) timed with each form, and from 256 ranges on through 5 500 more (contexts down to a five-hundredth of a row); time over that of decode_balanced and
-// its second launch:
-//   vector path, up to 2 rounds        0.63 to 0.72; from 1 024 ranges on by two waves 0.70 (2 048: 0.80; by four 0.85)
-//      to 3                            0.67 to 0.88
-//      to 4                            256 ranges and more 0.81 to 0.86, fewer by eight waves 0.84 to 0.91 (by four 0.98); from 512 on sorted 0.84 to 0.87
-//      to 6                            256 and more 0.92 to 0.95 (fewer 1.03 to 1.18); from 512 on sorted 0.87 to 0.90 (as they come 0.90 to 0.94)
-//      to 8                            1 024 and more, sorted, 0.91 (as they come 0.97), 512 by eight waves 0.90 to 0.92 (by four the same, but 4 layers of
-//                                      16 requests of 60 to 914 tokens, 40 heads, append included, 110 us against 99; in two launches 103); fewer 1.0 to 1.5
-//      to 12                           512 and more, sorted, by eight waves 0.91 to 0.97 (by four 0.96 up to 768; fewer ranges 0.99 to 1.1)
-//      to 16                           768 and more, sorted, by eight waves 0.92 to 0.96 (512 0.95, with skewed contexts 0.99)
-//      to 24                           1 536 and more, sorted, by eight waves 0.91 to 0.97 (768 0.95, with skewed contexts 1.01)
-//   matrix path, up to 12              0.47 to 0.92; from 1 024 ranges on by two waves up to 3 rounds, 0.60 (by four 0.69), and sorted from 6 on (512 and more
-//                                      0.78 to 0.84, as they come 0.83 to 0.85); from 8 on with fewer than 256 by eight waves (0.80 to 0.94, by four 0.82 to 0.95)
-//      to 16                           64 to 256 by eight waves, 0.78 to 0.96 (fewer 1.12)
-//      to 24                           256 to 512, sorted, by eight waves 0.82 to 0.91; more, sorted, by four 0.83 to 0.92 (fewer 1.01 to 1.18)
-//      to 32                           512 and more, sorted, 0.87 to 0.91 (fewer 0.89 to 0.99)
-//      to 48                           1 024 and more, sorted, 0.90 to 0.93 (768 0.92)
-// Longer rows gain as much where the work is even (230 of 256 requests of 32 to 8 192 tokens, 32 / 8 heads, 236 -> 226 us), but one long context among
-// short ones is walked by one workgroup: 256 requests of 200 tokens and one of 8 192 56 -> 99 us, and of 1 500, which the lines let through, 49 ->
-// 40.  Where they cost most: 15 plain requests of 30 tokens and one of 1 500, 40 heads, 15.8 -> 23.8; with the others at 200 24.5 -> 27.7, with two of them long
-// 27.9 -> 29.2.  Therefore eight waves where they are level with four.
-enum WholeForm { kNotWhole, kWholeTiny, kWholePlain, kWholeEight, kWholeSorted, kWholeSortedEight };
-template <typename R>
-WholeForm whole_form(const DecodeArgs &a, int HC)
-{
-    const long long ranges = (long long)a.batch * HC, row = (long long)a.max_blocks * a.block_size;
-    // (a row of more blocks than there are is no bound of contexts to go by)
-    if (ranges > 0x7fffffff / kThreads || a.max_blocks > a.num_blocks) return kNotWhole;
-    const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
-    const bool eight = 8 * a.heads_per_pass * (R::D + 2) * sizeof(float) <= (80u << 10);   // of the LDS: two workgroups to a CU
-    const bool order = a.batch <= 4 * kLaneBatch;     // what a wave can sort
-    const WholeForm sorted = order ? kWholeSorted : kNotWhole, sorted_eight = order && eight ? kWholeSortedEight : kNotWhole;
-    if (decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads)) {
-        if (rounds_to(3)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
-        if (rounds_to(12)) {
-            if (!rounds_to(6) && ranges >= (order ? 512 : 1024)) return sorted;
-            return ranges < 256 && eight && !rounds_to(8) ? kWholeEight : kWholePlain;
-        }
-        if (ranges < (order ? 256 : 512)) return rounds_to(16) && ranges >= 64 && eight ? kWholeEight : kNotWhole;
-        if (ranges < 512) return rounds_to(24) ? sorted_eight : kNotWhole;
-        return rounds_to(ranges < 1024 ? 32 : 48) ? sorted : kNotWhole;
-    }
-    if (rounds_to(2)) return ranges >= 1024 ? kWholeTiny : kWholePlain;
-    if (rounds_to(4) && !rounds_to(3) && ranges < 256 && eight) return kWholeEight;
-    if (rounds_to(8) && !rounds_to(3) && ranges >= 512 && order) return ranges < 1024 && !rounds_to(6) ? sorted_eight : kWholeSorted;
-    if (rounds_to(8) && ranges < 1024) return rounds_to(3) || ranges >= (rounds_to(4) ? 128 : rounds_to(6) ? 256 : 768) ? kWholePlain : kNotWhole;
-    if (rounds_to(6)) return kWholePlain;
-    return ranges >= (rounds_to(12) ? 512 : rounds_to(16) ? 768 : 1536) && rounds_to(24) ? sorted_eight : kNotWhole;
-}
-// Parts that ranges are cut into at most, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
-// records of decode_balanced are a third of the time.  Workgroups in all 256, or 512 where rows are long for them: the same 400 random launches of
-// up to 400 ranges, time over the other forms' with 256 / 512 / 1 024:
-//   vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 / 0.89, more 0.93 / 0.87 / 0.87
-//      16 to 32               4 to 16 rounds 0.85 / 0.86 / 0.90, to 128 0.98 / 0.89 / 0.93, more 1.10 / 0.98 / 1.01
-//      32 to 64               4 to 32 rounds 0.92 / 0.87 / 0.90, to 128 1.14 / 0.96 / 0.96, more 1.40 / 1.06 / 1.0
-//      64 to 128              4 to 32 rounds 1.1 / 0.95 / 0.95, more 1.6 and up / 1.1 and up / 1.02 and up;  more ranges 1.1 and up
-//   matrix path, fewer than 32 ranges, 8 to 128 rounds 0.79 / 0.84 / 0.86 (fewer 1.1), more 0.88 / 0.89 / 0.92
-//      32 to 64               8 to 128 rounds 0.89 / 0.89 / 0.96, more 0.98 / 0.97 / 1.03
-//      64 to 128              16 to 32 rounds 0.91 / 0.87 / 0.91 (else 1.0 and up);  more ranges 1.0 and up
-template <typename R>
-int cuts_of(const DecodeArgs &a, int HC)
-{
-    const long long ranges = (long long)a.batch * HC, row = (long long)a.max_blocks * a.block_size;
-    if (ranges >= 128 || a.max_blocks > a.num_blocks) return 0;
-    const auto rounds_to = [row](int n) { return row <= (long long)n * kWaves * R::CT; };
-    const bool matrix = decode_uses_tiled_layout(a.bf16, a.num_q_heads / a.num_kv_heads);
-    // (the more ranges, the more a long one among short ones costs: it has its parts and no others; 5 of 1 306 to 13 065 tokens on 8 heads of
-    // 64 1.1, 4 of 131 to 4 390 on 32 / 8 fp32 heads 1.15)
-    const int most = matrix ? (ranges < 32 ? 400 : ranges < 64 ? 128 : 32) : ranges < 16 ? 400 : ranges < 32 ? 64 : ranges < 64 ? 32 : 16;
-    const int least = matrix ? (ranges >= 64 ? 16 : R::D < 128 ? 12 : 8) : 4;
-    if (rounds_to(least) || !rounds_to(most)) return 0;
-    const bool few = matrix ? ranges < 64 && rounds_to(128) : ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
-    const int cuts = min(kMostCuts, (few ? 256 : 512) / (int)ranges);
-    return (size_t)ranges * cuts * a.heads_per_pass * (R::D + 2) * sizeof(float) <= a.partial_capacity ? cuts : 0;
-}
 template <typename R>
 hipError_t launch_parts(const DecodeArgs &a, int HC, int cuts, hipStream_t s)
 {
@@ -1066,12 +1118,19 @@ hipError_t launch_parts(const DecodeArgs &a, int HC, int cuts, hipStream_t s)
     hipLaunchKernelGGL(decode_merge_parts<R>, dim3(ranges, (a.heads_per_pass * a.head_dim + 127) / 128), dim3(64 * kPartWaves), 0, s, a, cuts);
     return hipGetLastError();
 }
-template <typename R, int W, bool SORTED>
+template <typename R, int W>
 hipError_t launch_whole(const DecodeArgs &a, int HC, hipStream_t s)
 {
     constexpr int kPer = W > kWaves ? 1 : kWaves / W, kAll = kPer * W;   // ranges and waves of a workgroup
-    hipLaunchKernelGGL((decode_whole<R, W, SORTED>), dim3((unsigned)(((long long)a.batch * HC + kPer - 1) / kPer)), dim3(64 * kAll),
+    hipLaunchKernelGGL((decode_whole<R, W>), dim3((unsigned)(((long long)a.batch * HC + kPer - 1) / kPer)), dim3(64 * kAll),
                        (size_t)kAll * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a);
+    return hipGetLastError();
+}
+template <typename R>
+hipError_t launch_cut(const DecodeArgs &a, int HC, bool matrix, hipStream_t s)
+{
+    const CutArgs c = {next_launch_tag(), rules::cut_spare(matrix)};
+    hipLaunchKernelGGL(decode_cut<R>, dim3((unsigned)(a.batch * HC + c.spare)), dim3(kThreads), (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a, c);
     return hipGetLastError();
 }
 
@@ -1107,15 +1166,16 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     const size_t fit = min((size_t)kMaxShares, a.partial_capacity / per_share);
     const int wgs = min(resident, (int)(fit / kWaves));
     if (wgs < 1) return hipErrorInvalidValue;
-    const int cuts = cuts_of<R>(a, HC);
-    if (cuts > 0) return launch_parts<R>(a, HC, cuts, s);
-    switch (whole_form<R>(a, HC)) {
-    case kWholeTiny: return launch_whole<R, 2, false>(a, HC, s);
-    case kWholePlain: return launch_whole<R, kWaves, false>(a, HC, s);
-    case kWholeEight: return launch_whole<R, 8, false>(a, HC, s);
-    case kWholeSorted: return launch_whole<R, kWaves, true>(a, HC, s);
-    case kWholeSortedEight: return launch_whole<R, 8, true>(a, HC, s);
-    case kNotWhole: break;
+    const bool matrix = decode_uses_tiled_layout(a.bf16, G);
+    const rules::DecodeLaunch launch = {(long long)a.batch * HC, a.batch, a.head_dim, (long long)a.max_blocks * a.block_size, kWaves * R::CT, matrix,
+                                        a.max_blocks <= a.num_blocks, (size_t)a.heads_per_pass * (R::D + 2) * sizeof(float), a.partial_capacity};
+    switch (rules::decode_form(launch)) {
+    case rules::kWholeTwo: return launch_whole<R, 2>(a, HC, s);
+    case rules::kWholeFour: return launch_whole<R, kWaves>(a, HC, s);
+    case rules::kWholeEight: return launch_whole<R, 8>(a, HC, s);
+    case rules::kCut: return launch_cut<R>(a, HC, matrix, s);
+    case rules::kParts: return launch_parts<R>(a, HC, rules::decode_cuts(launch), s);
+    case rules::kPlan: break;
     }
     // With eight waves and more to a range (if every request runs) they are better off together; with
     // six (16 requests of 60 to 1 500 tokens, 40 heads) the barriers cost 4 % more than they save.

@@ -1,0 +1,114 @@
+// Which form a decode launch takes, by what the host knows of it: the ranges, (request, kv head / pass), there can be, and the longest a context
+// can be, a table row, in rounds: the chunks that one of four waves walks through.  Lengths and masks are on the device; the forms of longer walks
+// look at them there, by the arithmetic at the end, which is the same on the host (where a test walks through it) and in the kernels.
+#pragma once
+#include <stddef.h>
+
+#include "prefill_split.h"
+
+namespace lamps {
+namespace rules {
+
+struct DecodeLaunch {
+    long long ranges;
+    int batch, head_dim;
+    long long row;                       // positions of a table row
+    int round;                           // positions of a round: four chunks
+    bool matrix;                         // MfmaReducer (else ValuReducer)
+    bool bounded;                        // a row has no more blocks than the pool
+    size_t state;                        // bytes of a range's (outputs, maximum, sum)
+    size_t capacity;                     // bytes of partial states a launch may leave behind
+};
+enum DecodeForm { kPlan, kWholeTwo, kWholeFour, kWholeEight, kCut, kParts };
+
+constexpr int kMostCuts = 64;            // parts of a range in a kParts launch
+constexpr int kCutBatch = 256;           // requests that a wave of a kCut launch can hold
+constexpr long long kMostItems = 1 << 19;   // workgroups of one (its divisions, and 64 rounds of chunks for each in 32 bits)
+
+// Workgroups of a kCut launch beyond one for each range: about what the chip holds at once, so that a launch in which much is cut is cut
+// evenly (512 / 1 024, time over the plan's, vector path: 512 to 1 024 ranges, 8 to 32 rounds 0.95 / 0.92, the slowest 1.22 / 1.08; 2 048 and more
+// 0.93 / 0.93, 1.32 / 1.10; matrix path, 256 to 512 ranges, 8 to 64 rounds 0.71 / 0.80, 1.06 / 1.05).
+constexpr int cut_spare(bool matrix) { return matrix ? 512 : 1024; }
+
+// All lines below are drawn through launches of which two thirds are skewed: one long context among short ones, a few, 2 to 60 % of the
+// requests running, or rows of 4 and 16 times the longest; 12 000 launches of 1 to 700 requests with rows of 17 to 65 536 positions, as many again with
+// each form in turn.  Figures are time over the plan's (decode_balanced and its second launch), geometric mean and slowest.
+
+// Parts that ranges are cut into at most, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
+// records of decode_balanced are a third of the time.  Workgroups in all 256, or 512 where rows are long for them: the same 400 random launches of
+// up to 400 ranges, time over the other forms' with 256 / 512 / 1 024:
+//   vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 / 0.89, more 0.93 / 0.87 / 0.87
+//      16 to 32               4 to 16 rounds 0.85 / 0.86 / 0.90, to 128 0.98 / 0.89 / 0.93, more 1.10 / 0.98 / 1.01
+//      32 to 64               4 to 32 rounds 0.92 / 0.87 / 0.90, to 128 1.14 / 0.96 / 0.96, more 1.40 / 1.06 / 1.0
+//      64 to 128              4 to 32 rounds 1.1 / 0.95 / 0.95, more 1.6 and up / 1.1 and up / 1.02 and up;  more ranges 1.1 and up
+//   matrix path, fewer than 32 ranges, 8 to 128 rounds 0.79 / 0.84 / 0.86 (fewer 1.1), more 0.88 / 0.89 / 0.92
+//      32 to 64               8 to 128 rounds 0.89 / 0.89 / 0.96, more 0.98 / 0.97 / 1.03
+//      64 to 128              16 to 32 rounds 0.91 / 0.87 / 0.91 (else 1.0 and up);  more ranges 1.0 and up
+inline int decode_cuts(const DecodeLaunch &l)
+{
+    if (!l.bounded || l.ranges >= 128) return 0;
+    const auto rounds_to = [&l](int n) { return l.row <= (long long)n * l.round; };
+    // (the more ranges, the more a long one among short ones costs: it has its parts and no others; 5 of 1 306 to 13 065 tokens on 8 heads of
+    // 64 1.1, 4 of 131 to 4 390 on 32 / 8 fp32 heads 1.15)
+    const int most = l.matrix ? (l.ranges < 32 ? 400 : l.ranges < 64 ? 128 : 32) : l.ranges < 16 ? 400 : l.ranges < 32 ? 64 : l.ranges < 64 ? 32 : 16;
+    const int least = l.matrix ? (l.ranges >= 64 ? 16 : l.head_dim < 128 ? 12 : 8) : 4;
+    if (rounds_to(least) || !rounds_to(most)) return 0;
+    const bool few = l.matrix ? l.ranges < 64 && rounds_to(128) : l.ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
+    const int share = (few ? 256 : 512) / (int)l.ranges, cuts = share < kMostCuts ? share : kMostCuts;
+    return l.ranges * cuts * l.state <= l.capacity ? cuts : 0;
+}
+
+inline DecodeForm decode_form(const DecodeLaunch &l)
+{
+    const long long n = l.ranges;
+    // (a row of more blocks than the pool has is sized for requests that are not there: left to the plan, which goes by the lengths alone)
+    if (!l.bounded || n > 0x7fffffff / 256) return kPlan;
+    const auto rounds_to = [&l](int k) { return l.row <= (long long)k * l.round; };
+    const bool sorts = l.batch <= kCutBatch && n + cut_spare(l.matrix) < kMostItems && (size_t)(n + cut_spare(l.matrix)) * (l.state + 8) <= l.capacity;
+    const bool eight = 8 * l.state <= (80u << 10);    // of the LDS: two workgroups to a CU
+    if (decode_cuts(l) > 0) return kParts;
+    // Ranges that are short: a workgroup each, by two waves where there are thousands of a round (1 024 and more, two / four: vector path 0.62, 0.86 / 0.65, 0.97;
+    // 4 096 and more 0.79, 1.10 / 0.95, 1.32; matrix path 0.57 / 0.65).  A waiting request's workgroups leave at once, but there are tens of thousands of them: 565
+    // requests of 161 positions at most, 40 heads, 18 of them running, 18.4 us by the plan and 20.7.
+    if (rounds_to(1)) return n >= 1024 ? kWholeTwo : kWholeFour;
+    if (l.matrix) {
+        if (rounds_to(3) && n >= 1024) return kWholeTwo;   // level with four, 0.44 to 0.71; where contexts are short against the row 0.83 of it
+        // to 12 rounds, any number of requests, 0.38 to 0.80, 1.11; fewer than 256 from 8 on by eight waves (0.80, by four 0.85), 64 and more to 16
+        // (0.83; with one long context among a dozen of 20 to 100 positions up to 1.25, 10.6 us against 8.5)
+        if (rounds_to(12)) return n < 256 && eight && !rounds_to(8) ? kWholeEight : kWholeFour;
+        if (n < 256) return n >= 64 && eight && rounds_to(16) ? kWholeEight : kPlan;
+        // 256 to 512 0.73, 1.13 (to 64 rounds with all contexts long 1.07 to 1.17); more 0.81, 1.03.  Whole by eight waves or longest first, without a look at the
+        // work: 0.87, 1.21 and 0.94, 1.65
+        return rounds_to(n < 512 ? 32 : 64) && sorts ? kCut : kPlan;
+    }
+    // to 2 rounds by four waves 0.61 to 0.77, 1.11 (by two 0.62 to 0.81, 1.18); 4 096 and more by two 0.85, 1.23 (four 0.90, 1.21)
+    if (rounds_to(2)) return n < 4096 ? kWholeFour : kWholeTwo;
+    // to 3 0.53 to 0.90, 1.11
+    if (rounds_to(3)) return kWholeFour;
+    if (l.batch > kCutBatch) return rounds_to(6) ? kWholeFour : kPlan;   // 0.50 to 0.82, 1.10 (more 0.89 to 1.09, 2.66)
+    // to 4 by eight waves 0.78, 0.91 (by four 0.91, 1.14); more by either 0.91 to 0.97, 1.07 to 1.41
+    if (n < 256) return rounds_to(4) ? kWholeEight : kPlan;
+    // 256 to 512 to 16 rounds 0.92, 1.19 (more 0.97, 1.27); to 1 024, to 16 0.85, 1.12, to 32 0.91, 1.07; to 4 096 0.89, 1.17 and 0.94, 1.22 (more rounds 0.98 to 1.01,
+    // 1.18; more ranges, to 8 rounds 0.97, 1.30).  The slowest have 2 to 15 % of their requests running and take 8 to 16 us.  Whole by eight waves or longest
+    // first, without a look at the work: 0.97 to 1.03, 1.5 to 2.2
+    return n < 4096 && rounds_to(n < 512 ? 16 : 32) && sorts ? kCut : kPlan;
+}
+
+// A kCut launch: chunks of a part, and those of a range that is not worth cutting.  An even share of all chunks there are over the spare workgroups, so
+// that these are enough for all parts beyond the first of their ranges; two rounds at least.  What is up to half as long again is not worth the
+// hand-over (up to two rounds longer: 16 requests of 60 to 1 500 tokens, 40 heads, 23.7 us and 24.8).  round: chunks of four waves.
+struct CutSize {
+    int size, worth;
+};
+__host__ __device__ inline CutSize cut_size(unsigned all, int spare, int round)
+{
+    const int even = (int)(all / (unsigned)spare) + 1, least = even > 2 * round ? even : 2 * round;
+    const int size = (least + round - 1) / round * round;
+    return CutSize{size, size + size / 2};
+}
+__host__ __device__ inline int cut_parts(int n, CutSize c) { return n > c.worth ? split::small_div(n + c.size - 1, c.size) : 0; }
+// Chunks of each part of a range that is cut into so many: whole chunks of a wave.
+__host__ __device__ inline int cut_each(int n, int parts, int chunk) { return (split::small_div(n + parts - 1, parts) + chunk - 1) / chunk * chunk; }
+
+}  // namespace rules
+}  // namespace lamps

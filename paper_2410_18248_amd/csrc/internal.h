@@ -57,6 +57,8 @@ hipError_t dispatch(const DecodeArgs &a, hipStream_t stream, size_t *demand);
 const char *decode_geometry(const lamps_config *cfg, DecodeArgs *a);
 // Sets the text lamps_last_error(NULL) returns on this thread (fixed buffer, no allocation).
 void set_thread_error(const char *text);
+// 48 bits, nonzero, that no other launch of the process has.
+uint64_t next_launch_tag();
 
 struct AppendArgs {
     const void *k_new, *v_new;   // [batch][H_kv][D]

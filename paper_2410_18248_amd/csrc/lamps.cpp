@@ -196,17 +196,6 @@ void fill_decode_args(lamps_ctx *c, lamps::DecodeArgs *pa, int32_t layer, int32_
     a.layer = layer;
 }
 
-// A number no other launch of this process has, 48 bits, nonzero, and unlike what memory is likely
-// to hold: a counter, mixed (a bijection on 64 bits would not stay one when cut to 48: an odd
-// multiplier is one modulo 2^48).
-uint64_t next_launch_tag()
-{
-    static std::atomic<uint64_t> launches{0};
-    const uint64_t mask = ((uint64_t)1 << 48) - 1;
-    const uint64_t n = launches.fetch_add(1, std::memory_order_relaxed) % mask + 1;
-    return n * 0x9E3779B97F4B15u & mask;
-}
-
 int fail(lamps_ctx *c, int code, const std::string &msg)
 {
     if (c) {
@@ -533,6 +522,17 @@ const char *decode_geometry(const lamps_config *cfg, DecodeArgs *a)
 
 void set_thread_error(const char *text) { thread_error(text); }
 
+// A number no other launch of this process has, 48 bits, nonzero, and unlike what memory is likely
+// to hold: a counter, mixed (a bijection on 64 bits would not stay one when cut to 48: an odd
+// multiplier is one modulo 2^48).
+uint64_t next_launch_tag()
+{
+    static std::atomic<uint64_t> launches{0};
+    const uint64_t mask = ((uint64_t)1 << 48) - 1;
+    const uint64_t n = launches.fetch_add(1, std::memory_order_relaxed) % mask + 1;
+    return n * 0x9E3779B97F4B15u & mask;
+}
+
 }  // namespace lamps
 
 extern "C" {
@@ -802,7 +802,7 @@ int lamps_prefill_attn(lamps_ctx *c, int32_t layer, int32_t n_req, int32_t total
         p.total_tokens = total_tokens;
         p.max_new_tokens = max_new_tokens > 0 && max_new_tokens < total_tokens ? max_new_tokens : total_tokens;
         p.force_rows = max_new_tokens < 0;
-        p.tag = next_launch_tag();
+        p.tag = lamps::next_launch_tag();
         LAMPS_HIP(lamps::launch_prefill(p, c->cs));
         return LAMPS_OK;
     }

@@ -1,6 +1,7 @@
 """lamps_decode_attn where workgroups take whole ranges, or ranges in parts, and on the other side of those lines: rows of few and of many rounds of
-chunks, few ranges and many, two waves to a range, four, eight, and four with the longest contexts first; contexts around a chunk, a part and at
-the end of the row, paused and empty requests, equal lengths, against the fp64 oracle; a call that is replayed from a HIP graph with other lengths."""
+chunks, few ranges and many, two waves to a range, four, eight, and four with the longest contexts first and cut; contexts around a chunk, a part and at
+the end of the row, paused and empty requests, equal lengths, a few long ones among many short ones, few that run, against the fp64 oracle; a call that
+is replayed from a HIP graph with other lengths."""
 import numpy as np
 import pytest
 import torch
@@ -66,7 +67,56 @@ def test_many_ranges(dtype, H, Hkv, D, bs, batch, row):
     _check(dtype, H, Hkv, D, bs, batch, row, 5)
 
 
-@pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100)])
+def _kinds(batch, row, rng):
+    """Lengths and masks: one long among short ones, a few, few that run, none, all as long as can be, anything."""
+    short = [int(x) for x in rng.randint(1, max(2, row // 20), batch)]
+    few = [row - i if i % 7 == 3 else c for i, c in enumerate(short)]
+    any_ = [int(x) for x in rng.randint(0, row + 1, batch)]
+    yield [row if i == batch // 3 else c for i, c in enumerate(short)], [1] * batch
+    yield few, [int(i % 5 != 1) for i in range(batch)]
+    yield any_, [int(i in (1, batch - 1)) for i in range(batch)]
+    yield any_, [0] * batch
+    yield [row] * batch, [1] * batch
+    yield any_, [int(x) for x in rng.rand(batch) < 0.7]
+    yield [0] * batch, [1] * batch
+
+
+def _skewed(dtype, H, Hkv, D, bs, batch, row):
+    """All requests read the same blocks, each as far as its context."""
+    rng = np.random.RandomState(batch + row)
+    nblk = (row + bs - 1) // bs
+    geom = W.Geometry(1, H, Hkv, D, bs, nblk + 2, nblk, dtype)
+    rig = Rig(geom, batch)
+    one, _ = W.deal_block_table(W.permutation(3, geom.num_blocks), [row], geom)
+    table = np.repeat(one, batch, axis=0)
+    K, V = W.logical_kv(70, geom, row)
+    rig.page_requests(0, one, [K], [V])
+    q = W.queries(6, geom, batch)
+    for ctx, running in _kinds(batch, row, rng):
+        rig.workspace.fill_(255)                         # NaN where no part writes
+        got = to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0))
+        on = np.asarray(running, dtype=bool)
+        assert (got[~on] == 7.0).all()
+        if on.any():
+            ref = oracle.decode_attn(q[on], [K[:c] for c, r in zip(ctx, running) if r], [V[:c] for c, r in zip(ctx, running) if r],
+                                     [c for c, r in zip(ctx, running) if r], [1] * int(on.sum()))
+            assert np.abs(got[on] - ref).max() <= tol(geom), (ctx, running)
+        assert np.array_equal(got, to_f64(rig.decode(0, q, table, ctx, running, sentinel=7.0)))
+    rig.close()
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
+    ("bf16", 32, 32, 64, 16, 17, 640), ("bf16", 8, 8, 64, 16, 70, 1500), ("bf16", 40, 40, 128, 16, 16, 1504), ("bf16", 16, 16, 256, 16, 20, 900),
+    ("bf16", 16, 8, 128, 16, 40, 2000), ("bf16", 16, 8, 64, 32, 66, 2048), ("bf16", 128, 4, 64, 16, 40, 1000), ("bf16", 10, 2, 256, 16, 129, 800),
+    ("f32", 8, 8, 32, 16, 40, 900), ("f32", 16, 2, 128, 32, 130, 400), ("f32", 6, 3, 64, 16, 100, 700), ("bf16", 4, 4, 128, 16, 256, 500),
+])
+def test_skewed_batches_of_many_ranges(dtype, H, Hkv, D, bs, batch, row):
+    """Ranges that are cut by the lengths of the call, and whole ones behind them."""
+    _skewed(dtype, H, Hkv, D, bs, batch, row)
+
+
+@pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100),
+                                                         ("bf16", 16, 8, 64, 70, 1600), ("f32", 8, 8, 64, 65, 1000)])
 def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
     """The same graph over contexts that grow, shrink and trade places: order and stretches are worked out in the launch."""
     rng = np.random.RandomState(9)
@@ -88,8 +138,10 @@ def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
     with torch.cuda.graph(graph, stream=rig.compute):
         rig.lamps.decode_attn(0, batch, dq, dt, dc, dm, out)
     for turn in range(3):
-        ctx = [int(x) for x in rng.randint(0, row + 1, batch)]
+        ctx = [int(x) for x in rng.randint(0, (row if turn != 1 else row // 16) + 1, batch)]
         mask = [int(x) for x in rng.rand(batch) < 0.8]
+        if turn == 1:
+            ctx[0] = row
         mask[0] = 1
         dc.copy_(torch.as_tensor(np.asarray(ctx, dtype=np.int32)))
         dm.copy_(torch.as_tensor(np.asarray(mask, dtype=np.uint8)))
