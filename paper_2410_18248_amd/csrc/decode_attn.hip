@@ -843,72 +843,88 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_cut(const Dec
     }
 }
 
-// The same with a range cut into up to `cuts` parts, a workgroup each, of at least a chunk per wave; the parts of a range are
-// added up by a second launch, which works them out from the lengths as this one does.  How many parts there can be is the
-// host's, so neither launch has a plan or records of shares in front of its first byte: one request of 1 999 tokens, 32 / 8 heads, 9.3 -> 7.2 us
+// Few ranges, all of them in parts of one size, a workgroup each; the parts of a range are added up by a second launch, which works them out from the
+// lengths as this one does, so neither launch has records of shares in front of its first byte: one request of 1 999 tokens, 32 / 8 heads, 9.3 -> 7.2 us
 // (5.2 + 3.7 -> 4.3 + 2.8), one of 4 000 on 8 plain heads of 64 9.0 -> 7.8.
-template <typename R, int W>
-__device__ __forceinline__ int part_chunks(int n, int cuts)
+struct PartArgs {
+    int even;                                         // parts of a range if all are alike: the launch's workgroups by the ranges there can be
+    int most;                                         // ... at most: there is room for so many
+};
+struct Parts {
+    int n, own, size;                                 // of the lane's request: chunks, parts; chunks of a part at most
+};
+__device__ __forceinline__ Parts parts_of(const DecodeArgs &a, const PartArgs &c, int2 q, int GT, int chunk)
 {
-    constexpr int kChunk = R::CT / R::GT;
-    return max(W * kChunk, ((n + cuts - 1) / cuts + kChunk - 1) / kChunk * kChunk);
+    Parts p;
+    p.n = chunks_of(q.x, q.y, GT);
+    p.size = rules::part_size(__builtin_amdgcn_readlane(wave_scan(p.n), 63), __builtin_amdgcn_readlane(wave_max_to(p.n), 63), a.batch, c.even, c.most, kWaves, chunk);
+    p.own = split::small_div(p.n + p.size - 1, p.size);
+    return p;
 }
 template <typename R>
-__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const DecodeArgs a, const int cuts)
+__global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const DecodeArgs a, const PartArgs c)
 {
-    constexpr int D = R::D;
+    constexpr int D = R::D, kChunk = R::CT / R::GT;
     extern __shared__ __align__(16) float parts[];    // [wave][head][D + 2]
-    const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes, ranges = a.batch * HC;
-    const int part = __builtin_amdgcn_readfirstlane(blockIdx.x / ranges), range = blockIdx.x - part * ranges;
-    const int r = __builtin_amdgcn_readfirstlane(range / HC), hc = range - r * HC;
-    const int2 q = request_of(a, r);
-    if (!__builtin_amdgcn_readfirstlane(q.x)) return;
-    const int C = __builtin_amdgcn_readfirstlane(q.y), n = chunks_of(1, C, R::GT);
-    const int each = part_chunks<R, kWaves>(n, cuts), c0 = part * each;
-    if (c0 >= n) return;
-    const bool all = each >= n;
-    float *slot = a.partials + ((size_t)range * cuts + part) * GH * (D + 2);
-    stretches<R, kWaves>(a, parts, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r, hc, c0, min(n, c0 + each), C, true,
+    const int lane = threadIdx.x & 63, GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
+    const int2 q = request_of(a, lane);
+    const Parts p = parts_of(a, c, q, R::GT, kChunk);
+    const int upto = wave_scan(p.own);
+    int at = split::small_div(blockIdx.x, HC);
+    const int hc = blockIdx.x - at * HC;
+    const int r = __popcll(__ballot(upto <= at));     // the first whose parts end behind `at`
+    if (r == 64) return;
+    at -= __builtin_amdgcn_readlane(upto - p.own, r);
+    const int of = __builtin_amdgcn_readlane(p.own, r), n = __builtin_amdgcn_readlane(p.n, r), C = __builtin_amdgcn_readlane(q.y, r);
+    const int c0 = at * p.size;
+    float *slot = a.partials + ((size_t)(r * HC + hc) * c.most + at) * GH * (D + 2);
+    stretches<R, kWaves>(a, parts, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r, hc, c0, min(n, c0 + p.size), C, true,
                          [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
-                             if (all)
+                             if (of == 1)
                                  store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
                              else
                                  store_partial(slot + (size_t)h * (D + 2), D, d, M, L, A);
                          });
 }
 
-// Adds the parts of a range up: 128 (head, dim) outputs a workgroup, two per lane, its waves every eighth part.  One round trip: the parts there
-// can be are asked for together with the length that says how many there are.
+// Adds the parts of a range up: 128 (head, dim) outputs a workgroup, two per lane, its waves every eighth part.  One round trip where ranges are about
+// alike: as many parts as they then have are asked for together with the lengths that say how many there are; a second one for those of longer ranges.
 constexpr int kPartWaves = 8;
-template <typename R>
-__global__ __launch_bounds__(64 * kPartWaves) void decode_merge_parts(const DecodeArgs a, const int cuts)
+template <bool BF16>
+__global__ __launch_bounds__(64 * kPartWaves) void decode_merge_parts(const DecodeArgs a, const PartArgs c, const int GT, const int chunk)
 {
-    constexpr int D = R::D, N = rules::kMostCuts / kPartWaves;
+    constexpr int N = rules::kMostCuts / kPartWaves;
     __shared__ float4 sums[kPartWaves][64];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int D = a.head_dim, log2_D = __builtin_ctz(D);   // (a power of two)
     const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
     const int range = blockIdx.x, r = range / HC, hc = range - r * HC;
-    const int idx = min((int)blockIdx.y * 128 + 2 * lane, GH * D - 2), h = idx / D, d = idx % D;
-    const int running = a.running[r], length = a.ctx_lens[r];
+    const int idx = min((int)blockIdx.y * 128 + 2 * lane, GH * D - 2), h = idx >> log2_D, d = idx & (D - 1);
+    const int2 q = request_of(a, lane);
     float2 ml[N], ao[N];
+    const auto ask = [&](int k) {
+        const float2 *x = reinterpret_cast<const float2 *>(a.partials + (((size_t)range * c.most + wv + kPartWaves * k) * GH + h) * (D + 2));
+        ml[k] = x[D / 2];
+        ao[k] = x[d / 2];
+    };
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const int part = wv + kPartWaves * k;
         ml[k] = make_float2(kLowest, 0.0f);
         ao[k] = make_float2(0.0f, 0.0f);
-        if (part < cuts) {                            // uniform
-            const float2 *x = reinterpret_cast<const float2 *>(a.partials + (((size_t)range * cuts + part) * GH + h) * (D + 2));
-            ml[k] = x[D / 2];
-            ao[k] = x[d / 2];
-        }
+        if (wv + kPartWaves * k < c.even) ask(k);     // uniform
     }
-    if (!running) return;                             // uniform
-    const int C = min(length, a.max_blocks * a.block_size), n = chunks_of(1, C, R::GT), each = part_chunks<R, kWaves>(n, cuts);
-    if (each >= n) return;                            // written already
+    const Parts p = parts_of(a, c, q, GT, chunk);
+    const int runs = __builtin_amdgcn_readlane(p.own, r);
+    if (runs <= 1) return;                            // does not run, or written already
+    if (runs > c.even) {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (wv + kPartWaves * k >= c.even && wv + kPartWaves * k < runs) ask(k);
+    }
     float M = kLowest, L = 0.0f, A[2] = {0.0f, 0.0f};
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        if ((wv + kPartWaves * k) * each >= n) break;
+        if (wv + kPartWaves * k >= runs) break;
         const float Mn = fmaxf(M, ml[k].x), f0 = fast_exp2(M - Mn), f = fast_exp2(ml[k].x - Mn);
         L = L * f0 + ml[k].y * f;
         A[0] = A[0] * f0 + ao[k].x * f;
@@ -928,7 +944,7 @@ __global__ __launch_bounds__(64 * kPartWaves) void decode_merge_parts(const Deco
         M = Mn;
     }
     if (blockIdx.y * 128 + 2 * lane < GH * D)
-        store_out<R::kBF16>(a.out, ((size_t)r * a.num_q_heads + hc * GH + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
+        store_out<BF16>(a.out, ((size_t)r * a.num_q_heads + hc * GH + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
 }
 
 // N pieces of a split range (first, first + 1, ... in slot order; at most cnt of them), their loads
@@ -1109,13 +1125,14 @@ hipError_t launch_balanced(const DecodeArgs &a, int wgs, hipStream_t s)
 }
 
 template <typename R>
-hipError_t launch_parts(const DecodeArgs &a, int HC, int cuts, hipStream_t s)
+hipError_t launch_parts(const DecodeArgs &a, int HC, int even, int most, hipStream_t s)
 {
-    const int ranges = a.batch * HC;
-    hipLaunchKernelGGL(decode_parts<R>, dim3(ranges * cuts), dim3(kThreads), (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a, cuts);
+    const PartArgs c = {even, most};
+    hipLaunchKernelGGL(decode_parts<R>, dim3(a.batch * HC * (even + 1)), dim3(kThreads), (size_t)kWaves * a.heads_per_pass * (R::D + 2) * sizeof(float), s, a, c);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_merge_parts<R>, dim3(ranges, (a.heads_per_pass * a.head_dim + 127) / 128), dim3(64 * kPartWaves), 0, s, a, cuts);
+    hipLaunchKernelGGL(decode_merge_parts<R::kBF16>, dim3(a.batch * HC, (a.heads_per_pass * a.head_dim + 127) / 128), dim3(64 * kPartWaves), 0, s, a, c,
+                       R::GT, R::CT / R::GT);
     return hipGetLastError();
 }
 template <typename R, int W>
@@ -1174,7 +1191,7 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     case rules::kWholeFour: return launch_whole<R, kWaves>(a, HC, s);
     case rules::kWholeEight: return launch_whole<R, 8>(a, HC, s);
     case rules::kCut: return launch_cut<R>(a, HC, matrix, s);
-    case rules::kParts: return launch_parts<R>(a, HC, rules::decode_cuts(launch), s);
+    case rules::kParts: return launch_parts<R>(a, HC, rules::decode_cuts(launch), rules::decode_most_cuts(launch), s);
     case rules::kPlan: break;
     }
     // With eight waves and more to a range (if every request runs) they are better off together; with

@@ -22,6 +22,7 @@ struct DecodeLaunch {
 enum DecodeForm { kPlan, kWholeTwo, kWholeFour, kWholeEight, kCut, kParts };
 
 constexpr int kMostCuts = 64;            // parts of a range in a kParts launch
+constexpr int kPartBatch = 64;           // requests of one, a lane's each
 constexpr int kCutBatch = 256;           // requests that a wave of a kCut launch can hold
 constexpr long long kMostItems = 1 << 19;   // workgroups of one (its divisions, and 64 rounds of chunks for each in 32 bits)
 
@@ -34,28 +35,31 @@ constexpr int cut_spare(bool matrix) { return matrix ? 512 : 1024; }
 // requests running, or rows of 4 and 16 times the longest; 12 000 launches of 1 to 700 requests with rows of 17 to 65 536 positions, as many again with
 // each form in turn.  Figures are time over the plan's (decode_balanced and its second launch), geometric mean and slowest.
 
-// Parts that ranges are cut into at most, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
-// records of decode_balanced are a third of the time.  Workgroups in all 256, or 512 where rows are long for them: the same 400 random launches of
-// up to 400 ranges, time over the other forms' with 256 / 512 / 1 024:
-//   vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 / 0.89, more 0.93 / 0.87 / 0.87
-//      16 to 32               4 to 16 rounds 0.85 / 0.86 / 0.90, to 128 0.98 / 0.89 / 0.93, more 1.10 / 0.98 / 1.01
-//      32 to 64               4 to 32 rounds 0.92 / 0.87 / 0.90, to 128 1.14 / 0.96 / 0.96, more 1.40 / 1.06 / 1.0
-//      64 to 128              4 to 32 rounds 1.1 / 0.95 / 0.95, more 1.6 and up / 1.1 and up / 1.02 and up;  more ranges 1.1 and up
-//   matrix path, fewer than 32 ranges, 8 to 128 rounds 0.79 / 0.84 / 0.86 (fewer 1.1), more 0.88 / 0.89 / 0.92
-//      32 to 64               8 to 128 rounds 0.89 / 0.89 / 0.96, more 0.98 / 0.97 / 1.03
-//      64 to 128              16 to 32 rounds 0.91 / 0.87 / 0.91 (else 1.0 and up);  more ranges 1.0 and up
+// Parts of a range if all are alike, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
+// records of decode_balanced are a third of the time:
+//   vector path, fewer than 16 ranges, 4 to 400 rounds 0.85, 0.99;  16 to 32, 4 to 64 0.83, 0.94;  32 to 64, 4 to 32 0.84, 0.97;  64 to 128, 4 to 16 0.87, 0.99
+//   matrix path, fewer than 16 ranges, 8 to 400 rounds 0.77, 0.94;  16 to 32, 8 to 128 0.79, 0.96, to 400 0.82, 0.97;  32 to 64, 8 to 32 0.80, 0.92, to 128
+//      0.85, 1.19 (all contexts long: 0.95, 1.15; twice that 1.0);  64 to 96, 16 to 32 0.85, 1.02 (96 to 128 0.96, 1.07)
+// (With the same number of parts for every range there can be: a context among 11 of 32 ranges, or 2 of 29 requests running, took up to 1.6 times the
+// plan's time.)
+// Workgroups in all 256, or 512 where rows are long for them (256 / 512 / 1 024, even batches: vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 /
+// 0.89, more 0.93 / 0.87 / 0.87; 16 to 32 ranges to 16 rounds 0.85 / 0.86 / 0.90; 32 to 64 0.92 / 0.87 / 0.90; matrix path, fewer than 32, 8 to 128
+// rounds 0.79 / 0.84 / 0.86, more 0.88 / 0.89 / 0.92; 32 to 64 0.89 / 0.89 / 0.96; 64 to 128, 16 to 32 rounds, 0.91 / 0.87 / 0.91).
+inline int decode_most_cuts(const DecodeLaunch &l)   // of one range, where others are shorter
+{
+    const long long room = (long long)(l.capacity / l.state) / l.ranges;
+    return room < kMostCuts ? (int)room : kMostCuts;
+}
 inline int decode_cuts(const DecodeLaunch &l)
 {
-    if (!l.bounded || l.ranges >= 128) return 0;
+    if (!l.bounded || l.ranges >= 128 || l.batch > kPartBatch) return 0;
     const auto rounds_to = [&l](int n) { return l.row <= (long long)n * l.round; };
-    // (the more ranges, the more a long one among short ones costs: it has its parts and no others; 5 of 1 306 to 13 065 tokens on 8 heads of
-    // 64 1.1, 4 of 131 to 4 390 on 32 / 8 fp32 heads 1.15)
-    const int most = l.matrix ? (l.ranges < 32 ? 400 : l.ranges < 64 ? 128 : 32) : l.ranges < 16 ? 400 : l.ranges < 32 ? 64 : l.ranges < 64 ? 32 : 16;
+    const int most = l.matrix ? (l.ranges < 32 ? 400 : l.ranges < 64 ? 128 : l.ranges < 96 ? 32 : 0) : l.ranges < 16 ? 400 : l.ranges < 32 ? 64 : l.ranges < 64 ? 32 : 16;
     const int least = l.matrix ? (l.ranges >= 64 ? 16 : l.head_dim < 128 ? 12 : 8) : 4;
     if (rounds_to(least) || !rounds_to(most)) return 0;
     const bool few = l.matrix ? l.ranges < 64 && rounds_to(128) : l.ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
     const int share = (few ? 256 : 512) / (int)l.ranges, cuts = share < kMostCuts ? share : kMostCuts;
-    return l.ranges * cuts * l.state <= l.capacity ? cuts : 0;
+    return cuts <= decode_most_cuts(l) ? cuts : 0;
 }
 
 inline DecodeForm decode_form(const DecodeLaunch &l)
@@ -109,6 +113,16 @@ __host__ __device__ inline CutSize cut_size(unsigned all, int spare, int round)
 __host__ __device__ inline int cut_parts(int n, CutSize c) { return n > c.worth ? split::small_div(n + c.size - 1, c.size) : 0; }
 // Chunks of each part of a range that is cut into so many: whole chunks of a wave.
 __host__ __device__ inline int cut_each(int n, int parts, int chunk) { return (split::small_div(n + parts - 1, parts) + chunk - 1) / chunk * chunk; }
+
+// A kParts launch: chunks of a part, the fewest (a chunk per wave at least) that give no more parts than `even` for each request there can be and one
+// for each that runs, and no range more than `most`.  chunk: of a wave, one or two.
+__host__ __device__ inline int part_size(int sum, int longest, int batch, int even, int most, int waves, int chunk)
+{
+    const int all = even * batch, share = split::small_div(sum + all - 1, all), room = split::small_div(longest + most - 1, most);
+    int size = waves * chunk > share ? waves * chunk : share;
+    size = size > room ? size : room;
+    return (size + chunk - 1) & -chunk;
+}
 
 }  // namespace rules
 }  // namespace lamps

@@ -25,6 +25,13 @@ int c_form(int kv_heads, int group, int bf16, int dim, int batch, long long row,
 {
     return rules::decode_form(launch(kv_heads, group, bf16, dim, batch, row, bounded, capacity));
 }
+int c_cuts(int kv_heads, int group, int bf16, int dim, int batch, long long row, long long capacity, int *most)
+{
+    const rules::DecodeLaunch l = launch(kv_heads, group, bf16, dim, batch, row, 1, capacity);
+    const int n = rules::decode_cuts(l);
+    *most = n ? rules::decode_most_cuts(l) : 0;
+    return n;
+}
 int c_spare(int matrix) { return rules::cut_spare(matrix); }
 void c_cut(unsigned all, int spare, int round, int n, int chunk, int *out)
 {
@@ -32,6 +39,7 @@ void c_cut(unsigned all, int spare, int round, int n, int chunk, int *out)
     out[0] = c.size; out[1] = c.worth; out[2] = rules::cut_parts(n, c);
     out[3] = out[2] ? rules::cut_each(n, out[2], chunk) : 0;
 }
+int c_part(int sum, int longest, int batch, int even, int most, int chunk) { return rules::part_size(sum, longest, batch, even, most, 4, chunk); }
 }
 """
 PLAN, TWO, FOUR, EIGHT, CUT, PARTS = range(6)
@@ -47,6 +55,7 @@ def lib(tmp_path_factory):
                            str(d / "rules.cpp"), "-o", so])
     lib = ctypes.CDLL(so)
     lib.c_form.argtypes = [ctypes.c_int] * 5 + [ctypes.c_longlong, ctypes.c_int, ctypes.c_longlong]
+    lib.c_cuts.argtypes = [ctypes.c_int] * 5 + [ctypes.c_longlong, ctypes.c_longlong, ctypes.POINTER(ctypes.c_int)]
     lib.c_cut.argtypes = [ctypes.c_uint] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     return lib
 
@@ -59,7 +68,7 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (32, 8, 128, "bf16", 1, 2000, PARTS), (32, 8, 128, "bf16", 1, 200, FOUR), (8, 8, 64, "bf16", 1, 4000, PARTS), (32, 8, 128, "bf16", 1, 32768, PLAN),
     # few ranges: parts on both sides of the lines
     (32, 8, 128, "bf16", 3, 8192, PARTS), (32, 8, 128, "bf16", 4, 8192, PARTS), (32, 8, 128, "bf16", 4, 8208, PLAN), (32, 8, 128, "bf16", 8, 2048, PARTS),
-    (32, 8, 128, "bf16", 12, 2064, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PARTS),
+    (32, 8, 128, "bf16", 12, 2048, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PLAN),
     # whole ranges
     (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 200, 256, TWO),
     (32, 8, 128, "bf16", 200, 64, TWO), (32, 8, 128, "bf16", 200, 256, FOUR), (32, 8, 128, "bf16", 256, 512, FOUR), (32, 8, 128, "bf16", 257, 512, FOUR),
@@ -74,6 +83,9 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (16, 8, 64, "bf16", 66, 2048, CUT), (128, 4, 64, "bf16", 40, 1008, CUT), (8, 8, 32, "f32", 40, 912, CUT), (16, 2, 128, "f32", 130, 416, CUT),
     (6, 3, 64, "f32", 100, 704, CUT), (4, 4, 128, "bf16", 256, 512, CUT), (32, 32, 128, "bf16", 34, 800, CUT), (16, 8, 64, "bf16", 70, 1600, CUT),
     (8, 8, 64, "f32", 65, 1008, CUT),
+    (8, 2, 128, "bf16", 10, 2512, PARTS), (32, 1, 128, "bf16", 20, 1504, PARTS), (16, 4, 64, "bf16", 16, 1600, PARTS), (2, 1, 128, "bf16", 64, 1600, PARTS),
+    (8, 8, 64, "bf16", 11, 1312, PARTS), (2, 2, 256, "bf16", 7, 2000, PARTS), (8, 2, 128, "f32", 30, 912, PARTS), (4, 4, 32, "f32", 16, 1120, PARTS),
+    (10, 2, 256, "bf16", 3, 5008, PARTS), (8, 2, 128, "bf16", 4, 2000, PARTS),
 ])
 def test_forms(lib, H, Hkv, D, dtype, batch, row, want):
     assert form(lib, H, Hkv, dtype, D, batch, row) == want
@@ -136,3 +148,24 @@ def test_cut_launches(lib):
             items += parts * heads
         assert items <= batch * heads + spare
 
+
+def test_parts(lib):
+    """The same of launches of few ranges: `even` workgroups for each range there can be and one for each that runs, `most` parts of a range."""
+    rng, most = random.Random(8), ctypes.c_int()
+    done = 0
+    while done < 4000:
+        H, Hkv, D, dtype = rng.choice([(32, 8, 128, "bf16"), (40, 40, 128, "bf16"), (8, 2, 64, "bf16"), (8, 8, 64, "f32"), (8, 1, 128, "bf16"), (10, 2, 256, "bf16")])
+        batch, row, room = rng.randint(1, 64), int(2 ** rng.uniform(6, 15)), rng.choice([ROOM, 31 << 20, 2 << 20])
+        even = lib.c_cuts(Hkv, H // Hkv, dtype == "bf16", D, batch, row, room, ctypes.byref(most))
+        if not even:
+            continue
+        done += 1
+        gt, chunk = (16, 1) if H > Hkv else (8, 2) if D == 128 else (16, 2)
+        if dtype == "f32":
+            gt, chunk = 16, 2
+        n = [(c + gt - 1) // gt for c in _contexts(rng, batch, row)]
+        size = lib.c_part(sum(n), max(n), batch, even, most.value, chunk)
+        own = [-(-c // size) for c in n]
+        assert even <= most.value <= 64 and max(own) <= most.value
+        assert sum(own) <= batch * even + sum(c > 0 for c in n)
+        assert size % chunk == 0 and size < max(4 * chunk, sum(n) / (batch * even) + 1, max(n) / most.value + 1) + chunk

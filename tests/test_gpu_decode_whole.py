@@ -115,6 +115,15 @@ def test_skewed_batches_of_many_ranges(dtype, H, Hkv, D, bs, batch, row):
     _skewed(dtype, H, Hkv, D, bs, batch, row)
 
 
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
+    ("bf16", 8, 2, 128, 16, 10, 2500), ("bf16", 32, 1, 128, 16, 20, 1500), ("bf16", 16, 4, 64, 32, 16, 1600), ("bf16", 2, 1, 128, 16, 64, 1600), ("bf16", 8, 8, 64, 16, 11, 1300),
+    ("bf16", 2, 2, 256, 16, 7, 2000), ("f32", 8, 2, 128, 16, 30, 900), ("f32", 4, 4, 32, 32, 16, 1100), ("bf16", 10, 2, 256, 16, 3, 5000),
+])
+def test_skewed_batches_of_few_ranges(dtype, H, Hkv, D, bs, batch, row):
+    """Ranges in parts of one size, which the lengths of the call decide."""
+    _skewed(dtype, H, Hkv, D, bs, batch, row)
+
+
 @pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100),
                                                          ("bf16", 16, 8, 64, 70, 1600), ("f32", 8, 8, 64, 65, 1000)])
 def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
