@@ -1,6 +1,7 @@
 """How a decode launch divides its work: one request per lane up to 64 of them, four per lane up to 256, by workgroups above;
 pieces of one range each while there are enough shares, equal shares that straddle ranges otherwise, by waves and by
-workgroups.  Batches on both sides of each line, with empty, paused and long requests among them, against the fp64 oracle."""
+workgroups.  Batches on both sides of each line, with empty, paused and long requests among them, against the fp64 oracle.
+Table rows are longer than the pool, so that no launch goes by what a row could hold (whole ranges, parts): those have tests of their own."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 def _check(H, Hkv, D, dtype, ctx, running, shift=0):
     blocks = [(c + 15) // 16 for c in ctx]
-    geom = W.Geometry(1, H, Hkv, D, 16, sum(blocks) + 4, max(max(blocks), 1), dtype)
+    geom = W.Geometry(1, H, Hkv, D, 16, sum(blocks) + 4, sum(blocks) + 5, dtype)
     rig = Rig(geom, len(ctx))
     table, _ = W.deal_block_table(W.permutation(6, geom.num_blocks), ctx, geom)
     K, V = zip(*[W.logical_kv(20 + 17 * r, geom, c) for r, c in enumerate(ctx)])

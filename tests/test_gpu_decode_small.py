@@ -1,7 +1,8 @@
 """lamps_decode_attn on small launches -- shares that are pieces of one range each, shares of a whole
 workgroup, and the two on either side of the rules that choose them -- against the fp64 oracle: single
 requests around a chunk and a share, paused and empty requests in between, one long context among short
-ones, more requests than threads, few and many ranges per resident wave."""
+ones, more requests than threads, few and many ranges per resident wave.  With table rows that the longest context fills, by which most of these
+go whole or in parts, and with rows longer than the pool, by which all of them go in shares."""
 import numpy as np
 import pytest
 import torch
@@ -19,11 +20,12 @@ GEOMS = [("bf16", 4, 4, 128, 16), ("bf16", 8, 2, 128, 16), ("bf16", 2, 2, 256, 3
          ("f32", 8, 2, 128, 16), ("f32", 4, 4, 32, 16)]
 
 
+@pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("dtype,H,Hkv,D,bs", GEOMS)
-def test_small_launches(dtype, H, Hkv, D, bs):
+def test_small_launches(dtype, H, Hkv, D, bs, wide):
     for ctx in ONE + MIX:
         blocks = [(c + bs - 1) // bs for c in ctx]
-        geom = W.Geometry(1, H, Hkv, D, bs, sum(blocks) + 4, max(max(blocks), 1), dtype)
+        geom = W.Geometry(1, H, Hkv, D, bs, sum(blocks) + 4, sum(blocks) + 5 if wide else max(max(blocks), 1), dtype)
         rig = Rig(geom, len(ctx))
         table, _ = W.deal_block_table(W.permutation(3, geom.num_blocks), ctx, geom)
         K, V = zip(*[W.logical_kv(70 + 17 * r, geom, c) for r, c in enumerate(ctx)])

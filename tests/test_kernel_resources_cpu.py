@@ -97,6 +97,17 @@ def test_decode_workgroups_per_cu(kernels):
     assert seen == len(least)
 
 
+def test_cut_decode_workgroups_per_cu(kernels):
+    """The spare workgroups of a launch that cuts ranges, 1 024 on the vector path and 512 on the matrix path, are about what the chip holds at once."""
+    seen = 0
+    for name, k in kernels.items():
+        m = re.search(r"decode_cut.*(Valu|Mfma)ReducerI(\w+?)EE", name)
+        if m:
+            assert _workgroups(k) >= (4 if m.group(1) == "Valu" else 1 if "256" in m.group(2) else 2), (name, k[".vgpr_count"])
+            seen += 1
+    assert seen == 15
+
+
 def test_teams_have_a_cu_to_themselves_and_no_scratch(kernels):
     """Two waves of a workgroup to a SIMD; and the waits for the loads of a stage count every load and store, which one to scratch memory
     between them would be."""
