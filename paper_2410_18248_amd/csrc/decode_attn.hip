@@ -48,6 +48,7 @@
 //     weights at the price of a second, nearly free, MFMA.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -1059,6 +1060,10 @@ __global__ __launch_bounds__(64 * kMergeShares) void decode_merge_balanced(const
 
 // ---------------------------------------------------------------- launchers
 
+// Bytes of partial states in the library's own scratch memory.  The form of a launch goes by the smaller of that and what a workspace has for the geometry,
+// so that a call has the same results from either.
+constexpr size_t kStaticPartialBytes = (size_t)LAMPS_STATIC_SCRATCH_BYTES - ((size_t)1 << 20);
+
 // LDS of a decode_balanced launch.
 template <typename R, bool TOGETHER>
 size_t balanced_lds(int batch, int heads_per_pass)
@@ -1185,7 +1190,8 @@ hipError_t launch_one(const DecodeArgs &a, hipStream_t s, size_t *demand)
     if (wgs < 1) return hipErrorInvalidValue;
     const bool matrix = decode_uses_tiled_layout(a.bf16, G);
     const rules::DecodeLaunch launch = {(long long)a.batch * HC, a.batch, a.head_dim, (long long)a.max_blocks * a.block_size, kWaves * R::CT, matrix,
-                                        a.max_blocks <= a.num_blocks, (size_t)a.heads_per_pass * (R::D + 2) * sizeof(float), a.partial_capacity};
+                                        a.max_blocks <= a.num_blocks, (size_t)a.heads_per_pass * (R::D + 2) * sizeof(float),
+                                        std::min({a.partial_capacity, (size_t)decode_max_shares(a.heads_per_pass, R::D) * per_share, kStaticPartialBytes})};
     switch (rules::decode_form(launch)) {
     case rules::kWholeTwo: return launch_whole<R, 2>(a, HC, s);
     case rules::kWholeFour: return launch_whole<R, kWaves>(a, HC, s);
@@ -1294,10 +1300,9 @@ hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream)
 // library runs on holds its own copy of the array, at its own address, until the process ends.
 namespace {
 
-constexpr size_t kStaticPartialBytes = (size_t)LAMPS_STATIC_SCRATCH_BYTES - ((size_t)1 << 20);
 constexpr size_t kStaticInfoBytes = (size_t)(lamps::kMaxShares + 1) * sizeof(int4);
 static_assert(kStaticInfoBytes <= ((size_t)1 << 20), "share records must fit the last MiB");
-static_assert(kStaticPartialBytes % 256 == 0, "the share records start 256-byte aligned");
+static_assert(lamps::kStaticPartialBytes % 256 == 0, "the share records start 256-byte aligned");
 
 static __device__ __align__(256) unsigned char scratch[LAMPS_STATIC_SCRATCH_BYTES];
 
@@ -1360,12 +1365,12 @@ extern "C" int lamps_decode_attn_static(const lamps_config *cfg, void *compute_s
     a.batch = batch;
     a.layer = layer;
     a.partials = reinterpret_cast<float *>(base);
-    a.partial_capacity = kStaticPartialBytes;
-    a.share_info = reinterpret_cast<int4 *>(base + kStaticPartialBytes);
+    a.partial_capacity = lamps::kStaticPartialBytes;
+    a.share_info = reinterpret_cast<int4 *>(base + lamps::kStaticPartialBytes);
     size_t demand = 0;
     if ((e = lamps::dispatch(a, nullptr, &demand)) != hipSuccess)
         return static_fail(LAMPS_ERR_HIP, hipGetErrorString(e));
-    if (demand > kStaticPartialBytes)
+    if (demand > lamps::kStaticPartialBytes)
         return static_fail(LAMPS_ERR_RANGE,
                            "lamps_decode_attn_static: this geometry's partial slots (two records of heads per "
                            "pass x (head_dim + 2) floats per resident wavefront) exceed the static scratch buffer");

@@ -69,6 +69,29 @@ def test_static_scratch_decode_equals_the_workspace_decode_twice_in_a_row(dtype,
     rig.close()
 
 
+def test_the_form_of_a_launch_does_not_go_by_where_its_scratch_memory_is():
+    """A launch whose ranges' states fit the workspace and not the static array: both calls take the form that fits either.  All requests read the
+    same blocks."""
+    B, H, Hkv, D, row = 230, 128, 16, 256, 960
+    geom = W.Geometry(1, H, Hkv, D, 16, row // 16 + 2, row // 16, "bf16")
+    rig = Rig(geom, max_batch=B)
+    g = torch.Generator(rig.dev).manual_seed(3)
+    for pool in (rig.k_pool, rig.v_pool):
+        pool.copy_(torch.randn(pool.shape, generator=g, device=rig.dev))
+    q = torch.randn((B, H, D), generator=g, device=rig.dev).to(rig.tdtype)
+    table = torch.arange(row // 16, dtype=torch.int32, device=rig.dev).repeat(B, 1)
+    lens = torch.as_tensor(np.asarray([row if r % 9 == 4 else 30 + r % 50 for r in range(B)], dtype=np.int32), device=rig.dev)
+    mask = torch.ones(B, dtype=torch.uint8, device=rig.dev)
+    want, got = torch.full_like(q, 7.0), torch.full_like(q, 5.0)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(rig.compute):
+        rig.lamps.decode_attn(0, B, q, table, lens, mask, want)
+        P.lamps_decode_attn_static(rig.cfg, rig.compute.cuda_stream, 0, B, q, rig.k_pool, rig.v_pool, table, lens, mask, got)
+    rig.compute.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    rig.close()
+
+
 def test_static_scratch_decode_captured_in_a_graph():
     """The callers the entry point is for: one eager call first (it looks the scratch array up),
     then the call is captured into a HIP graph -- nothing in it allocates or synchronises -- and
