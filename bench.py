@@ -43,19 +43,26 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 
-# HBM bytes per decode launch measured with rocprofv3 --pmc (FETCH_SIZE run + WRITE_SIZE run,
+# HBM bytes per launch measured with rocprofv3 --pmc (FETCH_SIZE run + WRITE_SIZE run,
 # each scaled by the same counter's reading for a plain 1 GiB copy: x2.0 and x1.0), keyed by
-# workload name; summaries in profiles/.  None where not measured.
-MEASURED_TRAFFIC_BYTES = {
-    "cfg1-7b-mha-bf16": 889187000,     # decode_balanced + decode_merge_balanced
-    "cfg2-8b-gqa-bf16": 1713836000,
-    "cfg3-long-gqa-bf16": 1546508000,
-    "cfg4-13b-40layer-bf16": 2177279000,   # per layer
-    # prefill_mfma, fetched + written (same counters, same scale factors)
-    "prefill-4x4096-new-on-0-cached-H32-Hkv8-D128": 359935000,
-    "prefill-4x4096-new-on-0-cached-H40-Hkv40-D128": 693023000,
-    "prefill-64x8-new-on-2048-cached-H32-Hkv8-D128": 550227000,
+# workload name, and the kernels that were measured; summaries in profiles/.
+MEASURED_TRAFFIC = {
+    "cfg1-7b-mha-bf16": (882679000, "decode_cut"),
+    "cfg2-8b-gqa-bf16": (1713836000, "decode_balanced + decode_merge_balanced"),
+    "cfg3-long-gqa-bf16": (1546508000, "decode_balanced + decode_merge_balanced"),
+    "cfg4-13b-40layer-bf16": (2177279000, "decode_balanced + decode_merge_balanced"),   # per layer
+    # fetched + written (same counters, same scale factors)
+    "prefill-4x4096-new-on-0-cached-H32-Hkv8-D128": (568153000, "prefill_teams"),
+    "prefill-4x4096-new-on-0-cached-H40-Hkv40-D128": (1474747000, "prefill_teams"),
+    "prefill-64x8-new-on-2048-cached-H32-Hkv8-D128": (550227000, "prefill_mfma"),
 }
+
+
+def measured(workload, part_tokens=0):
+    """HBM bytes of a launch and the kernels, where both were measured; the library chooses the form of a launch by its sizes."""
+    if part_tokens:
+        return None, "decode_partial"
+    return MEASURED_TRAFFIC.get(workload, (None, "by the sizes of the launch"))
 
 
 def parse():
@@ -651,8 +658,8 @@ def prefill_bench(a):
             "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
             "config": {"workload": workload},
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": MEASURED_TRAFFIC_BYTES.get(workload),
-                         "kernel": "prefill_mfma",
+                         "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": measured(workload)[0],
+                         "kernel": measured(workload)[1],
                          "algorithmic_flops_per_launch": flops, "kernel_us": attn_s / steps * 1e6,
                          "append_plus_attention_us": dev_s / steps * 1e6},
             # with few new tokens per request the same kernel is a stream over the cache instead:
@@ -666,7 +673,7 @@ def prefill_bench(a):
                              "max_abs_err_gpu_vs_oracle": err}}
     if line["hbm"]["frac"] > line["roofline"]["frac"]:     # the stream over the cache is what binds
         mf = line["roofline"]
-        line["roofline"] = dict(line["hbm"], bound="hbm", traffic=mf["traffic"], kernel="prefill_mfma", kernel_us=mf["kernel_us"],
+        line["roofline"] = dict(line["hbm"], bound="hbm", traffic=mf["traffic"], kernel=mf["kernel"], kernel_us=mf["kernel_us"],
                                 append_plus_attention_us=mf["append_plus_attention_us"])
         line["mfma"] = {k: mf[k] for k in ("achieved", "peak", "unit", "frac", "algorithmic_flops_per_launch")}
         del line["hbm"]
@@ -768,12 +775,12 @@ def measure_config(a, cfg_id, headline):
             "swaps_in_flight_when_timed_steps_ended": under["swaps_in_flight_at_end"]}
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": MEASURED_TRAFFIC_BYTES.get(job.wl.name),
-            "kernel": "decode_balanced" if int(job.cfg.part_tokens) == 0 else "decode_partial",
+            "traffic": measured(job.wl.name, int(job.cfg.part_tokens))[0],
+            "kernel": measured(job.wl.name, int(job.cfg.part_tokens))[1],
             "algorithmic_bytes_per_launch": job.algo_bytes,
             "kernel_us": kernel_s * 1e6,
             "timing": "HIP events on the compute stream around the timed steps / launches "
-                      "(includes the small merge kernel that follows each launch)"}
+                      "(includes the small merge kernel behind a launch that has one)"}
     if headline:
         line = {
             "metric": "decode-attention tokens/s (achieved HBM GB/s in roofline; swap GB/s in swap)",
@@ -809,7 +816,7 @@ def measure_config(a, cfg_id, headline):
                 "decode_slowdown_under_swap": under["event_s"] / alone["event_s"],
                 "kernel_us_under_swap": kernel_s * 1e6, "kernel_us_alone": alone["event_s"] / launches * 1e6,
                 "algorithmic_bytes_per_launch": job.algo_bytes,
-                "traffic": MEASURED_TRAFFIC_BYTES.get(job.wl.name),
+                "traffic": measured(job.wl.name, int(job.cfg.part_tokens))[0],
                 "decode_alone_trains": spread, "swap": swap, "config": cfgd}
         if not a.no_cpu_baseline:
             line["max_abs_err_gpu_vs_oracle"] = oracle_check(job, [L - 1], [int(r) for r in np.flatnonzero(job.running)])

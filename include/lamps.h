@@ -116,8 +116,8 @@ typedef struct {
     int32_t max_batch;          /* largest `batch` passed to lamps_decode_attn       */
     int32_t dtype;              /* lamps_dtype of q, the pools and out               */
     float softmax_scale;        /* 0 => 1/sqrt(head_dim), the Section 2.2 equation   */
-    int32_t part_tokens;        /* 0 => balanced shares (default: every wavefront gets
-                                   an equal part of all cached tokens); > 0 => fixed
+    int32_t part_tokens;        /* 0 => by the sizes of each call (default: all cached
+                                   tokens are dealt out evenly); > 0 => fixed
                                    partitions of this many tokens, multiple of
                                    block_size                                        */
     int64_t staging_bytes;      /* device staging per swap direction; 0 => default   */
@@ -231,10 +231,10 @@ int lamps_validate_args(lamps_ctx *ctx, int32_t batch, const int32_t *block_tabl
  * cannot allocate device memory: code running under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same kernels, same result,
  * bit for bit, as lamps_decode_attn on a context created from `cfg` with
- * part_tokens == 0; the split ranges' partial results and the per-share records
+ * part_tokens == 0; the split ranges' partial results and their records
  * go to the library's own LAMPS_STATIC_SCRATCH_BYTES array on the current device
  * instead of a caller-provided workspace.  The call allocates nothing (no
- * hipMalloc / hipFree, no host heap) and enqueues the two kernels on
+ * hipMalloc / hipFree, no host heap) and enqueues one kernel or two on
  * compute_stream (hipStream_t as void*, NULL = the default stream) of the
  * current device.
  *   cfg           host; validated as by lamps_create (staging / copy fields are ignored);
@@ -247,8 +247,8 @@ int lamps_validate_args(lamps_ctx *ctx, int32_t batch, const int32_t *block_tabl
  * 8.5 MB for 32 on 8, 34 MB -- too much -- for 64 on 4); a geometry beyond that
  * is refused with LAMPS_ERR_RANGE and nothing is enqueued.
  * All calls on one GPU share that GPU's array, which keeps the last call's
- * contents (nothing in it has to be cleared: every launch writes what it later
- * reads): calls that overlap on one GPU -- two streams, two threads -- race and
+ * contents (nothing in it has to be cleared: no launch uses what it has not
+ * written): calls that overlap on one GPU -- two streams, two threads -- race and
  * must be serialised by the caller.  The first call on a device looks the
  * array's address up and asks the occupancy of the kernel (both are kept per
  * device); make one eager call before capturing the call into a graph.

@@ -5,13 +5,17 @@
 // first ctx_lens[r] cached positions of r, with K and V reached through the
 // block table (paged attention, Section 7).
 //
-// Work decomposition.  The unit of work is a chunk of CT tokens of one
-// (request, kv head, pass over GH query heads of the group), in the balanced scheme
-// cut in GT tokens.  Two schemes share
-// the same inner loops:
-//   balanced (default): all chunks of all running requests form one flat
+// Work decomposition.  The unit of work is a chunk of CT tokens of one range: a (request, kv head, pass over GH query heads of
+// the group); in small launches cut in GT tokens.  All forms share the inner loops; decode_rules.h chooses among them by the ranges there can be and
+// the table row:
+//   whole (decode_whole): a workgroup takes a range, two, four or eight waves a stretch each, added up in LDS.  For rows of
+//     a few rounds of chunks: no plan, no pieces, no second launch.
+//   cut (decode_cut): the same for hundreds of ranges on longer rows, by the lengths: the longest first, those beyond an even share in parts,
+//     which the last of a range's workgroups to arrive adds up.
+//   parts (decode_parts, decode_merge_parts): few ranges, cut into parts of one size that both launches work out from the lengths.
+//   shares (decode_balanced, decode_merge_balanced): everything else.  All chunks of all running requests form one flat
 //     sequence (head outermost, then request, then position), cut into shares.
-//     With many ranges, (request, head) pairs, for the chip: as many wavefronts as it
+//     With many ranges for the chip: as many wavefronts as it
 //     holds at once each take an equal contiguous share, so every wavefront ends within
 //     a chunk of the others however skewed the context lengths are.  With eight resident
 //     waves and more to a range: a share belongs to a workgroup, whose four waves
@@ -19,16 +23,14 @@
 //     share: the shares are pieces of one range each, if there are enough.  A share is at most: the
 //     tail of one range, some whole ones, and the head of another;
 //     whole ones are written out directly, the two partial ends go to
-//     per-share slots that a second kernel merges.
+//     per-share slots that the second kernel merges.
 //   fixed partitions (part_tokens > 0): the context is cut every part_tokens
 //     tokens, one wavefront per (partition, request, kv head) in a dense grid.
-// The inner loops of a wavefront use no LDS and no barrier: with many short
-// requests there are far more ranges than workgroups, and four
-// waves cooperating on each would spend their time in start-up and hand-over; where
-// they do cooperate, they meet once per range.
-// Partitions are merged by a separate launch on purpose: a kernel boundary
-// makes the partials visible across the eight XCDs' L2s once, whereas a
-// device-scope fence per workgroup writes back and invalidates an L2 each time.
+// The inner loops of a wavefront use no LDS and no barrier; where waves cooperate, they meet once per range, part or piece.
+// Pieces of shares, parts of few ranges and partitions are merged by a separate launch: a kernel boundary
+// makes them visible across the eight XCDs' L2s once, whereas a
+// device-scope fence per workgroup writes back and invalidates an L2 each time, and where all of them end at the same time a hand-over by
+// agent-scope stores is on the way of each.  Only decode_cut, where what is cut is the exception, hands over inside the launch.
 //
 // Inner loops.  The path is a stream over K and V: every byte is used once, by
 // the G query heads of its group.
@@ -1374,8 +1376,8 @@ extern "C" int lamps_decode_attn_static(const lamps_config *cfg, void *compute_s
         return static_fail(LAMPS_ERR_RANGE,
                            "lamps_decode_attn_static: this geometry's partial slots (two records of heads per "
                            "pass x (head_dim + 2) floats per resident wavefront) exceed the static scratch buffer");
-    // every launch writes the share record of every wavefront it starts and reads only those,
-    // and reads only the partial slots those records name: nothing has to start at zero
+    // a launch of shares writes the record of every wavefront it starts and reads only those and the slots they name; the merge of parts may load a
+    // slot that no part has written, and does not use it; parts that are handed over count by a tag of the call: nothing has to start at zero
     if ((e = lamps::dispatch(a, static_cast<hipStream_t>(compute_stream), nullptr)) != hipSuccess)
         return static_fail(LAMPS_ERR_HIP, hipGetErrorString(e));
     return LAMPS_OK;

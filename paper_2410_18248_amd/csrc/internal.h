@@ -15,10 +15,11 @@ struct DecodeArgs {
     const int32_t *block_table;  // [batch][max_blocks]
     const int32_t *ctx_lens;     // [batch]
     const uint8_t *running;      // [batch]
-    float *partials;          // fixed partitions: [batch][H][max_parts][D + 2];
-                              // balanced: [wave share][2][heads per pass][D + 2]
-    size_t partial_capacity;  // bytes behind partials (balanced: bounds the number of shares)
-    int4 *share_info;         // balanced: [shares + 1] what each share leaves to the merge kernel
+    float *partials;          // fixed partitions: [batch][H][max_parts][D + 2]; shares: [share][2][heads per pass][D + 2];
+                              // parts: [range][most parts][heads per pass][D + 2]; cut: [workgroup][heads per pass][D + 2], then
+                              // a word per workgroup
+    size_t partial_capacity;  // bytes behind partials (bounds the number of shares; what has no room is not cut)
+    int4 *share_info;         // shares: [shares + 1] what each leaves to the merge kernel
     void *out;                // [batch][H][D]
     // (the place of bf16 is measured: with what follows it four bytes further up the compiler's scalar loads, and
     // with them the registers, of prefill_mfma come out such that 4 prompts of 4 096 tokens take 1.2 % longer)
@@ -45,12 +46,12 @@ int decode_max_shares(int heads_per_pass, int head_dim);
 size_t decode_share_bytes(int heads_per_pass, int head_dim);
 constexpr int kMaxDevices = 64;   // devices of one process the per-device tables cover
 
-// Enqueues one layer of decode attention.  part_tokens == 0 selects the balanced
-// scheme (then max_parts is ignored), part_tokens > 0 fixed partitions; either
-// way a small merge kernel follows unless no request can be split.
+// Enqueues one layer of decode attention.  part_tokens == 0: a form by the sizes of the call (decode_rules.h; max_parts is ignored), in one launch
+// where ranges go whole or are cut by their lengths, else with a small merge kernel behind it; part_tokens > 0: fixed partitions, and a merge
+// kernel unless no request can be split.
 hipError_t launch_decode(const DecodeArgs &a, hipStream_t stream);
 // The same dispatch; with demand != nullptr nothing is launched and *demand receives the bytes
-// of partial slots a balanced launch uses when every resident wavefront takes a share.
+// of partial slots a launch of shares uses when every resident wavefront takes one.
 hipError_t dispatch(const DecodeArgs &a, hipStream_t stream, size_t *demand);
 // Validates cfg as lamps_create does and fills the geometry fields of *a (everything but the
 // pointers, batch, layer and partial_capacity).  Returns nullptr or an error text; allocates nothing.
