@@ -854,15 +854,19 @@ struct PartArgs {
     int most;                                         // ... at most: there is room for so many
 };
 struct Parts {
-    int n, own, size;                                 // of the lane's request: chunks, parts; chunks of a part at most
+    int n, own, upto, size;                           // of the lane's request: chunks, parts, those of all up to it; chunks of a part at most
 };
 __device__ __forceinline__ Parts parts_of(const DecodeArgs &a, const PartArgs &c, int2 q, int GT, int chunk)
 {
     Parts p;
     p.n = chunks_of(q.x, q.y, GT);
     p.size = rules::part_size(__builtin_amdgcn_readlane(wave_scan(p.n), 63), __builtin_amdgcn_readlane(wave_max_to(p.n), 63), a.batch, c.even, c.most, kWaves, chunk);
-    p.own = split::small_div(p.n + p.size - 1, p.size);
-    return p;
+    for (int tries = rules::kPartTries;; --tries) {
+        p.own = split::small_div(p.n + p.size - 1, p.size);
+        p.upto = wave_scan(p.own);
+        if (tries == 0 || __builtin_amdgcn_readlane(p.upto, 63) <= c.even * a.batch) return p;
+        p.size += chunk;
+    }
 }
 template <typename R>
 __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const DecodeArgs a, const PartArgs c)
@@ -872,12 +876,11 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const D
     const int lane = threadIdx.x & 63, GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
     const int2 q = request_of(a, lane);
     const Parts p = parts_of(a, c, q, R::GT, kChunk);
-    const int upto = wave_scan(p.own);
     int at = split::small_div(blockIdx.x, HC);
     const int hc = blockIdx.x - at * HC;
-    const int r = __popcll(__ballot(upto <= at));     // the first whose parts end behind `at`
+    const int r = __popcll(__ballot(p.upto <= at));   // the first whose parts end behind `at`
     if (r == 64) return;
-    at -= __builtin_amdgcn_readlane(upto - p.own, r);
+    at -= __builtin_amdgcn_readlane(p.upto - p.own, r);
     const int of = __builtin_amdgcn_readlane(p.own, r), n = __builtin_amdgcn_readlane(p.n, r), C = __builtin_amdgcn_readlane(q.y, r);
     const int c0 = at * p.size;
     float *slot = a.partials + ((size_t)(r * HC + hc) * c.most + at) * GH * (D + 2);
