@@ -85,8 +85,9 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
         // work: 0.87, 1.21 and 0.94, 1.65
         return rounds_to(n < 512 ? 32 : 64) && sorts ? kCut : kPlan;
     }
-    // to 2 rounds by four waves 0.61 to 0.77, 1.11 (by two 0.62 to 0.81, 1.18); 4 096 and more by two 0.85, 1.23 (four 0.90, 1.21)
-    if (rounds_to(2)) return n < 4096 ? kWholeFour : kWholeTwo;
+    // to 2 rounds by four waves 0.61 to 0.77, 1.11 (by two 0.62 to 0.81, 1.18); 4 096 to 8 192 0.88, 1.10 (0.87, but with 3 to 50 % of the requests running 1.04, 1.41:
+    // long walks by two waves among workgroups that leave); more by two 0.82, 1.13 (four 0.87, 1.21)
+    if (rounds_to(2)) return n < 8192 ? kWholeFour : kWholeTwo;
     // to 3 0.53 to 0.90, 1.11
     if (rounds_to(3)) return kWholeFour;
     if (l.batch > kCutBatch) return rounds_to(6) ? kWholeFour : kPlan;   // 0.50 to 0.82, 1.10 (more 0.89 to 1.09, 2.66)

@@ -70,7 +70,7 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (32, 8, 128, "bf16", 3, 8192, PARTS), (32, 8, 128, "bf16", 4, 8192, PARTS), (32, 8, 128, "bf16", 4, 8208, PLAN), (32, 8, 128, "bf16", 8, 2048, PARTS),
     (32, 8, 128, "bf16", 12, 2048, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PLAN),
     # whole ranges
-    (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 200, 256, TWO),
+    (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 200, 256, FOUR), (40, 40, 128, "bf16", 210, 256, TWO),
     (32, 8, 128, "bf16", 200, 64, TWO), (32, 8, 128, "bf16", 200, 256, FOUR), (32, 8, 128, "bf16", 256, 512, FOUR), (32, 8, 128, "bf16", 257, 512, FOUR),
     (32, 8, 128, "bf16", 257, 784, PLAN), (32, 32, 128, "bf16", 6, 512, EIGHT), (32, 8, 128, "bf16", 10, 1024, EIGHT),
     # looked at on the device
