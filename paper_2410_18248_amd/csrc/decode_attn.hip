@@ -599,9 +599,9 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_balanced(cons
 // ---------------------------------------------------------------- whole ranges
 
 // Chunks c0 .. c1 - 1 of a range by W waves of a workgroup, a stretch each, whose states are added up through x0 ([wave][head][D + 2], LDS)
-// and given to out(first head's row, head, dim, M, L, two outputs).  `on`: false for waves that only keep others company at the barrier.
+// and given to out(first head's row, head, dim, M, L, two outputs).  A barrier: by all waves of the workgroup.
 template <typename R, int W, typename Out>
-__device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int sub, int r, int hc, int c0, int c1, int C, bool on, Out out)
+__device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int sub, int r, int hc, int c0, int c1, int C, Out out)
 {
     constexpr int D = R::D;
     constexpr bool kCut = R::CT != R::GT;
@@ -611,11 +611,9 @@ __device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int su
     if (kCut && each >= 2) each = (each + 1) & ~1;    // (by whole chunks)
     const int from = min(n, each * sub);
     const size_t rh0 = (size_t)r * a.num_q_heads + h0;
-    if (on)
-        R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * R::GT, min(C, (c0 + min(n, from + each)) * R::GT),
-               [&](int h, int d, float M, float L, const auto &A) { store_partial(x0 + (size_t)(sub * GH + h) * (D + 2), D, d, M, L, A); });
+    R::run(a, r, (size_t)r, g, h0, GH, (c0 + from) * R::GT, min(C, (c0 + min(n, from + each)) * R::GT),
+           [&](int h, int d, float M, float L, const auto &A) { store_partial(x0 + (size_t)(sub * GH + h) * (D + 2), D, d, M, L, A); });
     __syncthreads();
-    if (!on) return;
     for (int i = 2 * (64 * sub + lane); i < GH * D; i += 128 * W) {
         const int h = i / D, d = i % D;
         const float *x = x0 + h * (D + 2);
@@ -640,28 +638,39 @@ __device__ __forceinline__ void stretches(const DecodeArgs &a, float *x0, int su
 
 // W waves of a workgroup take a whole range, one (request, kv head / pass), each a stretch of its chunks, and add their states up in LDS:
 // no plan, no pieces and no second launch.  For launches of ranges that are short, or short against the work of the chip; lengths are on the
-// device, so the host goes by the bound of a table row (whole_form).  Bound by latency -- length, table entries, K / V, and at the end the
+// device, so the host goes by the bound of a table row (decode_rules.h).  Bound by latency -- length, table entries, K / V, and at the end the
 // sum -- where the launch is small, otherwise by memory as decode_balanced is.  Both ways, us: one request of 200 tokens, 32 / 8 heads of 128,
 // 7.0 / 4.4; 64 of 50 to 300 on 32 / 8 14.8 / 8.9; 40 of 16 to 130 on 40 plain heads 14.1 / 9.6; 200 of 20 to 250 on 32 / 8 20.6 / 12.9.
+// By two waves a workgroup has two ranges, half of the launch apart, and where one of them waits all four waves take the other: where few of thousands of
+// ranges run they are walks on an empty chip.  Time over the plan's, mean and slowest, 4 096 ranges and more of 2 and 3 rounds, of 2 to 25 % of the requests: by
+// two waves always 0.63, 1.84, so 0.58, 1.33, four 0.57, 1.27; all others 0.90, 1.34 / 0.89, 1.49 / 0.98, 1.73.
 template <typename R, int W>
 __global__ __launch_bounds__(64 * (W > kWaves ? W : kWaves), R::kLeastPerCu) void decode_whole(const DecodeArgs a)
 {
-    constexpr int D = R::D, kPer = W > kWaves ? 1 : kWaves / W;   // ranges of a workgroup
+    constexpr int D = R::D;
     extern __shared__ __align__(16) float parts[];    // [range][wave][head][D + 2]
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int GH = a.heads_per_pass, passes = a.passes, HC = a.num_kv_heads * passes;
-    const int of = wv / W, sub = wv % W;
-    const int item = blockIdx.x * kPer + of;
-    const int r = __builtin_amdgcn_readfirstlane(item / HC), hc = item - r * HC;
-    const int2 q = request_of(a, r);                  // (past the batch: does not run)
+    const int GH = a.heads_per_pass, HC = a.num_kv_heads * a.passes;
+    const auto take = [&](auto waves, float *x0, int sub, int r, int hc, int C) {
+        stretches<R, decltype(waves)::value>(a, x0, sub, r, hc, 0, chunks_of(1, C, R::GT), C, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
+            store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
+        });
+    };
+    const int item = blockIdx.x, r = __builtin_amdgcn_readfirstlane(item / HC);
+    const int2 q = request_of(a, r);
     const bool on = __builtin_amdgcn_readfirstlane(q.x) != 0;
-    const int C = __builtin_amdgcn_readfirstlane(q.y);
-    if (kPer == 1 && !on) return;                     // (else the workgroup's other range may)
-    const int n = chunks_of(1, C, R::GT);
-    float *x0 = parts + (size_t)of * W * GH * (D + 2);
-    stretches<R, W>(a, x0, sub, r, hc, 0, n, C, on, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
-        store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);
-    });
+    if constexpr (W >= kWaves) {
+        if (on) take(std::integral_constant<int, W>{}, parts, wv, r, item - r * HC, __builtin_amdgcn_readfirstlane(q.y));
+    } else {
+        const int item2 = item + gridDim.x, r2 = __builtin_amdgcn_readfirstlane(item2 / HC);
+        const int2 q2 = request_of(a, r2);            // (past the batch: does not run)
+        const bool on2 = __builtin_amdgcn_readfirstlane(q2.x) != 0;
+        if (!on && !on2) return;
+        const bool second = on && on2 ? wv / W != 0 : on2;
+        const int rr = second ? r2 : r, hc = (second ? item2 : item) - rr * HC, C = __builtin_amdgcn_readfirstlane(second ? q2.y : q.y);
+        if (on && on2) take(std::integral_constant<int, W>{}, parts + (size_t)(wv / W) * W * GH * (D + 2), wv % W, rr, hc, C);
+        else take(std::integral_constant<int, kWaves>{}, parts, wv, rr, hc, C);
+    }
 }
 
 // Ranges that may be long, in one launch that looks at the lengths itself: those of about the size of an even share go whole to a workgroup, the
@@ -801,7 +810,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_cut(const Dec
     const size_t slot = (size_t)GH * (D + 2);
     const bool wide = ((uintptr_t)a.out & 15) == 0;
     float *mine = a.partials + (size_t)(it.first + it.at * HC) * slot;
-    stretches<R, kWaves>(a, parts, wv, it.r, it.hc, it.c0, it.c1, it.C, true, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
+    stretches<R, kWaves>(a, parts, wv, it.r, it.hc, it.c0, it.c1, it.C, [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
         if (it.runs == 1) {
             store_out<R::kBF16>(a.out, (rh + h) * D + d, wide, L, A);
         } else {
@@ -884,7 +893,7 @@ __global__ __launch_bounds__(kThreads, R::kLeastPerCu) void decode_parts(const D
     const int of = __builtin_amdgcn_readlane(p.own, r), n = __builtin_amdgcn_readlane(p.n, r), C = __builtin_amdgcn_readlane(q.y, r);
     const int c0 = at * p.size;
     float *slot = a.partials + ((size_t)(r * HC + hc) * c.most + at) * GH * (D + 2);
-    stretches<R, kWaves>(a, parts, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r, hc, c0, min(n, c0 + p.size), C, true,
+    stretches<R, kWaves>(a, parts, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r, hc, c0, min(n, c0 + p.size), C,
                          [&](size_t rh, int h, int d, float M, float L, const float (&A)[2]) {
                              if (of == 1)
                                  store_out<R::kBF16>(a.out, (rh + h) * D + d, ((uintptr_t)a.out & 15) == 0, L, A);

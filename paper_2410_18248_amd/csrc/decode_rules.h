@@ -71,12 +71,12 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
     const bool sorts = l.batch <= kCutBatch && n + cut_spare(l.matrix) < kMostItems && (size_t)(n + cut_spare(l.matrix)) * (l.state + 8) <= l.capacity;
     const bool eight = 8 * l.state <= (80u << 10);    // of the LDS: two workgroups to a CU
     if (decode_cuts(l) > 0) return kParts;
-    // Ranges that are short: a workgroup each, by two waves where there are thousands of a round (1 024 and more, two / four: vector path 0.62, 0.86 / 0.65, 0.97;
-    // 4 096 and more 0.79, 1.10 / 0.95, 1.32; matrix path 0.57 / 0.65).  A waiting request's workgroups leave at once, but there are tens of thousands of them: 565
-    // requests of 161 positions at most, 40 heads, 18 of them running, 18.4 us by the plan and 20.7.
+    // Ranges that are short: by two waves where there are thousands of a round (1 024 and more, two / four: vector path 0.62, 0.86 / 0.65, 0.97;
+    // 4 096 and more 0.79, 1.10 / 0.95, 1.32; matrix path 0.57 / 0.65), or of a few.  A waiting request's workgroups leave at once, but there are tens of
+    // thousands of them: 565 requests of 161 positions at most, 40 heads, 18 of them running, 18.4 us by the plan and 20.7.
     if (rounds_to(1)) return n >= 1024 ? kWholeTwo : kWholeFour;
     if (l.matrix) {
-        if (rounds_to(3) && n >= 1024) return kWholeTwo;   // level with four, 0.44 to 0.71; where contexts are short against the row 0.83 of it
+        if (n >= (rounds_to(3) ? 1024 : 4096) && rounds_to(12)) return kWholeTwo;   // 4 096 and more, 4 to 12 rounds, two / four 0.69, 1.22 / 0.73, 1.32
         // to 12 rounds, any number of requests, 0.38 to 0.80, 1.11; fewer than 256 from 8 on by eight waves (0.80, by four 0.85), 64 and more to 16
         // (0.83; with one long context among a dozen of 20 to 100 positions up to 1.25, 10.6 us against 8.5)
         if (rounds_to(12)) return n < 256 && eight && !rounds_to(8) ? kWholeEight : kWholeFour;
@@ -85,12 +85,10 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
         // work: 0.87, 1.21 and 0.94, 1.65
         return rounds_to(n < 512 ? 32 : 64) && sorts ? kCut : kPlan;
     }
-    // to 2 rounds by four waves 0.61 to 0.77, 1.11 (by two 0.62 to 0.81, 1.18); 4 096 to 8 192 0.88, 1.10 (0.87, but with 3 to 50 % of the requests running 1.04, 1.41:
-    // long walks by two waves among workgroups that leave); more by two 0.82, 1.13 (four 0.87, 1.21)
-    if (rounds_to(2)) return n < 8192 ? kWholeFour : kWholeTwo;
-    // to 3 0.53 to 0.90, 1.11
-    if (rounds_to(3)) return kWholeFour;
-    if (l.batch > kCutBatch) return rounds_to(6) ? kWholeFour : kPlan;   // 0.50 to 0.82, 1.10 (more 0.89 to 1.09, 2.66)
+    // 2 and 3 rounds, up to 4 096 ranges, by four waves / two 0.67, 1.18 / 0.69, 1.10; more 0.74, 1.73 / 0.72, 1.49 (the slowest have contexts of 2 to 10 % of the
+    // row; without one range's waves taking the other's place, 0.75, 1.84: few of thousands of requests running)
+    if (rounds_to(3)) return n < 4096 ? kWholeFour : kWholeTwo;
+    if (l.batch > kCutBatch) return !rounds_to(6) ? kPlan : n < 8192 ? kWholeFour : kWholeTwo;   // 0.60, 1.13; two / four 0.70, 1.36 / 0.73, 1.37 (more than 6 rounds 0.89 to 1.09, 2.66)
     // to 4 by eight waves 0.78, 0.91 (by four 0.91, 1.14); more by either 0.91 to 0.97, 1.07 to 1.41
     if (n < 256) return rounds_to(4) ? kWholeEight : kPlan;
     // 256 to 512 to 16 rounds 0.92, 1.19 (more 0.97, 1.27); to 1 024, to 16 0.85, 1.12, to 32 0.91, 1.07; to 4 096 0.89, 1.17 and 0.94, 1.22 (more rounds 0.98 to 1.01,

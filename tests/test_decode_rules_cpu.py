@@ -70,19 +70,23 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (32, 8, 128, "bf16", 3, 8192, PARTS), (32, 8, 128, "bf16", 4, 8192, PARTS), (32, 8, 128, "bf16", 4, 8208, PLAN), (32, 8, 128, "bf16", 8, 2048, PARTS),
     (32, 8, 128, "bf16", 12, 2048, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PLAN),
     # whole ranges
-    (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 200, 256, FOUR), (40, 40, 128, "bf16", 210, 256, TWO),
+    (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 102, 256, FOUR), (40, 40, 128, "bf16", 103, 256, TWO), (40, 40, 128, "bf16", 103, 384, TWO),
     (32, 8, 128, "bf16", 200, 64, TWO), (32, 8, 128, "bf16", 200, 256, FOUR), (32, 8, 128, "bf16", 256, 512, FOUR), (32, 8, 128, "bf16", 257, 512, FOUR),
     (32, 8, 128, "bf16", 257, 784, PLAN), (32, 32, 128, "bf16", 6, 512, EIGHT), (32, 8, 128, "bf16", 10, 1024, EIGHT),
+    # thousands of ranges by two waves
+    (32, 8, 128, "bf16", 511, 256, FOUR), (32, 8, 128, "bf16", 512, 256, TWO), (32, 8, 128, "bf16", 512, 768, TWO), (32, 32, 128, "bf16", 300, 640, TWO),
     # looked at on the device
     (40, 40, 128, "bf16", 16, 1504, CUT), (40, 40, 128, "bf16", 16, 4096, CUT), (40, 40, 128, "bf16", 16, 4112, PLAN), (32, 32, 128, "bf16", 64, 2048, CUT),
     (32, 8, 128, "bf16", 64, 1504, CUT), (32, 8, 128, "bf16", 256, 8192, PLAN), (40, 40, 128, "bf16", 180, 1232, PLAN), (32, 32, 128, "bf16", 256, 512, PLAN),
-    (32, 32, 128, "bf16", 257, 768, FOUR), (32, 32, 128, "bf16", 257, 784, PLAN), (32, 8, 128, "f32", 24, 2512, PLAN), (32, 8, 128, "f32", 40, 512, CUT),
+    (32, 32, 128, "bf16", 257, 768, TWO), (31, 31, 128, "bf16", 257, 768, FOUR), (32, 32, 128, "bf16", 257, 784, PLAN), (32, 8, 128, "f32", 24, 2512, PLAN), (32, 8, 128, "f32", 40, 512, CUT),
     (10, 2, 256, "bf16", 129, 800, CUT),
     # what the GPU tests of skewed batches count on
     (32, 32, 64, "bf16", 17, 640, CUT), (8, 8, 64, "bf16", 70, 1504, CUT), (16, 16, 256, "bf16", 20, 912, CUT), (16, 8, 128, "bf16", 40, 2000, CUT),
     (16, 8, 64, "bf16", 66, 2048, CUT), (128, 4, 64, "bf16", 40, 1008, CUT), (8, 8, 32, "f32", 40, 912, CUT), (16, 2, 128, "f32", 130, 416, CUT),
     (6, 3, 64, "f32", 100, 704, CUT), (4, 4, 128, "bf16", 256, 512, CUT), (32, 32, 128, "bf16", 34, 800, CUT), (16, 8, 64, "bf16", 70, 1600, CUT),
     (8, 8, 64, "f32", 65, 1008, CUT),
+    (3, 3, 64, "bf16", 343, 112, TWO), (16, 16, 64, "bf16", 260, 256, TWO), (8, 8, 128, "bf16", 513, 384, TWO), (8, 8, 64, "f32", 515, 144, TWO), (16, 8, 64, "bf16", 131, 64, TWO),
+    (64, 32, 64, "bf16", 129, 512, TWO),
     (8, 2, 128, "bf16", 10, 2512, PARTS), (32, 1, 128, "bf16", 20, 1504, PARTS), (16, 4, 64, "bf16", 16, 1600, PARTS), (2, 1, 128, "bf16", 64, 1600, PARTS),
     (8, 8, 64, "bf16", 11, 1312, PARTS), (2, 2, 256, "bf16", 7, 2000, PARTS), (8, 2, 128, "f32", 30, 912, PARTS), (4, 4, 32, "f32", 16, 1120, PARTS),
     (10, 2, 256, "bf16", 3, 5008, PARTS), (8, 2, 128, "bf16", 4, 2000, PARTS),

@@ -124,6 +124,15 @@ def test_skewed_batches_of_few_ranges(dtype, H, Hkv, D, bs, batch, row):
     _skewed(dtype, H, Hkv, D, bs, batch, row)
 
 
+@pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
+    ("bf16", 3, 3, 64, 16, 343, 100), ("bf16", 16, 16, 64, 16, 260, 250), ("bf16", 8, 8, 128, 32, 513, 380), ("f32", 8, 8, 64, 16, 515, 130), ("bf16", 16, 8, 64, 16, 131, 60),
+    ("bf16", 64, 32, 64, 16, 129, 500),
+])
+def test_skewed_batches_of_ranges_in_pairs(dtype, H, Hkv, D, bs, batch, row):
+    """Two waves to a range, and four to one whose neighbour waits; an odd number of ranges."""
+    _skewed(dtype, H, Hkv, D, bs, batch, row)
+
+
 @pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100),
                                                          ("bf16", 16, 8, 64, 70, 1600), ("f32", 8, 8, 64, 65, 1000)])
 def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
