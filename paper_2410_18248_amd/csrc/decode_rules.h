@@ -55,7 +55,7 @@ inline int decode_cuts(const DecodeLaunch &l)
     if (!l.bounded || l.ranges >= 128 || l.batch > kPartBatch) return 0;
     const auto rounds_to = [&l](int n) { return l.row <= (long long)n * l.round; };
     const int most = l.matrix ? (l.ranges < 32 ? 400 : l.ranges < 64 ? 128 : l.ranges < 96 ? 32 : 0) : l.ranges < 16 ? 400 : l.ranges < 32 ? 64 : l.ranges < 64 ? 32 : 16;
-    const int least = l.matrix ? (l.ranges >= 64 ? 16 : l.head_dim < 128 ? 12 : 8) : 4;
+    const int least = l.matrix ? (l.ranges >= 64 ? 16 : l.head_dim < 128 ? 12 : l.head_dim < 256 ? 8 : 5) : 4;
     if (rounds_to(least) || !rounds_to(most)) return 0;
     const bool few = l.matrix ? l.ranges < 64 && rounds_to(128) : l.ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
     const int share = (few ? 256 : 512) / (int)l.ranges, cuts = share < kMostCuts ? share : kMostCuts;
@@ -77,9 +77,16 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
     if (rounds_to(1)) return n >= 1024 ? kWholeTwo : kWholeFour;
     if (l.matrix) {
         if (n >= (rounds_to(3) ? 1024 : 4096) && rounds_to(12)) return kWholeTwo;   // 4 096 and more, 4 to 12 rounds, two / four 0.69, 1.22 / 0.73, 1.32
+        // Heads of 256: a walk is as much longer as a chunk has products.  By four waves / eight / in parts of 256 workgroups: fewer than 64 ranges, to 4
+        // rounds 0.67, 0.97 / 0.69, 0.93 / 0.92, 1.14; 5 0.75, 1.15 / 0.76, 1.11 / 0.92, 1.01; 6 to 12 0.94, 1.90 / 0.91, 1.76 / 0.89, 1.08.  64 to 128, 5 to
+        // 9 rounds 0.82, 1.43 / 0.82, 1.31, to 12 0.97, 1.91 / 0.95, 1.73: the plan.  128 to 256, to 10 rounds 0.56, 1.45 / 0.57, 1.30; 11 to 16 0.69, 1.99 /
+        // 0.68, 1.81, cut by the lengths 0.66, 1.30; 256 to 1 024, 11 and 12, 0.77, 1.61 / cut 0.76, 1.39
+        const bool wide = l.head_dim >= 256;
+        if (wide && n < 128 && !rounds_to(9)) return kPlan;
+        if (wide && n < 1024 && !rounds_to(10) && rounds_to(16) && sorts) return kCut;
         // to 12 rounds, any number of requests, 0.38 to 0.80, 1.11; fewer than 256 from 8 on by eight waves (0.80, by four 0.85), 64 and more to 16
         // (0.83; with one long context among a dozen of 20 to 100 positions up to 1.25, 10.6 us against 8.5)
-        if (rounds_to(12)) return n < 256 && eight && !rounds_to(8) ? kWholeEight : kWholeFour;
+        if (rounds_to(12)) return n < 256 && eight && !rounds_to(wide ? 4 : 8) ? kWholeEight : kWholeFour;
         if (n < 256) return n >= 64 && eight && rounds_to(16) ? kWholeEight : kPlan;
         // 256 to 512 0.73, 1.13 (to 64 rounds with all contexts long 1.07 to 1.17); more 0.81, 1.03.  Whole by eight waves or longest first, without a look at the
         // work: 0.87, 1.21 and 0.94, 1.65

@@ -73,6 +73,10 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 102, 256, FOUR), (40, 40, 128, "bf16", 103, 256, TWO), (40, 40, 128, "bf16", 103, 384, TWO),
     (32, 8, 128, "bf16", 200, 64, TWO), (32, 8, 128, "bf16", 200, 256, FOUR), (32, 8, 128, "bf16", 256, 512, FOUR), (32, 8, 128, "bf16", 257, 512, FOUR),
     (32, 8, 128, "bf16", 257, 784, PLAN), (32, 32, 128, "bf16", 6, 512, EIGHT), (32, 8, 128, "bf16", 10, 1024, EIGHT),
+    # heads of 256: parts sooner, eight waves sooner, the plan and cuts in place of long walks by one workgroup
+    (16, 8, 256, "bf16", 4, 256, FOUR), (16, 8, 256, "bf16", 4, 272, EIGHT), (16, 8, 256, "bf16", 4, 320, EIGHT), (16, 8, 256, "bf16", 4, 336, PARTS),
+    (16, 8, 256, "bf16", 8, 576, EIGHT), (16, 8, 256, "bf16", 8, 592, PLAN), (16, 8, 256, "bf16", 16, 640, EIGHT), (16, 8, 256, "bf16", 16, 656, CUT),
+    (16, 8, 256, "bf16", 127, 768, CUT), (16, 8, 256, "bf16", 128, 768, FOUR), (128, 8, 256, "bf16", 8, 576, FOUR), (10, 2, 256, "bf16", 257, 768, FOUR),
     # thousands of ranges by two waves
     (32, 8, 128, "bf16", 511, 256, FOUR), (32, 8, 128, "bf16", 512, 256, TWO), (32, 8, 128, "bf16", 512, 768, TWO), (32, 32, 128, "bf16", 300, 640, TWO),
     # looked at on the device
@@ -86,7 +90,8 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     (6, 3, 64, "f32", 100, 704, CUT), (4, 4, 128, "bf16", 256, 512, CUT), (32, 32, 128, "bf16", 34, 800, CUT), (16, 8, 64, "bf16", 70, 1600, CUT),
     (8, 8, 64, "f32", 65, 1008, CUT),
     (3, 3, 64, "bf16", 343, 112, TWO), (16, 16, 64, "bf16", 260, 256, TWO), (8, 8, 128, "bf16", 513, 384, TWO), (8, 8, 64, "f32", 515, 144, TWO), (16, 8, 64, "bf16", 131, 64, TWO),
-    (64, 32, 64, "bf16", 129, 512, TWO),
+    (64, 32, 64, "bf16", 129, 512, TWO), (16, 8, 256, "bf16", 3, 400, PARTS), (16, 8, 256, "bf16", 9, 512, EIGHT), (16, 8, 256, "bf16", 20, 704, CUT),
+    (128, 8, 256, "bf16", 9, 512, FOUR), (10, 2, 256, "bf16", 70, 304, EIGHT),
     (8, 2, 128, "bf16", 10, 2512, PARTS), (32, 1, 128, "bf16", 20, 1504, PARTS), (16, 4, 64, "bf16", 16, 1600, PARTS), (2, 1, 128, "bf16", 64, 1600, PARTS),
     (8, 8, 64, "bf16", 11, 1312, PARTS), (2, 2, 256, "bf16", 7, 2000, PARTS), (8, 2, 128, "f32", 30, 912, PARTS), (4, 4, 32, "f32", 16, 1120, PARTS),
     (10, 2, 256, "bf16", 3, 5008, PARTS), (8, 2, 128, "bf16", 4, 2000, PARTS),

@@ -133,6 +133,12 @@ def test_skewed_batches_of_ranges_in_pairs(dtype, H, Hkv, D, bs, batch, row):
     _skewed(dtype, H, Hkv, D, bs, batch, row)
 
 
+@pytest.mark.parametrize("H,Hkv,batch,row", [(16, 8, 3, 400), (16, 8, 9, 500), (16, 8, 20, 700), (128, 8, 9, 500), (10, 2, 70, 300)])
+def test_skewed_batches_of_heads_of_256(H, Hkv, batch, row):
+    """In parts, by eight waves and four, cut by the lengths."""
+    _skewed("bf16", H, Hkv, 256, 16, batch, row)
+
+
 @pytest.mark.parametrize("dtype,H,Hkv,D,batch,row", [("bf16", 8, 2, 128, 4, 2000), ("bf16", 32, 32, 128, 34, 800), ("bf16", 8, 2, 128, 5, 300), ("bf16", 16, 8, 128, 130, 100),
                                                          ("bf16", 16, 8, 64, 70, 1600), ("f32", 8, 8, 64, 65, 1000)])
 def test_replays_with_other_lengths(dtype, H, Hkv, D, batch, row):
