@@ -24,7 +24,7 @@ enum DecodeForm { kPlan, kWholeTwo, kWholeFour, kWholeEight, kCut, kParts };
 constexpr int kMostCuts = 64;            // parts of a range in a kParts launch
 constexpr int kPartBatch = 64;           // requests of one, a lane's each
 constexpr int kCutBatch = 256;           // requests that a wave of a kCut launch can hold
-constexpr long long kMostItems = 1 << 19;   // workgroups of one (its divisions, and 64 rounds of chunks for each in 32 bits)
+constexpr long long kMostItems = 1 << 19;   // workgroups of one (its divisions, and 64 rounds of chunks for each, 256 for few, in 32 bits)
 
 // Workgroups of a kCut launch beyond one for each range: about what the chip holds at once, so that a launch in which much is cut is cut
 // evenly (512 / 1 024, time over the plan's, vector path: 512 to 1 024 ranges, 8 to 32 rounds 0.95 / 0.92, the slowest 1.22 / 1.08; 2 048 and more
@@ -88,9 +88,10 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
         // (0.83; with one long context among a dozen of 20 to 100 positions up to 1.25, 10.6 us against 8.5)
         if (rounds_to(12)) return n < 256 && eight && !rounds_to(wide ? 4 : 8) ? kWholeEight : kWholeFour;
         if (n < 256) return n >= 64 && eight && rounds_to(16) ? kWholeEight : kPlan;
-        // 256 to 512 0.73, 1.13 (to 64 rounds with all contexts long 1.07 to 1.17); more 0.81, 1.03.  Whole by eight waves or longest first, without a look at the
-        // work: 0.87, 1.21 and 0.94, 1.65
-        return rounds_to(n < 512 ? 32 : 64) && sorts ? kCut : kPlan;
+        // 256 to 512 ranges, to 32 rounds 0.67, 1.38 (to 128 0.84, but all contexts alike up to 1.17: 258 ranges of 8 500 tokens 91 us, and 106 by twice as many halves on 512
+        // places); 512 to 4 096, 13 to 64 0.75, 1.39, to 256 0.85, 1.36 (all contexts long 0.92, 1.15; more 0.97, 2.36 and 1.07).  The slowest have 2 to 15 % of their requests
+        // running.  Whole by eight waves or longest first, without a look at the work: to 64 rounds 0.87, 1.21 and 0.94, 1.65
+        return rounds_to(n < 512 ? 32 : n < 4096 ? 256 : 64) && sorts ? kCut : kPlan;
     }
     // 2 and 3 rounds, up to 4 096 ranges, by four waves / two 0.67, 1.18 / 0.69, 1.10; more 0.74, 1.73 / 0.72, 1.49 (the slowest have contexts of 2 to 10 % of the
     // row; without one range's waves taking the other's place, 0.75, 1.84: few of thousands of requests running)
@@ -98,10 +99,11 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
     if (l.batch > kCutBatch) return !rounds_to(6) ? kPlan : n < 8192 ? kWholeFour : kWholeTwo;   // 0.60, 1.13; two / four 0.70, 1.36 / 0.73, 1.37 (more than 6 rounds 0.89 to 1.09, 2.66)
     // to 4 by eight waves 0.78, 0.91 (by four 0.91, 1.14); more by either 0.91 to 0.97, 1.07 to 1.41
     if (n < 256) return rounds_to(4) ? kWholeEight : kPlan;
-    // 256 to 512 to 16 rounds 0.92, 1.19 (more 0.97, 1.27); to 1 024, to 16 0.85, 1.12, to 32 0.91, 1.07; to 4 096 0.89, 1.17 and 0.94, 1.22 (more rounds 0.98 to 1.01,
-    // 1.18; more ranges, to 8 rounds 0.97, 1.30).  The slowest have 2 to 15 % of their requests running and take 8 to 16 us.  Whole by eight waves or longest
-    // first, without a look at the work: 0.97 to 1.03, 1.5 to 2.2
-    return n < 4096 && rounds_to(n < 512 ? 16 : 32) && sorts ? kCut : kPlan;
+    // 256 to 512 ranges, to 16 rounds 0.84, 1.13, to 32 0.92, 1.23 (all contexts long 0.97; more 0.95, 1.22 and 1.03); 512 to 4 096, to 32 0.84, 1.23, to 128 0.92, 1.32 (1.00; more
+    // 0.99, 1.37 and 1.05; of 2 048 and more with contexts of a few tokens, which the plan puts several of into a share, 1.42); more ranges, to 8 rounds 0.97, 1.30.  A row that is sized for a server's longest possible request is most often much longer than the
+    // contexts, whose lengths are all that the launch goes by: 16 requests of 60 to 1 500 tokens, 40 heads, take 22 us with any row (the plan 25).  The slowest have 2 to
+    // 15 % of their requests running and take 8 to 16 us.  Whole by eight waves or longest first, without a look at the work: 0.97 to 1.03, 1.5 to 2.2
+    return n < 4096 && rounds_to(n < 512 || n >= 2048 ? 32 : 128) && sorts ? kCut : kPlan;
 }
 
 // A kCut launch: chunks of a part, and those of a range that is not worth cutting.  An even share of all chunks there are over the spare workgroups, so

@@ -80,8 +80,8 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
     # thousands of ranges by two waves
     (32, 8, 128, "bf16", 511, 256, FOUR), (32, 8, 128, "bf16", 512, 256, TWO), (32, 8, 128, "bf16", 512, 768, TWO), (32, 32, 128, "bf16", 300, 640, TWO),
     # looked at on the device
-    (40, 40, 128, "bf16", 16, 1504, CUT), (40, 40, 128, "bf16", 16, 4096, CUT), (40, 40, 128, "bf16", 16, 4112, PLAN), (32, 32, 128, "bf16", 64, 2048, CUT),
-    (32, 8, 128, "bf16", 64, 1504, CUT), (32, 8, 128, "bf16", 256, 8192, PLAN), (40, 40, 128, "bf16", 180, 1232, PLAN), (32, 32, 128, "bf16", 256, 512, PLAN),
+    (40, 40, 128, "bf16", 16, 1504, CUT), (40, 40, 128, "bf16", 16, 16384, CUT), (40, 40, 128, "bf16", 16, 16400, PLAN), (32, 32, 128, "bf16", 64, 4112, PLAN), (40, 40, 128, "bf16", 12, 4096, CUT), (40, 40, 128, "bf16", 12, 4112, PLAN), (32, 32, 128, "bf16", 64, 2048, CUT),
+    (32, 8, 128, "bf16", 64, 1504, CUT), (32, 8, 128, "bf16", 256, 8192, CUT), (32, 8, 128, "bf16", 256, 16400, PLAN), (32, 8, 128, "bf16", 64, 16384, CUT), (32, 8, 128, "bf16", 32, 2048, CUT), (32, 8, 128, "bf16", 32, 2064, PLAN), (64, 32, 64, "bf16", 128, 4112, PLAN), (40, 40, 128, "bf16", 180, 1232, PLAN), (32, 32, 128, "bf16", 256, 512, PLAN),
     (32, 32, 128, "bf16", 257, 768, TWO), (31, 31, 128, "bf16", 257, 768, FOUR), (32, 32, 128, "bf16", 257, 784, PLAN), (32, 8, 128, "f32", 24, 2512, PLAN), (32, 8, 128, "f32", 40, 512, CUT),
     (10, 2, 256, "bf16", 129, 800, CUT),
     # what the GPU tests of skewed batches count on
@@ -141,7 +141,7 @@ def test_cut_launches(lib):
     for _ in range(4000):
         chunk = rng.choice([1, 2])
         round_, spare, batch, heads = 4 * chunk, rng.choice([512, 1024]), rng.randint(1, 256), rng.choice([1, 2, 8, 32, 40])
-        n = _contexts(rng, batch, rng.randint(1, 512))
+        n = _contexts(rng, batch, rng.randint(1, rng.choice([512, 2048])))
         all_ = sum(n) * heads
         items = 0
         for c in n:
