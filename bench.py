@@ -48,7 +48,7 @@ HBM_PEAK_GBS = 8000.0     # MI355X published HBM3E bandwidth
 # workload name, and the kernels that were measured; summaries in profiles/.
 MEASURED_TRAFFIC = {
     "cfg1-7b-mha-bf16": (882679000, "decode_cut"),
-    "cfg2-8b-gqa-bf16": (1713836000, "decode_balanced + decode_merge_balanced"),
+    "cfg2-8b-gqa-bf16": (1700393000, "decode_cut"),
     "cfg3-long-gqa-bf16": (1546508000, "decode_balanced + decode_merge_balanced"),
     "cfg4-13b-40layer-bf16": (2177279000, "decode_balanced + decode_merge_balanced"),   # per layer
     # fetched + written (same counters, same scale factors)

@@ -10,7 +10,8 @@
 // one issue port with them besides), and a wave-stage of 32 x 32 takes 1 100 to 1 300 cycles for 544 of matrix work; here 830.  The stages'
 // tiles come by global_load_lds into a ring of 128 KiB, up to six stages ahead, and serve twice the columns.
 //
-// Bound by power: the chip runs this at 2.13 GHz (prefill_mfma at 2.3), and what takes fewer cycles at more energy loses.  With
+// Bound by the two phases -- matrix pipe busy 0.56 of the launch, LDS 0.66, 0.4 of that conflicts of the tiled layout's 8-byte value reads -- and by
+// power: the chip runs this at 2.2 GHz (prefill_mfma, matrix pipe 0.46, at 2.3), and what takes fewer cycles at more energy loses.  With
 // 32x32x16 products, 1 600 cycles to a pair of wave-stages in place of 1 665, it ran at 1.95 GHz: 4 prompts of 4 096, 32 / 8 heads of
 // 128, 501 us against 482.  Waves whose columns see no more of the positions do no products (ragged prompts -6 %).  Attention
 // alone, us, tiles of 128 by prefill_mfma / so: those 550 / 486, one of 8 000 511 / 438, 4 of 1 000 52 / 43, 16 of 500 on 2 000 to 4 000 cached

@@ -58,7 +58,7 @@ def test_parts(dtype, H, Hkv, D, bs):
     ("bf16", 8, 8, 64, 16, 130, 200), ("bf16", 8, 8, 64, 16, 300, 60), ("bf16", 32, 32, 128, 16, 33, 256), ("bf16", 32, 32, 128, 16, 33, 257),
     ("bf16", 32, 32, 128, 16, 34, 800), ("bf16", 32, 32, 128, 16, 65, 1600), ("bf16", 16, 8, 128, 16, 129, 190), ("bf16", 16, 8, 128, 16, 128, 400),
     ("bf16", 16, 8, 128, 16, 66, 1500), ("bf16", 16, 8, 64, 32, 257, 400), ("f32", 8, 8, 64, 16, 129, 600), ("f32", 12, 12, 32, 16, 100, 120),
-    # sorted, by eight waves: rows of 7 rounds to 24, 256 ranges and 1 536
+    # cut by the lengths, the longest first: rows of 7 rounds to 24, 256 ranges and 1 536
     ("bf16", 32, 32, 128, 16, 17, 900), ("bf16", 32, 32, 128, 16, 48, 2900), ("bf16", 8, 8, 64, 32, 97, 2000), ("bf16", 16, 16, 256, 16, 33, 600),
     ("f32", 32, 8, 128, 16, 65, 300), ("f32", 8, 8, 32, 16, 65, 1500), ("bf16", 8, 2, 64, 16, 128, 1536), ("bf16", 16, 8, 128, 16, 33, 1000),
     ("bf16", 10, 2, 256, 16, 129, 800),
