@@ -37,14 +37,15 @@ constexpr int cut_spare(bool matrix) { return matrix ? 512 : 1024; }
 
 // Parts of a range if all are alike, each a workgroup's (decode_parts); 0: not this way.  For few ranges of longer rows, where the plan and the
 // records of decode_balanced are a third of the time:
-//   vector path, fewer than 16 ranges, 4 to 400 rounds 0.85, 0.99;  16 to 32, 4 to 64 0.83, 0.94;  32 to 64, 4 to 32 0.84, 0.97;  64 to 128, 4 to 16 0.87, 0.99
-//   matrix path, fewer than 16 ranges, 8 to 400 rounds 0.77, 0.94;  16 to 32, 8 to 128 0.79, 0.96, to 400 0.82, 0.97;  32 to 64, 8 to 32 0.80, 0.92, to 128
-//      0.85, 1.19 (all contexts long: 0.95, 1.15; twice that 1.0);  64 to 96, 16 to 32 0.85, 1.02 (96 to 128 0.96, 1.07)
+//   vector path, fewer than 16 ranges, 4 to 400 rounds 0.85, 0.99 (to 1 024 0.95, 1.28; fewer than 4 1.06, 1.36);  16 to 32, 4 to 64 0.83, 0.94;  32 to 64, 4 to 32
+//      0.84, 0.97;  64 to 128, 4 to 16 0.87, 0.99;  16 to 128 on longer rows, to 400 0.90, 1.13, to 1 024 0.94, 1.24 (all contexts long 0.99, 1.11)
+//   matrix path, fewer than 16 ranges, 8 to 400 rounds 0.77, 0.94;  16 to 32, 8 to 128 0.79, 0.96, to 400 0.82, 0.97;  32 to 64, 8 to 32 0.80, 0.92;  all of them 401 to
+//      1 024 0.88, 1.17 (all contexts long 0.89, 1.00; more rounds 0.93, 1.43 and 0.96);  64 to 96, 16 to 32 0.85, 1.02 (to 128 0.93, 1.26; 96 to 128 0.96, 1.07)
 // (With the same number of parts for every range there can be: a context among 11 of 32 ranges, or 2 of 29 requests running, took up to 1.6 times the
-// plan's time.)
+// plan's time.  Rows longer than the contexts, a server's, are those of the contexts: one request of 1 999 tokens, 32 / 8 heads, 7.0 to 7.5 us with any row to 32 768, the plan 9.1.)
 // Workgroups in all 256, or 512 where rows are long for them (256 / 512 / 1 024, even batches: vector path, fewer than 16 ranges, 4 to 64 rounds 0.86 / 0.89 /
-// 0.89, more 0.93 / 0.87 / 0.87; 16 to 32 ranges to 16 rounds 0.85 / 0.86 / 0.90; 32 to 64 0.92 / 0.87 / 0.90; matrix path, fewer than 32, 8 to 128
-// rounds 0.79 / 0.84 / 0.86, more 0.88 / 0.89 / 0.92; 32 to 64 0.89 / 0.89 / 0.96; 64 to 128, 16 to 32 rounds, 0.91 / 0.87 / 0.91).
+// 0.89, more 0.93 / 0.87 / 0.87; 16 to 32 ranges to 16 rounds 0.85 / 0.86 / 0.90; 32 to 64 0.92 / 0.87 / 0.90; 16 to 64, 65 to 1 024 rounds 0.97 / 0.91; matrix path, fewer than 32, 8 to 128
+// rounds 0.79 / 0.84 / 0.86; 32 to 64 0.89 / 0.89 / 0.96; fewer than 64 with more rounds 0.86 / 0.89; 64 to 128, 16 to 32 rounds, 0.91 / 0.87 / 0.91).
 inline int decode_most_cuts(const DecodeLaunch &l)   // of one range, where others are shorter
 {
     const long long room = (long long)(l.capacity / l.state) / l.ranges;
@@ -53,11 +54,12 @@ inline int decode_most_cuts(const DecodeLaunch &l)   // of one range, where othe
 inline int decode_cuts(const DecodeLaunch &l)
 {
     if (!l.bounded || l.ranges >= 128 || l.batch > kPartBatch) return 0;
+    if ((l.row / l.round + 1) * 8 * l.batch + (1 << 12) >= split::kMostDividend) return 0;   // (half-chunks of all requests, and what is added to round up)
     const auto rounds_to = [&l](int n) { return l.row <= (long long)n * l.round; };
-    const int most = l.matrix ? (l.ranges < 32 ? 400 : l.ranges < 64 ? 128 : l.ranges < 96 ? 32 : 0) : l.ranges < 16 ? 400 : l.ranges < 32 ? 64 : l.ranges < 64 ? 32 : 16;
+    const int most = l.matrix ? (l.ranges < 64 ? 1024 : l.ranges < 96 ? 32 : 0) : l.ranges < 4 ? 400 : 1024;
     const int least = l.matrix ? (l.ranges >= 64 ? 16 : l.head_dim < 128 ? 12 : l.head_dim < 256 ? 8 : 5) : 4;
     if (rounds_to(least) || !rounds_to(most)) return 0;
-    const bool few = l.matrix ? l.ranges < 64 && rounds_to(128) : l.ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
+    const bool few = l.matrix ? l.ranges < 64 : l.ranges < (rounds_to(16) ? 32 : rounds_to(64) ? 16 : 0);
     const int share = (few ? 256 : 512) / (int)l.ranges, cuts = share < kMostCuts ? share : kMostCuts;
     return cuts <= decode_most_cuts(l) ? cuts : 0;
 }

@@ -65,10 +65,10 @@ def form(lib, H, Hkv, dtype, D, batch, row, bounded=1, room=ROOM):
 
 
 @pytest.mark.parametrize("H,Hkv,D,dtype,batch,row,want", [
-    (32, 8, 128, "bf16", 1, 2000, PARTS), (32, 8, 128, "bf16", 1, 200, FOUR), (8, 8, 64, "bf16", 1, 4000, PARTS), (32, 8, 128, "bf16", 1, 32768, PLAN),
+    (32, 8, 128, "bf16", 1, 2000, PARTS), (32, 8, 128, "bf16", 1, 200, FOUR), (8, 8, 64, "bf16", 1, 4000, PARTS), (32, 8, 128, "bf16", 1, 32768, PARTS), (32, 8, 128, "bf16", 1, 65536, PARTS), (32, 8, 128, "bf16", 1, 65552, PLAN),
     # few ranges: parts on both sides of the lines
-    (32, 8, 128, "bf16", 3, 8192, PARTS), (32, 8, 128, "bf16", 4, 8192, PARTS), (32, 8, 128, "bf16", 4, 8208, PLAN), (32, 8, 128, "bf16", 8, 2048, PARTS),
-    (32, 8, 128, "bf16", 12, 2048, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PLAN),
+    (32, 8, 128, "bf16", 3, 8192, PARTS), (32, 8, 128, "bf16", 4, 8192, PARTS), (32, 8, 128, "bf16", 4, 8208, PARTS), (8, 1, 128, "bf16", 60, 65536, PARTS), (1, 1, 128, "bf16", 64, 131072, PLAN), (1, 1, 128, "bf16", 63, 131072, PARTS), (3, 3, 128, "bf16", 1, 51200, PARTS), (3, 3, 128, "bf16", 1, 51216, PLAN), (32, 8, 128, "bf16", 11, 2048, PARTS), (32, 8, 128, "bf16", 11, 2064, PLAN), (32, 8, 128, "bf16", 8, 2048, PARTS),
+    (32, 8, 128, "bf16", 12, 2048, PLAN), (40, 40, 128, "bf16", 3, 2048, PARTS), (40, 40, 128, "bf16", 3, 2064, PARTS), (40, 40, 128, "bf16", 4, 2064, PLAN), (8, 1, 64, "bf16", 65, 1600, PLAN),
     # whole ranges
     (32, 8, 128, "bf16", 64, 304, FOUR), (40, 40, 128, "bf16", 40, 128, TWO), (40, 40, 128, "bf16", 40, 144, FOUR), (40, 40, 128, "bf16", 102, 256, FOUR), (40, 40, 128, "bf16", 103, 256, TWO), (40, 40, 128, "bf16", 103, 384, TWO),
     (32, 8, 128, "bf16", 200, 64, TWO), (32, 8, 128, "bf16", 200, 256, FOUR), (32, 8, 128, "bf16", 256, 512, FOUR), (32, 8, 128, "bf16", 257, 512, FOUR),
@@ -164,15 +164,14 @@ def test_parts(lib):
     done = 0
     while done < 4000:
         H, Hkv, D, dtype = rng.choice([(32, 8, 128, "bf16"), (40, 40, 128, "bf16"), (8, 2, 64, "bf16"), (8, 8, 64, "f32"), (8, 1, 128, "bf16"), (10, 2, 256, "bf16")])
-        batch, row, room = rng.randint(1, 64), int(2 ** rng.uniform(6, 15)), rng.choice([ROOM, 31 << 20, 2 << 20])
+        batch, row, room = rng.randint(1, 64), int(2 ** rng.uniform(6, 17.5)), rng.choice([ROOM, 31 << 20, 2 << 20])
         even = lib.c_cuts(Hkv, H // Hkv, dtype == "bf16", D, batch, row, room, ctypes.byref(most))
         if not even:
             continue
         done += 1
-        gt, chunk = (16, 1) if H > Hkv else (8, 2) if D == 128 else (16, 2)
-        if dtype == "f32":
-            gt, chunk = 16, 2
+        gt, chunk = 16, 1 if H > Hkv else 2
         n = [(c + gt - 1) // gt for c in _contexts(rng, batch, row)]
+        assert sum(n) + even * batch < 1 << 19             # what is divided
         size = lib.c_part(sum(n), max(n), batch, even, most.value, chunk)
         assert size % chunk == 0 and size < max(4 * chunk, sum(n) / (batch * even) + 1, max(n) / most.value + 1) + chunk
         for tries in range(9):

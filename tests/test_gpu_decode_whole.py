@@ -118,6 +118,7 @@ def test_skewed_batches_of_many_ranges(dtype, H, Hkv, D, bs, batch, row):
 @pytest.mark.parametrize("dtype,H,Hkv,D,bs,batch,row", [
     ("bf16", 8, 2, 128, 16, 10, 2500), ("bf16", 32, 1, 128, 16, 20, 1500), ("bf16", 16, 4, 64, 32, 16, 1600), ("bf16", 2, 1, 128, 16, 64, 1600), ("bf16", 8, 8, 64, 16, 11, 1300),
     ("bf16", 2, 2, 256, 16, 7, 2000), ("f32", 8, 2, 128, 16, 30, 900), ("f32", 4, 4, 32, 32, 16, 1100), ("bf16", 10, 2, 256, 16, 3, 5000),
+    ("bf16", 8, 1, 128, 32, 9, 40000), ("bf16", 2, 2, 64, 16, 8, 30000), ("f32", 4, 2, 128, 16, 20, 9000), ("bf16", 4, 2, 128, 16, 40, 8000),
 ])
 def test_skewed_batches_of_few_ranges(dtype, H, Hkv, D, bs, batch, row):
     """Ranges in parts of one size, which the lengths of the call decide."""
