@@ -101,10 +101,11 @@ inline DecodeForm decode_form(const DecodeLaunch &l)
     if (l.batch > kCutBatch) return !rounds_to(6) ? kPlan : n < 8192 ? kWholeFour : kWholeTwo;   // 0.60, 1.13; two / four 0.70, 1.36 / 0.73, 1.37 (more than 6 rounds 0.89 to 1.09, 2.66)
     // to 4 by eight waves 0.78, 0.91 (by four 0.91, 1.14); more by either 0.91 to 0.97, 1.07 to 1.41
     if (n < 256) return rounds_to(4) ? kWholeEight : kPlan;
-    // 256 to 512 ranges, to 16 rounds 0.84, 1.13, to 32 0.92, 1.23 (all contexts long 0.97; more 0.95, 1.22 and 1.03); 512 to 4 096, to 32 0.84, 1.23, to 128 0.92, 1.32 (1.00; more
-    // 0.99, 1.37 and 1.05; of 2 048 and more with contexts of a few tokens, which the plan puts several of into a share, 1.42); more ranges, to 8 rounds 0.97, 1.30.  A row that is sized for a server's longest possible request is most often much longer than the
-    // contexts, whose lengths are all that the launch goes by: 16 requests of 60 to 1 500 tokens, 40 heads, take 22 us with any row (the plan 25).  The slowest have 2 to
-    // 15 % of their requests running and take 8 to 16 us.  Whole by eight waves or longest first, without a look at the work: 0.97 to 1.03, 1.5 to 2.2
+    // 256 to 512 ranges, to 16 rounds 0.84, 1.13, to 32 0.92, 1.23 (all contexts long 0.97; more 0.95, 1.22 and 1.03); 512 to 4 096, to 32 0.84, 1.23, to 128 0.92, 1.32
+    // (1.00; more 0.99, 1.37 and 1.05; of 2 048 and more with contexts of a few tokens, which the plan puts several of into a share, 1.42); more ranges, to 8 rounds 0.97,
+    // 1.30.  A row that is sized for a server's longest possible request is most often much longer than the contexts, whose lengths are all that the launch goes by:
+    // 4 layers of append + decode of 16 requests of 60 to 1 500 tokens, 40 heads, take 91 us with any row to here, 103 by the plan.  The slowest have 2 to 15 % of
+    // their requests running and take 8 to 16 us.  Whole by eight waves or longest first, without a look at the work: 0.97 to 1.03, 1.5 to 2.2
     return n < 4096 && rounds_to(n < 512 || n >= 2048 ? 32 : 128) && sorts ? kCut : kPlan;
 }
 
